@@ -613,9 +613,9 @@ def decoder_layer(name: str, dev) -> dict:
 
 
 def attention_backward(name: str, dev) -> dict:
-    """earn_attn_backward (vector-ALU form) on the register-focused layers of `name` (compacted sequences of r rows) and
+    """earn_attn_backward on the register-focused layers of `name` (compacted sequences of r rows) and
     on one full-length layer of small_gqa: time and the rate of its algorithmic FLOPs, 10 d per causal (query, key) pair
-    and head (five products of 2 d: QK^T, dO V^T, P^T dO, dS K, dS^T Q), against the fp32 vector peak."""
+    and head (five products of 2 d: QK^T, dO V^T, P^T dO, dS K, dS^T Q), against the bf16 matrix-core peak."""
     from paper_2507_00715_amd import binding as B
     out = {}
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -643,8 +643,8 @@ def attention_backward(name: str, dev) -> dict:
         torch.cuda.synchronize()
         us = e0.elapsed_time(e1) * 1e3 / 5
         flops = 10.0 * c.head_dim * c.n_q_heads * sum(n * (n + 1) // 2 for n in lens)
-        out[label] = {"workload": cname, "us": us, "tflops": flops / us / 1e6, "frac_of_fp32_vector_peak": flops / us / 1e6 / PEAK_F32_TFLOPS,
-                      "bound": "alu"}
+        out[label] = {"workload": cname, "us": us, "tflops": flops / us / 1e6, "frac_of_bf16_peak": flops / us / 1e6 / PEAK_BF16_TFLOPS,
+                      "bound": "mfma"}
     return out
 
 

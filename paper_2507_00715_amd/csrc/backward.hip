@@ -4,18 +4,25 @@
 //   D_i  = sum_e dO_ie O_ie                    P_ij = exp(s_ij - lse_i),  s_ij = scale q_i . k_j   (j <= i)
 //   dV_j = sum_i P_ij dO_i                     dP_ij = dO_i . v_j          dS_ij = P_ij (dP_ij - D_i)
 //   dQ_i = scale sum_j dS_ij k_j               dK_j = scale sum_i dS_ij q_i
-// (sums over the query heads of a kv head's group for dK, dV).  A first form on the vector ALU, fp32 arithmetic for both
-// storage types, without atomics: one kernel owns query rows (dQ), one owns key rows (dK, dV); each recomputes the
-// probabilities it needs from lse.  Four lanes share a row and hold d/4 of its elements each.
+// (sums over the query heads of a kv head's group for dK, dV).  No atomics: one kernel owns query rows (D, dQ), one owns
+// key rows (dK, dV); each recomputes the probabilities it needs from lse.
+//   bf16  bwd_dq_mfma_kernel, bwd_dkv_mfma_kernel: the five products on the matrix cores.
+//   fp32  bwd_dsum_kernel, bwd_dq_kernel, bwd_dkv_kernel: vector ALU, four lanes share a row and hold d/4 of its elements
+//         each (the precise form for the small fp32 configuration).
+#include <algorithm>
+
 #include "common.h"
+#include "mfma_tiles.h"
 
 namespace earn {
 
 struct BwdParams {
   const void* q; const void* k; const void* v; const void* out; const float* lse; const void* d_out;
-  const int32_t* cu; float* dsum;  // D [tokens, Hq]
+  const int32_t* cu; float* dsum;  // D: [tokens, Hq] (fp32 kernels) or [Hq, tokens] (bf16 kernels)
   void* dq; void* dk; void* dv;
   int batch, hq, hkv, total, max_seqlen;
+  int n_blk;   // row blocks of the longest sequence (bf16 kernels)
+  int chunk;   // (sequence, kv head) pairs an XCD works on together (bf16 kernels)
   float scale, scale_log2;
   HeadMap heads;
 };
@@ -174,6 +181,412 @@ __global__ __launch_bounds__(256) void bwd_dkv_kernel(BwdParams p) {
   store_quarter<T, D>((T*)p.dv + jo * D, qt, dv);
 }
 
+// ------------------------------------------------------------------------------------------------------------------
+// bf16 on the matrix cores (v_mfma_f32_32x32x16_bf16; lane = (r32 = lane % 32, hf = lane / 32))
+//
+// Both kernels take the forward's register-level scheme: a score tile whose accumulator columns are the rows the wave
+// OWNS (queries for dQ, keys for dK / dV) gives a lane one owned row and 16 of the 32 rows it is paired with; the
+// accumulator registers, converted to bf16, are the B operand of the product that contracts over the paired rows, whose
+// A operand is the paired tile read transposed from LDS (ds_read_b64_tr_b16).  A wave keeps its 32 owned rows (q and dO, or
+// k and v) as B operands in registers; the paired rows stream through LDS in tiles shared by the workgroup:
+//   dQ:      S^T = K Q^T   dP^T = V dO^T    dQ^T += K^T dS^T                       (paired: keys)
+//   dK, dV:  S = Q K^T     dP = dO V^T      dV^T += dO^T P,  dK^T += Q^T dS        (paired: queries of every head of the group)
+// (dK, dV: -lse_i / scale and -D_i are the start values of the S and dP accumulators.)  P and dS enter the last products as TWO bf16 operands, the rounded value
+// and the rounded remainder (16 bits of significand): the arithmetic keeps the accuracy of fp32 probabilities, at 16 of
+// the 48 (dK, dV) and 8 of the 32 (dQ) matrix instructions per 32 x 32 tile and 128 dimensions.
+// Bound by the instruction chain of a wave (matrix products, exponentials and splits of one tile: about 2 us, 3 us when two
+// waves share a SIMD) times the tiles it walks.  Measured, forward included, against the vector-ALU form that these kernels
+// replaced: 16 sequences of 272-1040 rows, 32 / 8 heads of 128: 18.36 -> 0.53 ms; 64 sequences of 68 rows: 1.01 -> 0.12 ms.
+// ------------------------------------------------------------------------------------------------------------------
+struct BwdBlock { int c, a, b0, n, row0; bool valid; };
+// Workgroup -> (sequence, kv head, block of owned rows, query head of the group).  Consecutive ids go to the 8 XCDs in turn,
+// and an XCD keeps its own (sequence, kv head) pairs, whose rows its L2 then holds.  It takes them in chunks of p.chunk
+// pairs, within a chunk longest work first over ALL its pairs: a block's work is the number of rows it is paired with
+// (late queries; keys counted from the sequence's end), so with few pairs no long block is left to start when the GPU is
+// about to run dry.  (keys_own: the owned rows are keys.)
+__device__ __forceinline__ BwdBlock bwd_map_block(const BwdParams& p, int block_rows, int heads, bool keys_own) {
+  BwdBlock b;
+  b.valid = false;
+  const int gq = p.hq / p.hkv;
+  const int xcd = blockIdx.x % kXcds, k_in_xcd = blockIdx.x / kXcds;
+  const int per_chunk = p.chunk * p.n_blk * heads;
+  const int rem = k_in_xcd % per_chunk, j = rem / (p.chunk * heads);   // j: 0 = the longest work
+  const int pair = (k_in_xcd / per_chunk * p.chunk + rem / heads % p.chunk) * kXcds + xcd;
+  if (pair >= p.batch * p.hkv) return b;
+  b.c = pair % p.hkv;
+  b.a = head_of_slot(p.heads, b.c * gq + rem % heads);
+  clamped_bounds(p.cu, pair / p.hkv, p.total, p.max_seqlen, b.b0, b.n);
+  const int blk = keys_own ? (b.n + block_rows - 1) / block_rows - p.n_blk + j : p.n_blk - 1 - j;
+  b.row0 = blk * block_rows;
+  b.valid = blk >= 0 && b.row0 < b.n;
+  return b;
+}
+// Tiles of ROWS rows of one head of a packed [rows, heads, D] tensor into LDS (the swizzled layout of mfma_tiles.h).  The
+// descriptor is rebuilt per tile from a 64-bit base, so a sequence of any length can be addressed; rows past the end of
+// the sequence read as zeros.
+template <int D, int WAVES, int ROWS>
+struct BwdStager {
+  static constexpr int UPR = D / 8, NI = ROWS * UPR / kWave / WAVES, RPI = kWave / UPR;
+  static_assert(NI >= 1 && NI * WAVES * kWave == ROWS * UPR);
+  int voff[NI], row_bytes, wave;
+  __device__ __forceinline__ void init(int heads, int wave_, int lane) {
+    row_bytes = heads * D * 2;
+    wave = wave_;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int row = RPI * (wave + WAVES * i) + lane / UPR;
+      voff[i] = row * row_bytes + ((lane % UPR) ^ swz<D>(row)) * 16;
+    }
+  }
+  // rows [0, rows) of the tile starting at `base` exist (rows >= 1)
+  __device__ __forceinline__ void issue(const __bf16* base, int rows, unsigned lds_tile) const {
+    const u32x4 rsrc = raw_buffer(base, (min(rows, ROWS) - 1) * row_bytes + D * 2);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) dma16_to_lds(rsrc, lds_tile + (unsigned)((wave + WAVES * i) * 1024), voff[i]);
+  }
+};
+// 32 owned rows as B operands: lane (r32, hf) holds, per k-step ks, elements 16 ks + 8 hf + (0..7) of row r32
+template <int D>
+__device__ __forceinline__ void bwd_load_rows(const __bf16* row /* + 8 hf */, bf16x8 (&f)[D / 16]) {
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) f[ks] = *(const bf16x8*)(row + 16 * ks);
+}
+// acc += (32 tile rows at `tile`) x (owned rows: from registers, or from LDS rows `own`).  Fragments are requested AHEAD
+// products early; slot(ks) is vector work of the caller's that runs while product ks does.
+template <int D, int AHEAD, typename Slot>
+__device__ __forceinline__ void bwd_product(const __bf16* tile, const FragOffsets<D>& fo, const bf16x8 (&f)[D / 16], f32x16& acc, Slot&& slot) {
+  constexpr int KS = D / 16, N = AHEAD + 1;
+  bf16x8 r[N];
+#pragma unroll
+  for (int ks = 0; ks < AHEAD && ks < KS; ++ks) r[ks] = *(const bf16x8*)(tile + fo.k(ks));
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    if (ks + AHEAD < KS) r[(ks + AHEAD) % N] = *(const bf16x8*)(tile + fo.k(ks + AHEAD));
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[ks % N], f[ks], acc, 0, 0, 0);
+    slot(ks);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+template <int D, int AHEAD>
+__device__ __forceinline__ void bwd_product(const __bf16* tile, const __bf16* own, const FragOffsets<D>& fo, f32x16& acc) {
+  constexpr int KS = D / 16, N = AHEAD + 1;
+  bf16x8 r[N], f[N];
+#pragma unroll
+  for (int ks = 0; ks < AHEAD && ks < KS; ++ks) { r[ks] = *(const bf16x8*)(tile + fo.k(ks)); f[ks] = *(const bf16x8*)(own + fo.k(ks)); }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    if (ks + AHEAD < KS) {
+      r[(ks + AHEAD) % N] = *(const bf16x8*)(tile + fo.k(ks + AHEAD));
+      f[(ks + AHEAD) % N] = *(const bf16x8*)(own + fo.k(ks + AHEAD));
+    }
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[ks % N], f[ks % N], acc, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// x as the sum of two bf16 operands: hi = x rounded, lo = the remainder rounded.  Word (kk, j) of an operand packs
+// accumulator registers 8 kk + 2 j, + 1; w = 4 kk + j.
+struct SplitOperand {
+  u32x4 hi[2], lo[2];
+  __device__ __forceinline__ void set(int w, float a, float b) {
+    const unsigned h = pack_bf16(a, b);
+    hi[w >> 2][w & 3] = h;
+    lo[w >> 2][w & 3] = pack_bf16(a - bf16_lo(h), b - bf16_hi(h));
+  }
+};
+__device__ __forceinline__ int word_reg(int w) { return 8 * (w >> 2) + 2 * (w & 3); }  // first accumulator register of word w
+// o^T += (32 tile rows, transposed) x (hi + lo); a fragment requested two blocks ahead, the first two by the caller
+// (bwd_request), ahead of the vector work that produces hi and lo.  slot(i), i < 2 D / 32: the caller's vector work that
+// runs while block i's products do.
+struct TransposedPair { bf16x8 f[2]; };
+template <int D>
+__device__ __forceinline__ TransposedPair bwd_request(const __bf16* tile, const FragOffsets<D>& fo) {
+  return TransposedPair{read_v_fragment<D>(tile, fo, 0, 0), read_v_fragment<D>(tile, fo, 1, 0)};
+}
+template <int D, typename Slot>
+__device__ __forceinline__ void bwd_accumulate(const __bf16* tile, const FragOffsets<D>& fo, const TransposedPair& first,
+                                               const SplitOperand& x, f32x16 (&o)[D / 32], Slot&& slot) {
+  constexpr int DB = D / 32;
+  bf16x8 r[3] = {first.f[0], first.f[1]};
+#pragma unroll
+  for (int i = 0; i < 2 * DB; ++i) {
+    const int kk = i / DB, db = i % DB;
+    if (i + 2 < 2 * DB) r[(i + 2) % 3] = read_v_fragment<D>(tile, fo, (i + 2) % DB, (i + 2) / DB);
+    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i % 3], __builtin_bit_cast(bf16x8, x.hi[kk]), o[db], 0, 0, 0);
+    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i % 3], __builtin_bit_cast(bf16x8, x.lo[kk]), o[db], 0, 0, 0);
+    slot(i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// keeps the products that write these registers in front of what follows (the compiler otherwise starts the next
+// products early, at the price of registers)
+template <int N>
+__device__ __forceinline__ void pin(f32x16 (&o)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(o[i]));
+}
+template <int D>
+__device__ __forceinline__ void bwd_store_row(__bf16* row /* + 4 hf */, const f32x16 (&o)[D / 32], float scale) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *(u32x2*)(row + 32 * db + 8 * j) = u32x2{pack_bf16(o[db][4 * j] * scale, o[db][4 * j + 1] * scale),
+                                               pack_bf16(o[db][4 * j + 2] * scale, o[db][4 * j + 3] * scale)};
+}
+
+// D and dQ of 32 * WAVES query rows of one head
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void bwd_dq_mfma_kernel(BwdParams p) {
+  constexpr int ROWS = 16 * WAVES, BLOCK = 32 * WAVES;   // keys per tile, query rows per workgroup
+  __shared__ __bf16 smk[2][ROWS * D];
+  __shared__ __bf16 smv[2][ROWS * D];
+  const BwdBlock blk = bwd_map_block(p, BLOCK, p.hq / p.hkv, true);
+  if (!blk.valid) return;
+  const int b0 = blk.b0, n = blk.n;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int r32 = lane & 31, hf = lane >> 5;
+  const int qw = blk.row0 + wave * 32;               // first query row of this wave
+  const bool active = qw < n;
+  const int n_tiles = (min(blk.row0 + BLOCK, n) + ROWS - 1) / ROWS;
+  const __bf16* kg = (const __bf16*)p.k + ((long long)b0 * p.hkv + blk.c) * D;
+  const __bf16* vg = (const __bf16*)p.v + ((long long)b0 * p.hkv + blk.c) * D;
+  const long long tile_stride = (long long)ROWS * p.hkv * D;
+  BwdStager<D, WAVES, ROWS> st;
+  st.init(p.hkv, wave, lane);
+  const unsigned lds_k = (unsigned)(size_t)(lds_void_ptr)&smk[0][0], lds_v = (unsigned)(size_t)(lds_void_ptr)&smv[0][0];
+  auto issue = [&](int t) {
+    const unsigned at = (unsigned)((t & 1) * ROWS * D * 2);
+    st.issue(kg + t * tile_stride, n - t * ROWS, lds_k + at);
+    st.issue(vg + t * tile_stride, n - t * ROWS, lds_v + at);
+  };
+  issue(0);
+
+  const int qi = min(qw + r32, n - 1);
+  const long long io = (long long)(b0 + qi) * p.hq + blk.a;
+  bf16x8 qf[D / 16], gf[D / 16];
+  bwd_load_rows<D>((const __bf16*)p.q + io * D + 8 * hf, qf);
+  bwd_load_rows<D>((const __bf16*)p.d_out + io * D + 8 * hf, gf);
+  float dsum = 0.f;
+  {
+    const __bf16* orow = (const __bf16*)p.out + io * D + 8 * hf;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+      float o[8], g[8];
+      B8<__bf16>::load(orow + 16 * ks, o);
+      const u32x4 w = __builtin_bit_cast(u32x4, gf[ks]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { g[2 * j] = bf16_lo(w[j]); g[2 * j + 1] = bf16_hi(w[j]); }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dsum = __builtin_fmaf(o[j], g[j], dsum);
+    }
+    dsum = half_sum(dsum);
+    if (active && hf == 0 && qw + r32 < n) p.dsum[(long long)blk.a * p.total + b0 + qi] = dsum;
+  }
+  const float lse2 = p.lse[io] * 1.4426950408889634f;
+  FragOffsets<D> fo;
+  fo.init(lane);
+  f32x16 o[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+
+  for (int t = 0; t < n_tiles; ++t) {
+    drain_loads_and_barrier();
+    if (t + 1 < n_tiles) issue(t + 1);
+#pragma unroll
+    for (int h = 0; h < ROWS / 32; ++h) {
+      const int key0 = t * ROWS + 32 * h;
+      if (!active || key0 > qw + 31) continue;
+      const __bf16* tk = smk[t & 1] + h * 32 * D;
+      f32x16 s, ds;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { s[i] = 0.f; ds[i] = -dsum; }
+      bwd_product<D, 3>(tk, fo, qf, s, [](int) {});
+      // the exponentials run while the matrix core forms dP
+      constexpr int EPS = 16 / (D / 16);   // per slot
+      bwd_product<D, 3>(smv[t & 1] + h * 32 * D, fo, gf, ds, [&](int ks) {
+#pragma unroll
+        for (int i = EPS * ks; i < EPS * (ks + 1); ++i) s[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], p.scale_log2, -lse2));
+      });
+      const TransposedPair tp = bwd_request<D>(tk, fo);
+      if (key0 + 31 > qw) {   // the diagonal: query r32 sees keys up to its own index
+        const int bound = qw + r32 - key0 - 4 * hf;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (8 * (i >> 2) + (i & 3) > bound) s[i] = 0.f;
+      }
+      SplitOperand x;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) x.set(w, s[word_reg(w)] * ds[word_reg(w)], s[word_reg(w) + 1] * ds[word_reg(w) + 1]);
+      bwd_accumulate<D>(tk, fo, tp, x, o, [](int) {});
+    }
+  }
+  if (!active || qw + r32 >= n) return;
+  bwd_store_row<D>((__bf16*)p.dq + io * D + 4 * hf, o, p.scale);
+}
+
+// dK and dV of 32 * KW key rows of one kv head: walks the (head of the group, query tile) pairs from the block's own rows
+// to the end of the sequence.  G groups of KW waves take every G-th pair each; their sums are added through LDS at the end.
+// The 128 accumulators and 64 registers of owned rows of d = 128 leave too few for the rest of two waves per SIMD (24
+// registers spilled inside the loop, whose reloads wait for the tiles in flight), so the owned keys stay in LDS there.
+template <int D, int KW, int G>
+__global__ __launch_bounds__(64 * KW * G, 2) void bwd_dkv_mfma_kernel(BwdParams p) {
+  constexpr int ROWS = 32, BLOCK = 32 * KW, DB = D / 32;   // ROWS queries per tile, BLOCK key rows per workgroup
+  constexpr bool KEYS_IN_LDS = D == 128;
+  struct Stage { __bf16 q[ROWS * D], g[ROWS * D]; };
+  __shared__ Stage sm[G][2];                               // q and dO tiles; at the end, the merge buffer
+  __shared__ __bf16 smk[KEYS_IN_LDS ? BLOCK * D : 8];
+  __shared__ float sml[G][2][2 * ROWS];                    // -lse / scale, then -D, of a tile's queries: start values of S, dP
+  static_assert(G == 1 || sizeof(sm) >= sizeof(f32x16) * DB * 64 * KW);
+  const BwdBlock blk = bwd_map_block(p, BLOCK, 1, true);
+  if (!blk.valid) return;
+  const int b0 = blk.b0, n = blk.n, gq = p.hq / p.hkv;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave % KW);
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / (kWave * KW)), tid = threadIdx.x % (kWave * KW);
+  const int r32 = lane & 31, hf = lane >> 5;
+  const int kw = blk.row0 + wave * 32;                     // first key row of this wave
+  const bool active = kw < n;
+  const int q_first = blk.row0, tiles = (n - q_first + ROWS - 1) / ROWS, steps = tiles * gq;
+  BwdStager<D, KW, ROWS> st;
+  st.init(p.hq, wave, lane);
+  const unsigned lds_tiles = (unsigned)(size_t)(lds_void_ptr)&sm[grp][0];
+  // This thread's word of the next tile's statistics: row stat_row of lse (tid < ROWS) or D (the next ROWS threads).  It is
+  // requested with the tile and not touched before the tile is due: any arithmetic on it would wait for it here.
+  const bool is_lse = tid < ROWS;
+  const float inv_scale = 1.f / p.scale;
+  const int stat_row = tid % ROWS;
+  float stat = 0.f;
+  // query tile at q0 of head i of the group, into stage `buf`
+  auto issue = [&](int i, int q0, int buf) {
+    const int a = head_of_slot(p.heads, blk.c * gq + i);
+    const long long at = ((long long)(b0 + q0) * p.hq + a) * D;
+    if (tid < 2 * ROWS) {
+      const long long q = b0 + min(q0 + stat_row, n - 1);
+      const float* src = is_lse ? p.lse + q * p.hq + a : p.dsum + (long long)a * p.total + q;
+      stat = *src;
+    }
+    const unsigned to = lds_tiles + (unsigned)(buf * sizeof(Stage));
+    st.issue((const __bf16*)p.q + at, n - q0, to);
+    st.issue((const __bf16*)p.d_out + at, n - q0, to + (unsigned)(ROWS * D * 2));
+  };
+  const long long jo = (long long)(b0 + min(kw + r32, n - 1)) * p.hkv + blk.c;
+  bf16x8 kf[D / 16], vf[D / 16];
+  if constexpr (KEYS_IN_LDS) {
+    BwdStager<D, KW * G, BLOCK> sk;
+    sk.init(p.hkv, wave + KW * grp, lane);
+    sk.issue((const __bf16*)p.k + ((long long)(b0 + blk.row0) * p.hkv + blk.c) * D, n - blk.row0,
+             (unsigned)(size_t)(lds_void_ptr)&smk[0]);
+  } else {
+    bwd_load_rows<D>((const __bf16*)p.k + jo * D + 8 * hf, kf);
+  }
+  bwd_load_rows<D>((const __bf16*)p.v + jo * D + 8 * hf, vf);
+  // this group's next (head, tile) pair
+  int head = grp / tiles, tile = grp % tiles;
+  if (head < gq) issue(head, q_first + tile * ROWS, 0);
+  FragOffsets<D> fo;
+  fo.init(lane);
+  f32x16 dk[DB], dv[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { dk[db][i] = 0.f; dv[db][i] = 0.f; }
+
+  int buf = 0;
+  for (int step = 0; step < steps; step += G) {            // the same count in every group: they share the barrier
+    const bool have = head < gq;
+    const int q0 = q_first + tile * ROWS;
+    // rows past the end of the sequence: q = dO = 0 there, any finite value will do
+    if (tid < 2 * ROWS) sml[grp][buf][tid] = q0 + stat_row < n ? stat * (is_lse ? -inv_scale : -1.f) : 0.f;
+    drain_loads_and_barrier();
+    tile += G;
+    while (tile >= tiles) { tile -= tiles; ++head; }
+    if (head < gq) issue(head, q_first + tile * ROWS, buf ^ 1);
+    if (have && active && q0 + 31 >= kw) {
+      const __bf16* tq = sm[grp][buf].q;
+      const __bf16* tg = sm[grp][buf].g;
+      const float* stats = sml[grp][buf] + 4 * hf;
+      // The fragment addresses are worked out again for every product (one instruction each): kept, they would hold 16
+      // registers.
+      auto forget = [&] { asm volatile("" : "+v"(fo.k_base), "+v"(fo.v_base[0]), "+v"(fo.v_base[1])); };
+      forget();
+      f32x16 s, ds;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 l4 = *(const f32x4*)(stats + 8 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[4 * j + e] = l4[e];
+      }
+      if constexpr (KEYS_IN_LDS) bwd_product<D, 3>(tq, smk + wave * 32 * D, fo, s);
+      else bwd_product<D, 3>(tq, fo, kf, s, [](int) {});
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 d4 = *(const f32x4*)(stats + ROWS + 8 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ds[4 * j + e] = d4[e];
+      }
+      forget();
+      // the exponentials run while the matrix core forms dP
+      constexpr int EPS = 16 / (D / 16);   // per slot
+      bwd_product<D, 3>(tg, fo, vf, ds, [&](int ks) {
+#pragma unroll
+        for (int i = EPS * ks; i < EPS * (ks + 1); ++i) s[i] = __builtin_amdgcn_exp2f(s[i] * p.scale_log2);
+      });
+      TransposedPair tp = bwd_request<D>(tg, fo);
+      if (q0 < kw + 31) {     // the diagonal: key r32 is seen by queries from its own index on
+        const int bound = kw + r32 - q0 - 4 * hf;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (8 * (i >> 2) + (i & 3) < bound) s[i] = 0.f;
+      }
+      SplitOperand px, dx;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) px.set(w, s[word_reg(w)], s[word_reg(w) + 1]);
+      // dS = P (dP - D) is formed and split while the matrix core takes dV
+      constexpr int WPS = 8 / (2 * DB);    // words per slot
+      bwd_accumulate<D>(tg, fo, tp, px, dv, [&](int i) {
+#pragma unroll
+        for (int w = WPS * i; w < WPS * (i + 1); ++w) dx.set(w, s[word_reg(w)] * ds[word_reg(w)], s[word_reg(w) + 1] * ds[word_reg(w) + 1]);
+      });
+      forget();
+      tp = bwd_request<D>(tq, fo);
+      bwd_accumulate<D>(tq, fo, tp, dx, dk, [](int) {});
+      pin(dv);
+      pin(dk);
+    }
+    buf ^= 1;
+  }
+  // the groups' sums, added in group order (lane-wise: the layouts are identical)
+  float* merge = (float*)&sm[0][0] + (wave * kWave + lane) * 4;
+  auto add_groups = [&](f32x16 (&o)[DB]) {
+#pragma unroll
+    for (int g = 1; g < G; ++g) {
+      __syncthreads();
+      if (grp == g) {
+#pragma unroll
+        for (int i = 0; i < 4 * DB; ++i)
+          *(f32x4*)(merge + i * KW * kWave * 4) = f32x4{o[i / 4][4 * (i % 4)], o[i / 4][4 * (i % 4) + 1], o[i / 4][4 * (i % 4) + 2], o[i / 4][4 * (i % 4) + 3]};
+      }
+      __syncthreads();
+      if (grp == 0) {
+#pragma unroll
+        for (int i = 0; i < 4 * DB; ++i) {
+          const f32x4 x = *(const f32x4*)(merge + i * KW * kWave * 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[i / 4][4 * (i % 4) + e] += x[e];
+        }
+      }
+    }
+  };
+  add_groups(dv);
+  add_groups(dk);
+  if (grp > 0 || !active || kw + r32 >= n) return;
+  bwd_store_row<D>((__bf16*)p.dk + jo * D + 4 * hf, dk, p.scale);
+  bwd_store_row<D>((__bf16*)p.dv + jo * D + 4 * hf, dv, 1.f);
+}
+
 size_t attn_backward_workspace_bytes(int hq, int total_tokens) { return ((size_t)total_tokens * hq * sizeof(float) + 255) / 256 * 256; }
 
 template <typename T, int D>
@@ -184,6 +597,31 @@ static void launch_bwd_t(const BwdParams& p, int total_tokens, int max_seqlen, h
   const unsigned blocks = (unsigned)((max_seqlen + 63) / 64);
   hipLaunchKernelGGL((bwd_dq_kernel<T, D>), dim3(blocks, p.hq, p.batch), dim3(256), 0, stream, p);
   hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), dim3(blocks, p.hkv, p.batch), dim3(256), 0, stream, p);
+}
+
+// Workgroups of 128 owned rows as long as there are 512 of them (two per CU).  Below that, 64-row ones, and for dK / dV,
+// where an early block of a long sequence walks all its tiles once per grouped head, four groups of waves per workgroup:
+// the launch then takes as long as its longest chain of tiles (2 sequences of 2080 rows, 32 / 8 heads of 128, whole step:
+// 442 against 608 us in the 128-row form; 12 / 2 heads, 8 sequences of 500-1000: 190 against 333; where 736 workgroups have
+// work, 16 sequences of 272-1040, it is 578 against 519, and 64 sequences of 68 rows 142 against 118).
+template <int D>
+static void launch_bwd_mfma(BwdParams& p, hipStream_t stream) {
+  const int per_xcd = (int)(((long long)p.batch * p.hkv + kXcds - 1) / kXcds);  // pairs
+  auto fills = [&](int heads) { return (long long)per_xcd * kXcds * ((p.max_seqlen + 127) / 128) * heads >= 512; };
+  // fills the mapping fields of p
+  auto plan = [&](int rows, int heads) {
+    p.n_blk = (p.max_seqlen + rows - 1) / rows;
+    p.chunk = std::max(1, std::min(per_xcd, 256 / (p.n_blk * heads)));  // about four rounds of an XCD's 64 workgroup slots
+    return dim3((unsigned)((long long)((per_xcd + p.chunk - 1) / p.chunk) * p.chunk * p.n_blk * heads * kXcds));
+  };
+  const int gq = p.hq / p.hkv;
+  const bool dq_wide = p.max_seqlen > 64 && fills(gq), dkv_wide = fills(1);
+  dim3 grid = plan(dq_wide ? 128 : 64, gq);
+  if (dq_wide) hipLaunchKernelGGL((bwd_dq_mfma_kernel<D, 4>), grid, dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL((bwd_dq_mfma_kernel<D, 2>), grid, dim3(128), 0, stream, p);
+  grid = plan(dkv_wide ? 128 : 64, 1);
+  if (dkv_wide) hipLaunchKernelGGL((bwd_dkv_mfma_kernel<D, 4, 1>), grid, dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL((bwd_dkv_mfma_kernel<D, 2, 4>), grid, dim3(512), 0, stream, p);
 }
 
 int launch_attn_backward(const earn_attn_desc* desc, const void* q, const void* k, const void* v, const void* out,
@@ -201,7 +639,7 @@ int launch_attn_backward(const earn_attn_desc* desc, const void* q, const void* 
   if (desc->dtype == EARN_F32) {
     if (d == 64) launch_bwd_t<float, 64>(p, total_tokens, max_seqlen, stream); else launch_bwd_t<float, 128>(p, total_tokens, max_seqlen, stream);
   } else {
-    if (d == 64) launch_bwd_t<__bf16, 64>(p, total_tokens, max_seqlen, stream); else launch_bwd_t<__bf16, 128>(p, total_tokens, max_seqlen, stream);
+    if (d == 64) launch_bwd_mfma<64>(p, stream); else launch_bwd_mfma<128>(p, stream);
   }
   return hipGetLastError() == hipSuccess ? EARN_OK : EARN_ERR_HIP;
 }

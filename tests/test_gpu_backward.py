@@ -69,6 +69,20 @@ def test_attention_backward_matches_oracle(dtype, hq, hkv, d, lens, scale):
     check_grad(gv, ref["dv"], dtype, "dv")
 
 
+EDGE_LENS = [1, 31, 32, 33, 63, 64, 65, 95, 127, 128, 129, 161, 257]
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (2, 2, 128, EDGE_LENS), (6, 2, 128, EDGE_LENS), (3, 1, 64, EDGE_LENS),     # few blocks: 64-row workgroups
+    (16, 8, 128, EDGE_LENS * 2), (16, 8, 64, EDGE_LENS * 2),                   # 128-row workgroups
+    (16, 8, 128, [40, 64, 7] * 22),                                            # one block per sequence, all of them 128-row
+])
+def test_attention_backward_at_tile_edges(hq, hkv, d, lens):
+    """Lengths around the 32-row tiles and the 64- and 128-row blocks of the matrix-core kernels, in both workgroup shapes
+    (the 128-row ones from 512 (sequence, kv head, block) triples on)."""
+    test_attention_backward_matches_oracle(BF, hq, hkv, d, lens, 0.0)
+
+
 def test_attention_backward_argument_errors():
     B = _B()
     z = torch.zeros(8, 2, 64, dtype=BF, device=DEV)
