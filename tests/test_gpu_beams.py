@@ -54,6 +54,35 @@ def test_beam_topk_is_bit_exact(batch, beams, vocab):
         np.testing.assert_array_equal(t2, r2["token"])
 
 
+@pytest.mark.parametrize("kind", ["all equal", "one live beam", "all dead", "one thread holds the best", "ascending"])
+@pytest.mark.parametrize("beams,vocab", [(64, 127), (64, 128), (64, 129), (20, 3333), (3, 2731), (1, 1)])
+def test_beam_topk_threshold_edges(kind, beams, vocab):
+    """The selection's threshold and tie handling at their limits: every candidate equal, most of them -inf, the winners all
+    in one thread's share (four consecutive candidates out of every 1024), every candidate better than the one before;
+    one chunk of 8192 candidates exactly, one less, one more."""
+    B = _B()
+    batch = 2
+    lp = np.zeros((batch * beams, vocab), dtype=np.float32)
+    bs = np.zeros(batch * beams, dtype=np.float32)
+    flat = lp.reshape(batch, -1)
+    if kind == "one live beam":
+        lp[:] = np.round(np.random.default_rng(3).standard_normal(lp.shape) * 4) / 4
+        bs[:] = -np.inf
+        bs[beams - 1::beams] = 0.0
+    elif kind == "all dead":
+        lp[:] = -np.inf
+    elif kind == "one thread holds the best":
+        j = np.arange(flat.shape[1])
+        flat[:] = np.where((j // 4) % 256 == 5, 1.0 + (j * 7919 % 97) / 128, 0.5)
+    elif kind == "ascending":
+        flat[:] = np.arange(flat.shape[1]) / 65536
+    ref = O.beam_topk(bs, lp, batch, beams, vocab)
+    parent, token, score = gpu_topk(B, bs, lp, batch, beams, vocab)
+    np.testing.assert_array_equal(parent, ref["parent"])
+    np.testing.assert_array_equal(token, ref["token"])
+    np.testing.assert_array_equal(score, ref["score"])
+
+
 def test_beam_argument_errors_and_limits():
     B = _B()
     z = torch.zeros(4, 8, device=DEV)
