@@ -92,6 +92,8 @@ int earn_set_validation(int enabled);
  *   "decode_mfma_wgs"       workgroups the matrix-core decode kernel's key splits aim at (256)
  *   "decode_vec_wgs"        workgroups the vector decode kernel's key splits aim at (1024)
  *   "decode_vec_waves"      waves per workgroup of the vector decode kernel (1, 2 or 4)
+ *                           (bf16 key lists of up to 768 - 2304 rows otherwise have a kernel of their own; while any
+ *                           decode_* key is set, every call takes these two)
  *   "compact_blocks"        16 KB blocks one compaction workgroup copies (1..4)
  *   "linear_tile"           1 | 2: output tile of the projection GEMMs, 256 x 128 (1) or 256 x 256 (2); default by size
  *   "linear_splits"         splits of the inner dimension when a workspace is given (default by size; 1 = none)

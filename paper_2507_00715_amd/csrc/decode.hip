@@ -409,6 +409,265 @@ __global__ __launch_bounds__(kWave * WAVES) void decode_kernel(DecodeParams p) {
                                p.chunk, sm);
 }
 
+// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS traffic, not for its global loads.
+// (__syncthreads() also drains the vector-memory queue, which would cut the depth of the K/V stream below to the one
+// super-tile a single iteration can cover.)  The empty asm statements keep the compiler from moving memory accesses
+// across the barrier.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// ------------------------------------------------------------------------------------------------------------------
+// Key lists of up to a few hundred to two thousand rows (bf16): the register caches of the later layers, short prompts.  A
+// step over register caches moves a few hundred KB to a few MB; what it costs is its chain of dependent steps, so the kernel
+// has few of them and little code: a workgroup serves one (stream, kv head), every wave takes blocks of 32 keys (shared
+// rows first, then generated rows, whose last one is the new token), requests all K and V rows of a block at once, and
+// works on the matrix cores:
+//   S^T = K Q^T   (v_mfma_f32_16x16x32_bf16: 16 keys x 16 query columns, of which the gq heads of the group are used;
+//                  the K fragments are plain 16-byte loads of key rows, straight from memory into registers)
+//   O^T += V^T P^T (V through a swizzled LDS tile of the wave's own; the accumulator layout of two S^T tiles is the B
+//                  operand of this product, with the keys in the order 4 quad + i, 16 + 4 quad + i)
+// The group's queries and the new key are rotated once per workgroup; with every wave rotating its own copy the vector ALU
+// was the limit as soon as several workgroups shared a CU (64 sequences, 32 / 8 heads of 128, 16 rows: 16.4 us a layer in
+// a batched launch, now 7.6).  Queries and probabilities enter as the sum of two bf16 operands (value and remainder),
+// which keeps 16 mantissa bits and more of them, finer than the bf16 results.  The waves' states are merged once, in LDS.
+// Long lists stream K and V at 4.9 TB/s (64 sequences of 768 rows, 8 kv heads), about what a copy reaches.
+// ------------------------------------------------------------------------------------------------------------------
+// two numbers as two words of bf16 pairs: hi = the numbers rounded, lo = the remainders rounded
+__device__ __forceinline__ void split_pair(float a, float b, unsigned& hi, unsigned& lo) {
+  hi = pack_bf16(a, b);
+  lo = pack_bf16(a - bf16_lo(hi), b - bf16_hi(hi));
+}
+
+template <int D, int WAVES>
+__global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodeParams p) {
+  constexpr int KS = D / 32, DB = D / 16, UPR = D / 8;   // k-steps, 16-row blocks of O^T, 16-byte units per row
+  constexpr int BLK = 32;                                // keys per block
+  constexpr int NV = BLK * UPR / kWave;                  // V units per lane and block
+  union Tile { __bf16 v[BLK * D]; float o[8][D]; };      // a wave's V block; at the end its unnormalised outputs
+  __shared__ Tile tile[WAVES];
+  __shared__ f32x2 ml[WAVES][8];                         // (max, sum) per query of the group
+  __shared__ __align__(16) __bf16 rot[2][9][D + 8];      // rotated queries (value, remainder) and, in row gq, the new key
+  // Workgroup -> (stream, kv head): an XCD keeps a run of consecutive streams (beams of a sequence share its cache rows,
+  // the kv heads of a stream share DRAM rows), so what they share is fetched into one L2.
+  const int per_xcd = (p.n_streams + kXcds - 1) / kXcds;
+  const int at = blockIdx.x / kXcds, u = (blockIdx.x % kXcds) * per_xcd + at / p.hkv, c = at % p.hkv;
+  if (at / p.hkv >= per_xcd || u >= p.n_streams) return;
+  const DecodeLayer lv = layer_view(p, blockIdx.y);
+  const int gq = p.hq / p.hkv;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int r16 = lane & 15, quad = lane >> 4;
+  const int s = p.stream_to_seq ? max(min(p.stream_to_seq[u], p.batch - 1), 0) : u;
+  const int g = clamp_gen_len(p.gen_len[u], p.gen_cap);
+  const float pos = (float)p.q_pos[u];
+  int b0, ns;
+  shared_bounds(p, s, b0, ns);
+  const int n_shared = (ns + BLK - 1) / BLK, n_blocks = n_shared + (g + BLK) / BLK;
+
+  const long long row_stride = (long long)p.hkv * D;
+  const __bf16* kc = (const __bf16*)lv.shared_k + ((long long)b0 * p.hkv + c) * D;
+  const __bf16* vc = (const __bf16*)lv.shared_v + ((long long)b0 * p.hkv + c) * D;
+  const long long own = ((long long)u * p.gen_cap * p.hkv + c) * D, tok = ((long long)u * p.hkv + c) * D;
+  // offset of logical generated row j in gen_k / gen_v (under beam search: in the cache of the ancestor that wrote it)
+  auto gen_row = [&](int j) {
+    int src = u;
+    if (p.gen_src) src = max(min(p.gen_src[(long long)u * p.gen_cap + j], p.n_streams - 1), 0);
+    return (((long long)src * p.gen_cap + j) * p.hkv + c) * D;
+  };
+  // K fragments: lane (r16, quad) holds elements 32 ks + 8 quad + (0..7) of key 16 t + r16 of the block; V units: unit
+  // lane + 64 i of the block's rows.  Rows past the end are not read: their keys are masked, their values are zeros.
+  bf16x8 kf[2][KS];
+  u32x4 vr[NV];
+  auto load_block = [&](int blk) {
+    const bool shared = blk < n_shared;
+    const int j0 = (shared ? blk : blk - n_shared) * BLK;
+    const int last = shared ? ns - 1 : g - 1;            // the last row that is in a cache
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int j = j0 + 16 * t + r16;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[t][ks] = bf16x8{};
+      if (j <= last) {
+        const __bf16* row = (shared ? kc + j * row_stride : (const __bf16*)lv.gen_k + gen_row(j)) + 8 * quad;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kf[t][ks] = *(const bf16x8*)(row + 32 * ks);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int unit = lane + kWave * i, j = j0 + unit / UPR;
+      vr[i] = u32x4{0u, 0u, 0u, 0u};
+      if (j <= last) vr[i] = *(const u32x4*)((shared ? vc + j * row_stride : (const __bf16*)lv.gen_v + gen_row(j)) + (unit % UPR) * 8);
+      else if (!shared && j == g) vr[i] = *(const u32x4*)((const __bf16*)lv.v_new + tok + (unit % UPR) * 8);
+    }
+  };
+  // The group's queries and the new token's key are rotated once by the workgroup, 4 rotary pairs of a row per thread,
+  // and exchanged through LDS.  Their rows are requested ahead of the keys and values, which stay in flight meanwhile.
+  const int n_items = (gq + 1) * (D / 8);
+  const int head0 = c * gq;
+  u32x2 x_lo[2], x_hi[2];
+  f32x4 th[2], tl[2];
+  constexpr int MAX_ITEMS = (9 * (D / 8) + kWave * WAVES - 1) / (kWave * WAVES);
+  static_assert(MAX_ITEMS <= 2);
+#pragma unroll
+  for (int i = 0; i < MAX_ITEMS; ++i) {
+    const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
+    if (item >= n_items) continue;
+    const __bf16* src = (row < gq ? (const __bf16*)lv.q + ((long long)u * p.hq + head_of_slot(p.heads, head0 + row)) * D
+                                  : (const __bf16*)lv.k_new + tok) + e;
+    x_lo[i] = *(const u32x2*)src;
+    x_hi[i] = *(const u32x2*)(src + D / 2);
+    if (p.rope.enabled) {
+      th[i] = f32x4{p.rope.hi[e], p.rope.hi[e + 1], p.rope.hi[e + 2], p.rope.hi[e + 3]};
+      tl[i] = f32x4{p.rope.lo[e], p.rope.lo[e + 1], p.rope.lo[e + 2], p.rope.lo[e + 3]};
+    }
+  }
+  if (wave < n_blocks) load_block(wave);
+#pragma unroll
+  for (int i = 0; i < MAX_ITEMS; ++i) {
+    const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
+    if (item >= n_items) continue;
+    float y[2][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float sn = 0.f, cs = 1.f;
+      if (p.rope.enabled) sincos_turns_fast(rope_turns(pos, th[i][j], tl[i][j]), &sn, &cs);
+      const float a = j & 1 ? bf16_hi(x_lo[i][j / 2]) : bf16_lo(x_lo[i][j / 2]);
+      const float b = j & 1 ? bf16_hi(x_hi[i][j / 2]) : bf16_lo(x_hi[i][j / 2]);
+      y[0][j] = __builtin_fmaf(a, cs, -(b * sn));   // as the general kernels round it: the appended key is the same
+      y[1][j] = __builtin_fmaf(b, cs, a * sn);
+    }
+    const float scale = row < gq ? p.scale_log2 : 1.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      unsigned h0, h1, l0, l1;
+      split_pair(y[h][0] * scale, y[h][1] * scale, h0, l0);
+      split_pair(y[h][2] * scale, y[h][3] * scale, h1, l1);
+      *(u32x2*)&rot[0][row][e + h * (D / 2)] = u32x2{h0, h1};   // the new key's value part is the key as stored
+      if (row < gq) *(u32x2*)&rot[1][row][e + h * (D / 2)] = u32x2{l0, l1};
+    }
+  }
+  lds_barrier();
+
+  f32x4 o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float mrow = -INFINITY, lrow = 0.f;                    // of query r16; lrow: this lane's keys only
+  __bf16* smv = tile[wave].v;
+  const int q_row = min(r16, gq - 1);                    // columns beyond the group repeat its last query
+  // 16 consecutive rows share a chunk of a transposing read: two rows per chunk position at most
+  auto v_swz = [](int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); };
+  for (int blk = wave; blk < n_blocks; blk += WAVES) {
+    if (blk != wave) load_block(blk);
+    const bool shared = blk < n_shared;
+    const int j0 = (shared ? blk : blk - n_shared) * BLK;
+    const int count = shared ? ns - j0 : g + 1 - j0;     // keys from j0 on
+    if (blk == n_blocks - 1) {                           // the new token: its key rotated and rounded as stored, appended
+      const int j = g - j0;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 w = *(const bf16x8*)&rot[0][gq][32 * ks + 8 * quad];
+        if (j == r16) kf[0][ks] = w;
+        if (j == 16 + r16) kf[1][ks] = w;
+        if (r16 == 0) *(bf16x8*)((__bf16*)lv.gen_k + own + g * row_stride + 32 * ks + 8 * quad) = w;
+      }
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int unit = lane + kWave * i;
+        if (unit / UPR == j) *(u32x4*)((__bf16*)lv.gen_v + own + g * row_stride + (unit % UPR) * 8) = vr[i];
+      }
+    }
+    f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 ql = *(const bf16x8*)&rot[1][q_row][32 * ks + 8 * quad], qh = *(const bf16x8*)&rot[0][q_row][32 * ks + 8 * quad];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], ql, sc[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], qh, sc[t], 0, 0, 0);
+    }
+    // V to LDS; the wave's LDS operations complete in order, so only the compiler has to keep theirs
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int unit = lane + kWave * i, row = unit / UPR;
+      *(u32x4*)(smv + row * D + (((unit % UPR) ^ v_swz(row)) << 3)) = vr[i];
+    }
+    // softmax: lane (r16, quad) holds keys 16 t + 4 quad + i of query r16
+    float m = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (16 * t + 4 * quad + i >= count) sc[t][i] = -INFINITY;
+        m = fmaxf(m, sc[t][i]);
+      }
+    m = fmaxf(m, __shfl_xor(m, 16, kWave));
+    m = fmaxf(m, __shfl_xor(m, 32, kWave));
+    const float mnew = fmaxf(mrow, m), ref = mnew == -INFINITY ? 0.f : mnew;
+    const float alpha = __builtin_amdgcn_exp2f(mrow - ref);
+    mrow = mnew;
+    u32x4 ph, pl;
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        const float a = __builtin_amdgcn_exp2f(sc[t][i] - ref), b = __builtin_amdgcn_exp2f(sc[t][i + 1] - ref);
+        sum += a + b;
+        unsigned hi, lo;
+        split_pair(a, b, hi, lo);
+        ph[2 * t + i / 2] = hi; pl[2 * t + i / 2] = lo;
+      }
+    lrow = lrow * alpha + sum;
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      const int row = 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
+      const __bf16* a0 = smv + row * D + ((chunk ^ v_swz(row)) << 3) + 4 * (r16 & 1);
+      const __bf16* a1 = smv + (row + 16) * D + ((chunk ^ v_swz(row + 16)) << 3) + 4 * (r16 & 1);
+      const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a0);
+      const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a1);
+      const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[db][i] *= alpha;
+      o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pl), o[db], 0, 0, 0);
+      o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, ph), o[db], 0, 0, 0);
+    }
+    asm volatile("" ::: "memory");
+  }
+  // merge: a wave's outputs take the place of its V block
+  lrow += __shfl_xor(lrow, 16, kWave);
+  lrow += __shfl_xor(lrow, 32, kWave);
+  if (r16 < gq) {
+#pragma unroll
+    for (int db = 0; db < DB; ++db) *(f32x4*)&tile[wave].o[r16][16 * db + 4 * quad] = o[db];
+    if (quad == 0) ml[wave][r16] = f32x2{mrow, lrow};
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < gq * UPR; i += kWave * WAVES) {
+    const int a = i / UPR, e = (i % UPR) * 8;
+    float m = -INFINITY, l = 0.f, x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) m = fmaxf(m, ml[w][a][0]);
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      if (w >= n_blocks) continue;                       // a wave without keys: its tile holds nothing but zeros
+      const float f = ml[w][a][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[w][a][0] - m);
+      l += f * ml[w][a][1];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = __builtin_fmaf(f, tile[w].o[a][e + j], x[j]);
+    }
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] *= inv;
+    Row8<__bf16>::store((__bf16*)lv.out + ((long long)u * p.hq + head_of_slot(p.heads, c * gq + a)) * D + e, x);
+  }
+}
+
 // merge the partial results of the slots: one thread per (stream, head, 8-element group)
 template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __restrict__ part_o,
@@ -472,17 +731,6 @@ constexpr int kDsSuper = 128;            // key ranges of the splits are multipl
 constexpr float kDecSumLimit = kSumLimit;  // per lane: 16 exponentials of one query row and tile
 constexpr int kMaxStreamsPerSeq = 1024;  // beams of one sequence the stream list holds
 constexpr int kDsTabStreams = 16;        // streams whose rotary factors are tabulated in LDS
-
-// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS traffic, not for its global loads.
-// (__syncthreads() also drains the vector-memory queue, which would cut the depth of the K/V stream below to the one
-// super-tile a single iteration can cover.)  The empty asm statements keep the compiler from moving memory accesses
-// across the barrier.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 template <int D>
 struct DsSmem {
@@ -1052,12 +1300,38 @@ __global__ __launch_bounds__(256 * C, 1) void decode_shared_mfma_kernel(DecodePa
 // ------------------------------------------------------------------------------------------------------------------
 struct DecodePlan {
   bool mfma;      // shared and generated rows on the matrix cores + combine
+  bool few_keys;  // decode_short_kernel instead of what the other fields plan
   int n_splits;   // key-range splits of the shared (mfma) or whole (vector) key list
   int n_slots;    // partial slots per (stream, head)
   int chunk;      // keys per split
   int n_pass;     // matrix-core kernel: passes of 64 query rows that get workgroups of their own (1: the rows of a cache
                   // beyond the first 64, if any, are taken in further passes of the same workgroup)
 };
+
+// Does decode_short_kernel take the call?  (Only the launch depends on it: workspace sizes and limits are the general
+// plan's.)  It reads the shared rows once per stream and walks them 256 at a time, so it is the faster one up to a length,
+// and with beams up to an amount of re-read rows.  us per layer, one launch per layer / 6 - 28 layers in one launch, the
+// general kernels -> this one (a launch from the host takes 6 - 7 us by itself):
+//   grouped heads, one stream per sequence: 256 sequences, 12 / 2 heads of 128, 16 rows 14.5 / 6.6 -> 7.1 / 2.1, 128 rows
+//   27.8 / 23.5 -> 14.0 / 7.8, 512 rows 42.7 / 35.1 -> 33.3 / 28.2, 2080 rows 106 / 96 -> 103 / 95; 32 sequences, 14 / 2
+//   heads of 64, 64 rows 9.3 / 1.4 -> 6.7 / 0.4, 1024 rows 17.0 / 6.5 -> 12.8 / 3.4, 2080 rows 19.4 / 10.1 -> 19.9 / 6.0;
+//   one sequence, 32 / 8 heads, 1024 rows 19.1 / 5.1 -> 17.5 / 6.0, 1536 rows 21.1 / 5.8 -> 22.9 / 8.0.  So: 1024 keys, and
+//   2304 where the (stream, kv head) pairs fill the GPU twice over, which leaves the key splits nothing to win.
+//   single heads: the vector kernel wastes no query columns, but its fewer rows in flight only pay with many workgroups:
+//   256 pairs, 64 rows 13.0 -> 7.3, 512 rows 24.6 -> 18.8; 4 sequences of 4 heads, 1024 rows 11.5 -> 12.0; 2048 pairs, 32
+//   rows 15.4 / 8.7 -> 15.7 / 8.9.  So: up to 512 pairs and 768 keys.
+//   beams, 16 sequences x 10 of 32 / 8 heads: 32 rows 15.3 / 6.9 -> 8.6 / 4.4, 64 rows 15.4 / 6.8 -> 13.4 / 7.1, 128 rows
+//   16.5 / 7.7 -> 19.8 / 12.2; 32 x 4 of 12 / 2 heads, 128 rows 12.7 / 3.1 -> 8.2 / 2.7, 256 rows 16.9 / 3.8 -> 10.7 / 7.2,
+//   512 rows 19.9 -> 14.4.  So: 128 K rows re-read, 48 K per layer where the layers share a launch.
+static bool decode_few_keys(int dtype, int hq, int hkv, int n_streams, int batch, int max_shared_len, int gen_cap, int n_layers) {
+  if (dtype != EARN_BF16) return false;
+  for (Tuning t : {kTuneDecMfmaMinLen, kTuneDecMfmaShortWgs, kTuneDecMfmaWgs, kTuneDecVecWgs, kTuneDecVecWaves})
+    if (tuning(t, 0) != 0) return false;                 // a caller who sets the general kernels' launch shape gets them
+  const long long pairs = (long long)n_streams * hkv, keys = (long long)max_shared_len + gen_cap;
+  if (n_streams > batch) return pairs * max_shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024;
+  if (hq == hkv) return pairs * n_layers <= 512 && keys <= 768;
+  return keys <= (pairs * n_layers >= 512 ? 2304 : 1024);
+}
 
 static DecodePlan plan_decode(int dtype, int hq, int hkv, int n_streams, int batch, int max_shared_len, int gen_cap,
                               int n_layers = 1) {
@@ -1073,6 +1347,7 @@ static DecodePlan plan_decode(int dtype, int hq, int hkv, int n_streams, int bat
   pl.mfma = dtype == EARN_BF16 && (gq > 1 || n_streams > batch) &&
             (max_shared_len >= mfma_min || (long long)hkv * batch * n_layers <= mfma_wgs || n_streams >= 2 * batch);
   pl.n_pass = 1;
+  pl.few_keys = decode_few_keys(dtype, hq, hkv, n_streams, batch, max_shared_len, gen_cap, n_layers);
   if (pl.mfma) {
     // Beams beyond 64 query rows per cache (say 20 beams of 7 grouped heads) would make a workgroup walk its keys once
     // per 64 rows.  Planned from the average beam count, every such pass gets workgroups of its own, with fewer key
@@ -1136,6 +1411,16 @@ static void launch_vector(const DecodeParams& p, int gq, dim3 grid, hipStream_t 
   else launch_vector_w<T, D, 4>(p, gq, grid, stream);
 }
 
+// a wave per block of 32 keys for short lists (the generated rows make a block of their own), eight for longer ones
+template <int D>
+static void launch_short(const DecodeParams& p, hipStream_t stream, int n_layers) {
+  const dim3 grid((unsigned)((p.n_streams + kXcds - 1) / kXcds * kXcds * p.hkv), n_layers, 1);
+  if (p.max_shared_len <= 32) hipLaunchKernelGGL((decode_short_kernel<D, 2>), grid, dim3(128), 0, stream, p);
+  else if (p.max_shared_len <= 64) hipLaunchKernelGGL((decode_short_kernel<D, 3>), grid, dim3(192), 0, stream, p);
+  else if (p.max_shared_len <= 128) hipLaunchKernelGGL((decode_short_kernel<D, 4>), grid, dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL((decode_short_kernel<D, 8>), grid, dim3(512), 0, stream, p);
+}
+
 template <typename T, int D>
 static void launch_combine(const DecodeParams& p, hipStream_t stream, int n_layers = 1) {
   const int rows = p.n_streams * p.hq;
@@ -1146,6 +1431,9 @@ static void launch_combine(const DecodeParams& p, hipStream_t stream, int n_laye
 
 template <typename T, int D>
 static void launch_decode_t(DecodeParams& p, const DecodePlan& pl, int gq, hipStream_t stream, int n_layers) {
+  if constexpr (sizeof(T) == 2) {
+    if (pl.few_keys) { launch_short<D>(p, stream, n_layers); return; }
+  }
   if (!pl.mfma) {
     launch_vector<T, D>(p, gq, dim3((unsigned)(((long long)p.n_streams * p.n_splits + 7) / 8 * 8 * p.hkv), n_layers, 1), stream);
     if (p.n_slots > 1) launch_combine<T, D>(p, stream, n_layers);

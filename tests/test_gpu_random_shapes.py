@@ -160,3 +160,63 @@ def test_compaction_random_shape(case):
     np.testing.assert_array_equal(cu_c.cpu().numpy(), ref["cu"])
     for s, dd in zip(srcs, d_dst):
         assert np.array_equal(dd.cpu().numpy(), O.compact_registers(s.numpy(), cu, h, t)["dst"])
+
+
+# Short and medium key lists have a kernel of their own (blocks of 32 keys dealt to 2, 3, 4 or 8 waves); setting any launch
+# shape of the general decode kernels sends the call to those.  Both against the oracle, at the edges of the blocks, of the
+# wave counts and of the rule that chooses, with generated parts of one and several blocks, and through an ancestor table.
+SHORT_CASES = [
+    # hq, hkv, d, shared lengths, streams per sequence, gen_cap, generated lengths (cycled), ancestor table
+    (4, 4, 128, [0, 1, 31, 32], 1, 1, [0], False),
+    (12, 2, 128, [33, 63, 64, 2], 1, 34, [31, 32, 33, 0], False),
+    (14, 2, 64, [65, 96, 97, 127], 1, 5, [4, 0, 3], False),
+    (16, 2, 128, [128, 129, 255], 1, 3, [2, 1], False),
+    (2, 1, 64, [256, 257, 1000, 955], 1, 24, [23, 0, 11], False),
+    (8, 2, 64, [30, 33, 64], 5, 8, [7, 0, 3, 6], True),
+    (3, 3, 128, [60, 257], 3, 70, [69, 32, 31, 64], True),
+]
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("hq,hkv,d,slens,beams,gen_cap,glens,table", SHORT_CASES)
+def test_decode_short_key_lists(hq, hkv, d, slens, beams, gen_cap, glens, table, general):
+    B = _B()
+    batch, S = len(slens), len(slens) * beams
+    g = torch.Generator().manual_seed(sum(slens) + hq)
+    rnd = lambda *shape: torch.randn(*shape, generator=g).to(torch.bfloat16)
+    s2s = [u // beams for u in range(S)]
+    glens = [glens[u % len(glens)] for u in range(S)]
+    cu = np.concatenate([[0], np.cumsum(slens)]).astype(np.int32)
+    sk, sv, q, kn, vn = rnd(int(cu[-1]), hkv, d), rnd(int(cu[-1]), hkv, d), rnd(S, hq, d), rnd(S, hkv, d), rnd(S, hkv, d)
+    gk, gv = rnd(S, gen_cap, hkv, d), rnd(S, gen_cap, hkv, d)
+    q_pos = [slens[s2s[u]] + glens[u] for u in range(S)]
+    o_gk, o_gv, src = W.to_f64(gk), W.to_f64(gv), None
+    if table:   # the oracle's streams own copies of the rows that the table names
+        # an ancestor's row must not be one that this call appends
+        src = torch.tensor([[next(w for w in range((u * 7 + j) % S, 2 * S) if glens[w % S] != j) % S for j in range(gen_cap)]
+                            for u in range(S)], dtype=torch.int32)
+        o_gk, o_gv = (x[src.numpy(), np.arange(gen_cap)[None, :]].copy() for x in (o_gk, o_gv))
+    ref = O.decode_attn(W.to_f64(q), W.to_f64(kn), W.to_f64(vn), q_pos, W.to_f64(sk), W.to_f64(sv), cu, s2s, o_gk, o_gv, glens)
+    i32 = lambda x: torch.tensor(list(x), dtype=torch.int32, device=DEV)
+    dev = lambda x: x.to(DEV)
+    desc = B.make_desc(torch.bfloat16, hq, hkv, d)
+    d_gk, d_gv, out = dev(gk), dev(gv), torch.full((S, hq, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(max(B.earn_decode_workspace_bytes(desc, S, batch, max(slens), gen_cap), 256), dtype=torch.uint8, device=DEV)
+    args = (desc, dev(q), dev(kn), dev(vn), i32(q_pos), dev(sk), dev(sv), i32(cu), i32(s2s), d_gk, d_gv, i32(glens))
+    if general:
+        B.earn_set_tuning("decode_vec_wgs", 1024)   # the default, set: the general kernels
+    try:
+        if table:
+            B.earn_decode_attn_beams(*args, dev(src), gen_cap, S, batch, max(slens), out, ws)
+        else:
+            B.earn_decode_attn(*args, gen_cap, S, batch, max(slens), out, ws)
+        torch.cuda.synchronize()
+    finally:
+        if general:
+            B.earn_set_tuning("decode_vec_wgs", 0)
+    check(out, ref["out"], torch.bfloat16, "outputs")
+    at = torch.arange(S)
+    check(d_gk.cpu()[at, glens], o_gk[np.arange(S), glens], torch.bfloat16, "appended keys")
+    expect_k, expect_v = gk.clone(), gv.clone()
+    expect_k[at, glens], expect_v[at, glens] = d_gk.cpu()[at, glens], vn
+    assert torch.equal(d_gk.cpu(), expect_k) and torch.equal(d_gv.cpu(), expect_v)
