@@ -7,8 +7,8 @@
 //                        then reads rotated keys, so the sin/cos work is O(T), not O(T * blocks).
 //   prefill_pipe_kernel  bf16 flash-style attention on the matrix cores (v_mfma_f32_32x32x16_bf16), software pipelined:
 //                        long sequences.
-//   prefill_mfma_kernel  the same arithmetic in a plain per-tile schedule with smaller workgroups: medium sequences and
-//                        the register-only layers.
+//   prefill_mfma_kernel  the same arithmetic in a plain per-tile schedule with smaller workgroups: medium sequences.
+//   prefill_short_kernel rotation and attention of a whole (sequence, kv head) in one workgroup: the register-only layers.
 //   prefill_rows_kernel  fp32 attention on the vector ALU: one query row per 4 lanes. Used for the fp32
 //                        configuration, where the 1e-4 tolerance rules out bf16 operands.
 //
@@ -22,6 +22,8 @@
 //   transposing LDS reads (ds_read_b64_tr_b16: 4 consecutive keys of one d column) deliver from a V tile kept in its
 //   natural [key][d] layout.
 //   Each wave owns 32 query rows; the 64-key K/V tile in LDS is shared by the waves of a workgroup.
+#include <algorithm>
+
 #include "common.h"
 #include "mfma_tiles.h"
 
@@ -373,9 +375,9 @@ __device__ __forceinline__ void pf_store_row(__bf16* orow /* row + 4 hf */, cons
 // Plain schedule: per tile  barrier -> S^T -> exponentials -> O^T.  One 32-query column block per wave.
 //   WAVES = 4: 128 query rows per workgroup, two workgroups per CU: less idle time on the causal diagonal of medium
 //              sequences than 256-row workgroups, at the price of staging every K/V tile twice as often.
-//   WAVES = 2, STAGES = 1: the register-only-layer variant: every sequence fits one K/V tile, so there is nothing to
-//              double buffer, and the small footprint lets 4 workgroups share a CU, which is what hides the
-//              load -> rotate -> multiply latency chain of these tiny problems.
+//   WAVES = 2, STAGES = 1: sequences of one K/V tile with a kv head per query head: there is nothing to double buffer, and
+//              the small footprint lets 4 workgroups share a CU, which is what hides the load -> rotate -> multiply
+//              latency chain of these tiny problems.
 // ------------------------------------------------------------------------------------------------------------------
 //
 // Life-cycle timers, compiled in only with -DEARN_PF_TIMELINE (paper_2507_00715_amd/timeline.py builds that variant
@@ -564,6 +566,193 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
   pf_store_row<D>((__bf16*)lv.out + ((long long)(b0 + qi) * p.hq + blk.a) * D + 4 * hf, o, 1.f / ltot);
   if (lv.lse && hf == 0) lv.lse[(long long)(b0 + qi) * p.hq + blk.a] = (mrow + __builtin_log2f(ltot)) * 0.6931471805599453f;
   PF_STAMP(5);
+}
+
+// ------------------------------------------------------------------------------------------------------------------
+// Short sequences (up to NR rows): the register-only layers and short prompts.  One workgroup takes a whole (sequence, kv
+// head): it rotates the keys once, keeps them in LDS (and writes the cache copy), and its waves then take the gq * n query
+// rows of the group, packed head after head, 16 at a time, on v_mfma_f32_16x16x32_bf16:
+//   S^T = K Q^T   (16 keys x 16 rows per product; K rows padded to spread the fragment reads over the banks)
+//   O^T = V^T P^T (V in swizzled rows; the accumulators of two S^T tiles are the B operand, keys in the order 4 quad + i,
+//                  16 + 4 quad + i, which is what two transposing reads deliver)
+// All scores of a row fit the registers, so the softmax is exact and taken once.  What bounds these layers is the number of
+// dependent steps, not arithmetic: a rotation pass of its own, one workgroup per query head and 32-row column blocks that a
+// 16-row sequence half fills cost 24.2 + 5.3 us where this kernel takes 12 (256 sequences of 16 rows, 12 / 2
+// heads of 128; one launch per layer 29.8 -> 13.4 us, 24 layers in one launch 18.9 -> 8.2 us each).
+// ------------------------------------------------------------------------------------------------------------------
+template <int D, int NR, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void prefill_short_kernel(PrefillParams p, const void* k_in, long long ls_k_in, int store_k, int parts) {
+  constexpr int KS = D / 32, DB = D / 16, UPR = D / 8, NB = NR / 32, THREADS = 64 * WAVES;
+  constexpr int KI = NR * (D / 8) / THREADS, VI = NR * UPR / THREADS;   // K items (4 rotary pairs), V units per thread
+  constexpr int KP = D + 8, CP = D / 2 + 2;                             // row pitches of the K tile and of the rotary table
+  static_assert(KI >= 1 && KI * THREADS == NR * (D / 8) && VI >= 1 && THREADS % (D / 2) == 0);
+  __shared__ __align__(16) __bf16 smk[NR * KP];
+  __shared__ __align__(16) __bf16 smv[NR * D];
+  __shared__ __align__(16) f32x2 smc[NR * CP];
+  // an XCD takes a run of consecutive sequences; the kv heads of a sequence, whose rows are interleaved, stay together
+  const int per_xcd = (p.batch + kXcds - 1) / kXcds, per_seq = p.hkv * parts;
+  const int at = blockIdx.x / kXcds, s = (blockIdx.x % kXcds) * per_xcd + at / per_seq, c = at % per_seq % p.hkv, part = at % per_seq / p.hkv;
+  if (at / per_seq >= per_xcd || s >= p.batch) return;
+  int b0, n;
+  pf_seq_bounds(p, s, b0, n);
+  // this wave's first 16 query rows, and the rows to its next ones
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), m_first = 16 * (part * WAVES + wave), m_step = 16 * WAVES * parts;
+  if (n <= 0 || (part > 0 && 16 * part * WAVES >= p.hq / p.hkv * n)) return;
+  const PfLayer lv = pf_layer_view(p, blockIdx.y);
+  const int gq = p.hq / p.hkv, rows = gq * n;
+  const int lane = threadIdx.x % kWave, r16 = lane & 15, quad = lane >> 4;
+  const __bf16* kg = (const __bf16*)pf_layer_ptr(k_in, ls_k_in, blockIdx.y) + ((long long)b0 * p.hkv + c) * D;
+  const __bf16* vg = (const __bf16*)lv.v + ((long long)b0 * p.hkv + c) * D;
+  const long long row_stride = (long long)p.hkv * D;
+  // everything that comes from memory is requested before anything is used
+  u32x2 k_lo[KI], k_hi[KI];
+#pragma unroll
+  for (int i = 0; i < KI; ++i) {
+    const int item = threadIdx.x + i * THREADS, row = item / (D / 8), e = item % (D / 8) * 4;
+    if (row >= n) continue;
+    k_lo[i] = *(const u32x2*)(kg + row * row_stride + e);
+    k_hi[i] = *(const u32x2*)(kg + row * row_stride + e + D / 2);
+  }
+  u32x4 vr[VI];
+#pragma unroll
+  for (int i = 0; i < VI; ++i) {
+    const int unit = threadIdx.x + i * THREADS, row = unit / UPR;
+    vr[i] = u32x4{0u, 0u, 0u, 0u};       // rows past the end: weight 0, so the values must be finite
+    if (row < n) vr[i] = *(const u32x4*)(vg + row * row_stride + (unit % UPR) * 8);
+  }
+  // packed query row m is row m % n of the group's head m / n
+  u32x4 qr[KS];
+  auto q_index = [&](int m) { return (long long)(b0 + m % n) * p.hq + head_of_slot(p.heads, c * gq + m / n); };
+  auto load_q = [&](int m) {
+    const __bf16* q = (const __bf16*)lv.q + q_index(m) * D + 8 * quad;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qr[ks] = *(const u32x4*)(q + 32 * ks);
+  };
+  if (m_first < rows) load_q(min(m_first + r16, rows - 1));
+  if (p.rope.enabled) {
+    const int e = threadIdx.x % (D / 2);
+    const float hi = p.rope.hi[e], lo = p.rope.lo[e];
+    for (int row = threadIdx.x / (D / 2); row < n; row += THREADS / (D / 2)) {
+      const int pos = p.positions ? p.positions[b0 + row] : row;
+      float sn, cs;
+      sincos_turns_fast(rope_turns((float)pos, hi, lo), &sn, &cs);
+      smc[row * CP + e] = f32x2{cs, sn};
+    }
+    __syncthreads();
+  }
+  auto v_swz = [](int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); };
+#pragma unroll
+  for (int i = 0; i < KI; ++i) {
+    const int item = threadIdx.x + i * THREADS, row = item / (D / 8), e = item % (D / 8) * 4;
+    if (row >= n) continue;
+    if (p.rope.enabled) {
+      float x[4], y[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x2 t = smc[row * CP + e + j];
+        const float a = j & 1 ? bf16_hi(k_lo[i][j / 2]) : bf16_lo(k_lo[i][j / 2]);
+        const float b = j & 1 ? bf16_hi(k_hi[i][j / 2]) : bf16_lo(k_hi[i][j / 2]);
+        x[j] = __builtin_fmaf(a, t[0], -(b * t[1]));
+        y[j] = __builtin_fmaf(b, t[0], a * t[1]);
+      }
+      k_lo[i] = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+      k_hi[i] = u32x2{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+    }
+    *(u32x2*)(smk + row * KP + e) = k_lo[i];
+    *(u32x2*)(smk + row * KP + e + D / 2) = k_hi[i];
+    if (store_k && part == 0) {
+      __bf16* dst = (__bf16*)lv.k_rot + ((long long)(b0 + row) * p.hkv + c) * D + e;
+      *(u32x2*)dst = k_lo[i];
+      *(u32x2*)(dst + D / 2) = k_hi[i];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < VI; ++i) {
+    const int unit = threadIdx.x + i * THREADS, row = unit / UPR;
+    *(u32x4*)(smv + row * D + (((unit % UPR) ^ v_swz(row)) << 3)) = vr[i];
+  }
+  __syncthreads();
+
+  for (int m0 = m_first; m0 < rows; m0 += m_step) {
+    const int m = min(m0 + r16, rows - 1), qi = m % n;     // this lane's query row sees keys 0 .. qi
+    const long long io = q_index(m);
+    bf16x8 qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS / 2; ++ks) {
+      u32x4 wl, wh;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        f32x4 t = {1.f, 0.f, 1.f, 0.f};                    // (cos, sin) of pairs 32 ks + 8 quad + 2 j, + 1
+        if (p.rope.enabled) t = *(const f32x4*)&smc[qi * CP + 32 * ks + 8 * quad + 2 * j];
+        const float a0 = bf16_lo(qr[ks][j]), a1 = bf16_hi(qr[ks][j]);
+        const float c0 = bf16_lo(qr[ks + KS / 2][j]), c1 = bf16_hi(qr[ks + KS / 2][j]);
+        wl[j] = pack_bf16((a0 * t[0] - c0 * t[1]) * p.scale_log2, (a1 * t[2] - c1 * t[3]) * p.scale_log2);
+        wh[j] = pack_bf16((c0 * t[0] + a0 * t[1]) * p.scale_log2, (c1 * t[2] + a1 * t[3]) * p.scale_log2);
+      }
+      qf[ks] = __builtin_bit_cast(bf16x8, wl);
+      qf[ks + KS / 2] = __builtin_bit_cast(bf16x8, wh);
+    }
+    if (m0 + m_step < rows) load_q(min(m0 + m_step + r16, rows - 1));   // arrives while this one is worked on
+    // key blocks that some row of the 16 sees: rows of one head run on, a second head starts again at 0
+    const int last = m0 / n == min(m0 + 15, rows - 1) / n ? min(m0 + 15, rows - 1) % n : n - 1;
+    const int blocks = last / 32 + 1;
+    f32x4 sc[2 * NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (b >= blocks) continue;
+#pragma unroll
+      for (int t = 2 * b; t < 2 * b + 2; ++t) {
+        sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)(smk + (16 * t + r16) * KP + 32 * ks + 8 * quad), qf[ks], sc[t], 0, 0, 0);
+      }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 2 * NB; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (t / 2 >= blocks || 16 * t + 4 * quad + i > qi) sc[t][i] = -INFINITY;
+        mx = fmaxf(mx, sc[t][i]);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+    mx = half_max(mx);                                     // finite: every row sees key 0
+    f32x4 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float s0 = 0.f, s1 = 0.f;                              // row sums over the rounded weights
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (b >= blocks) continue;
+      u32x4 w;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4& x = sc[2 * b + j / 2];
+        w[j] = pack_bf16(__builtin_amdgcn_exp2f(x[2 * (j & 1)] - mx), __builtin_amdgcn_exp2f(x[2 * (j & 1) + 1] - mx));
+        add_pair(j & 1 ? s1 : s0, w[j]);
+      }
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        const int row = 32 * b + 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
+        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smv + row * D + ((chunk ^ v_swz(row)) << 3) + 4 * (r16 & 1)));
+        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smv + (row + 16) * D + ((chunk ^ v_swz(row + 16)) << 3) + 4 * (r16 & 1)));
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+        o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, w), o[db], 0, 0, 0);
+      }
+    }
+    float sum = add_chains(s0, s1);
+    sum += __shfl_xor(sum, 16, kWave);
+    sum = half_sum(sum);
+    if (m0 + r16 >= rows) continue;
+    const float inv = 1.f / sum;
+    __bf16* orow = (__bf16*)lv.out + io * D + 4 * quad;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      *(u32x2*)(orow + 16 * db) = u32x2{pack_bf16(o[db][0] * inv, o[db][1] * inv), pack_bf16(o[db][2] * inv, o[db][3] * inv)};
+    if (lv.lse && quad == 0) lv.lse[io] = (mx + __builtin_log2f(sum)) * 0.6931471805599453f;
+  }
 }
 
 // ------------------------------------------------------------------------------------------------------------------
@@ -901,6 +1090,15 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   p.rope = make_rope_table(desc->rope_base, d);
   if (make_head_map(desc, &p.heads, "earn_prefill_attn") != EARN_OK) return EARN_ERR_UNSUPPORTED;
   const bool f32 = desc->dtype == EARN_F32;
+  // prefill_short_kernel: grouped heads up to 128 rows, single heads up to 32.  us per layer with rotation, one launch per
+  // layer / 24 layers in one launch, the kernels of longer sequences (and a rotation pass) -> this one:
+  //   256 sequences, 12 / 2 heads of 128: 16 rows 29.8 / 18.9 -> 13.4 / 8.2, 64 rows 60.0 / 44.7 -> 41.0 / 32.4, 128 rows
+  //   105.9 / 90.5 -> 81.2 / 71.0; 64 sequences, 32 / 8 heads: 64 rows 43.2 / 31.3 -> 29.0 / 23.4, 128 rows 75.7 / 63.0 ->
+  //   61.0 / 49.9; 32 sequences, 14 / 2 heads of 64: 16 rows 9.4 / 1.6 -> 6.6 / 0.7, 128 rows 16.2 / 7.2 -> 12.5 / 5.1.
+  //   64 sequences, 32 / 32 heads, where every workgroup has keys of its own to stage and little to multiply: 32 rows
+  //   34.4 / 27.4 -> 29.5 / 21.8, 64 rows 57.6 / 53.4 -> 60.6 / 46.6 (without rotation 38.7 -> 40.4), 96 rows 85 / 75 ->
+  //   95 / 80.
+  const bool few_rows = max_seqlen <= (p.hq > p.hkv ? 128 : 32);
   if (f32) {
     if (!in_place) {
       if (d == 64) launch_rope_k<float, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
@@ -909,8 +1107,26 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
     dim3 grid((max_seqlen + 63) / 64, p.hq, batch * n_layers);
     if (d == 64) hipLaunchKernelGGL((prefill_rows_kernel<float, 64>), grid, dim3(256), 0, stream, p);
     else hipLaunchKernelGGL((prefill_rows_kernel<float, 128>), grid, dim3(256), 0, stream, p);
+  } else if (few_rows) {
+    auto launch = [&](auto kernel, int waves) {
+      // pairs of (sequence, kv head); groups of 16 query rows in a pair
+      const long long pairs = (long long)batch * p.hkv * n_layers, groups = ((long long)(p.hq / p.hkv) * max_seqlen + 15) / 16;
+      // few pairs: several workgroups per pair, each with its own copy of the keys, up to 512 of them (2 sequences, 32 / 8
+      // heads, 64 rows: 17.0 -> 10.2 us; up to 1024 gives 33.6 against 29.0 us at 64 sequences)
+      // (keys rotated in place have one reader: the others would race with its stores)
+      const int parts = k == k_rot_out ? 1 : (int)std::max<long long>(1, std::min<long long>((groups + waves - 1) / waves, 512 / pairs));
+      const dim3 grid((unsigned)((long long)(batch + kXcds - 1) / kXcds * kXcds * p.hkv * parts), n_layers, 1);
+      hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, stream, p, k, ls_k, k_rot_out ? 1 : 0, parts);
+    };
+    if (max_seqlen <= 32) {
+      if (d == 64) launch(prefill_short_kernel<64, 32, 4>, 4); else launch(prefill_short_kernel<128, 32, 4>, 4);
+    } else if (max_seqlen <= 64) {
+      if (d == 64) launch(prefill_short_kernel<64, 64, 4>, 4); else launch(prefill_short_kernel<128, 64, 4>, 4);
+    } else {
+      if (d == 64) launch(prefill_short_kernel<64, 128, 8>, 8); else launch(prefill_short_kernel<128, 128, 8>, 8);
+    }
   } else if (max_seqlen <= kTileKeys) {
-    // register-only layers: every sequence is a single K/V tile
+    // single heads, one K/V tile
     if (!in_place) {
       if (d == 64) launch_rope_k<__bf16, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
       else launch_rope_k<__bf16, 128>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);

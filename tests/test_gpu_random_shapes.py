@@ -220,3 +220,38 @@ def test_decode_short_key_lists(hq, hkv, d, slens, beams, gen_cap, glens, table,
     expect_k, expect_v = gk.clone(), gv.clone()
     expect_k[at, glens], expect_v[at, glens] = d_gk.cpu()[at, glens], vn
     assert torch.equal(d_gk.cpu(), expect_k) and torch.equal(d_gv.cpu(), expect_v)
+
+
+# Short sequences have a prefill kernel of their own (32, 64 or 128 rows; a pair's query rows in groups of 16 dealt to waves
+# and, with few pairs, to several workgroups): the edges of the groups, of the 32-key blocks and of the row limits, sequences
+# of one row and none, explicit positions, with and without rotation, a cache copy and the log-sum-exp.
+@pytest.mark.parametrize("rope,keep_keys", [(True, True), (True, False), (False, True), (False, False)])
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (4, 4, 128, [32, 1, 0, 17]), (12, 2, 128, [16, 15, 31]), (7, 1, 64, [33, 64, 63, 2]), (32, 8, 128, [64] * 70),
+    (6, 2, 128, [65, 96, 97, 128]), (8, 4, 64, [127, 3, 128])])
+def test_prefill_short_sequences(hq, hkv, d, lens, rope, keep_keys):
+    B = _B()
+    T, batch = sum(lens), len(lens)
+    g = torch.Generator().manual_seed(T + hq)
+    rnd = lambda heads: torch.randn(T, heads, d, generator=g).to(torch.bfloat16)
+    q, k, v = rnd(hq), rnd(hkv), rnd(hkv)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    pos = np.concatenate([np.sort(np.random.default_rng(n).choice(4000, n, replace=False)) for n in lens]).astype(np.int32)
+    base = 10000.0 if rope else 0.0
+    desc = B.make_desc(torch.bfloat16, hq, hkv, d, 0.0, base)
+    out = torch.full((T, hq, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((T, hq), float("nan"), dtype=torch.float32, device=DEV)
+    d_k = k.to(DEV)
+    k_rot = torch.full_like(d_k, float("nan")) if keep_keys else None
+    ws = torch.empty(max(B.earn_prefill_workspace_bytes(desc, batch, T, max(lens), keep_keys), 256), dtype=torch.uint8, device=DEV)
+    B.earn_prefill_attn(desc, q.to(DEV), d_k, v.to(DEV), torch.from_numpy(cu).to(DEV), torch.from_numpy(pos).to(DEV), batch, T,
+                        max(lens), out, k_rot, lse, ws)
+    torch.cuda.synchronize()
+    ref = O.prefill_attn(W.to_f64(q), W.to_f64(k), W.to_f64(v), cu, pos, rope_base=base)
+    for s in range(batch):
+        check(out[cu[s]:cu[s + 1]], ref["out"][cu[s]:cu[s + 1]], torch.bfloat16, f"sequence {s}")
+    # a score's terms are rounded to 2^-9 of themselves in both operands: 2 * 2^-9 * |q||k| / sqrt(d) <~ 2^-8 * sqrt(d) * 1.5
+    assert float((lse.cpu().double() - torch.from_numpy(ref["lse"])).abs().max()) <= 1.5 * d ** 0.5 / 256
+    if keep_keys:
+        check(k_rot, ref["k_rot"], torch.bfloat16, "rotated keys")
+        assert rope or torch.equal(k_rot, d_k)
