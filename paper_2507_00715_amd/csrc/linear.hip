@@ -19,6 +19,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "mfma_tiles.h"
@@ -285,6 +286,142 @@ __global__ __launch_bounds__(64 * (8 / RB) * WC, 1) void linear_kernel(LinearPar
   }
 }
 
+// Products of few rows (decode steps, small batches).  A tile of linear_kernel is 256 rows whatever the product has, so its
+// time is the same at 1 row as at 256 (0.86 us per K-tile of 64), on a third of the CUs: 1 row, k 4096, 11008 outputs 59 us,
+// here 21, with 18 for the weights' bytes at the rate of a large copy.  Here a tile is 32 NRB rows, just enough for the product's, x 64 columns, so two to eight
+// times as many workgroups share the weights and none multiplies padding beyond a 32-row block.  The four waves take one
+// 16-index step of every K-tile each (every byte of a tile is read from LDS once), and add their sums through LDS at the
+// end.  The ring of K-tiles takes most of the LDS: the weights' latency times rate is what has to be in flight.
+template <int NRB>
+constexpr int few_stages() { return NRB <= 2 ? 8 : NRB == 3 ? 7 : NRB == 4 ? 6 : 5; }
+template <int NRB>
+__global__ __launch_bounds__(256, 1) void linear_few_rows_kernel(LinearParams p) {
+  constexpr int ROWS = 32 * NRB, COLS = 64, KT = 64, S = few_stages<NRB>(), XI = NRB, WI = 2, LPT = XI + WI;
+  struct Stage { __bf16 x[ROWS * KT], w[COLS * KT]; };
+  union Shared { Stage ring[S]; f32x4 sum[4][4][4][kWave]; };   // at the end: [wave][tile of the round][quarter][lane]
+  __shared__ Shared sm;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int r32 = lane & 31, hf = lane >> 5;
+  const int n0 = blockIdx.x * COLS, kt0 = blockIdx.y * p.split_tiles, n_kt = min(p.k / KT - kt0, p.split_tiles);
+  const int pitch = p.k * 2;   // bytes, of activation and weight rows alike
+  const u32x4 x_rsrc = raw_buffer(p.x, p.rows * pitch), w_rsrc = raw_buffer(p.w + (long long)n0 * p.k, min(COLS, p.n - n0) * pitch);
+  // a load instruction fills 8 rows of 8 chunks; rows past the end of either operand read as zeros
+  int x_voff[XI], w_voff[WI];
+#pragma unroll
+  for (int i = 0; i < XI; ++i) {
+    const int row = 8 * (wave + 4 * i) + lane / 8;
+    x_voff[i] = row * pitch + ((lane % 8) ^ swz<64>(row)) * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < WI; ++i) {
+    const int row = 8 * (wave + 4 * i) + lane / 8;
+    w_voff[i] = row * pitch + ((lane % 8) ^ swz<64>(row)) * 16;
+  }
+  const unsigned lds = (unsigned)(size_t)(lds_void_ptr)&sm.ring[0];
+  auto issue = [&](int kt) {
+    const unsigned to = lds + (unsigned)((kt % S) * sizeof(Stage) + wave * 1024);
+    const int off = (kt0 + kt) * (KT * 2);
+#pragma unroll
+    for (int i = 0; i < WI; ++i) dma16_to_lds(w_rsrc, to + (unsigned)(ROWS * KT * 2 + i * 4096), w_voff[i] + off);
+#pragma unroll
+    for (int i = 0; i < XI; ++i) dma16_to_lds(x_rsrc, to + (unsigned)(i * 4096), x_voff[i] + off);
+  };
+#pragma unroll
+  for (int t = 0; t < S; ++t)
+    if (t < n_kt) issue(t);
+  f32x16 acc[NRB][2];
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[rb][cb][i] = 0.f;
+  // Tile kt is complete behind this barrier, and the fragments of the tile before are in every wave's registers.  Loads
+  // complete in order: at most `LATER` tiles' loads may still be in flight (none, when fewer than that were issued).
+  auto await = [&](int kt, auto later_c) {
+    constexpr int LATER = decltype(later_c)::value;
+    if (kt + LATER < n_kt) wait_vmcnt<LATER * LPT>(); else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  const int frag = (r32 * KT + ((hf ^ swz<64>(r32)) << 3)) ^ (wave << 4);   // step `wave` of the K-tile
+  bf16x8 xf[2][NRB], wf[2][2];
+  auto fetch = [&](int kt, int b) {
+    const Stage& st = sm.ring[kt % S];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) wf[b][cb] = *(const bf16x8*)(st.w + cb * 32 * KT + frag);
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) xf[b][rb] = *(const bf16x8*)(st.x + rb * 32 * KT + frag);
+  };
+  await(0, std::integral_constant<int, S - 1>{});
+  fetch(0, 0);
+  // fragments of the next tile are requested ahead of the products of this one
+  auto step = [&](int kt, auto b_c) {
+    constexpr int b = decltype(b_c)::value;
+    if (kt + 1 < n_kt) {
+      await(kt + 1, std::integral_constant<int, S - 2>{});
+      if (kt + S < n_kt) issue(kt + S);
+      fetch(kt + 1, b ^ 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+        acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][cb], xf[b][rb], acc[rb][cb], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int kt = 0; kt < n_kt; kt += 2) {
+    step(kt, std::integral_constant<int, 0>{});
+    if (kt + 1 < n_kt) step(kt + 1, std::integral_constant<int, 1>{});
+  }
+  // The waves' sums, four 32 x 32 tiles a round: wave w finishes tile 4 round + w, adding in wave order.  Lane (r32, hf)
+  // holds, of row 32 rb + r32, columns n0 + 32 cb + 8 j + 4 hf + (0..3).
+#pragma unroll
+  for (int t0 = 0; t0 < 2 * NRB; t0 += 4) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (t0 + i < 2 * NRB) {
+        const f32x16& a = acc[(t0 + i) / 2][(t0 + i) % 2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sm.sum[wave][i][j][lane] = f32x4{a[4 * j], a[4 * j + 1], a[4 * j + 2], a[4 * j + 3]};
+      }
+    __syncthreads();
+    const int t = t0 + wave, m = 32 * (t / 2) + r32;
+    if (t >= 2 * NRB || m >= p.rows) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int col = n0 + 32 * (t % 2) + 8 * j + 4 * hf;
+      if (col >= p.n) continue;   // n is a multiple of 8: a group of 4 columns is inside or outside as a whole
+      f32x4 c = sm.sum[0][wave][j][lane];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) c += sm.sum[w][wave][j][lane];
+      if (p.n_split > 1) {
+        *(f32x4*)(p.partial + ((long long)blockIdx.y * p.rows + m) * p.n + col) = c;
+        continue;
+      }
+      if (p.activation == 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[e] = c[e] / (1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * c[e]));  // SiLU
+      }
+      *(u32x2*)(p.out + (long long)m * p.n + col) = u32x2{pack_bf16(c[0], c[1]), pack_bf16(c[2], c[3])};
+    }
+  }
+}
+static void launch_few_rows(const LinearParams& p, hipStream_t stream) {
+  const dim3 grid((unsigned)((p.n + 63) / 64), (unsigned)p.n_split), block(256);
+  switch ((p.rows + 31) / 32) {
+    case 1: hipLaunchKernelGGL((linear_few_rows_kernel<1>), grid, block, 0, stream, p); break;
+    case 2: hipLaunchKernelGGL((linear_few_rows_kernel<2>), grid, block, 0, stream, p); break;
+    case 3: hipLaunchKernelGGL((linear_few_rows_kernel<3>), grid, block, 0, stream, p); break;
+    case 4: hipLaunchKernelGGL((linear_few_rows_kernel<4>), grid, block, 0, stream, p); break;
+    default: hipLaunchKernelGGL((linear_few_rows_kernel<5>), grid, block, 0, stream, p); break;
+  }
+}
+
 // Second kernel of a split product: adds the splits' sums and applies the epilogue.  One thread per row and group of 4
 // columns (EPI 0) or per row, head and group of 4 rotary pairs (EPI 1: the 4 low-half columns and their partners d/2 on).
 template <int EPI>
@@ -334,17 +471,29 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(LinearParams p) {
   }
 }
 
+// Does linear_few_rows_kernel take the product?  us, linear_kernel -> it, both with the splits they choose (k x n):
+//    1 row    4096 x 11008 59 -> 21   11008 x 4096 28 -> 22   4096 x 6144 19 -> 16   4096 x 4096 15 -> 11   1536 x 2048 11 -> 10
+//   64 rows                60 -> 28                30 -> 27               22 -> 19               17 -> 14                12 -> 10
+//  100 rows                61 -> 44                34 -> 36               25 -> 28               20 -> 19                14 -> 12
+//  160 rows                62 -> 55                38 -> 45               28 -> 34               22 -> 23                16 -> 15
+// Its activations come through every 64-column tile, linear_kernel's through every 128-column one, and what a CU loads into
+// its LDS (about 17 bytes a clock) is the limit of both: from about 96 rows on only those widths gain that linear_kernel
+// does not split, which leaves it on a third of the CUs (more than 64 of its tiles).
+static bool linear_few_rows(long long rows, int n) {
+  return tuning(kTuneLinearTile, 0) == 0 && rows <= (n > 64 * 128 ? 160 : 96);
+}
+
 // Splits of the inner dimension for a product with few output rows.  Without a split such a product has one workgroup
 // per 128 columns, a fraction of the CUs, each streaming its slice of the weights alone at the rate one workgroup's few
 // tiles in flight allow; with z splits there are z times as many, at the price of z * rows * n fp32 partial sums written
 // and read again.  The workgroups hold most of a CU's LDS (one per CU at a time), so z is the largest count that still
 // fits ONE round of 256 workgroups; at least 4 K-tiles per split, the partial sums no larger than the weights, and
 // within the workspace given.  Measured (160 rows, k = 4096): 4096 outputs 56 -> 23 us, 6144 outputs 57 -> 28 us; with
-// 86 or more tiles (11008 outputs) the unsplit launch already draws what this access pattern gets from HBM (128-byte
-// pieces of rows 8 KB apart: about 1.5 TB/s) and splitting only adds the partial sums.
+// 86 tiles (11008 outputs) two splits only add the partial sums (62 -> 70 us).  The 64-column tiles of the few-row kernel
+// follow the same rule with twice as many tiles.
 static int linear_splits(long long rows, int k, int n, size_t workspace_bytes) {
-  const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128);
-  long long z = tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
+  const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128), few = (n + 63) / 64;
+  long long z = linear_few_rows(rows, n) ? std::max<long long>(1, 256 / few) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
   z = std::min<long long>(z, k / 64 / 4);
   z = std::min<long long>(z, k / (2 * rows));
   z = std::min<long long>(z, 16);
@@ -406,7 +555,7 @@ static long long linear_grid(long long rows, int n, int cols, int* patch_rows, i
 }
 
 // tile shape, splits and grid of one product; fills the split fields of p
-struct LinearLaunch { bool wide; int splits; dim3 grid; };
+struct LinearLaunch { bool few, wide; int splits; dim3 grid; };
 static int plan_linear(const char* who, LinearParams& p, void* workspace, size_t workspace_bytes, LinearLaunch* out) {
   const int splits = workspace ? linear_splits(p.rows, p.k, p.n, workspace_bytes) : 1;
   const bool wide = splits == 1 && linear_wide_tile(p.rows, p.n);
@@ -417,7 +566,7 @@ static int plan_linear(const char* who, LinearParams& p, void* workspace, size_t
   p.split_tiles = (k_tiles + splits - 1) / splits;
   p.n_split = (k_tiles + p.split_tiles - 1) / p.split_tiles;  // no empty split
   p.partial = p.n_split > 1 ? (float*)workspace : nullptr;
-  out->wide = wide; out->splits = p.n_split; out->grid = dim3((unsigned)grid, (unsigned)p.n_split, 1);
+  out->few = linear_few_rows(p.rows, p.n); out->wide = wide; out->splits = p.n_split; out->grid = dim3((unsigned)grid, (unsigned)p.n_split, 1);
   return EARN_OK;
 }
 
@@ -430,7 +579,8 @@ int launch_linear(const void* x, const void* w, int rows, int k, int n, int acti
   p.x = (const __bf16*)x; p.w = (const __bf16*)w; p.rows = rows; p.k = k; p.n = n; p.out = (__bf16*)out; p.activation = activation;
   LinearLaunch ll;
   if ((rc = plan_linear("earn_linear", p, workspace, workspace_bytes, &ll)) != EARN_OK) return rc;
-  if (ll.wide) hipLaunchKernelGGL((linear_kernel<0, 128, LIN_WIDE>), ll.grid, dim3(LIN_WIDE_THREADS), 0, stream, p);
+  if (ll.few) launch_few_rows(p, stream);
+  else if (ll.wide) hipLaunchKernelGGL((linear_kernel<0, 128, LIN_WIDE>), ll.grid, dim3(LIN_WIDE_THREADS), 0, stream, p);
   else hipLaunchKernelGGL((linear_kernel<0, 128, 2, 1, 64, 3>), ll.grid, dim3(256), 0, stream, p);
   if (ll.splits > 1) {
     const long long threads = (long long)rows * (n / 4);
@@ -454,7 +604,9 @@ int launch_qkv_rope_project(const earn_attn_desc* desc, const void* x, const voi
   p.rope = make_rope_table(desc->rope_base, desc->head_dim);
   LinearLaunch ll;
   if ((rc = plan_linear("earn_qkv_rope_project", p, workspace, workspace_bytes, &ll)) != EARN_OK) return rc;
-  if (desc->head_dim == 64) {
+  if (ll.few && ll.splits > 1) {   // (the kernel has no rotating epilogue: unsplit products keep the general one)
+    launch_few_rows(p, stream);
+  } else if (desc->head_dim == 64) {
     if (ll.wide) hipLaunchKernelGGL((linear_kernel<1, 64, LIN_WIDE>), ll.grid, dim3(LIN_WIDE_THREADS), 0, stream, p);
     else hipLaunchKernelGGL((linear_kernel<1, 64, 2, 1, 64, 3>), ll.grid, dim3(256), 0, stream, p);
   } else {

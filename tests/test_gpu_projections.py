@@ -230,3 +230,30 @@ def test_full_size_projections_sampled_rows():
     check_attn(q[sample], ref["q"], BF, "q, sampled rows")
     check_attn(k[sample], ref["k"], BF, "k, sampled rows")
     check_attn(v[sample], ref["v"], BF, "v, sampled rows")
+
+
+# Up to 96 rows (160 for wide outputs) take a kernel with tiles of 32 to 160 rows x 64 columns (chosen by size, so without
+# the tile override): the edges of its row blocks, of its column tiles and of the rule, one K-tile, fewer and more K-tiles
+# than its ring holds, odd and even counts, split and unsplit.
+@pytest.mark.parametrize("with_ws", [False, True])
+@pytest.mark.parametrize("rows,k,n,act", [(1, 64, 8, 0), (32, 128, 64, 1), (33, 192, 72, 0), (64, 576, 200, 0), (96, 640, 1000, 1),
+                                          (65, 4096, 264, 0), (97, 448, 8200, 0), (128, 1024, 8264, 0), (129, 320, 8200, 1),
+                                          (160, 704, 8256, 0), (161, 320, 8200, 0), (97, 512, 264, 1)])
+def test_linear_few_rows(rows, k, n, act, with_ws):
+    B = _B()
+    g = torch.Generator().manual_seed(rows + k + n)
+    x = torch.randn(rows, k, generator=g).to(torch.bfloat16)
+    w = (torch.randn(n, k, generator=g) * k ** -0.5).to(torch.bfloat16)
+    out = torch.full((rows + 1, n), 7.0, dtype=torch.bfloat16, device=DEV)    # a row of guard values behind the result
+    size = B.earn_linear_workspace_bytes(rows, k, n)
+    ws = torch.empty(max(size, 256), dtype=torch.uint8, device=DEV) if with_ws else None
+    B.earn_linear(x.to(DEV), w.to(DEV), out[:rows], act, ws)
+    torch.cuda.synchronize()
+    ref = x.double() @ w.double().T
+    if act:
+        ref = ref / (1.0 + torch.exp(-ref))
+    got = out[:rows].cpu().double()
+    # fp32 sums of k products of size k^-1/2 (absolute part), then one rounding to the 8 significant bits of bf16: half a
+    # unit in the last place is at most 2^-8 of the value
+    assert bool(((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 2e-5).all())
+    assert bool((out[rows] == 7.0).all())
