@@ -43,9 +43,11 @@ HEADLINE = "long_beam"
 
 def dominant_kernel(cfg, w) -> tuple:
     """Name of the kernel a full-length prefill layer of this workload runs (the library picks by dtype and by the
-    lengths: register-sized, medium or long sequences), and the roofline that bounds it."""
+    lengths: short, one-tile, medium or long sequences), and the roofline that bounds it."""
     if cfg.dtype != "bf16":
         return "prefill_rows_kernel + rope_k_kernel (one full-length causal layer, vector ALU)", "alu"
+    if w.max_seqlen <= (128 if cfg.n_q_heads > cfg.n_kv_heads else 32):
+        return "prefill_short_kernel (one causal layer, rotation included)", "mfma"
     if w.max_seqlen <= 64:
         name = "prefill_mfma_kernel<D,2,1>"
     elif w.max_seqlen <= 3072 or w.total_tokens // cfg.batch <= 2048:
