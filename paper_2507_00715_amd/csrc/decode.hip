@@ -432,14 +432,22 @@ __device__ __forceinline__ void lds_barrier() {
 //                  operand of this product, with the keys in the order 4 quad + i, 16 + 4 quad + i)
 // The group's queries and the new key are rotated once per workgroup; with every wave rotating its own copy the vector ALU
 // was the limit as soon as several workgroups shared a CU (64 sequences, 32 / 8 heads of 128, 16 rows: 16.4 us a layer in
-// a batched launch, now 7.6).  Queries and probabilities enter as the sum of two bf16 operands (value and remainder),
-// which keeps 16 mantissa bits and more of them, finer than the bf16 results.  The waves' states are merged once, in LDS.
+// a batched launch, now 7.6).  Queries and probabilities enter as the sum of three bf16 operands (value, remainder and its
+// remainder: 24 significant bits), so the products are those of fp32 queries and probabilities, as in the vector kernel.
+// The waves' states are merged once, in LDS.
 // Long lists stream K and V at 4.9 TB/s (64 sequences of 768 rows, 8 kv heads), about what a copy reaches.
 // ------------------------------------------------------------------------------------------------------------------
-// two numbers as two words of bf16 pairs: hi = the numbers rounded, lo = the remainders rounded
-__device__ __forceinline__ void split_pair(float a, float b, unsigned& hi, unsigned& lo) {
-  hi = pack_bf16(a, b);
-  lo = pack_bf16(a - bf16_lo(hi), b - bf16_hi(hi));
+// Two fp32 numbers as three words of bf16 pairs whose sum they are: w[0] = the numbers rounded, w[1] = the remainders
+// rounded, w[2] = what is left.  (With two words, 16 to 17 bits, large scores and values that cancel lost what fp32 keeps:
+// 64 rows, 8 heads of 128, relative error of the outputs 1.6585039e-3 against 1.6585009e-3 of their rounding alone; with
+// three, as in fp32 arithmetic, the last digit at most differs from the rounding's.)
+__device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[3]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    w[i] = pack_bf16(a, b);
+    a -= bf16_lo(w[i]);
+    b -= bf16_hi(w[i]);
+  }
 }
 
 template <int D, int WAVES>
@@ -450,7 +458,7 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
   union Tile { __bf16 v[BLK * D]; float o[8][D]; };      // a wave's V block; at the end its unnormalised outputs
   __shared__ Tile tile[WAVES];
   __shared__ f32x2 ml[WAVES][8];                         // (max, sum) per query of the group
-  __shared__ __align__(16) __bf16 rot[2][9][D + 8];      // rotated queries (value, remainder) and, in row gq, the new key
+  __shared__ __align__(16) __bf16 rot[3][9][D + 8];      // rotated queries (three terms) and, in row gq, the new key
   // Workgroup -> (stream, kv head): an XCD keeps a run of consecutive streams (beams of a sequence share its cache rows,
   // the kv heads of a stream share DRAM rows), so what they share is fetched into one L2.
   const int per_xcd = (p.n_streams + kXcds - 1) / kXcds;
@@ -543,11 +551,12 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
     const float scale = row < gq ? p.scale_log2 : 1.f;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      unsigned h0, h1, l0, l1;
-      split_pair(y[h][0] * scale, y[h][1] * scale, h0, l0);
-      split_pair(y[h][2] * scale, y[h][3] * scale, h1, l1);
-      *(u32x2*)&rot[0][row][e + h * (D / 2)] = u32x2{h0, h1};   // the new key's value part is the key as stored
-      if (row < gq) *(u32x2*)&rot[1][row][e + h * (D / 2)] = u32x2{l0, l1};
+      unsigned w0[3], w1[3];
+      split_pair(y[h][0] * scale, y[h][1] * scale, w0);
+      split_pair(y[h][2] * scale, y[h][3] * scale, w1);
+#pragma unroll
+      for (int i = 0; i < 3; ++i)                               // the new key's first term is the key as stored
+        if (i == 0 || row < gq) *(u32x2*)&rot[i][row][e + h * (D / 2)] = u32x2{w0[i], w1[i]};
     }
   }
   lds_barrier();
@@ -582,13 +591,13 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
     }
     f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const bf16x8 ql = *(const bf16x8*)&rot[1][q_row][32 * ks + 8 * quad], qh = *(const bf16x8*)&rot[0][q_row][32 * ks + 8 * quad];
+    for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], ql, sc[t], 0, 0, 0);
+      for (int i = 2; i >= 0; --i) {
+        const bf16x8 q = *(const bf16x8*)&rot[i][q_row][32 * ks + 8 * quad];
 #pragma unroll
-      for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], qh, sc[t], 0, 0, 0);
-    }
+        for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], q, sc[t], 0, 0, 0);
+      }
     // V to LDS; the wave's LDS operations complete in order, so only the compiler has to keep theirs
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -609,7 +618,7 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
     const float mnew = fmaxf(mrow, m), ref = mnew == -INFINITY ? 0.f : mnew;
     const float alpha = __builtin_amdgcn_exp2f(mrow - ref);
     mrow = mnew;
-    u32x4 ph, pl;
+    u32x4 pw[3];
     float sum = 0.f;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -617,9 +626,10 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
       for (int i = 0; i < 4; i += 2) {
         const float a = __builtin_amdgcn_exp2f(sc[t][i] - ref), b = __builtin_amdgcn_exp2f(sc[t][i + 1] - ref);
         sum += a + b;
-        unsigned hi, lo;
-        split_pair(a, b, hi, lo);
-        ph[2 * t + i / 2] = hi; pl[2 * t + i / 2] = lo;
+        unsigned w[3];
+        split_pair(a, b, w);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) pw[j][2 * t + i / 2] = w[j];
       }
     lrow = lrow * alpha + sum;
     asm volatile("" ::: "memory");
@@ -634,8 +644,8 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
       const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
       for (int i = 0; i < 4; ++i) o[db][i] *= alpha;
-      o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pl), o[db], 0, 0, 0);
-      o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, ph), o[db], 0, 0, 0);
+#pragma unroll
+      for (int j = 2; j >= 0; --j) o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pw[j]), o[db], 0, 0, 0);
     }
     asm volatile("" ::: "memory");
   }
