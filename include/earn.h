@@ -352,8 +352,8 @@ size_t earn_linear_workspace_bytes(int32_t rows, int32_t k, int32_t n);
  * desc->rope_base must be <= 0 (nothing is rotated here); softmax_scale and q_to_kv as in the forward.
  *   workspace: at least earn_attn_backward_workspace_bytes(desc, total_tokens) bytes (one float per (token, query head))
  * Errors: NULL pointer, non-positive size -> INVALID_ARG; rope_base > 0 -> UNSUPPORTED; workspace -> WORKSPACE_TOO_SMALL.
- * bf16: the products run on the matrix cores, the probabilities and dS entering them as pairs of bf16 operands (value and
- * remainder), so that the arithmetic stays that of fp32 probabilities.  fp32: vector ALU.
+ * bf16: the products run on the matrix cores, the probabilities and dS entering them as the sum of three bf16 operands (24
+ * significant bits), so that the arithmetic stays that of fp32 probabilities.  fp32: vector ALU.
  */
 int earn_attn_backward(const earn_attn_desc* desc, const void* q, const void* k, const void* v, const void* out,
                        const float* lse, const void* d_out, const int32_t* cu_seqlens, int32_t batch,

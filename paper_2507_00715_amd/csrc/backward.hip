@@ -191,12 +191,13 @@ __global__ __launch_bounds__(256) void bwd_dkv_kernel(BwdParams p) {
 // k and v) as B operands in registers; the paired rows stream through LDS in tiles shared by the workgroup:
 //   dQ:      S^T = K Q^T   dP^T = V dO^T    dQ^T += K^T dS^T                       (paired: keys)
 //   dK, dV:  S = Q K^T     dP = dO V^T      dV^T += dO^T P,  dK^T += Q^T dS        (paired: queries of every head of the group)
-// (dK, dV: -lse_i / scale and -D_i are the start values of the S and dP accumulators.)  P and dS enter the last products as TWO bf16 operands, the rounded value
-// and the rounded remainder (16 bits of significand): the arithmetic keeps the accuracy of fp32 probabilities, at 16 of
-// the 48 (dK, dV) and 8 of the 32 (dQ) matrix instructions per 32 x 32 tile and 128 dimensions.
+// (dK, dV: -lse_i / scale and -D_i are the start values of the S and dP accumulators.)  P and dS enter the last products as
+// THREE bf16 operands, value, remainder and its remainder, 24 significant bits: the products are those of fp32 probabilities,
+// at 32 of the 64 (dK, dV) and 16 of the 40 (dQ) matrix instructions per 32 x 32 tile and 128 dimensions.  (Two operands, 16
+// bits: 604 -> 518 and 123 -> 115 us at the sizes below, and every term of a sum wrong by up to 2^-18 of itself.)
 // Bound by the instruction chain of a wave (matrix products, exponentials and splits of one tile: about 2 us, 3 us when two
 // waves share a SIMD) times the tiles it walks.  Measured, forward included, against the vector-ALU form that these kernels
-// replaced: 16 sequences of 272-1040 rows, 32 / 8 heads of 128: 18.36 -> 0.53 ms; 64 sequences of 68 rows: 1.01 -> 0.12 ms.
+// replaced: 16 sequences of 272-1040 rows, 32 / 8 heads of 128: 18.36 -> 0.60 ms; 64 sequences of 68 rows: 1.01 -> 0.12 ms.
 // ------------------------------------------------------------------------------------------------------------------
 struct BwdBlock { int c, a, b0, n, row0; bool valid; };
 // Workgroup -> (sequence, kv head, block of owned rows, query head of the group).  Consecutive ids go to the 8 XCDs in turn,
@@ -285,36 +286,46 @@ __device__ __forceinline__ void bwd_product(const __bf16* tile, const __bf16* ow
     __builtin_amdgcn_sched_barrier(0);
   }
 }
-// x as the sum of two bf16 operands: hi = x rounded, lo = the remainder rounded.  Word (kk, j) of an operand packs
-// accumulator registers 8 kk + 2 j, + 1; w = 4 kk + j.
-struct SplitOperand {
-  u32x4 hi[2], lo[2];
-  __device__ __forceinline__ void set(int w, float a, float b) {
-    const unsigned h = pack_bf16(a, b);
-    hi[w >> 2][w & 3] = h;
-    lo[w >> 2][w & 3] = pack_bf16(a - bf16_lo(h), b - bf16_hi(h));
-  }
-};
 __device__ __forceinline__ int word_reg(int w) { return 8 * (w >> 2) + 2 * (w & 3); }  // first accumulator register of word w
-// o^T += (32 tile rows, transposed) x (hi + lo); a fragment requested two blocks ahead, the first two by the caller
-// (bwd_request), ahead of the vector work that produces hi and lo.  slot(i), i < 2 D / 32: the caller's vector work that
-// runs while block i's products do.
+// o^T += (32 tile rows, transposed) x the fp32 tile of which src(w, a, b) gives registers word_reg(w), + 1, as three bf16
+// operands: the values rounded, the remainders rounded, and what is left.  The second half of the tile is split while the
+// first half's products run.  A fragment is requested two blocks ahead, the first two by the caller (bwd_request), ahead of
+// the vector work that produces the tile.  slot(i), i < 2 D / 32: the caller's vector work that runs while block i's
+// products do.
 struct TransposedPair { bf16x8 f[2]; };
 template <int D>
 __device__ __forceinline__ TransposedPair bwd_request(const __bf16* tile, const FragOffsets<D>& fo) {
   return TransposedPair{read_v_fragment<D>(tile, fo, 0, 0), read_v_fragment<D>(tile, fo, 1, 0)};
 }
-template <int D, typename Slot>
+template <int D, typename Src, typename Slot>
 __device__ __forceinline__ void bwd_accumulate(const __bf16* tile, const FragOffsets<D>& fo, const TransposedPair& first,
-                                               const SplitOperand& x, f32x16 (&o)[D / 32], Slot&& slot) {
+                                               Src&& src, f32x16 (&o)[D / 32], Slot&& slot) {
   constexpr int DB = D / 32;
+  u32x4 x[2][3];   // [half][term]
+  auto split = [&](int w) {
+    float a, b;
+    src(w, a, b);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const unsigned h = pack_bf16(a, b);
+      x[w >> 2][i][w & 3] = h;
+      a -= bf16_lo(h);
+      b -= bf16_hi(h);
+    }
+  };
+#pragma unroll
+  for (int w = 0; w < 4; ++w) split(w);
   bf16x8 r[3] = {first.f[0], first.f[1]};
 #pragma unroll
   for (int i = 0; i < 2 * DB; ++i) {
     const int kk = i / DB, db = i % DB;
     if (i + 2 < 2 * DB) r[(i + 2) % 3] = read_v_fragment<D>(tile, fo, (i + 2) % DB, (i + 2) / DB);
-    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i % 3], __builtin_bit_cast(bf16x8, x.hi[kk]), o[db], 0, 0, 0);
-    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i % 3], __builtin_bit_cast(bf16x8, x.lo[kk]), o[db], 0, 0, 0);
+#pragma unroll
+    for (int t = 2; t >= 0; --t) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i % 3], __builtin_bit_cast(bf16x8, x[kk][t]), o[db], 0, 0, 0);
+    if (kk == 0) {
+#pragma unroll
+      for (int w = 4 + db * (4 / DB); w < 4 + (db + 1) * (4 / DB); ++w) split(w);
+    }
     slot(i);
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -418,10 +429,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bwd_dq_mfma_kernel(BwdParams p)
         for (int i = 0; i < 16; ++i)
           if (8 * (i >> 2) + (i & 3) > bound) s[i] = 0.f;
       }
-      SplitOperand x;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) x.set(w, s[word_reg(w)] * ds[word_reg(w)], s[word_reg(w) + 1] * ds[word_reg(w) + 1]);
-      bwd_accumulate<D>(tk, fo, tp, x, o, [](int) {});
+      auto d_score = [&](int w, float& a, float& b) {
+        a = s[word_reg(w)] * ds[word_reg(w)];
+        b = s[word_reg(w) + 1] * ds[word_reg(w) + 1];
+      };
+      bwd_accumulate<D>(tk, fo, tp, d_score, o, [](int) {});
     }
   }
   if (!active || qw + r32 >= n) return;
@@ -541,18 +553,16 @@ __global__ __launch_bounds__(64 * KW * G, 2) void bwd_dkv_mfma_kernel(BwdParams 
         for (int i = 0; i < 16; ++i)
           if (8 * (i >> 2) + (i & 3) < bound) s[i] = 0.f;
       }
-      SplitOperand px, dx;
+      auto words_of = [](const f32x16& x) { return [&x](int w, float& a, float& b) { a = x[word_reg(w)]; b = x[word_reg(w) + 1]; }; };
+      // dS = P (dP - D) is formed while the matrix core takes dV
+      constexpr int RPS = 16 / (2 * DB);   // registers per slot
+      bwd_accumulate<D>(tg, fo, tp, words_of(s), dv, [&](int i) {
 #pragma unroll
-      for (int w = 0; w < 8; ++w) px.set(w, s[word_reg(w)], s[word_reg(w) + 1]);
-      // dS = P (dP - D) is formed and split while the matrix core takes dV
-      constexpr int WPS = 8 / (2 * DB);    // words per slot
-      bwd_accumulate<D>(tg, fo, tp, px, dv, [&](int i) {
-#pragma unroll
-        for (int w = WPS * i; w < WPS * (i + 1); ++w) dx.set(w, s[word_reg(w)] * ds[word_reg(w)], s[word_reg(w) + 1] * ds[word_reg(w) + 1]);
+        for (int r = RPS * i; r < RPS * (i + 1); ++r) ds[r] *= s[r];
       });
       forget();
       tp = bwd_request<D>(tq, fo);
-      bwd_accumulate<D>(tq, fo, tp, dx, dk, [](int) {});
+      bwd_accumulate<D>(tq, fo, tp, words_of(ds), dk, [](int) {});
       pin(dv);
       pin(dk);
     }

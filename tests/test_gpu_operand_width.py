@@ -101,3 +101,56 @@ def test_decode_values_that_cancel(h, d):
     # small scores (|s| < 1): a probability is right to about 2^-22 of itself in fp32
     bound = 2.0 ** -8 * np.abs(ref) + 2.0 ** -21 * size
     assert (np.abs(got - ref) <= bound).all(), float((np.abs(got - ref) / bound).max())
+
+
+@pytest.mark.parametrize("which", ["dq", "dk", "dv"])
+@pytest.mark.parametrize("hq,hkv,d,n", [(2, 2, 64, 8), (2, 2, 128, 40), (32, 32, 128, 8)])
+def test_backward_sums_that_cancel(hq, hkv, d, n, which):
+    """dV of key 0, dK of key 0 or dQ of the last query as a sum of four terms that cancel.  q and k score with their first
+    half only, so the second half of the other operand is free to be chosen.  (n = 40 spans two 32-row tiles.)"""
+    B = _B()
+    batch = 64 if hq == 32 else 2          # 64 x 32 pairs: the 128-row workgroups
+    scale, half = 0.02, d // 2
+    rng = np.random.default_rng(n + d + len(which))
+    q, k = bf16(rng.standard_normal((batch, n, hq, d))), bf16(rng.standard_normal((batch, n, hkv, d)))
+    q[..., half:], k[..., half:] = 0.0, 0.0
+    # few bits: dP and D come out (almost) exact, the error under test is that of P and dS as operands
+    v, g = (rng.integers(-3, 4, (batch, n, hq, d)) / 2.0 for _ in range(2))
+    s = np.einsum("bihd,bjhd->bhij", q, k) * scale
+    s = np.where(np.arange(n)[:, None] >= np.arange(n)[None], s, -np.inf)
+    lse = np.log(np.exp(s).sum(-1))                                    # [batch, h, n]
+    lse32 = lse.astype(np.float32).astype(np.float64)
+    p = np.exp(s - lse32[..., None])
+    rows = np.array([0, 2, n - 3, n - 1])
+    if which == "dv":
+        w = np.moveaxis(p[:, :, rows, 0], 2, 0)[..., None]             # [4, batch, h, 1]
+        g = np.zeros_like(g)
+        g[:, rows] = np.moveaxis(cancelling(w, bf16(rng.uniform(1, 2, (batch, hq, d)))), 0, 1)
+    out = bf16(np.einsum("bhij,bjhd->bihd", p, v))
+    dp = np.einsum("bihd,bjhd->bhij", g, v)
+    big_d = np.einsum("bihd,bihd->bhi", out, g)
+    ds = p * (dp - big_d[..., None])
+    if which in ("dk", "dq"):
+        w = np.moveaxis(ds[:, :, rows, 0] if which == "dk" else ds[:, :, n - 1, rows], 2, 0)[..., None]
+        w = np.where(np.abs(w) < 1e-3, 1e-3, w)
+        first = bf16(rng.uniform(1, 2, (batch, hq, half)))
+        x = q if which == "dk" else k
+        x[:, rows, :, half:] = np.clip(np.moveaxis(cancelling(w, first), 0, 1), -1e4, 1e4)
+    dq, dk, dv = (np.einsum(e, m, x) * f for e, m, x, f in (("bhij,bjhd->bihd", ds, k, scale), ("bhij,bihd->bjhd", ds, q, scale),
+                                                            ("bhij,bihd->bjhd", p, g, 1.0)))
+    ads = np.abs(p) * (np.abs(dp) + np.abs(big_d)[..., None])
+    aq, ak, av = (np.einsum(e, m, np.abs(x)) * f for e, m, x, f in (
+        ("bhij,bjhd->bihd", ads, k, scale), ("bhij,bihd->bjhd", ads, q, scale), ("bhij,bihd->bjhd", np.abs(p), g, 1.0)))
+    ref, size = {"dq": (dq, aq), "dk": (dk, ak), "dv": (dv, av)}[which]
+
+    to = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(BF).to(DEV).reshape(batch * n, -1, d)
+    desc = B.make_desc(BF, hq, hkv, d, scale, 0.0)
+    d_lse = torch.from_numpy(np.ascontiguousarray(np.moveaxis(lse, 1, 2)).astype(np.float32)).to(DEV).reshape(batch * n, hq)
+    grads = [torch.full_like(to(x), float("nan")) for x in (q, k, v)]
+    B.earn_attn_backward(desc, to(q), to(k), to(v), to(out), d_lse, to(g), i32(range(0, (batch + 1) * n, n)), batch, batch * n, n, *grads)
+    torch.cuda.synchronize()
+    got = grads[("dq", "dk", "dv").index(which)].cpu().double().numpy().reshape(ref.shape)
+    row = n - 1 if which == "dq" else 0
+    # every term right to a few units in the last place of fp32
+    err, bound = np.abs(got - ref)[:, row], (2.0 ** -8 * np.abs(ref) + 2.0 ** -21 * size)[:, row]
+    assert (err <= bound).all(), float((err / np.maximum(bound, 1e-30)).max())
