@@ -562,93 +562,127 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
   lds_barrier();
 
   f32x4 o[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float mrow = -INFINITY, lrow = 0.f;                    // of query r16; lrow: this lane's keys only
+  float mrow, lrow;                                      // of query r16; lrow: this lane's keys only
   __bf16* smv = tile[wave].v;
   const int q_row = min(r16, gq - 1);                    // columns beyond the group repeat its last query
   // 16 consecutive rows share a chunk of a transposing read: two rows per chunk position at most
   auto v_swz = [](int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); };
-  for (int blk = wave; blk < n_blocks; blk += WAVES) {
-    if (blk != wave) load_block(blk);
-    const bool shared = blk < n_shared;
-    const int j0 = (shared ? blk : blk - n_shared) * BLK;
-    const int count = shared ? ns - j0 : g + 1 - j0;     // keys from j0 on
-    if (blk == n_blocks - 1) {                           // the new token: its key rotated and rounded as stored, appended
-      const int j = g - j0;
+  // An operand in three terms times an infinite key or value element is inf - inf where the terms differ in sign, or 0 * inf
+  // where one is zero, instead of the infinity that the whole operand gives.  So a result that came out as NaN is worked out
+  // again (CAREFUL) with the first term's products on their own: where they are infinite, they are the result.
+  auto walk = [&](auto careful_c) {
+    constexpr bool CAREFUL = decltype(careful_c)::value;
+    auto settle = [](f32x4& first, const f32x4& rest) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 w = *(const bf16x8*)&rot[0][gq][32 * ks + 8 * quad];
-        if (j == r16) kf[0][ks] = w;
-        if (j == 16 + r16) kf[1][ks] = w;
-        if (r16 == 0) *(bf16x8*)((__bf16*)lv.gen_k + own + g * row_stride + 32 * ks + 8 * quad) = w;
+      for (int i = 0; i < 4; ++i) first[i] = __builtin_isinf(first[i]) ? first[i] : first[i] + rest[i];
+    };
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    mrow = -INFINITY;
+    lrow = 0.f;
+    for (int blk = wave; blk < n_blocks; blk += WAVES) {
+      if (CAREFUL || blk != wave) load_block(blk);
+      const bool shared = blk < n_shared;
+      const int j0 = (shared ? blk : blk - n_shared) * BLK;
+      const int count = shared ? ns - j0 : g + 1 - j0;     // keys from j0 on
+      if (blk == n_blocks - 1) {                           // the new token: its key rotated and rounded as stored, appended
+        const int j = g - j0;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const bf16x8 w = *(const bf16x8*)&rot[0][gq][32 * ks + 8 * quad];
+          if (j == r16) kf[0][ks] = w;
+          if (j == 16 + r16) kf[1][ks] = w;
+          if (r16 == 0) *(bf16x8*)((__bf16*)lv.gen_k + own + g * row_stride + 32 * ks + 8 * quad) = w;
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          const int unit = lane + kWave * i;
+          if (unit / UPR == j) *(u32x4*)((__bf16*)lv.gen_v + own + g * row_stride + (unit % UPR) * 8) = vr[i];
+        }
       }
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int unit = lane + kWave * i;
-        if (unit / UPR == j) *(u32x4*)((__bf16*)lv.gen_v + own + g * row_stride + (unit % UPR) * 8) = vr[i];
-      }
-    }
-    f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
+      f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, sc_rest[2];
 #pragma unroll
       for (int i = 2; i >= 0; --i) {
-        const bf16x8 q = *(const bf16x8*)&rot[i][q_row][32 * ks + 8 * quad];
+        if (CAREFUL && i == 0) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], q, sc[t], 0, 0, 0);
+          for (int t = 0; t < 2; ++t) { sc_rest[t] = sc[t]; sc[t] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const bf16x8 q = *(const bf16x8*)&rot[i][q_row][32 * ks + 8 * quad];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], q, sc[t], 0, 0, 0);
+        }
       }
-    // V to LDS; the wave's LDS operations complete in order, so only the compiler has to keep theirs
+      if (CAREFUL) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int unit = lane + kWave * i, row = unit / UPR;
-      *(u32x4*)(smv + row * D + (((unit % UPR) ^ v_swz(row)) << 3)) = vr[i];
+        for (int t = 0; t < 2; ++t) settle(sc[t], sc_rest[t]);
+      }
+      // V to LDS; the wave's LDS operations complete in order, so only the compiler has to keep theirs
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int unit = lane + kWave * i, row = unit / UPR;
+        *(u32x4*)(smv + row * D + (((unit % UPR) ^ v_swz(row)) << 3)) = vr[i];
+      }
+      // softmax: lane (r16, quad) holds keys 16 t + 4 quad + i of query r16
+      float m = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (16 * t + 4 * quad + i >= count) sc[t][i] = -INFINITY;
+          m = fmaxf(m, sc[t][i]);
+        }
+      m = fmaxf(m, __shfl_xor(m, 16, kWave));
+      m = fmaxf(m, __shfl_xor(m, 32, kWave));
+      const float mnew = fmaxf(mrow, m), ref = mnew == -INFINITY ? 0.f : mnew;
+      const float alpha = __builtin_amdgcn_exp2f(mrow - ref);
+      mrow = mnew;
+      u32x4 pw[3];
+      float sum = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+          const float a = __builtin_amdgcn_exp2f(sc[t][i] - ref), b = __builtin_amdgcn_exp2f(sc[t][i + 1] - ref);
+          sum += a + b;
+          unsigned w[3];
+          split_pair(a, b, w);
+#pragma unroll
+          for (int j = 0; j < 3; ++j) pw[j][2 * t + i / 2] = w[j];
+        }
+      lrow = lrow * alpha + sum;
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        const int row = 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
+        const __bf16* a0 = smv + row * D + ((chunk ^ v_swz(row)) << 3) + 4 * (r16 & 1);
+        const __bf16* a1 = smv + (row + 16) * D + ((chunk ^ v_swz(row + 16)) << 3) + 4 * (r16 & 1);
+        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a0);
+        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a1);
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[db][i] *= alpha;
+        f32x4 acc = CAREFUL ? f32x4{0.f, 0.f, 0.f, 0.f} : o[db], acc_rest;
+#pragma unroll
+        for (int j = 2; j >= 0; --j) {
+          if (CAREFUL && j == 0) { acc_rest = acc; acc = o[db]; }
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pw[j]), acc, 0, 0, 0);
+        }
+        if (CAREFUL) settle(acc, acc_rest);
+        o[db] = acc;
+      }
+      asm volatile("" ::: "memory");
     }
-    // softmax: lane (r16, quad) holds keys 16 t + 4 quad + i of query r16
-    float m = -INFINITY;
+  };
+  walk(std::false_type{});
+  float probe = lrow;                                    // NaN where anything is, or where infinities of both signs meet
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (16 * t + 4 * quad + i >= count) sc[t][i] = -INFINITY;
-        m = fmaxf(m, sc[t][i]);
-      }
-    m = fmaxf(m, __shfl_xor(m, 16, kWave));
-    m = fmaxf(m, __shfl_xor(m, 32, kWave));
-    const float mnew = fmaxf(mrow, m), ref = mnew == -INFINITY ? 0.f : mnew;
-    const float alpha = __builtin_amdgcn_exp2f(mrow - ref);
-    mrow = mnew;
-    u32x4 pw[3];
-    float sum = 0.f;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; i += 2) {
-        const float a = __builtin_amdgcn_exp2f(sc[t][i] - ref), b = __builtin_amdgcn_exp2f(sc[t][i + 1] - ref);
-        sum += a + b;
-        unsigned w[3];
-        split_pair(a, b, w);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) pw[j][2 * t + i / 2] = w[j];
-      }
-    lrow = lrow * alpha + sum;
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      const int row = 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
-      const __bf16* a0 = smv + row * D + ((chunk ^ v_swz(row)) << 3) + 4 * (r16 & 1);
-      const __bf16* a1 = smv + (row + 16) * D + ((chunk ^ v_swz(row + 16)) << 3) + 4 * (r16 & 1);
-      const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a0);
-      const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a1);
-      const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[db][i] *= alpha;
-#pragma unroll
-      for (int j = 2; j >= 0; --j) o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pw[j]), o[db], 0, 0, 0);
-    }
-    asm volatile("" ::: "memory");
-  }
+    for (int i = 0; i < 4; ++i) probe += o[db][i];
+  if (__any(probe != probe)) walk(std::true_type{});
   // merge: a wave's outputs take the place of its V block
   lrow += __shfl_xor(lrow, 16, kWave);
   lrow += __shfl_xor(lrow, 32, kWave);
