@@ -8,7 +8,7 @@
 // key rows (dK, dV); each recomputes the probabilities it needs from lse.
 //   bf16  bwd_dq_mfma_kernel, bwd_dkv_mfma_kernel: the five products on the matrix cores.
 //   fp32  bwd_dsum_kernel, bwd_dq_kernel, bwd_dkv_kernel: vector ALU, four lanes share a row and hold d/4 of its elements
-//         each (the precise form for the small fp32 configuration).
+//         each (the precise form for the small fp32 configuration; in bf16, of rows with infinities or NaN).
 #include <algorithm>
 
 #include "common.h"
@@ -51,28 +51,31 @@ template <> struct B8<__bf16> {
     *(u32x4*)p = w;
   }
 };
-// the D/4 elements of a row this lane holds: pieces [qt*E, +E) and [D/2 + qt*E, +E), E = D/8
-template <typename T, int D>
-__device__ __forceinline__ void load_quarter(const T* row, int qt, float* x) {
-  constexpr int E = D / 8;
+// A row shared by L lanes (4, or 8 where registers are short): lane `part` holds pieces [part*E, +E) and [D/2 + part*E, +E),
+// E = D / (2 L)
+template <typename T, int D, int L>
+__device__ __forceinline__ void load_part(const T* row, int part, float* x) {
+  constexpr int E = D / 2 / L;
+  static_assert(E % 8 == 0);
 #pragma unroll
-  for (int e = 0; e < E; e += 8) { B8<T>::load(row + qt * E + e, x + e); B8<T>::load(row + D / 2 + qt * E + e, x + E + e); }
+  for (int e = 0; e < E; e += 8) { B8<T>::load(row + part * E + e, x + e); B8<T>::load(row + D / 2 + part * E + e, x + E + e); }
 }
-template <typename T, int D>
-__device__ __forceinline__ void store_quarter(T* row, int qt, const float* x) {
-  constexpr int E = D / 8;
+template <typename T, int D, int L>
+__device__ __forceinline__ void store_part(T* row, int part, const float* x) {
+  constexpr int E = D / 2 / L;
 #pragma unroll
-  for (int e = 0; e < E; e += 8) { B8<T>::store(row + qt * E + e, x + e); B8<T>::store(row + D / 2 + qt * E + e, x + E + e); }
+  for (int e = 0; e < E; e += 8) { B8<T>::store(row + part * E + e, x + e); B8<T>::store(row + D / 2 + part * E + e, x + E + e); }
 }
-__device__ __forceinline__ float quad_sum(float x) {
-  x += __shfl_xor(x, 1, kWave);
-  x += __shfl_xor(x, 2, kWave);
+template <int L>
+__device__ __forceinline__ float row_sum(float x) {
+#pragma unroll
+  for (int o = 1; o < L; o <<= 1) x += __shfl_xor(x, o, kWave);
   return x;
 }
 
-// D_i = dO_i . O_i for every (token, query head): one thread per 8 elements, four... one quad per row
-template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_dsum_kernel(const T* __restrict__ out, const T* __restrict__ d_out,
+// D_i = dO_i . O_i for every (token, query head): a quad per row
+template <int D>
+__global__ __launch_bounds__(256) void bwd_dsum_kernel(const float* __restrict__ out, const float* __restrict__ d_out,
                                                        float* __restrict__ dsum, long long rows) {
   const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
   const long long row = t >> 2;
@@ -80,105 +83,113 @@ __global__ __launch_bounds__(256) void bwd_dsum_kernel(const T* __restrict__ out
   float acc = 0.f;
   if (row < rows) {
     float o[D / 4], g[D / 4];
-    load_quarter<T, D>(out + row * D, qt, o);
-    load_quarter<T, D>(d_out + row * D, qt, g);
+    load_part<float, D, 4>(out + row * D, qt, o);
+    load_part<float, D, 4>(d_out + row * D, qt, g);
 #pragma unroll
     for (int e = 0; e < D / 4; ++e) acc = __builtin_fmaf(o[e], g[e], acc);
   }
-  acc = quad_sum(acc);
+  acc = row_sum<4>(acc);
   if (row < rows && qt == 0) dsum[row] = acc;
 }
 
-// dQ: 64 query rows per workgroup (grid: row block, query-head slot, sequence); the rows of a wave walk the keys together
-template <typename T, int D>
+// dQ of query row i by the L lanes that own it; the rows of a wave walk the keys 0 .. wave_last together.  dsum: the row's D.
+// Pairs that are masked are passed over, not multiplied by zero: a later key's or value's infinity stays its own.
+template <typename T, int D, int L>
+__device__ __forceinline__ void bwd_dq_row(const BwdParams& p, int b0, int n, int c, int a, int i, int wave_last, float dsum, int part) {
+  constexpr int N = D / L;
+  const bool row_ok = i < n;
+  const int ic = row_ok ? i : n - 1;
+  const long long io = ((long long)(b0 + ic) * p.hq + a);
+  float q[N], g[N], dq[N];
+  load_part<T, D, L>((const T*)p.q + io * D, part, q);
+  load_part<T, D, L>((const T*)p.d_out + io * D, part, g);
+#pragma unroll
+  for (int e = 0; e < N; ++e) { q[e] *= p.scale_log2; dq[e] = 0.f; }
+  const float lse2 = p.lse[io] * 1.4426950408889634f;
+  const T* kbase = (const T*)p.k + ((long long)b0 * p.hkv + c) * D;
+  const T* vbase = (const T*)p.v + ((long long)b0 * p.hkv + c) * D;
+  const long long rs = (long long)p.hkv * D;
+  for (int j = 0; j <= wave_last; ++j) {
+    float kx[N], vx[N];
+    load_part<T, D, L>(kbase + j * rs, part, kx);
+    load_part<T, D, L>(vbase + j * rs, part, vx);
+    float sc = 0.f, dp = 0.f;
+#pragma unroll
+    for (int e = 0; e < N; ++e) { sc = __builtin_fmaf(q[e], kx[e], sc); dp = __builtin_fmaf(g[e], vx[e], dp); }
+    sc = row_sum<L>(sc);
+    dp = row_sum<L>(dp);
+    if (j > ic) continue;   // causal: keys 0 .. i
+    const float ds = __builtin_amdgcn_exp2f(sc - lse2) * (dp - dsum);
+#pragma unroll
+    for (int e = 0; e < N; ++e) dq[e] = __builtin_fmaf(ds, kx[e], dq[e]);
+  }
+  if (!row_ok) return;
+#pragma unroll
+  for (int e = 0; e < N; ++e) dq[e] *= p.scale;
+  store_part<T, D, L>((T*)p.dq + io * D, part, dq);
+}
+// dK and dV of key row j by the L lanes that own it: query rows j .. n-1 of every query head of the group, which the rows of a
+// wave walk together from wave_first on.  (Masked pairs: as above.)
+template <typename T, int D, int L>
+__device__ __forceinline__ void bwd_dkv_row(const BwdParams& p, int b0, int n, int c, int j, int wave_first, int part) {
+  constexpr int N = D / L;
+  const int gq = p.hq / p.hkv;
+  const bool key_ok = j < n;
+  const int jc = key_ok ? j : n - 1;
+  const long long jo = ((long long)(b0 + jc) * p.hkv + c);
+  float kx[N], vx[N], dk[N], dv[N];
+  load_part<T, D, L>((const T*)p.k + jo * D, part, kx);
+  load_part<T, D, L>((const T*)p.v + jo * D, part, vx);
+#pragma unroll
+  for (int e = 0; e < N; ++e) { kx[e] *= p.scale_log2; dk[e] = 0.f; dv[e] = 0.f; }
+  for (int ai = 0; ai < gq; ++ai) {
+    const int a = head_of_slot(p.heads, c * gq + ai);
+    for (int i = wave_first; i < n; ++i) {
+      const long long io = ((long long)(b0 + i) * p.hq + a);
+      float q[N], g[N];
+      load_part<T, D, L>((const T*)p.q + io * D, part, q);
+      load_part<T, D, L>((const T*)p.d_out + io * D, part, g);
+      float sc = 0.f, dp = 0.f;
+#pragma unroll
+      for (int e = 0; e < N; ++e) { sc = __builtin_fmaf(q[e], kx[e], sc); dp = __builtin_fmaf(g[e], vx[e], dp); }
+      sc = row_sum<L>(sc);
+      dp = row_sum<L>(dp);
+      if (jc > i) continue;   // query i sees keys 0 .. i
+      const float pr = __builtin_amdgcn_exp2f(sc - p.lse[io] * 1.4426950408889634f);
+      const float ds = pr * (dp - p.dsum[sizeof(T) == 2 ? (long long)a * p.total + b0 + i : io]);
+#pragma unroll
+      for (int e = 0; e < N; ++e) { dv[e] = __builtin_fmaf(pr, g[e], dv[e]); dk[e] = __builtin_fmaf(ds, q[e], dk[e]); }
+    }
+  }
+  if (!key_ok) return;
+#pragma unroll
+  for (int e = 0; e < N; ++e) dk[e] *= p.scale;
+  store_part<T, D, L>((T*)p.dk + jo * D, part, dk);
+  store_part<T, D, L>((T*)p.dv + jo * D, part, dv);
+}
+
+// dQ: 64 query rows per workgroup (grid: row block, query-head slot, sequence)
+template <int D>
 __global__ __launch_bounds__(256) void bwd_dq_kernel(BwdParams p) {
-  constexpr int Q4 = D / 4;
   const int slot = blockIdx.y, s = blockIdx.z;
   const int a = head_of_slot(p.heads, slot), c = slot / (p.hq / p.hkv);
   int b0, n;
   clamped_bounds(p.cu, s, p.total, p.max_seqlen, b0, n);
   const int row0 = blockIdx.x * 64;
   if (row0 >= n) return;
-  const int qt = threadIdx.x & 3;
   const int i = row0 + (threadIdx.x >> 2);
-  const bool row_ok = i < n;
-  const int ic = row_ok ? i : n - 1;
-  const long long io = ((long long)(b0 + ic) * p.hq + a);
-  float q[Q4], g[Q4], dq[Q4];
-  load_quarter<T, D>((const T*)p.q + io * D, qt, q);
-  load_quarter<T, D>((const T*)p.d_out + io * D, qt, g);
-#pragma unroll
-  for (int e = 0; e < Q4; ++e) { q[e] *= p.scale_log2; dq[e] = 0.f; }
-  const float lse2 = p.lse[io] * 1.4426950408889634f, dsum = p.dsum[io];
   const int wave_last = min(n - 1, row0 + (int)(threadIdx.x / kWave) * 16 + 15);
-  const T* kbase = (const T*)p.k + ((long long)b0 * p.hkv + c) * D;
-  const T* vbase = (const T*)p.v + ((long long)b0 * p.hkv + c) * D;
-  const long long rs = (long long)p.hkv * D;
-  for (int j = 0; j <= wave_last; ++j) {
-    float kx[Q4], vx[Q4];
-    load_quarter<T, D>(kbase + j * rs, qt, kx);
-    load_quarter<T, D>(vbase + j * rs, qt, vx);
-    float sc = 0.f, dp = 0.f;
-#pragma unroll
-    for (int e = 0; e < Q4; ++e) { sc = __builtin_fmaf(q[e], kx[e], sc); dp = __builtin_fmaf(g[e], vx[e], dp); }
-    sc = quad_sum(sc);
-    dp = quad_sum(dp);
-    const float pr = j <= ic ? __builtin_amdgcn_exp2f(sc - lse2) : 0.f;   // causal: keys 0 .. i
-    const float ds = pr * (dp - dsum);
-#pragma unroll
-    for (int e = 0; e < Q4; ++e) dq[e] = __builtin_fmaf(ds, kx[e], dq[e]);
-  }
-  if (!row_ok) return;
-#pragma unroll
-  for (int e = 0; e < Q4; ++e) dq[e] *= p.scale;
-  store_quarter<T, D>((T*)p.dq + io * D, qt, dq);
+  bwd_dq_row<float, D, 4>(p, b0, n, c, a, i, wave_last, p.dsum[(long long)(b0 + min(i, n - 1)) * p.hq + a], threadIdx.x & 3);
 }
 
-// dK, dV: 64 key rows per workgroup (grid: key block, kv head, sequence); a quad owns one key row and walks the query
-// rows j .. n-1 of every query head of the group
-template <typename T, int D>
+// dK, dV: 64 key rows per workgroup (grid: key block, kv head, sequence)
+template <int D>
 __global__ __launch_bounds__(256) void bwd_dkv_kernel(BwdParams p) {
-  constexpr int Q4 = D / 4;
-  const int c = blockIdx.y, s = blockIdx.z;
-  const int gq = p.hq / p.hkv;
   int b0, n;
-  clamped_bounds(p.cu, s, p.total, p.max_seqlen, b0, n);
+  clamped_bounds(p.cu, blockIdx.z, p.total, p.max_seqlen, b0, n);
   const int key0 = blockIdx.x * 64;
   if (key0 >= n) return;
-  const int qt = threadIdx.x & 3;
-  const int j = key0 + (threadIdx.x >> 2);
-  const bool key_ok = j < n;
-  const int jc = key_ok ? j : n - 1;
-  const long long jo = ((long long)(b0 + jc) * p.hkv + c);
-  float kx[Q4], vx[Q4], dk[Q4], dv[Q4];
-  load_quarter<T, D>((const T*)p.k + jo * D, qt, kx);
-  load_quarter<T, D>((const T*)p.v + jo * D, qt, vx);
-#pragma unroll
-  for (int e = 0; e < Q4; ++e) { kx[e] *= p.scale_log2; dk[e] = 0.f; dv[e] = 0.f; }
-  const int wave_first = key0 + (int)(threadIdx.x / kWave) * 16;   // the wave's keys are wave_first .. wave_first + 15
-  for (int ai = 0; ai < gq; ++ai) {
-    const int a = head_of_slot(p.heads, c * gq + ai);
-    for (int i = wave_first; i < n; ++i) {
-      const long long io = ((long long)(b0 + i) * p.hq + a);
-      float q[Q4], g[Q4];
-      load_quarter<T, D>((const T*)p.q + io * D, qt, q);
-      load_quarter<T, D>((const T*)p.d_out + io * D, qt, g);
-      float sc = 0.f, dp = 0.f;
-#pragma unroll
-      for (int e = 0; e < Q4; ++e) { sc = __builtin_fmaf(q[e], kx[e], sc); dp = __builtin_fmaf(g[e], vx[e], dp); }
-      sc = quad_sum(sc);
-      dp = quad_sum(dp);
-      const float pr = jc <= i ? __builtin_amdgcn_exp2f(sc - p.lse[io] * 1.4426950408889634f) : 0.f;   // query i sees keys 0 .. i
-      const float ds = pr * (dp - p.dsum[io]);
-#pragma unroll
-      for (int e = 0; e < Q4; ++e) { dv[e] = __builtin_fmaf(pr, g[e], dv[e]); dk[e] = __builtin_fmaf(ds, q[e], dk[e]); }
-    }
-  }
-  if (!key_ok) return;
-#pragma unroll
-  for (int e = 0; e < Q4; ++e) dk[e] *= p.scale;
-  store_quarter<T, D>((T*)p.dk + jo * D, qt, dk);
-  store_quarter<T, D>((T*)p.dv + jo * D, qt, dv);
+  bwd_dkv_row<float, D, 4>(p, b0, n, blockIdx.y, key0 + (threadIdx.x >> 2), key0 + (int)(threadIdx.x / kWave) * 16, threadIdx.x & 3);
 }
 
 // ------------------------------------------------------------------------------------------------------------------
@@ -337,6 +348,16 @@ __device__ __forceinline__ void pin(f32x16 (&o)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(o[i]));
 }
+// Is there a NaN in the wave's sums (or infinities of both signs)?  A masked pair enters the products with weight 0, which an
+// infinity or NaN on its other side turns into NaN, and an infinity times an operand of three terms may be inf - inf: such
+// rows are worked out again on the vector ALU, pair by pair.
+template <int N>
+__device__ __forceinline__ bool any_nan(const f32x16 (&o)[N]) {
+  float x = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16 * N; ++i) x += o[i / 16][i % 16];
+  return __any(x != x);
+}
 template <int D>
 __device__ __forceinline__ void bwd_store_row(__bf16* row /* + 4 hf */, const f32x16 (&o)[D / 32], float scale) {
 #pragma unroll
@@ -436,8 +457,17 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bwd_dq_mfma_kernel(BwdParams p)
       bwd_accumulate<D>(tk, fo, tp, d_score, o, [](int) {});
     }
   }
-  if (!active || qw + r32 >= n) return;
-  bwd_store_row<D>((__bf16*)p.dq + io * D + 4 * hf, o, p.scale);
+  if (!active) return;
+  constexpr int L = D / 16;   // lanes per row of the vector form
+  if (any_nan(o)) {
+#pragma unroll 1
+    for (int r = 0; r < 32 && qw + r < n; r += kWave / L) {
+      const int i = r + lane / L;
+      bwd_dq_row<__bf16, D, L>(p, b0, n, blk.c, blk.a, qw + i, min(n, qw + r + kWave / L) - 1, __shfl(dsum, i, kWave), lane % L);
+    }
+    return;
+  }
+  if (qw + r32 < n) bwd_store_row<D>((__bf16*)p.dq + io * D + 4 * hf, o, p.scale);
 }
 
 // dK and dV of 32 * KW key rows of one kv head: walks the (head of the group, query tile) pairs from the block's own rows
@@ -592,21 +622,30 @@ __global__ __launch_bounds__(64 * KW * G, 2) void bwd_dkv_mfma_kernel(BwdParams 
   };
   add_groups(dv);
   add_groups(dk);
-  if (grp > 0 || !active || kw + r32 >= n) return;
+  if (grp > 0 || !active) return;
+  constexpr int L = D / 16;   // lanes per row of the vector form
+  if (any_nan(dk) || any_nan(dv)) {
+    int at = lane;
+    asm volatile("" : "+v"(at));   // nothing of this branch is worked out ahead of the loop above, which has no register to spare
+#pragma unroll 1
+    for (int r = 0; r < 32 && kw + r < n; r += kWave / L) bwd_dkv_row<__bf16, D, L>(p, b0, n, blk.c, kw + r + at / L, kw + r, at % L);
+    return;
+  }
+  if (kw + r32 >= n) return;
   bwd_store_row<D>((__bf16*)p.dk + jo * D + 4 * hf, dk, p.scale);
   bwd_store_row<D>((__bf16*)p.dv + jo * D + 4 * hf, dv, 1.f);
 }
 
 size_t attn_backward_workspace_bytes(int hq, int total_tokens) { return ((size_t)total_tokens * hq * sizeof(float) + 255) / 256 * 256; }
 
-template <typename T, int D>
-static void launch_bwd_t(const BwdParams& p, int total_tokens, int max_seqlen, hipStream_t stream) {
+template <int D>
+static void launch_bwd_f32(const BwdParams& p, int total_tokens, int max_seqlen, hipStream_t stream) {
   const long long rows = (long long)total_tokens * p.hq;
-  hipLaunchKernelGGL((bwd_dsum_kernel<T, D>), dim3((unsigned)((rows * 4 + 255) / 256)), dim3(256), 0, stream, (const T*)p.out,
-                     (const T*)p.d_out, p.dsum, rows);
+  hipLaunchKernelGGL((bwd_dsum_kernel<D>), dim3((unsigned)((rows * 4 + 255) / 256)), dim3(256), 0, stream, (const float*)p.out,
+                     (const float*)p.d_out, p.dsum, rows);
   const unsigned blocks = (unsigned)((max_seqlen + 63) / 64);
-  hipLaunchKernelGGL((bwd_dq_kernel<T, D>), dim3(blocks, p.hq, p.batch), dim3(256), 0, stream, p);
-  hipLaunchKernelGGL((bwd_dkv_kernel<T, D>), dim3(blocks, p.hkv, p.batch), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((bwd_dq_kernel<D>), dim3(blocks, p.hq, p.batch), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((bwd_dkv_kernel<D>), dim3(blocks, p.hkv, p.batch), dim3(256), 0, stream, p);
 }
 
 // Workgroups of 128 owned rows as long as there are 512 of them (two per CU).  Below that, 64-row ones, and for dK / dV,
@@ -647,7 +686,7 @@ int launch_attn_backward(const earn_attn_desc* desc, const void* q, const void* 
   if (make_head_map(desc, &p.heads, "earn_attn_backward") != EARN_OK) return EARN_ERR_UNSUPPORTED;
   if (batch > 65535 || p.hq > 65535) { set_error("earn_attn_backward: batch or head count beyond 65535"); return EARN_ERR_UNSUPPORTED; }
   if (desc->dtype == EARN_F32) {
-    if (d == 64) launch_bwd_t<float, 64>(p, total_tokens, max_seqlen, stream); else launch_bwd_t<float, 128>(p, total_tokens, max_seqlen, stream);
+    if (d == 64) launch_bwd_f32<64>(p, total_tokens, max_seqlen, stream); else launch_bwd_f32<128>(p, total_tokens, max_seqlen, stream);
   } else {
     if (d == 64) launch_bwd_mfma<64>(p, stream); else launch_bwd_mfma<128>(p, stream);
   }

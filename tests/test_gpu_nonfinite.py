@@ -57,3 +57,58 @@ def test_decode_non_finite_rows(kind, hq, hkv, d, n):
     elif kind == "value inf":
         assert (ref[1, head:, 7] == INF).all() and (ref[1, head:, 8] == -INF).all() and (ref[1, head:, 9] == INF).all()
     same(got, ref, 4.0 * np.ones_like(ref), kind)
+
+
+@pytest.mark.parametrize("dtype", [BF, torch.float32])
+@pytest.mark.parametrize("hq,hkv,d,n,batch", [(2, 2, 64, 40, 2), (4, 2, 128, 70, 2), (4, 1, 128, 70, 1), (32, 32, 128, 40, 32)])
+@pytest.mark.parametrize("kind", ["late key inf", "late key NaN", "late value inf", "late value NaN", "early query inf",
+                                  "early gradient inf", "early gradient NaN", "gradients of both signs"])
+def test_backward_non_finite_rows(kind, hq, hkv, d, n, batch, dtype):
+    """A row's infinity or NaN reaches the pairs (query i, key j <= i) that it is part of and no others: what is masked is not
+    multiplied by zero.  One sequence holds it; n is past the 32-row tile, the element in the middle of one."""
+    from paper_2507_00715_amd import binding as B
+    rng = np.random.default_rng(n + d + hq)
+    q, g, out = (bf16(rng.standard_normal((batch, n, hq, d))) for _ in range(3))
+    k, v = (bf16(rng.standard_normal((batch, n, hkv, d))) for _ in range(2))
+    q[..., 5] = bf16(-np.abs(q[..., 5]) - 0.5)      # the sign of an infinite key's scores is known: -inf
+    gq, scale, b, c = hq // hkv, d ** -0.5, batch - 1, hkv - 1
+    see = np.arange(n)[:, None] >= np.arange(n)[None]
+    with np.errstate(invalid="ignore", over="ignore"):
+        def scores(bb, a):
+            return (q[bb, :, a] @ k[bb, :, a // gq].T) * scale
+        lse = np.array([[np.log(np.where(see, np.exp(scores(bb, a)), 0.0).sum(1)) for a in range(hq)] for bb in range(batch)])
+        lse = lse.astype(np.float32).astype(np.float64)
+        where = {"late": n - 5, "early": 4, "gradients": 4}[kind.split()[0]]
+        value = NAN if kind.endswith("NaN") else INF
+        if "key" in kind: k[b, where, c, 5] = value
+        elif "value" in kind: v[b, where, c, 5] = value
+        elif "query" in kind: q[b, where, c * gq, 5] = -value
+        else: g[b, where, c * gq, 5] = value
+        if kind == "gradients of both signs": g[b, where + 2, c * gq, 5] = -value
+        ref = {x: np.zeros_like(t) for x, t in (("dq", q), ("dk", k), ("dv", v))}
+        size = {x: np.zeros_like(t) for x, t in ref.items()}
+
+        def add(x, at, term):
+            ref[x][at] += term
+            size[x][at] += np.abs(np.where(np.isfinite(term), term, 0.0))
+
+        for bb, a in [(b, aa) for aa in range(c * gq, hq)]:     # the heads that share the kv head; the others must just be finite
+            cc = a // gq
+            d_i = (g[bb, :, a] * out[bb, :, a]).sum(-1)
+            for i in range(n):
+                for j in range(i + 1):
+                    p = np.exp((q[bb, i, a] * k[bb, j, cc]).sum() * scale - lse[bb, a, i])
+                    ds = p * ((g[bb, i, a] * v[bb, j, cc]).sum() - d_i[i])
+                    add("dq", (bb, i, a), ds * scale * k[bb, j, cc])
+                    add("dk", (bb, j, cc), ds * scale * q[bb, i, a])
+                    add("dv", (bb, j, cc), p * g[bb, i, a])
+    to = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dtype).to(DEV).reshape(batch * n, -1, d)
+    d_lse = torch.from_numpy(np.ascontiguousarray(np.moveaxis(lse, 1, 2)).astype(np.float32)).to(DEV).reshape(batch * n, hq)
+    grads = [torch.full_like(to(x), 7.0) for x in (q, k, v)]
+    B.earn_attn_backward(B.make_desc(dtype, hq, hkv, d, scale, 0.0), to(q), to(k), to(v), to(out), d_lse, to(g),
+                         i32(range(0, (batch + 1) * n, n)), batch, batch * n, n, *grads)
+    torch.cuda.synchronize()
+    for x, t, heads in zip(("dq", "dk", "dv"), grads, (slice(c * gq, hq), slice(c, hkv), slice(c, hkv))):
+        got = t.cpu().double().numpy().reshape(ref[x].shape)
+        same(got[b][:, heads], ref[x][b][:, heads], size[x][b][:, heads], f"{kind}: {x}")
+        assert np.isfinite(got[:b]).all() and np.isfinite(np.delete(got[b], np.arange(heads.start, heads.stop), axis=1)).all()
