@@ -108,7 +108,11 @@ __device__ __forceinline__ int list_from_exact_threshold(const TopkValues& v, in
     for (int e = 0; e < 4; ++e) mine += __popcll(__ballot((own >> e) & 1) & ((1ull << lane) - 1ull));
 #pragma unroll 1
     for (unsigned m = own; m; m &= m - 1, ++mine)
-      if (mine < need) { sm.list_v[n_above + mine] = t; sm.list_i[n_above + mine] = position_of(4 * s + __ffs(m) - 1); }
+      if (mine < need) {   // its own value, not t: zeros of either sign are equal
+        const int bit = 4 * s + __ffs(m) - 1;
+        sm.list_v[n_above + mine] = value_of(v, bit);
+        sm.list_i[n_above + mine] = position_of(bit);
+      }
   }
   return n_above + min(at, need);
 }

@@ -83,6 +83,22 @@ def test_beam_topk_threshold_edges(kind, beams, vocab):
     np.testing.assert_array_equal(score, ref["score"])
 
 
+@pytest.mark.parametrize("beams,vocab", [(3, 2730), (4, 100), (20, 3333)])
+def test_beam_topk_keeps_the_sign_of_zero(beams, vocab):
+    """Zeros of both signs are equal scores; a pick returns its own bits."""
+    B = _B()
+    batch = 2
+    rng = np.random.default_rng(vocab)
+    lp = np.where(rng.random((batch * beams, vocab)) < 0.5, np.float32(-0.0), np.float32(0.0)).astype(np.float32)
+    bs = np.full(batch * beams, -0.0, dtype=np.float32)
+    ref = O.beam_topk(bs, lp, batch, beams, vocab)
+    assert np.signbit(ref["score"]).any()
+    parent, token, score = gpu_topk(B, bs, lp, batch, beams, vocab)
+    np.testing.assert_array_equal(parent, ref["parent"])
+    np.testing.assert_array_equal(token, ref["token"])
+    np.testing.assert_array_equal(score.view(np.int32), ref["score"].view(np.int32))
+
+
 def test_beam_argument_errors_and_limits():
     B = _B()
     z = torch.zeros(4, 8, device=DEV)
