@@ -9,8 +9,6 @@
 //   bf16  bwd_dq_mfma_kernel, bwd_dkv_mfma_kernel: the five products on the matrix cores.
 //   fp32  bwd_dsum_kernel, bwd_dq_kernel, bwd_dkv_kernel: vector ALU, four lanes share a row and hold d/4 of its elements
 //         each (the precise form for the small fp32 configuration; in bf16, of rows with infinities or NaN).
-#include <algorithm>
-
 #include "common.h"
 #include "mfma_tiles.h"
 
@@ -21,8 +19,7 @@ struct BwdParams {
   const int32_t* cu; float* dsum;  // D: [tokens, Hq] (fp32 kernels) or [Hq, tokens] (bf16 kernels)
   void* dq; void* dk; void* dv;
   int batch, hq, hkv, total, max_seqlen;
-  int n_blk;   // row blocks of the longest sequence (bf16 kernels)
-  int chunk;   // (sequence, kv head) pairs an XCD works on together (bf16 kernels)
+  BackwardPlan plan;   // of this launch (bf16 kernels)
   float scale, scale_log2;
   HeadMap heads;
 };
@@ -211,24 +208,17 @@ __global__ __launch_bounds__(256) void bwd_dkv_kernel(BwdParams p) {
 // replaced: 16 sequences of 272-1040 rows, 32 / 8 heads of 128: 18.36 -> 0.60 ms; 64 sequences of 68 rows: 1.01 -> 0.12 ms.
 // ------------------------------------------------------------------------------------------------------------------
 struct BwdBlock { int c, a, b0, n, row0; bool valid; };
-// Workgroup -> (sequence, kv head, block of owned rows, query head of the group).  Consecutive ids go to the 8 XCDs in turn,
-// and an XCD keeps its own (sequence, kv head) pairs, whose rows its L2 then holds.  It takes them in chunks of p.chunk
-// pairs, within a chunk longest work first over ALL its pairs: a block's work is the number of rows it is paired with
-// (late queries; keys counted from the sequence's end), so with few pairs no long block is left to start when the GPU is
-// about to run dry.  (keys_own: the owned rows are keys.)
-__device__ __forceinline__ BwdBlock bwd_map_block(const BwdParams& p, int block_rows, int heads, bool keys_own) {
+// Workgroup -> (sequence, kv head, block of owned rows, query head of the group)
+template <Owned ROWS_ARE>
+__device__ __forceinline__ BwdBlock bwd_map_block(const BwdParams& p, int block_rows, int heads) {
   BwdBlock b;
   b.valid = false;
-  const int gq = p.hq / p.hkv;
-  const int xcd = blockIdx.x % kXcds, k_in_xcd = blockIdx.x / kXcds;
-  const int per_chunk = p.chunk * p.n_blk * heads;
-  const int rem = k_in_xcd % per_chunk, j = rem / (p.chunk * heads);   // j: 0 = the longest work
-  const int pair = (k_in_xcd / per_chunk * p.chunk + rem / heads % p.chunk) * kXcds + xcd;
-  if (pair >= p.batch * p.hkv) return b;
-  b.c = pair % p.hkv;
-  b.a = head_of_slot(p.heads, b.c * gq + rem % heads);
-  clamped_bounds(p.cu, pair / p.hkv, p.total, p.max_seqlen, b.b0, b.n);
-  const int blk = keys_own ? (b.n + block_rows - 1) / block_rows - p.n_blk + j : p.n_blk - 1 - j;
+  const BackwardItem it = backward_item(p.plan, heads, blockIdx.x);
+  if (it.pair >= p.batch * p.hkv) return b;
+  b.c = it.pair % p.hkv;
+  b.a = head_of_slot(p.heads, b.c * (p.hq / p.hkv) + it.head);
+  clamped_bounds(p.cu, it.pair / p.hkv, p.total, p.max_seqlen, b.b0, b.n);
+  const int blk = backward_block(ROWS_ARE, p.plan, (b.n + block_rows - 1) / block_rows, it.step);
   b.row0 = blk * block_rows;
   b.valid = blk >= 0 && b.row0 < b.n;
   return b;
@@ -368,13 +358,14 @@ __device__ __forceinline__ void bwd_store_row(__bf16* row /* + 4 hf */, const f3
                                                pack_bf16(o[db][4 * j + 2] * scale, o[db][4 * j + 3] * scale)};
 }
 
-// D and dQ of 32 * WAVES query rows of one head
+// D and dQ of 32 * WAVES query rows of one head.  (Late queries, which see the most keys, are dispatched first: with early ones
+// first, 2 sequences of 2080 rows, 32 / 8 heads of 128, took 442 us for 423, 8 of 500-1000 with 12 / 2 heads 197 for 184.)
 template <int D, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void bwd_dq_mfma_kernel(BwdParams p) {
   constexpr int ROWS = 16 * WAVES, BLOCK = 32 * WAVES;   // keys per tile, query rows per workgroup
   __shared__ __bf16 smk[2][ROWS * D];
   __shared__ __bf16 smv[2][ROWS * D];
-  const BwdBlock blk = bwd_map_block(p, BLOCK, p.hq / p.hkv, true);
+  const BwdBlock blk = bwd_map_block<Owned::kQueries>(p, BLOCK, p.hq / p.hkv);
   if (!blk.valid) return;
   const int b0 = blk.b0, n = blk.n;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -483,7 +474,7 @@ __global__ __launch_bounds__(64 * KW * G, 2) void bwd_dkv_mfma_kernel(BwdParams 
   __shared__ __bf16 smk[KEYS_IN_LDS ? BLOCK * D : 8];
   __shared__ float sml[G][2][2 * ROWS];                    // -lse / scale, then -D, of a tile's queries: start values of S, dP
   static_assert(G == 1 || sizeof(sm) >= sizeof(f32x16) * DB * 64 * KW);
-  const BwdBlock blk = bwd_map_block(p, BLOCK, 1, true);
+  const BwdBlock blk = bwd_map_block<Owned::kKeys>(p, BLOCK, 1);
   if (!blk.valid) return;
   const int b0 = blk.b0, n = blk.n, gq = p.hq / p.hkv;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave % KW);
@@ -655,13 +646,11 @@ static void launch_bwd_f32(const BwdParams& p, int total_tokens, int max_seqlen,
 // work, 16 sequences of 272-1040, it is 578 against 519, and 64 sequences of 68 rows 142 against 118).
 template <int D>
 static void launch_bwd_mfma(BwdParams& p, hipStream_t stream) {
-  const int per_xcd = (int)(((long long)p.batch * p.hkv + kXcds - 1) / kXcds);  // pairs
-  auto fills = [&](int heads) { return (long long)per_xcd * kXcds * ((p.max_seqlen + 127) / 128) * heads >= 512; };
-  // fills the mapping fields of p
+  const long long pairs = (long long)p.batch * p.hkv;
+  auto fills = [&](int heads) { return (pairs + kXcds - 1) / kXcds * kXcds * ((p.max_seqlen + 127) / 128) * heads >= 512; };
   auto plan = [&](int rows, int heads) {
-    p.n_blk = (p.max_seqlen + rows - 1) / rows;
-    p.chunk = std::max(1, std::min(per_xcd, 256 / (p.n_blk * heads)));  // about four rounds of an XCD's 64 workgroup slots
-    return dim3((unsigned)((long long)((per_xcd + p.chunk - 1) / p.chunk) * p.chunk * p.n_blk * heads * kXcds));
+    p.plan = backward_plan(pairs, p.max_seqlen, rows, heads);
+    return dim3((unsigned)backward_workgroups(p.plan, heads));
   };
   const int gq = p.hq / p.hkv;
   const bool dq_wide = p.max_seqlen > 64 && fills(gq), dkv_wide = fills(1);

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/earn.h"
+#include "work_order.h"
 
 namespace earn {
 
@@ -55,8 +56,6 @@ __device__ __forceinline__ void clamped_bounds(const int32_t* cu, int s, int tot
   b0 = min(max(cu[s], 0), total);
   n = min(min(max(cu[s + 1] - b0, 0), total - b0), max_len);
 }
-
-constexpr int kXcds = 8;  // accelerator complex dies, each with a private L2; consecutive workgroup ids go to them in turn
 
 enum Tuning { kTunePrefillBlockRows, kTuneDecMfmaMinLen, kTuneDecMfmaShortWgs, kTuneDecMfmaWgs, kTuneDecVecWgs,
               kTuneDecVecWaves, kTuneCompactBlocks, kTuneLinearTile, kTuneLinearSplits, kTuneCount };

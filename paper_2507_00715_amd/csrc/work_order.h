@@ -1,0 +1,47 @@
+// Which work a workgroup takes: index arithmetic of the launches and kernels, free of device code, so that it can be checked
+// on the host for every workgroup of a launch.
+#pragma once
+#ifdef __HIPCC__
+#define EARN_INDEX __host__ __device__ __forceinline__
+#else
+#define EARN_INDEX inline
+#endif
+
+namespace earn {
+
+constexpr int kXcds = 8;  // accelerator complex dies, each with a private L2; consecutive workgroup ids go to them in turn
+
+// ---- attention backward (bf16): (sequence, kv head) pairs, blocks of owned rows, query heads of the group ----
+// An XCD keeps its own pairs, whose rows its L2 then holds.  It takes them in chunks, within a chunk longest work first over
+// ALL its pairs: a block's work is the number of rows it is paired with (keys up to a query, queries from a key on), so with
+// few pairs no long block is left to start when the GPU is about to run dry.
+struct BackwardPlan {
+  int n_blk;      // row blocks of the longest sequence
+  int chunk;      // pairs an XCD works on together: about four rounds of its 64 workgroup slots
+  int per_xcd;    // pairs of an XCD
+};
+EARN_INDEX BackwardPlan backward_plan(long long pairs, int max_seqlen, int block_rows, int heads) {
+  BackwardPlan b;
+  b.per_xcd = (int)((pairs + kXcds - 1) / kXcds);
+  b.n_blk = (max_seqlen + block_rows - 1) / block_rows;
+  const int fit = 256 / (b.n_blk * heads);
+  b.chunk = fit < 1 ? 1 : fit < b.per_xcd ? fit : b.per_xcd;
+  return b;
+}
+EARN_INDEX long long backward_workgroups(const BackwardPlan& b, int heads) {
+  return (long long)((b.per_xcd + b.chunk - 1) / b.chunk) * b.chunk * b.n_blk * heads * kXcds;
+}
+// step: 0 = the longest work of a chunk, n_blk - 1 the shortest.  pair may lie past the last one.
+struct BackwardItem { int pair, head, step; };
+EARN_INDEX BackwardItem backward_item(const BackwardPlan& b, int heads, int id) {
+  const int xcd = id % kXcds, k = id / kXcds, per_chunk = b.chunk * b.n_blk * heads, rem = k % per_chunk;
+  return BackwardItem{(k / per_chunk * b.chunk + rem / heads % b.chunk) * kXcds + xcd, rem % heads, rem / (b.chunk * heads)};
+}
+// The block of a sequence of `blocks` blocks that is step `step`; outside [0, blocks): none.  Queries are paired with the
+// keys before them, so the last block is the longest work; keys with the queries after them: the first.
+enum class Owned { kQueries, kKeys };
+EARN_INDEX int backward_block(Owned rows, const BackwardPlan& b, int blocks, int step) {
+  return rows == Owned::kQueries ? b.n_blk - 1 - step : blocks - b.n_blk + step;
+}
+
+}  // namespace earn

@@ -1,0 +1,72 @@
+"""The launches' index arithmetic (csrc/work_order.h), compiled for the host: every workgroup of a launch, in dispatch order."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_00715_amd", "csrc")
+SOURCE = r'''
+#include "work_order.h"
+using namespace earn;
+extern "C" long long backward(long long pairs, int max_seqlen, int rows, int heads, int* chunk, int (*out)[3], long long limit) {
+  const BackwardPlan b = backward_plan(pairs, max_seqlen, rows, heads);
+  const long long n = backward_workgroups(b, heads);
+  *chunk = b.chunk;
+  for (long long i = 0; i < n && i < limit; ++i) {
+    const BackwardItem it = backward_item(b, heads, (int)i);
+    out[i][0] = it.pair; out[i][1] = it.head; out[i][2] = it.step;
+  }
+  return n;
+}
+extern "C" int block_of(int keys, long long pairs, int max_seqlen, int rows, int heads, int blocks, int step) {
+  return backward_block(keys ? Owned::kKeys : Owned::kQueries, backward_plan(pairs, max_seqlen, rows, heads), blocks, step);
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("order")
+    (d / "order.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "order.so"), str(d / "order.cpp")],
+                   check=True)
+    so = ctypes.CDLL(str(d / "order.so"))
+    so.backward.restype = ctypes.c_longlong
+    so.backward.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_longlong]
+    so.block_of.argtypes = [ctypes.c_int, ctypes.c_longlong, *[ctypes.c_int] * 5]
+    return so
+
+
+@pytest.mark.parametrize("keys", [False, True])
+@pytest.mark.parametrize("rows", [64, 128])
+@pytest.mark.parametrize("batch,hkv,gq,lo,hi", [(16, 8, 4, 272, 1040), (1, 1, 1, 1, 64), (3, 2, 7, 0, 2080), (64, 8, 4, 68, 68),
+                                                (5, 32, 1, 1, 300), (2, 8, 4, 4096, 4096)])
+def test_backward_covers_every_block_longest_first(lib, batch, hkv, gq, lo, hi, rows, keys):
+    rng = np.random.default_rng(batch + hi)
+    lens = rng.integers(lo, hi + 1, batch)
+    lens[batch // 2] = hi
+    heads, pairs = (1 if keys else gq), batch * hkv
+    chunk = ctypes.c_int()
+    n = lib.backward(pairs, hi, rows, heads, ctypes.byref(chunk), None, 0)
+    item = np.empty((n, 3), dtype=np.int32)
+    assert lib.backward(pairs, hi, rows, heads, ctypes.byref(chunk), item.ctypes.data, n) == n
+    seen, last = {}, {}
+    for i, (pair, head, step) in enumerate(item.tolist()):
+        if pair >= pairs:
+            continue
+        length = int(lens[pair // hkv])
+        blocks = (length + rows - 1) // rows
+        blk = lib.block_of(keys, pairs, hi, rows, heads, blocks, step)
+        if not 0 <= blk < blocks:
+            continue
+        seen[pair, head, blk] = seen.get((pair, head, blk), 0) + 1
+        # the XCD that a workgroup id goes to keeps the pair; within a chunk of its pairs the work does not grow
+        assert pair % 8 == i % 8
+        work = (blocks - blk) if keys else blk + 1
+        group = (i % 8, pair // 8 // chunk.value)
+        assert last.get(group, 1 << 30) >= work
+        last[group] = work
+    assert set(seen.values()) <= {1}
+    assert len(seen) == sum((int(x) + rows - 1) // rows for x in lens) * hkv * heads
