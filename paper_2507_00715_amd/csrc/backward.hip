@@ -213,11 +213,11 @@ template <Owned ROWS_ARE>
 __device__ __forceinline__ BwdBlock bwd_map_block(const BwdParams& p, int block_rows, int heads) {
   BwdBlock b;
   b.valid = false;
-  const BackwardItem it = backward_item(p.plan, heads, blockIdx.x);
-  if (it.pair >= p.batch * p.hkv) return b;
-  b.c = it.pair % p.hkv;
+  const BackwardItem it = backward_item(p.plan, heads, blockIdx.z * gridDim.y + blockIdx.y, blockIdx.x);
+  if (it.pair >= (long long)p.batch * p.hkv) return b;
+  b.c = (int)it.pair % p.hkv;
   b.a = head_of_slot(p.heads, b.c * (p.hq / p.hkv) + it.head);
-  clamped_bounds(p.cu, it.pair / p.hkv, p.total, p.max_seqlen, b.b0, b.n);
+  clamped_bounds(p.cu, (int)it.pair / p.hkv, p.total, p.max_seqlen, b.b0, b.n);
   const int blk = backward_block(ROWS_ARE, p.plan, (b.n + block_rows - 1) / block_rows, it.step);
   b.row0 = blk * block_rows;
   b.valid = blk >= 0 && b.row0 < b.n;
@@ -650,7 +650,8 @@ static void launch_bwd_mfma(BwdParams& p, hipStream_t stream) {
   auto fills = [&](int heads) { return (pairs + kXcds - 1) / kXcds * kXcds * ((p.max_seqlen + 127) / 128) * heads >= 512; };
   auto plan = [&](int rows, int heads) {
     p.plan = backward_plan(pairs, p.max_seqlen, rows, heads);
-    return dim3((unsigned)backward_workgroups(p.plan, heads));
+    const BackwardGrid g = backward_grid(p.plan, heads);
+    return dim3(g.x, g.y, g.z);
   };
   const int gq = p.hq / p.hkv;
   const bool dq_wide = p.max_seqlen > 64 && fills(gq), dkv_wide = fills(1);

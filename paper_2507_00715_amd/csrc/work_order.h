@@ -28,14 +28,19 @@ EARN_INDEX BackwardPlan backward_plan(long long pairs, int max_seqlen, int block
   b.chunk = fit < 1 ? 1 : fit < b.per_xcd ? fit : b.per_xcd;
   return b;
 }
-EARN_INDEX long long backward_workgroups(const BackwardPlan& b, int heads) {
-  return (long long)((b.per_xcd + b.chunk - 1) / b.chunk) * b.chunk * b.n_blk * heads * kXcds;
+// A chunk is a row of the grid: what all chunks hold together may be more than one grid dimension takes (65535 sequences, 32
+// heads, 9 blocks are 19 million workgroups).
+struct BackwardGrid { unsigned x, y, z; };
+EARN_INDEX BackwardGrid backward_grid(const BackwardPlan& b, int heads) {
+  const unsigned chunks = (unsigned)((b.per_xcd + b.chunk - 1) / b.chunk), y = chunks < 32768u ? chunks : 32768u;
+  return BackwardGrid{(unsigned)b.chunk * b.n_blk * heads * kXcds, y, (chunks + y - 1) / y};
 }
-// step: 0 = the longest work of a chunk, n_blk - 1 the shortest.  pair may lie past the last one.
-struct BackwardItem { int pair, head, step; };
-EARN_INDEX BackwardItem backward_item(const BackwardPlan& b, int heads, int id) {
-  const int xcd = id % kXcds, k = id / kXcds, per_chunk = b.chunk * b.n_blk * heads, rem = k % per_chunk;
-  return BackwardItem{(k / per_chunk * b.chunk + rem / heads % b.chunk) * kXcds + xcd, rem % heads, rem / (b.chunk * heads)};
+// Workgroup `id` of chunk `chunk`.  step: 0 = the longest work of a chunk, n_blk - 1 the shortest.  pair may lie past the last
+// one.
+struct BackwardItem { long long pair; int head, step; };
+EARN_INDEX BackwardItem backward_item(const BackwardPlan& b, int heads, int chunk, int id) {
+  const int xcd = id % kXcds, k = id / kXcds;
+  return BackwardItem{((long long)chunk * b.chunk + k / heads % b.chunk) * kXcds + xcd, k % heads, k / (b.chunk * heads)};
 }
 // The block of a sequence of `blocks` blocks that is step `step`; outside [0, blocks): none.  Queries are paired with the
 // keys before them, so the last block is the longest work; keys with the queries after them: the first.

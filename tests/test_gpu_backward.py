@@ -83,6 +83,16 @@ def test_attention_backward_at_tile_edges(hq, hkv, d, lens):
     test_attention_backward_matches_oracle(BF, hq, hkv, d, lens, 0.0)
 
 
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (64, 8, 64, [300, 61, 129, 200, 7, 257, 90, 128, 33, 300, 64, 150]),     # dQ: 12 pairs per XCD in chunks of 10
+    (8, 8, 64, [300] + [1 + 7 * i % 40 for i in range(87)]),                 # 88 pairs per XCD in chunks of 85
+])
+def test_attention_backward_in_several_chunks(hq, hkv, d, lens):
+    """More (sequence, kv head) pairs than an XCD works on together: several chunks, the last one partly filled.  (The
+    gradients start as NaN, so a block that no workgroup takes shows.)"""
+    test_attention_backward_matches_oracle(BF, hq, hkv, d, lens, 0.0)
+
+
 def test_attention_backward_argument_errors():
     B = _B()
     z = torch.zeros(8, 2, 64, dtype=BF, device=DEV)

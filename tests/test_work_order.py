@@ -12,13 +12,18 @@ SOURCE = r'''
 using namespace earn;
 extern "C" long long backward(long long pairs, int max_seqlen, int rows, int heads, int* chunk, int (*out)[3], long long limit) {
   const BackwardPlan b = backward_plan(pairs, max_seqlen, rows, heads);
-  const long long n = backward_workgroups(b, heads);
+  const BackwardGrid g = backward_grid(b, heads);
+  const long long n = (long long)g.x * g.y * g.z;
   *chunk = b.chunk;
   for (long long i = 0; i < n && i < limit; ++i) {
-    const BackwardItem it = backward_item(b, heads, (int)i);
-    out[i][0] = it.pair; out[i][1] = it.head; out[i][2] = it.step;
+    const BackwardItem it = backward_item(b, heads, (int)(i / g.x), (int)(i % g.x));
+    out[i][0] = (int)it.pair; out[i][1] = it.head; out[i][2] = it.step;
   }
   return n;
+}
+extern "C" void backward_grid_of(long long pairs, int max_seqlen, int rows, int heads, long long (*g)[3]) {
+  const BackwardGrid b = backward_grid(backward_plan(pairs, max_seqlen, rows, heads), heads);
+  (*g)[0] = b.x; (*g)[1] = b.y; (*g)[2] = b.z;
 }
 extern "C" int block_of(int keys, long long pairs, int max_seqlen, int rows, int heads, int blocks, int step) {
   return backward_block(keys ? Owned::kKeys : Owned::kQueries, backward_plan(pairs, max_seqlen, rows, heads), blocks, step);
@@ -70,3 +75,14 @@ def test_backward_covers_every_block_longest_first(lib, batch, hkv, gq, lo, hi, 
         last[group] = work
     assert set(seen.values()) <= {1}
     assert len(seen) == sum((int(x) + rows - 1) // rows for x in lens) * hkv * heads
+
+
+@pytest.mark.parametrize("rows,threads", [(128, 256), (64, 512)])
+@pytest.mark.parametrize("batch,hkv,gq,longest", [(65535, 8, 4, 1040), (65535, 32, 1, 2080), (65535, 64, 1, 64), (1, 1, 8, 262144)])
+def test_backward_grid_fits_a_launch(lib, batch, hkv, gq, longest, rows, threads):
+    """Every batch that the entry point takes (up to 65535 sequences) is one launch: 2^32 threads in x, 65535 workgroups in y, z."""
+    for heads in (1, gq):
+        g = (ctypes.c_longlong * 3)()
+        lib.backward_grid_of(ctypes.c_longlong(batch * hkv), longest, rows, heads, ctypes.byref(g))
+        assert g[0] * threads < 2 ** 32 and g[1] <= 65535 and g[2] <= 65535
+        assert g[0] * g[1] * g[2] >= batch * hkv * heads * ((longest + rows - 1) // rows)
