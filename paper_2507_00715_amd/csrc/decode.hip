@@ -86,6 +86,7 @@ struct DecodeParams {
   // used with causal rows, where passes differ widely in length and the long ones of a (sequence, kv head) then run
   // side by side on one XCD, sharing the keys in its L2.
   int n_pass;
+  int even_runs;  // decode_short_kernel: how its streams are dealt to the XCDs
   float scale_log2;
   // byte strides between the layers of a layer-batched launch (grid row y = layer); all zero for a single layer
   long long ls_q, ls_kv_new, ls_shared, ls_gen, ls_out, ls_part_o, ls_part_ml;
@@ -461,9 +462,9 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
   __shared__ __align__(16) __bf16 rot[3][9][D + 8];      // rotated queries (three terms) and, in row gq, the new key
   // Workgroup -> (stream, kv head): an XCD keeps a run of consecutive streams (beams of a sequence share its cache rows,
   // the kv heads of a stream share DRAM rows), so what they share is fetched into one L2.
-  const int per_xcd = (p.n_streams + kXcds - 1) / kXcds;
-  const int at = blockIdx.x / kXcds, u = (blockIdx.x % kXcds) * per_xcd + at / p.hkv, c = at % p.hkv;
-  if (at / p.hkv >= per_xcd || u >= p.n_streams) return;
+  const RunItem run = run_item(blockIdx.x, p.n_streams, p.hkv, p.even_runs);
+  if (!run.valid) return;
+  const int u = run.item, c = run.sub;
   const DecodeLayer lv = layer_view(p, blockIdx.y);
   const int gq = p.hq / p.hkv;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1456,9 +1457,15 @@ static void launch_vector(const DecodeParams& p, int gq, dim3 grid, hipStream_t 
 }
 
 // a wave per block of 32 keys for short lists (the generated rows make a block of their own), eight for longer ones
+// The XCDs take even runs of the streams, except where eight-wave workgroups outnumber the CUs: then a CU with two of them is
+// what the launch waits for, and it is done sooner when the last XCD leaves its share of the bandwidth to the others.  us per
+// layer, one launch per layer / 4 layers in one launch, whole -> even runs, 32 / 8 heads: 9 streams of 1000 rows 18.4 / 11.7 ->
+// 18.9 / 10.5, 17 of 600 14.3 / 10.7 -> 13.3 / 10.2, 25 of 600 16.6 / 13.8 -> 14.9 / 13.4, 33 of 64 (three waves) 7.2 / 3.8 ->
+// 6.7 / 3.4, but 33 of 768 35.5 / 23.4 -> 37.0 / 24.3, 65 of 2000 125 / 101 -> 130 / 104.
 template <int D>
-static void launch_short(const DecodeParams& p, hipStream_t stream, int n_layers) {
-  const dim3 grid((unsigned)((p.n_streams + kXcds - 1) / kXcds * kXcds * p.hkv), n_layers, 1);
+static void launch_short(DecodeParams& p, hipStream_t stream, int n_layers) {
+  p.even_runs = p.max_shared_len <= 128 || (long long)p.n_streams * p.hkv <= 256;
+  const dim3 grid((unsigned)run_workgroups(p.n_streams, p.hkv), n_layers, 1);
   if (p.max_shared_len <= 32) hipLaunchKernelGGL((decode_short_kernel<D, 2>), grid, dim3(128), 0, stream, p);
   else if (p.max_shared_len <= 64) hipLaunchKernelGGL((decode_short_kernel<D, 3>), grid, dim3(192), 0, stream, p);
   else if (p.max_shared_len <= 128) hipLaunchKernelGGL((decode_short_kernel<D, 4>), grid, dim3(256), 0, stream, p);

@@ -11,6 +11,19 @@ namespace earn {
 
 constexpr int kXcds = 8;  // accelerator complex dies, each with a private L2; consecutive workgroup ids go to them in turn
 
+// ---- short decode and prefill: an XCD takes a run of consecutive items (streams, sequences), each of `per` workgroups ----
+// Even runs: XCD x has items [x n / 8, (x + 1) n / 8), n / 8 of them rounded down or up.  Whole runs: n / 8 rounded up each,
+// and what is left to the last ones (9 items keep 5 XCDs busy, 17 six).
+EARN_INDEX long long run_workgroups(int n, int per) { return ((long long)n + kXcds - 1) / kXcds * kXcds * per; }
+struct RunItem { int item, sub; bool valid; };   // sub: 0 .. per - 1
+EARN_INDEX RunItem run_item(unsigned id, int n, int per, bool even) {
+  const int xcd = (int)(id % kXcds), all = (int)(id / kXcds), at = all / per;
+  const int base = n / kXcds, extra = n % kXcds, whole = base + (extra > 0 ? 1 : 0);
+  const int first = even ? xcd * base + xcd * extra / kXcds : xcd * whole;
+  const int count = even ? base + ((xcd + 1) * extra / kXcds - xcd * extra / kXcds) : whole;
+  return RunItem{first + at, all - at * per, at < count && first + at < n};
+}
+
 // ---- attention backward (bf16): (sequence, kv head) pairs, blocks of owned rows, query heads of the group ----
 // An XCD keeps its own pairs, whose rows its L2 then holds.  It takes them in chunks, within a chunk longest work first over
 // ALL its pairs: a block's work is the number of rows it is paired with (keys up to a query, queries from a key on), so with

@@ -10,6 +10,14 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = r'''
 #include "work_order.h"
 using namespace earn;
+extern "C" long long runs(int n, int per, int even, int (*out)[3], long long limit) {
+  const long long w = run_workgroups(n, per);
+  for (long long i = 0; i < w && i < limit; ++i) {
+    const RunItem r = run_item((int)i, n, per, even);
+    out[i][0] = r.item; out[i][1] = r.sub; out[i][2] = r.valid;
+  }
+  return w;
+}
 extern "C" long long backward(long long pairs, int max_seqlen, int rows, int heads, int* chunk, int (*out)[3], long long limit) {
   const BackwardPlan b = backward_plan(pairs, max_seqlen, rows, heads);
   const BackwardGrid g = backward_grid(b, heads);
@@ -38,6 +46,8 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "order.so"), str(d / "order.cpp")],
                    check=True)
     so = ctypes.CDLL(str(d / "order.so"))
+    so.runs.restype = ctypes.c_longlong
+    so.runs.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_longlong]
     so.backward.restype = ctypes.c_longlong
     so.backward.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_longlong]
     so.block_of.argtypes = [ctypes.c_int, ctypes.c_longlong, *[ctypes.c_int] * 5]
@@ -86,3 +96,20 @@ def test_backward_grid_fits_a_launch(lib, batch, hkv, gq, longest, rows, threads
         lib.backward_grid_of(ctypes.c_longlong(batch * hkv), longest, rows, heads, ctypes.byref(g))
         assert g[0] * threads < 2 ** 32 and g[1] <= 65535 and g[2] <= 65535
         assert g[0] * g[1] * g[2] >= batch * hkv * heads * ((longest + rows - 1) // rows)
+
+
+@pytest.mark.parametrize("even", [True, False])
+@pytest.mark.parametrize("per", [1, 2, 8, 24])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 10, 17, 20, 25, 64, 255, 1000])
+def test_runs_cover_every_item_once(lib, n, per, even):
+    w = lib.runs(n, per, even, None, 0)
+    out = np.empty((w, 3), dtype=np.int32)
+    lib.runs(n, per, even, out.ctypes.data, w)
+    xcd = np.arange(w) % 8
+    ok = out[:, 2] == 1
+    assert sorted(map(tuple, out[ok, :2].tolist())) == [(i, s) for i in range(n) for s in range(per)]
+    counts = np.bincount(xcd[ok], minlength=8)
+    assert not even or counts.max() - counts.min() <= per     # an item more or less, not five XCDs out of eight
+    for x in range(8):                                         # consecutive items
+        items = np.unique(out[ok & (xcd == x), 0])
+        assert items.size == 0 or items[-1] - items[0] + 1 == items.size
