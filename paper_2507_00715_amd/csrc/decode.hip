@@ -1456,7 +1456,6 @@ static void launch_vector(const DecodeParams& p, int gq, dim3 grid, hipStream_t 
   else launch_vector_w<T, D, 4>(p, gq, grid, stream);
 }
 
-// a wave per block of 32 keys for short lists (the generated rows make a block of their own), eight for longer ones
 // The XCDs take even runs of the streams, except where eight-wave workgroups outnumber the CUs: then a CU with two of them is
 // what the launch waits for, and it is done sooner when the last XCD leaves its share of the bandwidth to the others.  us per
 // layer, one launch per layer / 4 layers in one launch, whole -> even runs, 32 / 8 heads: 9 streams of 1000 rows 18.4 / 11.7 ->
@@ -1464,11 +1463,12 @@ static void launch_vector(const DecodeParams& p, int gq, dim3 grid, hipStream_t 
 // 6.7 / 3.4, but 33 of 768 35.5 / 23.4 -> 37.0 / 24.3, 65 of 2000 125 / 101 -> 130 / 104.
 template <int D>
 static void launch_short(DecodeParams& p, hipStream_t stream, int n_layers) {
-  p.even_runs = p.max_shared_len <= 128 || (long long)p.n_streams * p.hkv <= 256;
+  const int waves = short_decode_waves(p.max_shared_len, p.gen_cap, (long long)p.n_streams * p.hkv * n_layers);
+  p.even_runs = waves < 8 || (long long)p.n_streams * p.hkv <= 256;
   const dim3 grid((unsigned)run_workgroups(p.n_streams, p.hkv), n_layers, 1);
-  if (p.max_shared_len <= 32) hipLaunchKernelGGL((decode_short_kernel<D, 2>), grid, dim3(128), 0, stream, p);
-  else if (p.max_shared_len <= 64) hipLaunchKernelGGL((decode_short_kernel<D, 3>), grid, dim3(192), 0, stream, p);
-  else if (p.max_shared_len <= 128) hipLaunchKernelGGL((decode_short_kernel<D, 4>), grid, dim3(256), 0, stream, p);
+  if (waves == 2) hipLaunchKernelGGL((decode_short_kernel<D, 2>), grid, dim3(128), 0, stream, p);
+  else if (waves == 3) hipLaunchKernelGGL((decode_short_kernel<D, 3>), grid, dim3(192), 0, stream, p);
+  else if (waves == 4) hipLaunchKernelGGL((decode_short_kernel<D, 4>), grid, dim3(256), 0, stream, p);
   else hipLaunchKernelGGL((decode_short_kernel<D, 8>), grid, dim3(512), 0, stream, p);
 }
 

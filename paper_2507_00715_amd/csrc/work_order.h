@@ -24,6 +24,18 @@ EARN_INDEX RunItem run_item(unsigned id, int n, int per, bool even) {
   return RunItem{first + at, all - at * per, at < count && first + at < n};
 }
 
+// Waves of a short decode workgroup: one per block of 32 shared keys and one for the generated rows, eight for longer lists.
+// With no more workgroups than CUs, nothing else hides a wave's round trips, so the blocks that the generated rows may come to
+// count too.  us, 16 shared rows, waves by shared rows -> by all: one sequence, 32 / 8 heads, 249 / 999 generated rows 14.5 /
+// 39.8 -> 9.5 / 18.8, 4 heads of 64 in 8 sequences, 499 / 739 rows 15.9 / 21.1 -> 9.3 / 10.7 (general kernels 10.6 / 11.0);
+// place for 499 but 62 in use, 8.0 -> 6.8.  With more workgroups the fewer waves leave room for more of them: 256 sequences, 12
+// / 2 heads, 31 of 250 rows in use 7.2 -> 11.8, all 249 19.8 -> 22.2.
+EARN_INDEX int short_decode_waves(int max_shared_len, int gen_cap, long long workgroups) {
+  const long long generated = workgroups <= 256 ? ((long long)gen_cap + 31) / 32 : 1;
+  const long long blocks = ((long long)max_shared_len + 31) / 32 + generated;
+  return blocks <= 2 ? 2 : blocks == 3 ? 3 : blocks <= 5 ? 4 : 8;
+}
+
 // ---- attention backward (bf16): (sequence, kv head) pairs, blocks of owned rows, query heads of the group ----
 // An XCD keeps its own pairs, whose rows its L2 then holds.  It takes them in chunks, within a chunk longest work first over
 // ALL its pairs: a block's work is the number of rows it is paired with (keys up to a query, queries from a key on), so with

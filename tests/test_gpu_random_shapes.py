@@ -174,6 +174,9 @@ SHORT_CASES = [
     (2, 1, 64, [256, 257, 1000, 955], 1, 24, [23, 0, 11], False),
     (8, 2, 64, [30, 33, 64], 5, 8, [7, 0, 3, 6], True),
     (3, 3, 128, [60, 257], 3, 70, [69, 32, 31, 64], True),
+    (12, 2, 128, [16, 0, 5], 1, 500, [499, 0, 262], False),       # register rows and a long generated part, few workgroups
+    (4, 4, 64, [16, 30], 1, 130, [129, 95], False),
+    (8, 2, 64, [16] * 140, 1, 70, [69, 3, 33], False),            # more workgroups than CUs
 ]
 
 

@@ -10,6 +10,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = r'''
 #include "work_order.h"
 using namespace earn;
+extern "C" int waves(int max_shared_len, int gen_cap, long long workgroups) { return short_decode_waves(max_shared_len, gen_cap, workgroups); }
 extern "C" long long runs(int n, int per, int even, int (*out)[3], long long limit) {
   const long long w = run_workgroups(n, per);
   for (long long i = 0; i < w && i < limit; ++i) {
@@ -113,3 +114,11 @@ def test_runs_cover_every_item_once(lib, n, per, even):
     for x in range(8):                                         # consecutive items
         items = np.unique(out[ok & (xcd == x), 0])
         assert items.size == 0 or items[-1] - items[0] + 1 == items.size
+
+
+@pytest.mark.parametrize("shared,gen_cap,workgroups,waves", [
+    (0, 32, 8, 2), (32, 32, 10000, 2), (33, 16, 256, 3), (64, 16, 257, 3), (65, 1, 8, 4), (128, 32, 5000, 4), (129, 1, 8, 8),
+    # generated rows count where a CU has one workgroup at most
+    (16, 33, 256, 3), (16, 33, 257, 2), (16, 96, 256, 4), (16, 129, 256, 8), (16, 1000, 8, 8), (16, 1000, 2048, 2), (64, 1000, 2048, 3)])
+def test_short_decode_waves(lib, shared, gen_cap, workgroups, waves):
+    assert lib.waves(shared, gen_cap, ctypes.c_longlong(workgroups)) == waves
