@@ -1372,6 +1372,7 @@ static bool decode_few_keys(int dtype, int hq, int hkv, int n_streams, int batch
   if (dtype != EARN_BF16) return false;
   for (Tuning t : {kTuneDecMfmaMinLen, kTuneDecMfmaShortWgs, kTuneDecMfmaWgs, kTuneDecVecWgs, kTuneDecVecWaves})
     if (tuning(t, 0) != 0) return false;                 // a caller who sets the general kernels' launch shape gets them
+  if (!run_fits(n_streams, hkv, 512)) return false;      // 8 million (stream, kv head) pairs: the general kernels' smaller workgroups
   const long long pairs = (long long)n_streams * hkv, keys = (long long)max_shared_len + gen_cap;
   if (n_streams > batch) return pairs * max_shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024;
   if (hq == hkv) return pairs * n_layers <= 512 && keys <= 768;

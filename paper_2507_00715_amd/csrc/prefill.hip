@@ -1099,7 +1099,8 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   //   64 sequences, 32 / 32 heads, where every workgroup has keys of its own to stage and little to multiply: 32 rows
   //   34.4 / 27.4 -> 29.5 / 21.8, 64 rows 57.6 / 53.4 -> 60.6 / 46.6 (without rotation 38.7 -> 40.4), 96 rows 85 / 75 ->
   //   95 / 80.
-  const bool few_rows = max_seqlen <= (p.hq > p.hkv ? 128 : 32);
+  // (and as many pairs as its grid takes: single heads have twice the room in the other kernel's smaller workgroups)
+  const bool few_rows = max_seqlen <= (p.hq > p.hkv ? 128 : 32) && run_fits(batch, p.hkv, max_seqlen <= 64 ? 256 : 512);
   if (f32) {
     if (!in_place) {
       if (d == 64) launch_rope_k<float, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);

@@ -15,6 +15,8 @@ constexpr int kXcds = 8;  // accelerator complex dies, each with a private L2; c
 // Even runs: XCD x has items [x n / 8, (x + 1) n / 8), n / 8 of them rounded down or up.  Whole runs: n / 8 rounded up each,
 // and what is left to the last ones (9 items keep 5 XCDs busy, 17 six).
 EARN_INDEX long long run_workgroups(int n, int per) { return ((long long)n + kXcds - 1) / kXcds * kXcds * per; }
+// what one grid dimension takes: fewer than 2^32 threads
+EARN_INDEX bool run_fits(int n, int per, int threads) { return run_workgroups(n, per) * threads < (1ll << 32); }
 struct RunItem { int item, sub; bool valid; };   // sub: 0 .. per - 1
 EARN_INDEX RunItem run_item(unsigned id, int n, int per, bool even) {
   const int xcd = (int)(id % kXcds), all = (int)(id / kXcds), at = all / per;

@@ -11,6 +11,7 @@ SOURCE = r'''
 #include "work_order.h"
 using namespace earn;
 extern "C" int waves(int max_shared_len, int gen_cap, long long workgroups) { return short_decode_waves(max_shared_len, gen_cap, workgroups); }
+extern "C" int fits(int n, int per, int threads) { return run_fits(n, per, threads); }
 extern "C" long long runs(int n, int per, int even, int (*out)[3], long long limit) {
   const long long w = run_workgroups(n, per);
   for (long long i = 0; i < w && i < limit; ++i) {
@@ -122,3 +123,9 @@ def test_runs_cover_every_item_once(lib, n, per, even):
     (16, 33, 256, 3), (16, 33, 257, 2), (16, 96, 256, 4), (16, 129, 256, 8), (16, 1000, 8, 8), (16, 1000, 2048, 2), (64, 1000, 2048, 3)])
 def test_short_decode_waves(lib, shared, gen_cap, workgroups, waves):
     assert lib.waves(shared, gen_cap, ctypes.c_longlong(workgroups)) == waves
+
+
+@pytest.mark.parametrize("n,per,threads,fits", [(8, 8, 512, True), ((1 << 20) - 8, 8, 512, True), (1 << 20, 8, 512, False),
+                                                ((1 << 20) - 7, 8, 512, False), (1 << 24, 1, 256, False), ((1 << 31) - 1, 64, 256, False)])
+def test_run_fits_a_grid_dimension(lib, n, per, threads, fits):
+    assert bool(lib.fits(n, per, threads)) == fits
