@@ -23,6 +23,7 @@
 //   natural [key][d] layout.
 //   Each wave owns 32 query rows; the 64-key K/V tile in LDS is shared by the waves of a workgroup.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "mfma_tiles.h"
@@ -581,7 +582,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
 // heads of 128; one launch per layer 29.8 -> 13.4 us, 24 layers in one launch 18.9 -> 8.2 us each).
 // ------------------------------------------------------------------------------------------------------------------
 template <int D, int NR, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void prefill_short_kernel(PrefillParams p, const void* k_in, long long ls_k_in, int store_k, int parts) {
+__global__ __launch_bounds__(64 * WAVES, D == 64 && NR == 128 ? 4 : 1) void prefill_short_kernel(PrefillParams p, const void* k_in, long long ls_k_in, int store_k, int parts) {
   constexpr int KS = D / 32, DB = D / 16, UPR = D / 8, NB = NR / 32, THREADS = 64 * WAVES;
   constexpr int KI = NR * (D / 8) / THREADS, VI = NR * UPR / THREADS;   // K items (4 rotary pairs), V units per thread
   constexpr int KP = D + 8, CP = D / 2 + 2;                             // row pitches of the K tile and of the rotary table
@@ -723,26 +724,43 @@ __global__ __launch_bounds__(64 * WAVES) void prefill_short_kernel(PrefillParams
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
     float s0 = 0.f, s1 = 0.f;                              // row sums over the rounded weights
+    auto weigh = [&](auto early_c) {
+      constexpr bool EARLY = decltype(early_c)::value;
+      f32x4 o_early[DB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      if (b >= blocks) continue;
-      u32x4 w;
+      for (int b = 0; b < NB; ++b) {
+        if (b >= blocks) continue;
+        if (EARLY && b == 2) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x4& x = sc[2 * b + j / 2];
-        w[j] = pack_bf16(__builtin_amdgcn_exp2f(x[2 * (j & 1)] - mx), __builtin_amdgcn_exp2f(x[2 * (j & 1) + 1] - mx));
-        add_pair(j & 1 ? s1 : s0, w[j]);
+          for (int db = 0; db < DB; ++db) o_early[db] = o[db];
+        }
+        u32x4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const f32x4& x = sc[2 * b + j / 2];
+          w[j] = pack_bf16(__builtin_amdgcn_exp2f(x[2 * (j & 1)] - mx), __builtin_amdgcn_exp2f(x[2 * (j & 1) + 1] - mx));
+          add_pair(j & 1 ? s1 : s0, w[j]);
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          typedef short s16x8 __attribute__((ext_vector_type(8)));
+          const int row = 32 * b + 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
+          const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smv + row * D + ((chunk ^ v_swz(row)) << 3) + 4 * (r16 & 1)));
+          const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smv + (row + 16) * D + ((chunk ^ v_swz(row + 16)) << 3) + 4 * (r16 & 1)));
+          const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+          o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, w), o[db], 0, 0, 0);
+        }
       }
+      if (EARLY) {
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        typedef short s16x8 __attribute__((ext_vector_type(8)));
-        const int row = 32 * b + 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
-        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smv + row * D + ((chunk ^ v_swz(row)) << 3) + 4 * (r16 & 1)));
-        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smv + (row + 16) * D + ((chunk ^ v_swz(row + 16)) << 3) + 4 * (r16 & 1)));
-        const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-        o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, w), o[db], 0, 0, 0);
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[db][i] = qi < 64 ? o_early[db][i] : o[db][i];
       }
-    }
+    };
+    // Rows of the first 64 among later ones (a group that spans two heads, or row 64) are done with the first 64 keys: the
+    // weights of later ones are 0 for them, but 0 times an infinite value is NaN.
+    if (NB > 2 && blocks > 2 && __any(qi < 64)) weigh(std::true_type{}); else weigh(std::false_type{});
     float sum = add_chains(s0, s1);
     sum += __shfl_xor(sum, 16, kWave);
     sum = half_sum(sum);

@@ -112,3 +112,34 @@ def test_backward_non_finite_rows(kind, hq, hkv, d, n, batch, dtype):
         got = t.cpu().double().numpy().reshape(ref[x].shape)
         same(got[b][:, heads], ref[x][b][:, heads], size[x][b][:, heads], f"{kind}: {x}")
         assert np.isfinite(got[:b]).all() and np.isfinite(np.delete(got[b], np.arange(heads.start, heads.stop), axis=1)).all()
+
+
+@pytest.mark.parametrize("value", [INF, NAN])
+@pytest.mark.parametrize("hq,hkv,d,lens", [(4, 1, 128, [100, 70, 65]), (8, 2, 64, [128, 75]), (6, 2, 128, [90] * 40)])
+def test_short_prefill_non_finite_late_values(hq, hkv, d, lens, value):
+    """A value from row 64 on never reaches the queries before it (nor does a key: masked scores are dropped whatever they are).
+    The kernel packs the query rows of a group's heads 16 at a time, so early and late rows meet in one product."""
+    from paper_2507_00715_amd import binding as B
+    T, cu = sum(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    g = torch.Generator().manual_seed(T)
+    q, k, v = (torch.randn(T, h, d, generator=g).to(BF) for h in (hq, hkv, hkv))
+
+    def run(k, v):
+        desc = B.make_desc(BF, hq, hkv, d)
+        out, lse = torch.full((T, hq, d), 7.0, dtype=BF, device=DEV), torch.full((T, hq), 7.0, device=DEV)
+        ws = torch.empty(max(B.earn_prefill_workspace_bytes(desc, len(lens), T, max(lens), False), 256), dtype=torch.uint8, device=DEV)
+        B.earn_prefill_attn(desc, q.to(DEV), k.to(DEV), v.to(DEV), i32(cu), None, len(lens), T, max(lens), out, None, lse, ws)
+        torch.cuda.synchronize()
+        return out.cpu(), lse.cpu()
+
+    clean = run(k, v)
+    for s, n in enumerate(lens):
+        k[cu[s] + 64:cu[s] + n, hkv - 1, 3], v[cu[s] + 64:cu[s] + n, hkv - 1, 3] = value, value
+    got = run(k, v)
+    early = torch.cat([torch.arange(cu[s], cu[s] + 64) for s in range(len(lens))])
+    for x, y in zip(got, clean):
+        assert torch.equal(x[early], y[early])
+    gq = hq // hkv
+    late = torch.cat([torch.arange(cu[s] + 64, cu[s + 1]) for s in range(len(lens))])
+    assert torch.equal(got[0][late, :hq - gq], clean[0][late, :hq - gq])          # other kv heads
+    assert not torch.isfinite(got[0][late, hq - gq:].float()).all()
