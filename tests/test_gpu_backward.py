@@ -12,6 +12,7 @@ import torch
 from oracle import earn_oracle as O
 from paper_2507_00715_amd import workloads as W
 from parity import rel_fro, to_np
+from test_gpu_desc_options import permuted_map
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -47,7 +48,7 @@ CASES = [
 
 
 @pytest.mark.parametrize("dtype,hq,hkv,d,lens,scale", CASES)
-def test_attention_backward_matches_oracle(dtype, hq, hkv, d, lens, scale):
+def test_attention_backward_matches_oracle(dtype, hq, hkv, d, lens, scale, q_to_kv=None):
     B = _B()
     T, batch = sum(lens), len(lens)
     g = torch.Generator().manual_seed(T + hq)
@@ -55,7 +56,7 @@ def test_attention_backward_matches_oracle(dtype, hq, hkv, d, lens, scale):
     q, k, v, go = rnd(T, hq, d), rnd(T, hkv, d), rnd(T, hkv, d), rnd(T, hq, d)
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     dcu = torch.from_numpy(cu).to(DEV)
-    desc = B.make_desc(dtype, hq, hkv, d, scale, 0.0)      # rotation off: q, k are what the attention sees
+    desc = B.make_desc(dtype, hq, hkv, d, scale, 0.0, q_to_kv)      # rotation off: q, k are what the attention sees
     dq_, dk_, dv_, dgo = q.to(DEV), k.to(DEV), v.to(DEV), go.to(DEV)
     out = torch.empty(T, hq, d, dtype=dtype, device=DEV)
     lse = torch.empty(T, hq, dtype=torch.float32, device=DEV)
@@ -63,7 +64,7 @@ def test_attention_backward_matches_oracle(dtype, hq, hkv, d, lens, scale):
     gq, gk, gv = (torch.full(t.shape, float("nan"), dtype=dtype, device=DEV) for t in (q, k, v))
     B.earn_attn_backward(desc, dq_, dk_, dv_, out, lse, dgo, dcu, batch, T, max(lens), gq, gk, gv)
     torch.cuda.synchronize()
-    ref = O.attn_backward(W.to_f64(q), W.to_f64(k), W.to_f64(v), W.to_f64(go), cu, scale=scale)
+    ref = O.attn_backward(W.to_f64(q), W.to_f64(k), W.to_f64(v), W.to_f64(go), cu, q_to_kv, scale)
     check_grad(gq, ref["dq"], dtype, "dq")
     check_grad(gk, ref["dk"], dtype, "dk")
     check_grad(gv, ref["dv"], dtype, "dv")
@@ -91,6 +92,12 @@ def test_attention_backward_in_several_chunks(hq, hkv, d, lens):
     """More (sequence, kv head) pairs than an XCD works on together: several chunks, the last one partly filled.  (The
     gradients start as NaN, so a block that no workgroup takes shows.)"""
     test_attention_backward_matches_oracle(BF, hq, hkv, d, lens, 0.0)
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,lens", [(BF, 14, 2, 64, [65, 200, 33]), (BF, 16, 8, 128, EDGE_LENS * 2), (F32, 6, 2, 64, [70, 5])])
+def test_attention_backward_with_a_permuted_head_map(dtype, hq, hkv, d, lens):
+    """q_to_kv: every kernel form finds the query heads of its kv head through the map (64- and 128-row workgroups, fp32)."""
+    test_attention_backward_matches_oracle(dtype, hq, hkv, d, lens, 0.0, permuted_map(hq, hkv, hq + d))
 
 
 def test_attention_backward_argument_errors():
