@@ -288,8 +288,9 @@ __global__ __launch_bounds__(64 * (8 / RB) * WC, 1) void linear_kernel(LinearPar
 
 // Products of few rows (decode steps, small batches).  A tile of linear_kernel is 256 rows whatever the product has, so its
 // time is the same at 1 row as at 256 (0.86 us per K-tile of 64), on a third of the CUs: 1 row, k 4096, 11008 outputs 59 us,
-// here 21, with 18 for the weights' bytes at the rate of a large copy.  Here a tile is 32 NRB rows, just enough for the product's, x 64 columns, so two to eight
-// times as many workgroups share the weights and none multiplies padding beyond a 32-row block.  The four waves take one
+// here 21, with 18 for the weights' bytes at the rate of a large copy.  Here a tile is 32 NRB rows, just enough for the product's,
+// x 64 columns: twice as many tiles share the weights (a product that is split either way has as many workgroups, in half the
+// splits), and none multiplies padding beyond a 32-row block.  The four waves take one
 // 16-index step of every K-tile each (every byte of a tile is read from LDS once), and add their sums through LDS at the
 // end.  The ring of K-tiles takes most of the LDS: the weights' latency times rate is what has to be in flight.
 template <int NRB>
@@ -471,16 +472,48 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(LinearParams p) {
   }
 }
 
+// workgroups: whole patches, a multiple of 8 of them (one per XCD and round); workgroups outside the matrix leave at once
+// Patch shape: 4 x 8 tiles when that leaves every XCD at least two patches, else the largest of 2 x 4, 1 x 2 and single
+// tiles that does.
+static long long linear_grid(long long rows, int n, int cols, int* patch_rows, int* patch_cols) {
+  const long long n_rt = (rows + kLinRows - 1) / kLinRows, n_ct = (n + cols - 1) / cols;
+  static const int shapes[4][2] = {{4, 8}, {2, 4}, {1, 2}, {1, 1}};
+  long long patches = 0;
+  for (int i = 0; i < 4; ++i) {
+    *patch_rows = shapes[i][0]; *patch_cols = shapes[i][1];
+    patches = ((n_rt + *patch_rows - 1) / *patch_rows) * ((n_ct + *patch_cols - 1) / *patch_cols);
+    if (patches >= 2 * kXcds) break;
+  }
+  return (patches + kXcds - 1) / kXcds * kXcds * (*patch_rows * *patch_cols);
+}
+
 // Does linear_few_rows_kernel take the product?  us, linear_kernel -> it, both with the splits they choose (k x n):
 //    1 row    4096 x 11008 59 -> 21   11008 x 4096 28 -> 22   4096 x 6144 19 -> 16   4096 x 4096 15 -> 11   1536 x 2048 11 -> 10
 //   64 rows                60 -> 28                30 -> 27               22 -> 19               17 -> 14                12 -> 10
-//  100 rows                61 -> 44                34 -> 36               25 -> 28               20 -> 19                14 -> 12
+//   96 rows                58 -> 38                32 -> 33               22 -> 24               19 -> 17                13 -> 11
 //  160 rows                62 -> 55                38 -> 45               28 -> 34               22 -> 23                16 -> 15
 // Its activations come through every 64-column tile, linear_kernel's through every 128-column one, and what a CU loads into
-// its LDS (about 17 bytes a clock) is the limit of both: from about 96 rows on only those widths gain that linear_kernel
-// does not split, which leaves it on a third of the CUs (more than 64 of its tiles).
-static bool linear_few_rows(long long rows, int n) {
-  return tuning(kTuneLinearTile, 0) == 0 && rows <= (n > 64 * 128 ? 160 : 96);
+// its LDS (about 17 bytes a clock) is the limit of both.  Up to 64 rows every size gains.  With three blocks of 32 rows those
+// do that linear_kernel takes more than one round for (the splits of its tiles fill some XCD's 32 CUs and leave others idle:
+// 40 tiles, 0.62 - 0.70 of its time), not those where it just fits (44 - 60 tiles but 50: 1.00 - 1.11 of its time from k = 3072
+// on, 44 - 48, where the few-row tiles also leave CUs idle, up to 1.29; 24 - 32 tiles: 0.90 - 1.00 up to k = 8192, 1.00 - 1.04
+// beyond).  From there on only those widths gain that linear_kernel does not split, which leaves it on a third of the CUs (more
+// than 64 of its tiles), up to five blocks (rows: k x n):
+//  128, 160: 4096 x 8256 57 -> 42, 57 -> 53   4096 x 14336 57 -> 44, 57 -> 54   8192 x 10240 115 -> 78, 117 -> 99
+//            5120 x 13824 71 -> 55, 70 -> 66  2048 x 16384 62 -> 27, 61 -> 32   8192 x 28672 422 -> 159, 423 -> 199
+//  161-192 (a sixth block of accumulators, built to measure): 57 -> 60, 57 -> 61, 119 -> 113, 71 -> 76; only from 16384
+//            outputs on a gain, 62 -> 36, 425 -> 227.  193 and more: the accumulators spill, 58 -> 124 and up.
+static bool linear_few_rows(long long rows, int k, int n) {
+  if (tuning(kTuneLinearTile, 0) != 0) return false;
+  if (rows <= 64) return true;
+  const int tiles = (n + 127) / 128;
+  if (tiles > 64) return rows <= 160;
+  if (rows > 96) return false;
+  int patch_rows, patch_cols;
+  linear_grid(rows, n, 128, &patch_rows, &patch_cols);
+  const int patches = (tiles + patch_cols - 1) / patch_cols, fullest = (patches + kXcds - 1) / kXcds * patch_cols;
+  const bool one_round = patch_rows == 1 && fullest * (256 / tiles) <= 32;
+  return !(one_round && (tiles >= 44 ? k >= 3072 : tiles >= 24 && k > 8192));
 }
 
 // Splits of the inner dimension for a product with few output rows.  Without a split such a product has one workgroup
@@ -490,10 +523,12 @@ static bool linear_few_rows(long long rows, int n) {
 // fits ONE round of 256 workgroups; at least 4 K-tiles per split, the partial sums no larger than the weights, and
 // within the workspace given.  Measured (160 rows, k = 4096): 4096 outputs 56 -> 23 us, 6144 outputs 57 -> 28 us; with
 // 86 tiles (11008 outputs) two splits only add the partial sums (62 -> 70 us).  The 64-column tiles of the few-row kernel
-// follow the same rule with twice as many tiles.
+// follow the same rule with twice as many tiles.  (Q/K/V products of 8193 to 16384 outputs and k >= 8192 are left without a
+// split and with the general kernel, as its rotating epilogue asks: 8192 x 10240, 1 / 64 / 160 rows 109 / 115 / 118 us, in two
+// splits 112 / 115 / 121.)
 static int linear_splits(long long rows, int k, int n, size_t workspace_bytes) {
   const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128), few = (n + 63) / 64;
-  long long z = linear_few_rows(rows, n) ? std::max<long long>(1, 256 / few) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
+  long long z = linear_few_rows(rows, k, n) ? std::max<long long>(1, 256 / few) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
   z = std::min<long long>(z, k / 64 / 4);
   z = std::min<long long>(z, k / (2 * rows));
   z = std::min<long long>(z, 16);
@@ -539,21 +574,6 @@ static bool linear_wide_tile(long long rows, int n) {
   return (double)((wide + cus - 1) / cus) <= 0.62 * (double)((narrow + cus - 1) / cus);
 }
 
-// workgroups: whole patches, a multiple of 8 of them (one per XCD and round); workgroups outside the matrix leave at once
-// Patch shape: 4 x 8 tiles when that leaves every XCD at least two patches, else the largest of 2 x 4, 1 x 2 and single
-// tiles that does.
-static long long linear_grid(long long rows, int n, int cols, int* patch_rows, int* patch_cols) {
-  const long long n_rt = (rows + kLinRows - 1) / kLinRows, n_ct = (n + cols - 1) / cols;
-  static const int shapes[4][2] = {{4, 8}, {2, 4}, {1, 2}, {1, 1}};
-  long long patches = 0;
-  for (int i = 0; i < 4; ++i) {
-    *patch_rows = shapes[i][0]; *patch_cols = shapes[i][1];
-    patches = ((n_rt + *patch_rows - 1) / *patch_rows) * ((n_ct + *patch_cols - 1) / *patch_cols);
-    if (patches >= 2 * kXcds) break;
-  }
-  return (patches + kXcds - 1) / kXcds * kXcds * (*patch_rows * *patch_cols);
-}
-
 // tile shape, splits and grid of one product; fills the split fields of p
 struct LinearLaunch { bool few, wide; int splits; dim3 grid; };
 static int plan_linear(const char* who, LinearParams& p, void* workspace, size_t workspace_bytes, LinearLaunch* out) {
@@ -566,7 +586,7 @@ static int plan_linear(const char* who, LinearParams& p, void* workspace, size_t
   p.split_tiles = (k_tiles + splits - 1) / splits;
   p.n_split = (k_tiles + p.split_tiles - 1) / p.split_tiles;  // no empty split
   p.partial = p.n_split > 1 ? (float*)workspace : nullptr;
-  out->few = linear_few_rows(p.rows, p.n); out->wide = wide; out->splits = p.n_split; out->grid = dim3((unsigned)grid, (unsigned)p.n_split, 1);
+  out->few = linear_few_rows(p.rows, p.k, p.n); out->wide = wide; out->splits = p.n_split; out->grid = dim3((unsigned)grid, (unsigned)p.n_split, 1);
   return EARN_OK;
 }
 

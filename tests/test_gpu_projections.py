@@ -238,7 +238,8 @@ def test_full_size_projections_sampled_rows():
 @pytest.mark.parametrize("with_ws", [False, True])
 @pytest.mark.parametrize("rows,k,n,act", [(1, 64, 8, 0), (32, 128, 64, 1), (33, 192, 72, 0), (64, 576, 200, 0), (96, 640, 1000, 1),
                                           (65, 4096, 264, 0), (97, 448, 8200, 0), (128, 1024, 8264, 0), (129, 320, 8200, 1),
-                                          (160, 704, 8256, 0), (161, 320, 8200, 0), (97, 512, 264, 1)])
+                                          (160, 704, 8256, 0), (161, 320, 8200, 0), (97, 512, 264, 1), (65, 3072, 5632, 0),
+                                          (96, 3008, 5632, 1), (80, 3072, 6400, 0), (72, 8256, 3072, 0), (96, 8192, 3072, 1)])
 def test_linear_few_rows(rows, k, n, act, with_ws):
     B = _B()
     g = torch.Generator().manual_seed(rows + k + n)
