@@ -581,15 +581,24 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
 // 16-row sequence half fills cost 24.2 + 5.3 us where this kernel takes 12 (256 sequences of 16 rows, 12 / 2
 // heads of 128; one launch per layer 29.8 -> 13.4 us, 24 layers in one launch 18.9 -> 8.2 us each).
 // ------------------------------------------------------------------------------------------------------------------
-template <int D, int NR, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, D == 64 && NR == 128 ? 4 : 1) void prefill_short_kernel(PrefillParams p, const void* k_in, long long ls_k_in, int store_k, int parts) {
+// LDS of a workgroup, and workgroups that a CU is given: as many as fit, by LDS and 16 waves (up to 128 registers); two at most
+// where each of a pair's workgroups would rotate the keys again (256 sequences of 16 rows, 12 / 2 heads, in four a CU: whole
+// path of 28 layers 1586 -> 1696 us)
+constexpr int short_lds(int d, int nr, bool rope) { return nr * (d + 8) * 2 + nr * d * 2 + (rope ? nr * (d / 2 + 2) * 8 : 0); }
+constexpr int short_per_cu(int d, int nr, int waves, bool rope) {
+  const int by_lds = 160 * 1024 / short_lds(d, nr, rope), by_waves = 16 / waves;
+  const int fit = by_lds < by_waves ? by_lds : by_waves;
+  return rope && fit > 2 ? 2 : fit;
+}
+template <int D, int NR, int WAVES, bool ROPE>
+__global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1) void prefill_short_kernel(PrefillParams p, const void* k_in, long long ls_k_in, int store_k, int parts) {
   constexpr int KS = D / 32, DB = D / 16, UPR = D / 8, NB = NR / 32, THREADS = 64 * WAVES;
   constexpr int KI = NR * (D / 8) / THREADS, VI = NR * UPR / THREADS;   // K items (4 rotary pairs), V units per thread
   constexpr int KP = D + 8, CP = D / 2 + 2;                             // row pitches of the K tile and of the rotary table
   static_assert(KI >= 1 && KI * THREADS == NR * (D / 8) && VI >= 1 && THREADS % (D / 2) == 0);
   __shared__ __align__(16) __bf16 smk[NR * KP];
   __shared__ __align__(16) __bf16 smv[NR * D];
-  __shared__ __align__(16) f32x2 smc[NR * CP];
+  __shared__ __align__(16) f32x2 smc[ROPE ? NR * CP : 1];
   // an XCD takes a run of consecutive sequences; the kv heads of a sequence, whose rows are interleaved, stay together.  (Even
   // runs: 25 sequences of 128 rows, 32 / 8 heads of 128: 30.0 -> 28.8 us, 33 of 64 rows 21.1 -> 20.0 against runs rounded up.)
   const RunItem run = run_item(blockIdx.x, p.batch, p.hkv * parts, true);
@@ -631,7 +640,7 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 && NR == 128 ? 4 : 1) void pref
     for (int ks = 0; ks < KS; ++ks) qr[ks] = *(const u32x4*)(q + 32 * ks);
   };
   if (m_first < rows) load_q(min(m_first + r16, rows - 1));
-  if (p.rope.enabled) {
+  if constexpr (ROPE) {
     const int e = threadIdx.x % (D / 2);
     const float hi = p.rope.hi[e], lo = p.rope.lo[e];
     for (int row = threadIdx.x / (D / 2); row < n; row += THREADS / (D / 2)) {
@@ -647,7 +656,7 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 && NR == 128 ? 4 : 1) void pref
   for (int i = 0; i < KI; ++i) {
     const int item = threadIdx.x + i * THREADS, row = item / (D / 8), e = item % (D / 8) * 4;
     if (row >= n) continue;
-    if (p.rope.enabled) {
+    if constexpr (ROPE) {
       float x[4], y[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -685,7 +694,7 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 && NR == 128 ? 4 : 1) void pref
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         f32x4 t = {1.f, 0.f, 1.f, 0.f};                    // (cos, sin) of pairs 32 ks + 8 quad + 2 j, + 1
-        if (p.rope.enabled) t = *(const f32x4*)&smc[qi * CP + 32 * ks + 8 * quad + 2 * j];
+        if constexpr (ROPE) t = *(const f32x4*)&smc[qi * CP + 32 * ks + 8 * quad + 2 * j];
         const float a0 = bf16_lo(qr[ks][j]), a1 = bf16_hi(qr[ks][j]);
         const float c0 = bf16_lo(qr[ks + KS / 2][j]), c1 = bf16_hi(qr[ks + KS / 2][j]);
         wl[j] = pack_bf16((a0 * t[0] - c0 * t[1]) * p.scale_log2, (a1 * t[2] - c1 * t[3]) * p.scale_log2);
@@ -1109,8 +1118,8 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   p.rope = make_rope_table(desc->rope_base, d);
   if (make_head_map(desc, &p.heads, "earn_prefill_attn") != EARN_OK) return EARN_ERR_UNSUPPORTED;
   const bool f32 = desc->dtype == EARN_F32;
-  // prefill_short_kernel: grouped heads up to 128 rows, single heads up to 32.  us per layer with rotation, one launch per
-  // layer / 24 layers in one launch, the kernels of longer sequences (and a rotation pass) -> this one:
+  // prefill_short_kernel: grouped heads up to 128 rows (beyond 64: short_prefill_takes), single heads up to 32.  us per layer
+  // with rotation, one launch per layer / 24 layers in one launch, the kernels of longer sequences (and a rotation pass) -> this one:
   //   256 sequences, 12 / 2 heads of 128: 16 rows 29.8 / 18.9 -> 13.4 / 8.2, 64 rows 60.0 / 44.7 -> 41.0 / 32.4, 128 rows
   //   105.9 / 90.5 -> 81.2 / 71.0; 64 sequences, 32 / 8 heads: 64 rows 43.2 / 31.3 -> 29.0 / 23.4, 128 rows 75.7 / 63.0 ->
   //   61.0 / 49.9; 32 sequences, 14 / 2 heads of 64: 16 rows 9.4 / 1.6 -> 6.6 / 0.7, 128 rows 16.2 / 7.2 -> 12.5 / 5.1.
@@ -1118,7 +1127,8 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   //   34.4 / 27.4 -> 29.5 / 21.8, 64 rows 57.6 / 53.4 -> 60.6 / 46.6 (without rotation 38.7 -> 40.4), 96 rows 85 / 75 ->
   //   95 / 80.
   // (and as many pairs as its grid takes: single heads have twice the room in the other kernel's smaller workgroups)
-  const bool few_rows = max_seqlen <= (p.hq > p.hkv ? 128 : 32) && run_fits(batch, p.hkv, max_seqlen <= 64 ? 256 : 512);
+  const bool few_rows = max_seqlen <= (p.hq > p.hkv ? 128 : 32) && run_fits(batch, p.hkv, max_seqlen <= 64 ? 256 : 512) &&
+                        short_prefill_takes(max_seqlen, total_tokens / batch, (long long)batch * p.hkv * n_layers, in_place);
   if (f32) {
     if (!in_place) {
       if (d == 64) launch_rope_k<float, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
@@ -1128,23 +1138,27 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
     if (d == 64) hipLaunchKernelGGL((prefill_rows_kernel<float, 64>), grid, dim3(256), 0, stream, p);
     else hipLaunchKernelGGL((prefill_rows_kernel<float, 128>), grid, dim3(256), 0, stream, p);
   } else if (few_rows) {
-    auto launch = [&](auto kernel, int waves) {
-      // pairs of (sequence, kv head); groups of 16 query rows in a pair
-      const long long pairs = (long long)batch * p.hkv * n_layers, groups = ((long long)(p.hq / p.hkv) * max_seqlen + 15) / 16;
-      // few pairs: several workgroups per pair, each with its own copy of the keys, up to 512 of them (2 sequences, 32 / 8
-      // heads, 64 rows: 17.0 -> 10.2 us; up to 1024 gives 33.6 against 29.0 us at 64 sequences)
-      // (keys rotated in place have one reader: the others would race with its stores)
-      const int parts = k == k_rot_out ? 1 : (int)std::max<long long>(1, std::min<long long>((groups + waves - 1) / waves, 512 / pairs));
+    auto launch = [&](auto kernel, int waves, int per_cu) {
+      // Few (sequence, kv head) pairs: several workgroups per pair, each with its own copy of the keys, as many as the fullest
+      // XCD holds at a time, per_cu on each of its 32 CUs (2 sequences, 32 / 8 heads, 64 rows: 17.0 -> 10.2 us).
+      // groups: of 16 query rows, in a pair.  (Keys rotated in place have one reader: the others would race with its stores.)
+      const long long groups = ((long long)(p.hq / p.hkv) * max_seqlen + 15) / 16;
+      const long long on_xcd = (long long)((batch + kXcds - 1) / kXcds) * p.hkv * n_layers;
+      const int parts = k == k_rot_out ? 1 : (int)std::max<long long>(1, std::min<long long>((groups + waves - 1) / waves, 32 * per_cu / on_xcd));
       const dim3 grid((unsigned)run_workgroups(batch, p.hkv * parts), n_layers, 1);
       hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, stream, p, k, ls_k, k_rot_out ? 1 : 0, parts);
     };
-    if (max_seqlen <= 32) {
-      if (d == 64) launch(prefill_short_kernel<64, 32, 4>, 4); else launch(prefill_short_kernel<128, 32, 4>, 4);
-    } else if (max_seqlen <= 64) {
-      if (d == 64) launch(prefill_short_kernel<64, 64, 4>, 4); else launch(prefill_short_kernel<128, 64, 4>, 4);
-    } else {
-      if (d == 64) launch(prefill_short_kernel<64, 128, 8>, 8); else launch(prefill_short_kernel<128, 128, 8>, 8);
-    }
+    auto launch_d = [&](auto rope_c) {
+      constexpr bool ROPE = decltype(rope_c)::value;
+      if (max_seqlen <= 32) {
+        if (d == 64) launch(prefill_short_kernel<64, 32, 4, ROPE>, 4, short_per_cu(64, 32, 4, ROPE)); else launch(prefill_short_kernel<128, 32, 4, ROPE>, 4, short_per_cu(128, 32, 4, ROPE));
+      } else if (max_seqlen <= 64) {
+        if (d == 64) launch(prefill_short_kernel<64, 64, 4, ROPE>, 4, short_per_cu(64, 64, 4, ROPE)); else launch(prefill_short_kernel<128, 64, 4, ROPE>, 4, short_per_cu(128, 64, 4, ROPE));
+      } else {
+        if (d == 64) launch(prefill_short_kernel<64, 128, 8, ROPE>, 8, short_per_cu(64, 128, 8, ROPE)); else launch(prefill_short_kernel<128, 128, 8, ROPE>, 8, short_per_cu(128, 128, 8, ROPE));
+      }
+    };
+    if (p.rope.enabled) launch_d(std::true_type{}); else launch_d(std::false_type{});
   } else if (max_seqlen <= kTileKeys) {
     // single heads, one K/V tile
     if (!in_place) {

@@ -26,6 +26,20 @@ EARN_INDEX RunItem run_item(unsigned id, int n, int per, bool even) {
   return RunItem{first + at, all - at * per, at < count && first + at < n};
 }
 
+// Does the short prefill kernel take a batch of grouped heads whose longest sequence has `longest` rows (up to 128) and its
+// average one `mean`?  Up to 64 rows always.  Beyond, a pair is one 8-wave workgroup, one or two to a CU, and what counts is
+// whether the pairs fill the GPU.  The medium kernel -> it, us a layer.  512 pairs and more: 64 sequences, 32 / 8 heads of 128,
+// 96 rows 24.3 -> 17.1, lengths of 1-128 31.9 -> 30.6; 200, 12 / 2 heads, 128 rows 61 -> 57; at worst 400, 14 / 2 heads of 64,
+// lengths of 1-128 39 -> 42.  Fewer pairs, keys read in place: even lengths up to 96 rows on 128 - 256 pairs gain (64, 14 / 2
+// heads, 65 / 96 rows 14.1 -> 10.4, 16.0 -> 14.8), the rest lose (260 pairs, 128 rows 21.9 -> 30.0, ragged 17.4 -> 28; 66 pairs,
+// 128 rows 1.25 times the time; 40 pairs, 12 / 2 heads 9.4 -> 11.7).  With keys to rotate or copy, a launch of its own for the
+// medium kernel, it gains except where most sequences are much shorter than the longest (130, 14 / 2 heads, one of 128 rows
+// among some of about 12: 18.6 -> 23.2; 8 / 1 heads 23.2 -> 32.5).
+EARN_INDEX bool short_prefill_takes(int longest, int mean, long long pairs, bool keys_in_place) {
+  if (longest <= 64 || pairs >= 512) return true;
+  if (keys_in_place) return pairs >= 128 && pairs <= 256 && longest <= 96 && 4ll * mean >= 3ll * longest;
+  return pairs < 128 || 4ll * mean >= longest;
+}
 // Waves of a short decode workgroup: one per block of 32 shared keys and one for the generated rows, eight for longer lists.
 // With no more workgroups than CUs, nothing else hides a wave's round trips, so the blocks that the generated rows may come to
 // count too.  us, 16 shared rows, waves by shared rows -> by all: one sequence, 32 / 8 heads, 249 / 999 generated rows 14.5 /

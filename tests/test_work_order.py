@@ -10,6 +10,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = r'''
 #include "work_order.h"
 using namespace earn;
+extern "C" int takes(int longest, int mean, long long pairs, int in_place) { return short_prefill_takes(longest, mean, pairs, in_place); }
 extern "C" int waves(int max_shared_len, int gen_cap, long long workgroups) { return short_decode_waves(max_shared_len, gen_cap, workgroups); }
 extern "C" int fits(int n, int per, int threads) { return run_fits(n, per, threads); }
 extern "C" long long runs(int n, int per, int even, int (*out)[3], long long limit) {
@@ -129,3 +130,11 @@ def test_short_decode_waves(lib, shared, gen_cap, workgroups, waves):
                                                 ((1 << 20) - 7, 8, 512, False), (1 << 24, 1, 256, False), ((1 << 31) - 1, 64, 256, False)])
 def test_run_fits_a_grid_dimension(lib, n, per, threads, fits):
     assert bool(lib.fits(n, per, threads)) == fits
+
+
+@pytest.mark.parametrize("longest,mean,pairs,in_place,short", [
+    (64, 1, 260, True, True), (1, 1, 1, True, True), (128, 10, 512, True, True), (128, 10, 511, True, False),
+    (96, 72, 128, True, True), (96, 71, 128, True, False), (97, 97, 128, True, False), (65, 65, 127, True, False), (65, 65, 257, True, False),
+    (128, 32, 260, False, True), (128, 31, 260, False, False), (128, 10, 127, False, True), (128, 128, 40, False, True)])
+def test_short_prefill_takes(lib, longest, mean, pairs, in_place, short):
+    assert bool(lib.takes(longest, mean, ctypes.c_longlong(pairs), in_place)) == short
