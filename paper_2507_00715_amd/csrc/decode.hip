@@ -460,8 +460,8 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
   __shared__ Tile tile[WAVES];
   __shared__ f32x2 ml[WAVES][8];                         // (max, sum) per query of the group
   __shared__ __align__(16) __bf16 rot[3][9][D + 8];      // rotated queries (three terms) and, in row gq, the new key
-  // Workgroup -> (stream, kv head): an XCD keeps a run of consecutive streams (beams of a sequence share its cache rows,
-  // the kv heads of a stream share DRAM rows), so what they share is fetched into one L2.
+  // Workgroup -> (stream, kv head): an XCD keeps a run of consecutive pairs of them (beams of a sequence share its cache rows,
+  // the kv heads of a stream share DRAM rows), so most of what they share is fetched into one L2.
   const RunItem run = run_item(blockIdx.x, p.n_streams, p.hkv, p.even_runs);
   if (!run.valid) return;
   const int u = run.item, c = run.sub;
@@ -1460,8 +1460,9 @@ static void launch_vector(const DecodeParams& p, int gq, dim3 grid, hipStream_t 
 // The XCDs take even runs of the streams, except where eight-wave workgroups outnumber the CUs: then a CU with two of them is
 // what the launch waits for, and it is done sooner when the last XCD leaves its share of the bandwidth to the others.  us per
 // layer, one launch per layer / 4 layers in one launch, whole -> even runs, 32 / 8 heads: 9 streams of 1000 rows 18.4 / 11.7 ->
-// 18.9 / 10.5, 17 of 600 14.3 / 10.7 -> 13.3 / 10.2, 25 of 600 16.6 / 13.8 -> 14.9 / 13.4, 33 of 64 (three waves) 7.2 / 3.8 ->
-// 6.7 / 3.4, but 33 of 768 35.5 / 23.4 -> 37.0 / 24.3, 65 of 2000 125 / 101 -> 130 / 104.
+// 18.2 / 9.3, 17 of 600 14.3 / 10.7 -> 13.1 / 9.2, 25 of 600 16.6 / 13.8 -> 15.7 / 12.3, 33 of 64 (three waves) 7.2 / 3.8 ->
+// 7.0 / 3.3, one of 700 with 32 / 32 heads - / 13.2 -> - / 3.7, but 33 of 768 35.5 / 23.4 -> 37.0 / 24.3, 65 of 2000 125 / 101 ->
+// 130 / 104.
 template <int D>
 static void launch_short(DecodeParams& p, hipStream_t stream, int n_layers) {
   const int waves = short_decode_waves(p.max_shared_len, p.gen_cap, (long long)p.n_streams * p.hkv * n_layers);

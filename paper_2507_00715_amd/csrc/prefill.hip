@@ -599,8 +599,9 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
   __shared__ __align__(16) __bf16 smk[NR * KP];
   __shared__ __align__(16) __bf16 smv[NR * D];
   __shared__ __align__(16) f32x2 smc[ROPE ? NR * CP : 1];
-  // an XCD takes a run of consecutive sequences; the kv heads of a sequence, whose rows are interleaved, stay together.  (Even
-  // runs: 25 sequences of 128 rows, 32 / 8 heads of 128: 30.0 -> 28.8 us, 33 of 64 rows 21.1 -> 20.0 against runs rounded up.)
+  // An XCD takes a run of consecutive workgroups of consecutive sequences, the kv heads of a sequence, whose rows are interleaved,
+  // next to each other.  (Against runs of whole sequences, rounded up: 9 sequences of 128 rows, 32 / 8 heads of 128, 20.7 -> 14.7
+  // us, 25 of 128 30.0 -> 23.3, 33 of 64 21.1 -> 20.5.)
   const RunItem run = run_item(blockIdx.x, p.batch, p.hkv * parts, true);
   if (!run.valid) return;
   const int s = run.item, c = run.sub % p.hkv, part = run.sub / p.hkv;
@@ -1139,11 +1140,11 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
     else hipLaunchKernelGGL((prefill_rows_kernel<float, 128>), grid, dim3(256), 0, stream, p);
   } else if (few_rows) {
     auto launch = [&](auto kernel, int waves, int per_cu) {
-      // Few (sequence, kv head) pairs: several workgroups per pair, each with its own copy of the keys, as many as the fullest
-      // XCD holds at a time, per_cu on each of its 32 CUs (2 sequences, 32 / 8 heads, 64 rows: 17.0 -> 10.2 us).
+      // Few (sequence, kv head) pairs: several workgroups per pair, each with its own copy of the keys, as many as an XCD
+      // holds at a time, per_cu on each of its 32 CUs (2 sequences, 32 / 8 heads, 64 rows: 17.0 -> 10.2 us).
       // groups: of 16 query rows, in a pair.  (Keys rotated in place have one reader: the others would race with its stores.)
       const long long groups = ((long long)(p.hq / p.hkv) * max_seqlen + 15) / 16;
-      const long long on_xcd = (long long)((batch + kXcds - 1) / kXcds) * p.hkv * n_layers;
+      const long long on_xcd = ((long long)batch * p.hkv * n_layers + kXcds - 1) / kXcds;
       const int parts = k == k_rot_out ? 1 : (int)std::max<long long>(1, std::min<long long>((groups + waves - 1) / waves, 32 * per_cu / on_xcd));
       const dim3 grid((unsigned)run_workgroups(batch, p.hkv * parts), n_layers, 1);
       hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, stream, p, k, ls_k, k_rot_out ? 1 : 0, parts);

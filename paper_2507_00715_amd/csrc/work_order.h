@@ -11,19 +11,21 @@ namespace earn {
 
 constexpr int kXcds = 8;  // accelerator complex dies, each with a private L2; consecutive workgroup ids go to them in turn
 
-// ---- short decode and prefill: an XCD takes a run of consecutive items (streams, sequences), each of `per` workgroups ----
-// Even runs: XCD x has items [x n / 8, (x + 1) n / 8), n / 8 of them rounded down or up.  Whole runs: n / 8 rounded up each,
-// and what is left to the last ones (9 items keep 5 XCDs busy, 17 six).
+// ---- short decode and prefill: an XCD takes a run of consecutive units, `per` workgroups of each item (stream, sequence) ----
+// Even runs: XCD x has units [x n per / 8, (x + 1) n per / 8), whichever items they belong to, so that a single item is spread
+// over the XCDs too.  Whole runs: n / 8 items, rounded up, each, and what is left to the last ones (9 items keep 5 XCDs busy, 17
+// six).
 EARN_INDEX long long run_workgroups(int n, int per) { return ((long long)n + kXcds - 1) / kXcds * kXcds * per; }
 // what one grid dimension takes: fewer than 2^32 threads
 EARN_INDEX bool run_fits(int n, int per, int threads) { return run_workgroups(n, per) * threads < (1ll << 32); }
 struct RunItem { int item, sub; bool valid; };   // sub: 0 .. per - 1
 EARN_INDEX RunItem run_item(unsigned id, int n, int per, bool even) {
-  const int xcd = (int)(id % kXcds), all = (int)(id / kXcds), at = all / per;
-  const int base = n / kXcds, extra = n % kXcds, whole = base + (extra > 0 ? 1 : 0);
+  const int xcd = (int)(id % kXcds), at = (int)(id / kXcds), units = n * per;
+  const int base = units / kXcds, extra = units % kXcds, whole = (n + kXcds - 1) / kXcds * per;
   const int first = even ? xcd * base + xcd * extra / kXcds : xcd * whole;
   const int count = even ? base + ((xcd + 1) * extra / kXcds - xcd * extra / kXcds) : whole;
-  return RunItem{first + at, all - at * per, at < count && first + at < n};
+  const int unit = first + at, item = unit / per;
+  return RunItem{item, unit - item * per, at < count && unit < units};
 }
 
 // Does the short prefill kernel take a batch of grouped heads whose longest sequence has `longest` rows (up to 128) and its
