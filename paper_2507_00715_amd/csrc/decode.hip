@@ -1345,7 +1345,7 @@ __global__ __launch_bounds__(256 * C, 1) void decode_shared_mfma_kernel(DecodePa
 // ------------------------------------------------------------------------------------------------------------------
 struct DecodePlan {
   bool mfma;      // shared and generated rows on the matrix cores + combine
-  bool few_keys;  // decode_short_kernel instead of what the other fields plan
+  bool few_keys = false;  // decode_short_kernel instead of what the other fields plan (launch_decode)
   int n_splits;   // key-range splits of the shared (mfma) or whole (vector) key list
   int n_slots;    // partial slots per (stream, head)
   int chunk;      // keys per split
@@ -1367,14 +1367,18 @@ struct DecodePlan {
 //   rows 15.4 / 8.7 -> 15.7 / 8.9.  So: up to 512 pairs and 768 keys.
 //   beams, 16 sequences x 10 of 32 / 8 heads: 32 rows 15.3 / 6.9 -> 8.6 / 4.4, 64 rows 15.4 / 6.8 -> 13.4 / 7.1, 128 rows
 //   16.5 / 7.7 -> 19.8 / 12.2; 32 x 4 of 12 / 2 heads, 128 rows 12.7 / 3.1 -> 8.2 / 2.7, 256 rows 16.9 / 3.8 -> 10.7 / 7.2,
-//   512 rows 19.9 -> 14.4.  So: 128 K rows re-read, 48 K per layer where the layers share a launch.
-static bool decode_few_keys(int dtype, int hq, int hkv, int n_streams, int batch, int max_shared_len, int gen_cap, int n_layers) {
+//   512 rows 19.9 -> 14.4.  So: 128 K rows re-read, 48 K per layer where the layers share a launch, and no more in all than
+//   the general kernel's rounds allow (short_decode_takes_beams).
+static bool decode_few_keys(int dtype, int hq, int hkv, int d, int n_streams, int batch, int max_shared_len, int gen_cap, int n_layers,
+                            int n_pass) {
   if (dtype != EARN_BF16) return false;
   for (Tuning t : {kTuneDecMfmaMinLen, kTuneDecMfmaShortWgs, kTuneDecMfmaWgs, kTuneDecVecWgs, kTuneDecVecWaves})
     if (tuning(t, 0) != 0) return false;                 // a caller who sets the general kernels' launch shape gets them
   if (!run_fits(n_streams, hkv, 512)) return false;      // 8 million (stream, kv head) pairs: the general kernels' smaller workgroups
   const long long pairs = (long long)n_streams * hkv, keys = (long long)max_shared_len + gen_cap;
-  if (n_streams > batch) return pairs * max_shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024;
+  if (n_streams > batch)
+    return pairs * max_shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024 &&
+           short_decode_takes_beams(pairs * n_layers, (long long)batch * hkv * n_layers * n_pass, max_shared_len, d);
   if (hq == hkv) return pairs * n_layers <= 512 && keys <= 768;
   return keys <= (pairs * n_layers >= 512 ? 2304 : 1024);
 }
@@ -1393,7 +1397,6 @@ static DecodePlan plan_decode(int dtype, int hq, int hkv, int n_streams, int bat
   pl.mfma = dtype == EARN_BF16 && (gq > 1 || n_streams > batch) &&
             (max_shared_len >= mfma_min || (long long)hkv * batch * n_layers <= mfma_wgs || n_streams >= 2 * batch);
   pl.n_pass = 1;
-  pl.few_keys = decode_few_keys(dtype, hq, hkv, n_streams, batch, max_shared_len, gen_cap, n_layers);
   if (pl.mfma) {
     // Beams beyond 64 query rows per cache (say 20 beams of 7 grouped heads) would make a workgroup walk its keys once
     // per 64 rows.  Planned from the average beam count, every such pass gets workgroups of its own, with fewer key
@@ -1510,7 +1513,8 @@ int launch_decode(const earn_attn_desc* desc, const void* q, const void* k_new, 
   const int hq = desc->n_q_heads, hkv = desc->n_kv_heads, d = desc->head_dim, gq = hq / hkv;
   const int n_layers = layers ? layers->n_layers : 1;
   if (gq > 8) { set_error("earn_decode_attn: more than 8 query heads per kv head is not supported"); return EARN_ERR_UNSUPPORTED; }
-  const DecodePlan pl = plan_decode(desc->dtype, hq, hkv, n_streams, batch, max_shared_len, gen_cap, n_layers);
+  DecodePlan pl = plan_decode(desc->dtype, hq, hkv, n_streams, batch, max_shared_len, gen_cap, n_layers);
+  pl.few_keys = decode_few_keys(desc->dtype, hq, hkv, d, n_streams, batch, max_shared_len, gen_cap, n_layers, pl.n_pass);
   if (pl.mfma && (long long)(max_shared_len + kDsSuper) * hkv * d * 2 >= (1ll << 31)) {
     set_error("earn_decode_attn: a shared cache of %d rows exceeds the 2 GiB addressing range of one sequence", max_shared_len);
     return EARN_ERR_UNSUPPORTED;

@@ -42,6 +42,16 @@ EARN_INDEX bool short_prefill_takes(int longest, int mean, long long pairs, bool
   if (keys_in_place) return pairs >= 128 && pairs <= 256 && longest <= 96 && 4ll * mean >= 3ll * longest;
   return pairs < 128 || 4ll * mean >= longest;
 }
+// Does the short decode kernel take streams that share caches (beams)?  It reads a cache once per stream, about 0.1 us for 1024
+// rows of 128 elements all told; the general kernel reads it once, but its workgroups hold a CU each and take about 13 us a
+// round of 256.  pairs: (stream, kv head, layer); general_workgroups: (sequence, kv head, layer, pass of 64 query rows).
+// us a layer, general -> short: 8 sequences x 10, 12 / 2 heads, 16 layers in a launch, 32 / 48 / 200 rows 1.06 / 1.05 / 1.29 ->
+// 0.95 / 1.33 / 3.69 (taken: up to 32); 16 x 10, 32 / 8 heads, 24 layers, 32 / 64 rows 6.9 / 6.8 -> 4.4 / 7.1 (32); one layer,
+// 64 / 100 rows 15.3 / 15.4 -> 13.4 / 18.8 (64).
+EARN_INDEX bool short_decode_takes_beams(long long pairs, long long general_workgroups, int shared_len, int d) {
+  const long long rounds = (general_workgroups + 255) / 256;
+  return pairs * shared_len * (d + 64) / 192 <= (128 * rounds - 40) * 1024;
+}
 // Waves of a short decode workgroup: one per block of 32 shared keys and one for the generated rows, eight for longer lists.
 // With no more workgroups than CUs, nothing else hides a wave's round trips, so the blocks that the generated rows may come to
 // count too.  us, 16 shared rows, waves by shared rows -> by all: one sequence, 32 / 8 heads, 249 / 999 generated rows 14.5 /

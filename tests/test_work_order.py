@@ -11,6 +11,7 @@ SOURCE = r'''
 #include "work_order.h"
 using namespace earn;
 extern "C" int takes(int longest, int mean, long long pairs, int in_place) { return short_prefill_takes(longest, mean, pairs, in_place); }
+extern "C" int takes_beams(long long pairs, long long general, int len, int d) { return short_decode_takes_beams(pairs, general, len, d); }
 extern "C" int waves(int max_shared_len, int gen_cap, long long workgroups) { return short_decode_waves(max_shared_len, gen_cap, workgroups); }
 extern "C" int fits(int n, int per, int threads) { return run_fits(n, per, threads); }
 extern "C" long long runs(int n, int per, int even, int (*out)[3], long long limit) {
@@ -138,3 +139,12 @@ def test_run_fits_a_grid_dimension(lib, n, per, threads, fits):
     (128, 32, 260, False, True), (128, 31, 260, False, False), (128, 10, 127, False, True), (128, 128, 40, False, True)])
 def test_short_prefill_takes(lib, longest, mean, pairs, in_place, short):
     assert bool(lib.takes(longest, mean, ctypes.c_longlong(pairs), in_place)) == short
+
+
+@pytest.mark.parametrize("batch,beams,hkv,d,layers,rows,short", [
+    (8, 10, 2, 128, 16, 32, True), (8, 10, 2, 128, 16, 48, False),          # one round of the general kernel
+    (16, 10, 8, 128, 24, 32, True), (16, 10, 8, 128, 24, 64, False),        # twelve
+    (16, 10, 8, 128, 1, 64, True), (16, 10, 8, 128, 1, 100, False), (32, 4, 2, 64, 1, 512, True), (1, 1, 1, 64, 1, 0, True)])
+def test_short_decode_takes_beams(lib, batch, beams, hkv, d, layers, rows, short):
+    ll = ctypes.c_longlong
+    assert bool(lib.takes_beams(ll(batch * beams * hkv * layers), ll(batch * hkv * layers), rows, d)) == short
