@@ -13,10 +13,10 @@ stay one launch per layer.  The same steps with one launch per layer (the form a
 depends on layer l) are timed right after and reported under "per_layer_launch", and once more with those per-layer
 launches replayed from HIP graphs ("per_layer_launch_graph").
 
-Prints ONE JSON line.  `value` is the prefill-attention rate in algorithmic causal TFLOP/s
+Prints ONE JSON line of the contract's keys and the dominant kernel's roofline.  `value` is the prefill-attention rate in algorithmic causal TFLOP/s
 (4*d*Hq*sum_s m_s(m_s+1)/2 per layer, summed over all N prefill launches, divided by the time the prefill
-launches took inside the timed steps); decode and compaction figures, a roofline object for the dominant
-kernel and the CPU oracle timed on the host cores are carried in the same line.
+launches took inside the timed steps); the same object with every other figure (decode, compaction, the further
+workloads, the CPU oracle timed on the host cores) goes to standard error as one line.
 """
 from __future__ import annotations
 
@@ -46,7 +46,9 @@ def dominant_kernel(cfg, w) -> tuple:
     lengths: short, one-tile, medium or long sequences), and the roofline that bounds it."""
     if cfg.dtype != "bf16":
         return "prefill_rows_kernel + rope_k_kernel (one full-length causal layer, vector ALU)", "alu"
-    if w.max_seqlen <= (128 if cfg.n_q_heads > cfg.n_kv_heads else 32):
+    mean, pairs = w.total_tokens // cfg.batch, cfg.batch * cfg.n_kv_heads
+    short = w.max_seqlen <= 64 or w.max_seqlen <= 128 and (pairs >= 512 or pairs < 128 or 4 * mean >= w.max_seqlen)
+    if short if cfg.n_q_heads > cfg.n_kv_heads else w.max_seqlen <= 32:
         return "prefill_short_kernel (one causal layer, rotation included)", "mfma"
     if w.max_seqlen <= 64:
         name = "prefill_mfma_kernel<D,2,1>"
@@ -817,6 +819,17 @@ def cfg_has_decode(name: str) -> bool:
     return W.CONFIGS[name].decode_steps > 0 and W.CONFIGS[name].dtype == "bf16"
 
 
+def short_line(line: dict) -> dict:
+    """The line of standard output: what the run is, its value and its roofline, in under 1500 characters, so that it is
+    read whole where only the end of the output is kept.  All other figures go to standard error, as one JSON line too."""
+    keys = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+            "dtype", "data", "config")
+    roof = ("kernel", "bound", "achieved", "peak", "unit", "frac")
+    short = dict({k: line[k] for k in keys}, roofline={k: line["roofline"][k] for k in roof})
+    short["config"] = {k: v for k, v in line["config"].items() if k != "seq_lengths"}   # (total, shortest and longest stay)
+    return short
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -898,7 +911,8 @@ def main():
         "attention_only_vs_vanilla": head["attention_only_vs_vanilla"],
         "other_workloads": {n: {kk: vv for kk, vv in r.items()} for n, r in others.items()},
     }
-    print(json.dumps(line))
+    print(json.dumps(line), file=sys.stderr, flush=True)
+    print(json.dumps(short_line(line)))
 
 
 if __name__ == "__main__":

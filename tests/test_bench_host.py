@@ -1,5 +1,6 @@
 """Host-side parts of bench.py (no GPU): the algorithmic work counts behind the reported rates, pinned to the closed
 forms and to the figures of the configurations; and the command line's refusal of more than one GPU."""
+import json
 import os
 import subprocess
 import sys
@@ -66,6 +67,22 @@ def test_prefill_bytes_per_layer():
     T = c.batch * (c.n_head_reg + 8192 + c.n_tail_reg)
     # Q in, O out (Hq rows each); K in, rotated K out, V in (Hkv rows each)
     assert bench.algorithmic_prefill_bytes("long_beam") == T * c.head_dim * 2 * (2 * c.n_q_heads + 3 * c.n_kv_heads)
+
+
+def test_the_reported_line_is_short():
+    """Standard output carries the contract's keys and the roofline only, whatever else was measured."""
+    contract = {"metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+                "dtype", "data", "config"}
+    for name in W.CONFIG_ORDER:
+        w = W.Workload(W.CONFIGS[name])
+        kernel, bound = bench.dominant_kernel(w.cfg, w)
+        line = {k: 1234.5678901234567 for k in contract}
+        line.update(metric=bench.METRIC, config=dict(w.describe(), launch_mode="layer-batched register-cache and decode phases"),
+                    roofline={k: 1234.5678901234567 for k in ("achieved", "peak", "frac", "traffic", "flops_per_launch")},
+                    other_workloads={"x": "y" * 10000}, decode={"us": 1.0})
+        line["roofline"].update(kernel=kernel, bound=bound, unit="TFLOP/s", measured_peak={"x": "y" * 1000})
+        short = bench.short_line(line)
+        assert set(short) == contract | {"roofline"} and len(json.dumps(short)) < 1500
 
 
 @pytest.mark.parametrize("args", [["--gpus", "2"], ["--gpus", "8"]])
