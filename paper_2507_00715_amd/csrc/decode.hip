@@ -431,12 +431,13 @@ __device__ __forceinline__ void lds_barrier() {
 //                  the K fragments are plain 16-byte loads of key rows, straight from memory into registers)
 //   O^T += V^T P^T (V through a swizzled LDS tile of the wave's own; the accumulator layout of two S^T tiles is the B
 //                  operand of this product, with the keys in the order 4 quad + i, 16 + 4 quad + i)
-// The group's queries and the new key are rotated once per workgroup; with every wave rotating its own copy the vector ALU
-// was the limit as soon as several workgroups shared a CU (64 sequences, 32 / 8 heads of 128, 16 rows: 16.4 us a layer in
-// a batched launch, now 7.6).  Queries and probabilities enter as the sum of three bf16 operands (value, remainder and its
-// remainder: 24 significant bits), so the products are those of fp32 queries and probabilities, as in the vector kernel.
+// The group's queries and the new key are rotated once per workgroup: with every wave rotating its own copy the vector ALU
+// was the limit as soon as several workgroups shared a CU.  (64 sequences, 32 / 8 heads of 128, 16 rows, 24 layers in a launch:
+// 4.5 us a layer in the general kernel, 2.1 here.)  Queries and probabilities enter as the sum of three bf16 operands (value,
+// remainder and its remainder: 24 significant bits), so the products are those of fp32 queries and probabilities, as in the
+// vector kernel.
 // The waves' states are merged once, in LDS.
-// Long lists stream K and V at 4.9 TB/s (64 sequences of 768 rows, 8 kv heads), about what a copy reaches.
+// Long lists stream K and V at 5.1 TB/s (64 sequences of 768 rows, 8 kv heads: 39 us), about what a copy reaches.
 // ------------------------------------------------------------------------------------------------------------------
 // Two fp32 numbers as three words of bf16 pairs whose sum they are: w[0] = the numbers rounded, w[1] = the remainders
 // rounded, w[2] = what is left.  (With two words, 16 to 17 bits, large scores and values that cancel lost what fp32 keeps:
@@ -1357,14 +1358,15 @@ struct DecodePlan {
 // plan's.)  It reads the shared rows once per stream and walks them 256 at a time, so it is the faster one up to a length,
 // and with beams up to an amount of re-read rows.  us per layer, one launch per layer / 6 - 28 layers in one launch, the
 // general kernels -> this one (a launch from the host takes 6 - 7 us by itself):
-//   grouped heads, one stream per sequence: 256 sequences, 12 / 2 heads of 128, 16 rows 14.5 / 6.6 -> 7.1 / 2.1, 128 rows
-//   27.8 / 23.5 -> 14.0 / 7.8, 512 rows 42.7 / 35.1 -> 33.3 / 28.2, 2080 rows 106 / 96 -> 103 / 95; 32 sequences, 14 / 2
-//   heads of 64, 64 rows 9.3 / 1.4 -> 6.7 / 0.4, 1024 rows 17.0 / 6.5 -> 12.8 / 3.4, 2080 rows 19.4 / 10.1 -> 19.9 / 6.0;
-//   one sequence, 32 / 8 heads, 1024 rows 19.1 / 5.1 -> 17.5 / 6.0, 1536 rows 21.1 / 5.8 -> 22.9 / 8.0.  So: 1024 keys, and
-//   2304 where the (stream, kv head) pairs fill the GPU twice over, which leaves the key splits nothing to win.
+//   grouped heads, one stream per sequence: 256 sequences, 12 / 2 heads of 128, 16 rows 13.1 / 6.4 -> 7.3 / 2.2, 128 rows
+//   25.8 / 23.7 -> 11.3 / 7.5, 512 rows 38.7 -> 29.1, 2080 rows 106.8 -> 101.2; 32 sequences, 14 / 2 heads of 64, 64 rows
+//   9.2 / 1.4 -> 6.7 / 0.5, 1024 rows 15.7 / 4.9 -> 15.6 / 3.1, 2080 rows 18.8 / 7.6 -> 18.9 / 6.0; one sequence, 32 / 8
+//   heads, 1024 rows 18.1 / 4.3 -> 18.0 / 4.4, 1536 rows 21.1 / 5.8 -> 22.9 / 8.0.  So: 1024 keys, and 2304 where the
+//   (stream, kv head) pairs fill the GPU twice over, which leaves the key splits nothing to win.
 //   single heads: the vector kernel wastes no query columns, but its fewer rows in flight only pay with many workgroups:
-//   256 pairs, 64 rows 13.0 -> 7.3, 512 rows 24.6 -> 18.8; 4 sequences of 4 heads, 1024 rows 11.5 -> 12.0; 2048 pairs, 32
-//   rows 15.4 / 8.7 -> 15.7 / 8.9.  So: up to 512 pairs and 768 keys.
+//   256 pairs, 64 rows 7.5 -> 6.8, 512 rows 13.6 -> 9.6; one sequence of 32 heads, 16 layers in a launch, 64 / 700 rows 1.4 /
+//   6.4 -> 0.6 / 2.3; 2048 pairs, 32 rows 15.4 / 8.7 -> 15.7 / 8.9; 320 pairs, a round and a quarter of the CUs, 500 rows
+//   21.7 -> 25.3, the worst there is.  So: up to 512 pairs and 768 keys.
 //   beams, 16 sequences x 10 of 32 / 8 heads: 32 rows 15.3 / 6.9 -> 8.6 / 4.4, 64 rows 15.4 / 6.8 -> 13.4 / 7.1, 128 rows
 //   16.5 / 7.7 -> 19.8 / 12.2; 32 x 4 of 12 / 2 heads, 128 rows 12.7 / 3.1 -> 8.2 / 2.7, 256 rows 16.9 / 3.8 -> 10.7 / 7.2,
 //   512 rows 19.9 -> 14.4.  So: 128 K rows re-read, 48 K per layer where the layers share a launch, and no more in all than

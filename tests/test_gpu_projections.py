@@ -232,7 +232,7 @@ def test_full_size_projections_sampled_rows():
     check_attn(v[sample], ref["v"], BF, "v, sampled rows")
 
 
-# Up to 96 rows (160 for wide outputs) take a kernel with tiles of 32 to 160 rows x 64 columns (chosen by size, so without
+# Up to 64 rows (96 or 160 by the width of the outputs) take a kernel with tiles of 32 to 160 rows x 64 columns (chosen by size, so without
 # the tile override): the edges of its row blocks, of its column tiles and of the rule, one K-tile, fewer and more K-tiles
 # than its ring holds, odd and even counts, split and unsplit.
 @pytest.mark.parametrize("with_ws", [False, True])
