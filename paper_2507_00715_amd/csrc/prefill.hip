@@ -32,11 +32,12 @@ namespace earn {
 
 struct PrefillParams {
   const void* q; const void* k_rot; const void* v; const int32_t* cu; const int32_t* positions;
-  const f32x2* cs;  // [tokens][d/2] (cos, sin) of every token's rotary angles, written by rope_k_kernel (bf16 paths)
+  const f32x4* cs;  // [d/4][tokens] (cos, sin) of two rotary pairs of every token, written by rope_k_kernel (bf16 paths)
   void* out; float* lse;
   int batch, hq, hkv, max_seqlen;
   int total;   // rows of the packed tensors
   int n_qblk;  // query blocks of the longest sequence
+  FastDiv by_pair, by_group, by_kv;  // workgroups per (sequence, kv head), query heads per kv head, kv heads (pf_map_block)
   // chosen-rows mode of the vector kernel (rows_per_seq > 0): q and out hold rows_per_seq rows per sequence in
   // compacted order, row m of sequence s being token row_pos[s * rows_per_seq + m] (ascending) of the sequence
   const int32_t* row_pos;
@@ -104,14 +105,15 @@ template <> struct Vec8<__bf16> {
 
 // One thread per (token, group of 8 rotary pairs): the sin/cos of the group are computed once and applied to every kv
 // head of the token.  bf16 rows use the hardware sin/cos (error ~1e-6, far below bf16 resolution).
-// cs_out (optional): the (cos, sin) pairs themselves, [token][d/2].  The attention kernels rotate their query rows with
-// them: a workgroup per query head would otherwise recompute the same angles once per head, and on short sequences
-// that prologue costs as much as the attention itself.
+// cs_out (optional): the (cos, sin) pairs themselves, two at a time, [d/4][token].  The attention kernels rotate their query
+// rows with them: a workgroup per query head would otherwise recompute the same angles once per head, and on short sequences
+// that prologue costs as much as the attention itself.  (Tokens innermost: the lanes of a wave hold consecutive query rows, and
+// 16 loads of one row per lane kept a workgroup's memory pipeline busy for longer than the rows take to arrive.)
 template <typename T, int D>
 __global__ __launch_bounds__(256) void rope_k_kernel(const T* __restrict__ k, T* __restrict__ k_rot,
                                                      const int32_t* __restrict__ cu,
                                                      const int32_t* __restrict__ positions, int batch, int total,
-                                                     int hkv, RopeTable rope, f32x2* __restrict__ cs_out,
+                                                     int hkv, RopeTable rope, f32x4* __restrict__ cs_out,
                                                      int heads_per_thread, long long ls_k, long long ls_k_rot) {
   constexpr int G = D / 16;  // groups of 8 pairs per head
   const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -136,9 +138,8 @@ __global__ __launch_bounds__(256) void rope_k_kernel(const T* __restrict__ k, T*
     for (int i = 0; i < 8; ++i) { sn[i] = 0.f; cs[i] = 1.f; }
   }
   if (cs_out && blockIdx.y == 0 && blockIdx.z == 0) {
-    f32x4* dst4 = (f32x4*)(cs_out + (long long)token * (D / 2) + g * 8);
 #pragma unroll
-    for (int i = 0; i < 8; i += 2) dst4[i / 2] = f32x4{cs[i], sn[i], cs[i + 1], sn[i + 1]};
+    for (int i = 0; i < 8; i += 2) cs_out[(long long)(g * 4 + i / 2) * total + token] = f32x4{cs[i], sn[i], cs[i + 1], sn[i + 1]};
   }
   const T* src = k + (long long)token * hkv * D + g * 8;
   T* dst = k_rot + (long long)token * hkv * D + g * 8;
@@ -271,16 +272,14 @@ struct PfBlock {
 __device__ __forceinline__ PfBlock pf_map_block(const PrefillParams& p, int block_rows) {
   PfBlock b;
   b.valid = false;
-  const int gq = p.hq / p.hkv;
-  const int xcd = blockIdx.x % kXcds, k_in_xcd = blockIdx.x / kXcds;
-  const int per_pair = p.n_qblk * gq;
-  const int pair = (k_in_xcd / per_pair) * kXcds + xcd;
-  if (pair >= p.batch * p.hkv) return b;
-  const int rem = k_in_xcd % per_pair;
-  const int qblk = p.n_qblk - 1 - rem / gq;
-  const int s = pair / p.hkv;
-  b.c = pair % p.hkv;
-  b.a = head_of_slot(p.heads, b.c * gq + rem % gq);
+  const unsigned gq = p.by_group.d, k_in_xcd = blockIdx.x / kXcds;
+  const unsigned nth = p.by_pair.div(k_in_xcd), pair = nth * kXcds + blockIdx.x % kXcds;
+  if (pair >= (unsigned)(p.batch * p.hkv)) return b;
+  const unsigned rem = k_in_xcd - nth * p.by_pair.d, from_last = p.by_group.div(rem);
+  const int qblk = p.n_qblk - 1 - (int)from_last;
+  const unsigned s = p.by_kv.div(pair);
+  b.c = (int)(pair - s * p.by_kv.d);
+  b.a = head_of_slot(p.heads, b.c * (int)gq + (int)(rem - from_last * gq));
   pf_seq_bounds(p, s, b.b0, b.n);
   b.q0 = qblk * block_rows;
   b.valid = b.q0 < b.n;
@@ -289,22 +288,28 @@ __device__ __forceinline__ PfBlock pf_map_block(const PrefillParams& p, int bloc
 
 // ---- Q fragments: rotate at the original position (tabulated cos/sin), fold in scale*log2(e), keep as bf16 B operands ----
 // lane (r32, hf) holds, for k-step ks, dims 16 ks + 8 hf + (0..7) of query r32
+// unit(ks): those 8 elements as they came; c: the lane's (cos, sin) pairs (no table: no rotation)
 template <int D>
-__device__ __forceinline__ void pf_load_q(const PrefillParams& p, const __bf16* qrow /* row + 8 hf */,
-                                          const f32x2* csrow /* token's table row + 8 hf */, bf16x8 (&qf)[D / 16]) {
+__device__ __forceinline__ void pf_load_cs(const PrefillParams& p, long long token, int hf, f32x4 (&c)[D / 8]) {
+  const f32x4* cs = p.cs + (long long)(4 * hf) * p.total + token;
+#pragma unroll
+  for (int i = 0; i < D / 8; ++i)    // pairs 16 (i / 4) + 8 hf + 2 (i % 4), + 1
+    c[i] = p.cs ? cs[(long long)(8 * (i / 4) + i % 4) * p.total] : f32x4{1.f, 0.f, 1.f, 0.f};
+}
+template <int D, typename Unit>
+__device__ __forceinline__ void pf_rotate_q(const PrefillParams& p, Unit&& unit, const f32x4 (&c)[D / 8], bf16x8 (&qf)[D / 16]) {
   constexpr int KSTEPS = D / 16;
 #pragma unroll
   for (int ks = 0; ks < KSTEPS / 2; ++ks) {
     float lo[8], hi[8];
-    Vec8<__bf16>::load(qrow + 16 * ks, lo);
-    Vec8<__bf16>::load(qrow + 16 * ks + D / 2, hi);
-    const f32x4* cs4 = (const f32x4*)(csrow + 16 * ks);  // pairs 16 ks + 8 hf + (0..7)
+    Vec8<__bf16>::load(unit(ks), lo);
+    Vec8<__bf16>::load(unit(ks + KSTEPS / 2), hi);
     u32x4 wl, wh;
 #pragma unroll
     for (int j = 0; j < 8; j += 2) {
-      const f32x4 c = p.cs ? cs4[j / 2] : f32x4{1.f, 0.f, 1.f, 0.f};  // (cos, sin) of pairs j, j + 1; no table: no rotation
-      const float x0 = (lo[j] * c[0] - hi[j] * c[1]) * p.scale_log2, y0 = (hi[j] * c[0] + lo[j] * c[1]) * p.scale_log2;
-      const float x1 = (lo[j + 1] * c[2] - hi[j + 1] * c[3]) * p.scale_log2, y1 = (hi[j + 1] * c[2] + lo[j + 1] * c[3]) * p.scale_log2;
+      const f32x4 t = c[4 * ks + j / 2];
+      const float x0 = (lo[j] * t[0] - hi[j] * t[1]) * p.scale_log2, y0 = (hi[j] * t[0] + lo[j] * t[1]) * p.scale_log2;
+      const float x1 = (lo[j + 1] * t[2] - hi[j + 1] * t[3]) * p.scale_log2, y1 = (hi[j + 1] * t[2] + lo[j + 1] * t[3]) * p.scale_log2;
       wl[j / 2] = pack_bf16(x0, x1);
       wh[j / 2] = pack_bf16(y0, y1);
     }
@@ -313,14 +318,25 @@ __device__ __forceinline__ void pf_load_q(const PrefillParams& p, const __bf16* 
   }
 }
 
+// 32 query rows of a wave, whole rows at a time, into its own 32 x D region of LDS (swizzled like a K tile); rows past the
+// sequence's end read as zeros.
+template <int D>
+__device__ __forceinline__ void pf_stage_q(const __bf16* q /* first row */, int rows, int row_bytes, unsigned lds, int lane) {
+  constexpr int UPR = D / 8, RPI = kWave / UPR;
+  const u32x4 rsrc = raw_buffer(q, (min(rows, 32) - 1) * row_bytes + D * 2);
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int row = RPI * i + lane / UPR;
+    dma16_to_lds(rsrc, lds + (unsigned)(i * 1024), row * row_bytes + ((lane % UPR) ^ swz<D>(row)) * 16);
+  }
+}
 // S^T (+)= K Q^T for the K tile at smk: two 32-key blocks, K fragments requested AHEAD k-steps before the MFMAs that use
 // them.  ZERO: start from 0, else from `init` in every register (the steady state starts at -m, which takes the
 // subtraction of the reference maximum off the vector ALU).
-template <int D, bool ZERO>
+template <int D, bool ZERO, int AHEAD = ZERO ? 1 : 2>  // the exact paths are short of registers, not of time
 __device__ __forceinline__ void score_tile(const __bf16* smk, const FragOffsets<D>& fo, const bf16x8 (&qf)[D / 16],
                                            const f32x16& init, f32x16 (&sc)[2]) {
   constexpr int KSTEPS = D / 16;
-  constexpr int AHEAD = ZERO ? 1 : (2 < KSTEPS ? 2 : KSTEPS);  // the exact paths are short of registers, not of time
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   bf16x8 kf[2][KSTEPS];
 #pragma unroll
@@ -372,10 +388,37 @@ __device__ __forceinline__ void pf_store_row(__bf16* orow /* row + 4 hf */, cons
     }
 }
 
+// The same through a 32 x D region of LDS that is the wave's own: whole rows leave in 16-byte units.
+template <int D>
+__device__ __forceinline__ void pf_store_rows(__bf16* out /* first row */, int rows, long long row_elems, __bf16* sm,
+                                              const f32x16 (&o)[D / 32], float inv, int lane) {
+  constexpr int UPR = D / 8, RPI = kWave / UPR;
+  const int r32 = lane & 31, hf = lane >> 5;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *(u32x2*)(sm + r32 * D + (((4 * db + j) ^ swz<D>(r32)) << 3) + 4 * hf) =
+          u32x2{pack_bf16(o[db][4 * j] * inv, o[db][4 * j + 1] * inv), pack_bf16(o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv)};
+  asm volatile("" ::: "memory");   // a wave's LDS operations complete in order: only the compiler has to keep theirs
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int row = RPI * i + lane / UPR;
+    const u32x4 x = *(const u32x4*)(sm + row * D + (lane % UPR) * 8);
+    if (row < rows) *(u32x4*)(out + row * row_elems + (((lane % UPR) ^ swz<D>(row)) << 3)) = x;
+  }
+}
+
 // ------------------------------------------------------------------------------------------------------------------
 // Plain schedule: per tile  barrier -> S^T -> exponentials -> O^T.  One 32-query column block per wave.
 //   WAVES = 4: 128 query rows per workgroup, two workgroups per CU: less idle time on the causal diagonal of medium
-//              sequences than 256-row workgroups, at the price of staging every K/V tile twice as often.
+//              sequences than 256-row workgroups, at the price of staging every K/V tile twice as often.  The two are at
+//              1.4 PFLOP/s while both are inside their tiles; what counts is the rest of a workgroup's life.  Queries and
+//              outputs therefore pass through the stage that is free at the time, whole rows at a time, the rotary table is
+//              read along the tokens, and tile 0 rescales nothing (one row per lane and load: 32.3 us of life for 12.6
+//              tiles, 5.1 of them waiting for rows, 4.3 in tile 0 and 2.3 storing; now 26.5, 3.3, 3.1, 1.8.  64 sequences
+//              of 288-2080 rows, 32 heads of 128: 1.49 -> 1.37 ms; 256 of 80-1040, 12 / 2 heads: 404 -> 332 us).
+//              The pipelined schedule below in 128-row workgroups, two per CU, is slower here: 1.49 -> 1.72 ms.
 //   WAVES = 2, STAGES = 1: sequences of one K/V tile with a kv head per query head: there is nothing to double buffer, and
 //              the small footprint lets 4 workgroups share a CU, which is what hides the load -> rotate -> multiply
 //              latency chain of these tiny problems.
@@ -447,16 +490,31 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
       if (t + 1 < n_tiles) issue_tile(t + 1);
     }
   };
-  issue_tile(0);  // in flight while the queries are loaded and rotated
-
-  bf16x8 qf[D / 16];
-  {
-    const int qi = min(qw + r32, n - 1);
-    pf_load_q<D>(p, (const __bf16*)lv.q + ((long long)(b0 + qi) * p.hq + blk.a) * D + 8 * hf,
-                 p.cs + (long long)(b0 + qi) * (D / 2) + 8 * hf, qf);
-  }
   FragOffsets<D> fo;
   fo.init(lane);
+  // The wave's own 32 x D region inside stage x (two stages only): waves 0, 1 in its K tile, 2, 3 in its V tile.
+  auto own_region = [&](int x) { return (wave & 2 ? smv[x] : smk[x]) + (wave & 1) * 32 * D; };
+  bf16x8 qf[D / 16];
+  const int q_c = min(qw + r32, n - 1);
+  f32x4 cs[D / 8];
+  if constexpr (STAGES == 2) {
+    // through the second stage, which nothing uses before the first barrier
+    const __bf16* own = own_region(1);
+    if (wave_active)
+      pf_stage_q<D>((const __bf16*)lv.q + ((long long)(b0 + qw) * p.hq + blk.a) * D, n - qw, p.hq * D * 2,
+                    (unsigned)(size_t)(lds_void_ptr)own, lane);
+    issue_tile(0);
+    pf_load_cs<D>(p, b0 + q_c, hf, cs);
+    asm volatile("" ::: "memory");
+    wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    pf_rotate_q<D>(p, [&](int ks) { return own + fo.k(ks); }, cs, qf);
+  } else {
+    pf_load_cs<D>(p, b0 + q_c, hf, cs);
+    issue_tile(0);  // in flight while the queries are loaded and rotated
+    const __bf16* qrow = (const __bf16*)lv.q + ((long long)(b0 + q_c) * p.hq + blk.a) * D + 8 * hf;
+    pf_rotate_q<D>(p, [&](int ks) { return qrow + 16 * ks; }, cs, qf);
+  }
   PF_TIMELINE(__builtin_amdgcn_s_waitcnt(0x0F70);)  // vmcnt(0)
   PF_STAMP(2);
 
@@ -494,14 +552,15 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kk][db], __builtin_bit_cast(bf16x8, w[kk]), o[db], 0, 0, 0);
   };
   // The exact path: raw scores, exact row maxima, rescale of everything accumulated so far.
-  // synced = the tile fell out of the steady-state loop, which has passed the tile's barrier already.
-  auto exact_tile = [&](int t, bool synced) {
-    if (!synced) sync_and_stage(t);
+  // Tile 0 has nothing to rescale yet; any other one fell out of the steady-state loop, which has passed its barrier already.
+  auto exact_tile = [&](int t, auto first_c) {
+    constexpr bool FIRST = decltype(first_c)::value;
+    if (FIRST) sync_and_stage(t);
     f32x16 sc[2];
     bf16x8 vf[4][DB];
     u32x4 w[4];
     float lsum;
-    score_tile<D, true>(smk[t % STAGES], fo, qf, neg_m, sc);
+    score_tile<D, true, FIRST ? 3 : 1>(smk[t % STAGES], fo, qf, neg_m, sc);
     if (t == t_diag) mask_diagonal(sc, q_in_tile, r32, hf);
     float m = sc[0][0];
 #pragma unroll
@@ -509,15 +568,17 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
 #pragma unroll
       for (int i = 0; i < 16; ++i) m = fmaxf(m, sc[kb][i]);
     const float mnew = fmaxf(mrow, half_max(m));  // finite: tile 0 holds key 0, visible to every query
-    const float alpha = __builtin_amdgcn_exp2f(mrow - mnew);
+    if (!FIRST) {
+      const float alpha = __builtin_amdgcn_exp2f(mrow - mnew);
+      lrow *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+    }
     mrow = mnew;
-    lrow *= alpha;
 #pragma unroll
     for (int i = 0; i < 16; ++i) neg_m[i] = -mnew;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
     fetch_v(smv[t % STAGES], vf);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
@@ -531,12 +592,16 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
   // exponentials against the reference maxima it already has and never touches the output accumulators with the
   // vector ALU.  It does not even compute row maxima: a reference is stale exactly when some exponential is large, so
   // the (already needed) partial row sums are compared with kSumLimit instead.  A wave that fails leaves the loop,
-  // recomputes the tile's scores, takes the exact maxima, rescales, finishes the tile and re-enters.  Tile 0 (reference
-  // still -inf) always takes the exact path; the wave's diagonal tile is the only one that needs the causal mask.
+  // recomputes the tile's scores, takes the exact maxima, rescales, finishes the tile and re-enters.  Tile 0 (no reference
+  // yet) always takes the exact path; the wave's diagonal tile is the only one that needs the causal mask.
   int t = 0;
+  if (wave_active) {
+    exact_tile(0, std::true_type{});
+    t = 1;
+    PF_STAMP(3);
+  }
   while (t < n_tiles) {
-    bool exact = wave_active && t == 0, synced = false;
-    if (!exact)
+    bool exact = false;
     for (; t < n_tiles; ++t) {
       const bool work = wave_active && t <= t_diag;  // else rows past the sequence end or a tile past the diagonal: only stage
       sync_and_stage(t);
@@ -549,23 +614,27 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
         if (t == t_diag) mask_diagonal(sc, q_in_tile, r32, hf);  // masked scores give weight 0 on this path as well
         fetch_v(smv[t % STAGES], vf);
         softmax_tile(sc, w, lsum);
-        if (__any(!(lsum <= kSumLimit))) { exact = synced = true; break; }
+        if (__any(!(lsum <= kSumLimit))) { exact = true; break; }
         accumulate(w, lsum, vf);
       }
     }
     if (!exact) break;
-    exact_tile(t, synced);
+    exact_tile(t, std::false_type{});
     ++t;
-    PF_TIMELINE(if (t == 1) PF_STAMP(3);)
   }
   PF_STAMP(4);
 
   if (!wave_active) return;
   const int qi = qw + r32;
-  const float ltot = half_sum(lrow);
-  if (qi >= n) return;
-  pf_store_row<D>((__bf16*)lv.out + ((long long)(b0 + qi) * p.hq + blk.a) * D + 4 * hf, o, 1.f / ltot);
-  if (lv.lse && hf == 0) lv.lse[(long long)(b0 + qi) * p.hq + blk.a] = (mrow + __builtin_log2f(ltot)) * 0.6931471805599453f;
+  const float ltot = half_sum(lrow), inv = 1.f / ltot;
+  __bf16* out = (__bf16*)lv.out + ((long long)(b0 + qw) * p.hq + blk.a) * D;
+  if (lv.lse && hf == 0 && qi < n) lv.lse[(long long)(b0 + qi) * p.hq + blk.a] = (mrow + __builtin_log2f(ltot)) * 0.6931471805599453f;
+  if constexpr (STAGES == 2) {
+    // through the stage that the last tile, behind the last barrier, is not in
+    pf_store_rows<D>(out, n - qw, (long long)p.hq * D, own_region(n_tiles & 1), o, inv, lane);
+  } else if (qi < n) {
+    pf_store_row<D>(out + (long long)r32 * p.hq * D + 4 * hf, o, inv);
+  }
   PF_STAMP(5);
 }
 
@@ -844,8 +913,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_pipe_k
   bf16x8 qf[KSTEPS];
   {
     const int qi = min(qw + r32, n - 1);
-    pf_load_q<D>(p, (const __bf16*)lv.q + ((long long)(b0 + qi) * p.hq + blk.a) * D + 8 * hf,
-                 p.cs + (long long)(b0 + qi) * (D / 2) + 8 * hf, qf);
+    const __bf16* qrow = (const __bf16*)lv.q + ((long long)(b0 + qi) * p.hq + blk.a) * D + 8 * hf;
+    f32x4 cs[D / 8];
+    pf_load_cs<D>(p, b0 + qi, hf, cs);
+    pf_rotate_q<D>(p, [&](int ks) { return qrow + 16 * ks; }, cs, qf);
   }
   FragOffsets<D> fo;
   fo.init(lane);
@@ -1036,7 +1107,7 @@ size_t prefill_workspace_bytes(const earn_attn_desc* desc, int total_tokens, int
 
 template <typename T, int D>
 static void launch_rope_k(const void* k, void* k_rot, const int32_t* cu, const int32_t* positions, int batch, int total,
-                          int hkv, const RopeTable& rope, f32x2* cs_out, hipStream_t stream, int n_layers = 1,
+                          int hkv, const RopeTable& rope, f32x4* cs_out, hipStream_t stream, int n_layers = 1,
                           long long ls_k = 0, long long ls_k_rot = 0) {
   long long threads = (long long)total * (D / 16);
   const unsigned gx = (unsigned)((threads + 255) / 256);
@@ -1106,7 +1177,7 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   // no rotation and no cache copy asked for: the keys (already rotated by their producer) are read where they are
   const bool in_place = !(desc->rope_base > 0.f) && !k_rot_out;
   const void* k_rot = in_place ? k : (k_rot_out ? k_rot_out : workspace);
-  f32x2* cs = !in_place && cs_table_bytes(desc, total_tokens) ? (f32x2*)((char*)workspace + (k_rot_out ? 0 : k_rot_bytes(desc, total_tokens))) : nullptr;
+  f32x4* cs = !in_place && cs_table_bytes(desc, total_tokens) ? (f32x4*)((char*)workspace + (k_rot_out ? 0 : k_rot_bytes(desc, total_tokens))) : nullptr;
   PrefillParams p;
   p.cs = cs; p.row_pos = nullptr; p.rows_per_seq = 0;
   p.q = q; p.k_rot = k_rot; p.v = v; p.cu = cu_seqlens; p.positions = positions; p.out = out; p.lse = lse_out;
@@ -1119,6 +1190,11 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   p.rope = make_rope_table(desc->rope_base, d);
   if (make_head_map(desc, &p.heads, "earn_prefill_attn") != EARN_OK) return EARN_ERR_UNSUPPORTED;
   const bool f32 = desc->dtype == EARN_F32;
+  auto set_query_blocks = [&p](int n) {
+    const unsigned gq = (unsigned)(p.hq / p.hkv);
+    p.n_qblk = n;
+    p.by_pair = FastDiv::of(n * gq); p.by_group = FastDiv::of(gq); p.by_kv = FastDiv::of((unsigned)p.hkv);
+  };
   // prefill_short_kernel: grouped heads up to 128 rows (beyond 64: short_prefill_takes), single heads up to 32.  us per layer
   // with rotation, one launch per layer / 24 layers in one launch, the kernels of longer sequences (and a rotation pass) -> this one:
   //   256 sequences, 12 / 2 heads of 128: 16 rows 29.8 / 18.9 -> 13.4 / 8.2, 64 rows 60.0 / 44.7 -> 41.0 / 32.4, 128 rows
@@ -1166,7 +1242,7 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
       if (d == 64) launch_rope_k<__bf16, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
       else launch_rope_k<__bf16, 128>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
     }
-    p.n_qblk = 1;
+    set_query_blocks(1);
     const long long pairs8 = ((long long)batch * p.hkv + kXcds - 1) / kXcds * kXcds;
     dim3 grid((unsigned)(pairs8 * (p.hq / p.hkv)), n_layers, 1);
     if (d == 64) hipLaunchKernelGGL((prefill_mfma_kernel<64, 2, 1>), grid, dim3(128), 0, stream, p);
@@ -1184,7 +1260,7 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
     const int rows_set = tuning(kTunePrefillBlockRows, 0);
     const bool medium = max_seqlen <= 3072 || total_tokens / batch <= 2048;
     const int block_rows = rows_set == 128 || rows_set == 256 ? rows_set : (medium ? 128 : 256);
-    p.n_qblk = (max_seqlen + block_rows - 1) / block_rows;
+    set_query_blocks((max_seqlen + block_rows - 1) / block_rows);
     const long long pairs8 = ((long long)batch * p.hkv + kXcds - 1) / kXcds * kXcds;
     dim3 grid((unsigned)(pairs8 * p.n_qblk * (p.hq / p.hkv)), n_layers, 1);
     if (block_rows == 128) {

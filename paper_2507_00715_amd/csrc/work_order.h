@@ -9,6 +9,21 @@
 
 namespace earn {
 
+// Division of n < 2^31 by a divisor that the host knows: a multiplication in the kernel, where dividing a wave-uniform number
+// takes some thirty vector instructions.  2^(31 + shift) <= mul d < 2^(31 + shift) + d with d <= 2^shift, so n mul / 2^(31 +
+// shift) is less than 1 / d above n / d and rounds down to the same.
+struct FastDiv {
+  unsigned d, mul;
+  int shift;
+  static FastDiv of(unsigned d) {
+    FastDiv f{d, 0, 0};
+    while ((1ull << f.shift) < d) ++f.shift;
+    f.mul = (unsigned)(((1ull << (31 + f.shift)) + d - 1) / d);
+    return f;
+  }
+  EARN_INDEX unsigned div(unsigned n) const { return (unsigned)((unsigned long long)n * mul >> (31 + shift)); }
+};
+
 constexpr int kXcds = 8;  // accelerator complex dies, each with a private L2; consecutive workgroup ids go to them in turn
 
 // ---- short decode and prefill: an XCD takes a run of consecutive units, `per` workgroups of each item (stream, sequence) ----

@@ -13,6 +13,10 @@ using namespace earn;
 extern "C" int takes(int longest, int mean, long long pairs, int in_place) { return short_prefill_takes(longest, mean, pairs, in_place); }
 extern "C" int takes_beams(long long pairs, long long general, int len, int d) { return short_decode_takes_beams(pairs, general, len, d); }
 extern "C" int waves(int max_shared_len, int gen_cap, long long workgroups) { return short_decode_waves(max_shared_len, gen_cap, workgroups); }
+extern "C" void divide(unsigned d, const unsigned* n, unsigned* out, int count) {
+  const FastDiv f = FastDiv::of(d);
+  for (int i = 0; i < count; ++i) out[i] = f.div(n[i]);
+}
 extern "C" int fits(int n, int per, int threads) { return run_fits(n, per, threads); }
 extern "C" long long runs(int n, int per, int even, int (*out)[3], long long limit) {
   const long long w = run_workgroups(n, per);
@@ -148,3 +152,14 @@ def test_short_prefill_takes(lib, longest, mean, pairs, in_place, short):
 def test_short_decode_takes_beams(lib, batch, beams, hkv, d, layers, rows, short):
     ll = ctypes.c_longlong
     assert bool(lib.takes_beams(ll(batch * beams * hkv * layers), ll(batch * hkv * layers), rows, d)) == short
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 5, 7, 12, 17, 32, 100, 1041, 65535, 65537, 524288, 2 ** 30 + 1, 2 ** 31 - 1])
+def test_division_by_multiplication(lib, d):
+    k = np.arange(1, 2000, dtype=np.uint64)
+    n = np.concatenate([np.arange(2000, dtype=np.uint64), 2 ** 31 - k, k * d, k * d - 1, 2 ** 31 // d * d - np.array([0, 1], dtype=np.uint64),
+                        np.random.default_rng(d).integers(0, 2 ** 31, 20000, dtype=np.uint64)])
+    n = n[n < 2 ** 31].astype(np.uint32)
+    out = np.empty_like(n)
+    lib.divide(ctypes.c_uint(d), n.ctypes.data_as(ctypes.c_void_p), out.ctypes.data_as(ctypes.c_void_p), len(n))
+    assert np.array_equal(out, n // np.uint32(d))
