@@ -45,7 +45,7 @@ def dominant_kernel(cfg, w) -> tuple:
     """Name of the kernel a full-length prefill layer of this workload runs (the library picks by dtype and by the
     lengths: short, one-tile, medium or long sequences), and the roofline that bounds it."""
     if cfg.dtype != "bf16":
-        return "prefill_rows_kernel + rope_k_kernel (one full-length causal layer, vector ALU)", "alu"
+        return "prefill_f32_kernel (one full-length causal layer, fp32 matrix products)", "alu"
     mean, pairs = w.total_tokens // cfg.batch, cfg.batch * cfg.n_kv_heads
     short = w.max_seqlen <= 64 or w.max_seqlen <= 128 and (pairs >= 512 or pairs < 128 or 4 * mean >= w.max_seqlen)
     if short if cfg.n_q_heads > cfg.n_kv_heads else w.max_seqlen <= 32:

@@ -9,8 +9,8 @@
 //                        long sequences.
 //   prefill_mfma_kernel  the same arithmetic in a plain per-tile schedule with smaller workgroups: medium sequences.
 //   prefill_short_kernel rotation and attention of a whole (sequence, kv head) in one workgroup: the register-only layers.
-//   prefill_rows_kernel  fp32 attention on the vector ALU: one query row per 4 lanes. Used for the fp32
-//                        configuration, where the 1e-4 tolerance rules out bf16 operands.
+//   prefill_f32_kernel   fp32 attention on fp32 matrix products, for the fp32 configuration, where the 1e-4 tolerance rules
+//                        out bf16 operands.
 //
 // MFMA kernel layout (all shapes in the 32x32x16 tile of the instruction, 64 lanes, lane = (r32 = lane%32, hf = lane/32)):
 //   The kernels compute the TRANSPOSED score tile S^T = K Q^T (keys x queries).  Its accumulator layout gives every lane
@@ -38,7 +38,7 @@ struct PrefillParams {
   int total;   // rows of the packed tensors
   int n_qblk;  // query blocks of the longest sequence
   FastDiv by_pair, by_group, by_kv;  // workgroups per (sequence, kv head), query heads per kv head, kv heads (pf_map_block)
-  // chosen-rows mode of the vector kernel (rows_per_seq > 0): q and out hold rows_per_seq rows per sequence in
+  // chosen-rows mode of the fp32 kernel (rows_per_seq > 0): q and out hold rows_per_seq rows per sequence in
   // compacted order, row m of sequence s being token row_pos[s * rows_per_seq + m] (ascending) of the sequence
   const int32_t* row_pos;
   int rows_per_seq;
@@ -162,96 +162,249 @@ __global__ __launch_bounds__(256) void rope_k_kernel(const T* __restrict__ k, T*
 }
 
 // ------------------------------------------------------------------------------------------------------------------
-// vector-ALU attention: 64 query rows per workgroup, 4 lanes per row (each holds D/4 elements of q and of the output)
+// fp32 attention on fp32 matrix products (v_mfma_f32_16x16x4_f32: exact products, fp32 sums).  A workgroup takes 16 QB query
+// rows of one head; its waves take the 16-key blocks in turn and merge their states through LDS at the end, so that a short
+// sequence is a few steps of many waves instead of a walk of few waves over all its keys.
+//   S^T = K Q^T    lane (r16, quad) holds elements [quad E, + E) and [D/2 + quad E, + E) of key / query r16 (E = D/8): both
+//                  sides of its rotary pairs, and any order of the contraction will do as long as both operands have it
+//   O^T = V^T P^T  register s of S^T is key 4 quad + s of query r16: the B operand of a product over keys {4 quad + s}.  A lane
+//                  reads dimensions 64 h + 4 r16 + (0..3) of its key, whole rows per wave instruction, and ends up with
+//                  16 consecutive dimensions of its query.
+// Nothing but the merge goes through LDS: every fragment is a 16-byte load of the wave's own.
+//
+// ROTATE: the keys are rotated here, every workgroup for itself, and the workgroup whose queries are the same rows writes the
+// cache copy: one launch instead of two where the launch, not the arithmetic, is what a layer costs.
+//
+// Before, 4 lanes shared a query row on the vector ALU and 64 rows walked all their keys together.  us, with the rotation of the
+// keys: 2 sequences of 132 rows, 4 heads of 64 55.1 -> 10.9 (17 round trips to memory in a row, now at most two); 16 of 512, 32 / 8
+// heads of 128 6770 -> 1270, 27 TFLOP/s: one 4-wave workgroup a CU, whose loads nothing covers.  Relative error against 64 bits
+// 1.8e-7 -> 1.5e-7 and 2.8e-7 -> 1.9e-7.
 // ------------------------------------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(256) void prefill_rows_kernel(PrefillParams p) {
-  constexpr int E = D / 8;  // elements per contiguous piece; a lane holds pieces [qt*E, +E) and [D/2 + qt*E, +E)
+template <int D, int QB, int WAVES, bool ROTATE>
+__global__ __launch_bounds__(64 * WAVES, D == 64 || QB == 1 ? 2 : 1) void prefill_f32_kernel(PrefillParams p, const float* k_in, long long ls_k_in, float* k_out) {
+  constexpr int E = D / 8, H = D / 64, ROWS = 16 * QB, BLK = 16, OP = D + 4;   // OP: row pitch of the merge buffer
+  __shared__ float smo[WAVES][ROWS][OP];
+  __shared__ float sml[WAVES][ROWS][2];
   const int slot = blockIdx.y, s = blockIdx.z % p.batch;  // slot: the query heads in kv-head order
   const PfLayer lv = pf_layer_view(p, blockIdx.z / p.batch);
-  const int a = head_of_slot(p.heads, slot);
+  const int a = head_of_slot(p.heads, slot), gq = p.hq / p.hkv, c = slot / gq;
   int b0, n;
   pf_seq_bounds(p, s, b0, n);
-  const int row0 = blockIdx.x * 64;
   const int r = p.rows_per_seq;           // 0: every row of the sequence
   const int n_rows = r > 0 ? r : n;
+  const int row0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * ROWS;   // late rows, which see the most keys, first
   if (row0 >= n_rows || n <= 0) return;
-  const int qt = threadIdx.x & 3;
-  const int mrow = row0 + (threadIdx.x >> 2);                  // row of the sequence's row list
-  const bool row_ok = mrow < n_rows;
-  const int mc = row_ok ? mrow : n_rows - 1;
-  // its token index: it sees keys 0 .. ic (a row_pos outside the sequence is held inside it: wrong values, no stray access)
-  const int ic = r > 0 ? min(max(p.row_pos[s * r + mc], 0), n - 1) : mc;
-  const long long io = r > 0 ? (long long)s * r + mc : (long long)b0 + mc;  // its row in q / out / lse
-  const int c = slot / (p.hq / p.hkv);
-  const T* qrow = (const T*)lv.q + (io * p.hq + a) * D;
-  float ql[E], qh[E];
-#pragma unroll
-  for (int e = 0; e < E; e += 8) { Vec8<T>::load(qrow + qt * E + e, ql + e); Vec8<T>::load(qrow + D / 2 + qt * E + e, qh + e); }
-  const int pos = (p.positions && r == 0) ? p.positions[b0 + ic] : ic;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    float sn = 0.f, cs = 1.f;
-    if (p.rope.enabled) sincos_turns_precise(rope_turns((float)pos, p.rope.hi[qt * E + e], p.rope.lo[qt * E + e]), &sn, &cs);
-    float x = ql[e], y = qh[e];
-    ql[e] = (x * cs - y * sn) * p.scale_log2;
-    qh[e] = (y * cs + x * sn) * p.scale_log2;
-  }
-  float ol[E], oh[E], m = -INFINITY, l = 0.f;
-#pragma unroll
-  for (int e = 0; e < E; ++e) { ol[e] = 0.f; oh[e] = 0.f; }
-  // all rows of a wave walk the keys together up to the wave's last row
-  const int wave_last_row = min(n_rows - 1, row0 + (int)(threadIdx.x / kWave) * 16 + 15);
-  const int wave_last = r > 0 ? min(max(p.row_pos[s * r + wave_last_row], 0), n - 1) : wave_last_row;
-  const T* kbase = (const T*)lv.k_rot + ((long long)b0 * p.hkv + c) * D;
-  const T* vbase = (const T*)lv.v + ((long long)b0 * p.hkv + c) * D;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int r16 = lane & 15, quad = lane >> 4;
   const long long rs = (long long)p.hkv * D;
-  // NB keys per step: their rows are requested together and their scores formed side by side (the walk is otherwise a
-  // chain of memory round trips); the softmax state still takes them one after the other, in key order
-  constexpr int NB = D == 64 ? 4 : 2;
-  for (int j0 = 0; j0 <= wave_last; j0 += NB) {
-    float kl[NB][E], kh[NB][E], vl[NB][E], vh[NB][E], sc[NB];
+  const float* kbase = (ROTATE ? pf_layer_ptr(k_in, ls_k_in, blockIdx.z / p.batch) : (const float*)lv.k_rot) + ((long long)b0 * p.hkv + c) * D + quad * E;
+  const float* vbase = (const float*)lv.v + ((long long)b0 * p.hkv + c) * D + 4 * r16;
+  // row of the sequence's row list -> its token: it sees keys 0 .. token (a row_pos outside the sequence is held inside it: wrong
+  // values, no stray access)
+  auto token_of = [&](int row) {
+    const int m = min(row, n_rows - 1);
+    return r > 0 ? min(max(p.row_pos[(long long)s * r + m], 0), n - 1) : m;
+  };
+  const int last_key = token_of(row0 + ROWS - 1), first_token = token_of(row0);   // rows ascend
+  const int n_blocks = last_key / BLK + 1;
+
+  float kx[2 * E];
+  f32x4 vx[4][H];
+  auto load_block = [&](int blk) {
+    const float* krow = kbase + min(blk * BLK + r16, n - 1) * rs;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int j = min(j0 + b, wave_last);
+    for (int e = 0; e < E; e += 8) { Vec8<float>::load(krow + e, kx + e); Vec8<float>::load(krow + D / 2 + e, kx + E + e); }
 #pragma unroll
-      for (int e = 0; e < E; e += 8) {
-        Vec8<T>::load(kbase + j * rs + qt * E + e, kl[b] + e);
-        Vec8<T>::load(kbase + j * rs + D / 2 + qt * E + e, kh[b] + e);
-        Vec8<T>::load(vbase + j * rs + qt * E + e, vl[b] + e);
-        Vec8<T>::load(vbase + j * rs + D / 2 + qt * E + e, vh[b] + e);
+    for (int i = 0; i < 4; ++i) {
+      const float* vrow = vbase + min(blk * BLK + 4 * quad + i, n - 1) * rs;
+#pragma unroll
+      for (int h = 0; h < H; ++h) vx[i][h] = *(const f32x4*)(vrow + 64 * h);
+    }
+  };
+  auto rotate = [&](float* x, int token) {
+    const int pos = (p.positions && r == 0) ? p.positions[b0 + token] : token;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      float sn, cs;
+      sincos_turns_precise(rope_turns((float)pos, p.rope.hi[quad * E + e], p.rope.lo[quad * E + e]), &sn, &cs);
+      const float lo = x[e], hi = x[E + e];
+      x[e] = lo * cs - hi * sn;
+      x[E + e] = hi * cs + lo * sn;
+    }
+  };
+  // queries: rotated and scaled; row of q / out / lse
+  int ic[QB];
+  long long io[QB];
+  float qx[QB][2 * E];
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    const int row = min(row0 + 16 * b + r16, n_rows - 1);
+    ic[b] = token_of(row);
+    io[b] = r > 0 ? (long long)s * r + row : (long long)b0 + row;
+    const float* q = (const float*)lv.q + (io[b] * p.hq + a) * D + quad * E;
+#pragma unroll
+    for (int e = 0; e < E; e += 8) { Vec8<float>::load(q + e, qx[b] + e); Vec8<float>::load(q + D / 2 + e, qx[b] + E + e); }
+  }
+  if (wave < n_blocks) load_block(wave);
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    if (p.rope.enabled) rotate(qx[b], ic[b]);
+#pragma unroll
+    for (int e = 0; e < 2 * E; ++e) qx[b][e] *= p.scale_log2;
+  }
+
+  f32x4 o[QB][H][4];
+  float mrow[QB], lrow[QB];    // lrow: of this lane's keys
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    mrow[b] = -INFINITY; lrow[b] = 0.f;
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[b][h][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int blk = wave; blk < n_blocks; blk += WAVES) {
+    const int j0 = blk * BLK;
+    if (blk != wave) load_block(blk);
+    if constexpr (ROTATE) {
+      const int key = min(j0 + r16, n - 1);
+      rotate(kx, key);
+      // this block's own rows, by the first head of the group
+      if (k_out && j0 >= row0 && j0 < row0 + ROWS && slot % gq == 0 && j0 + r16 < n) {
+        float* dst = pf_layer_ptr(k_out, p.ls_k_rot, blockIdx.z / p.batch) + ((long long)(b0 + key) * p.hkv + c) * D + quad * E;
+#pragma unroll
+        for (int e = 0; e < E; e += 8) { Vec8<float>::store(dst + e, kx + e); Vec8<float>::store(dst + D / 2 + e, kx + E + e); }
       }
     }
+    // Four partial sums: one would round a score D times in a row, twice the error (D = 128) of four lanes' sums added up.
+    f32x4 sc[QB], part[QB][4];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      float d = 0.f;
+    for (int b = 0; b < QB; ++b)
 #pragma unroll
-      for (int e = 0; e < E; ++e) d = __builtin_fmaf(ql[e], kl[b][e], __builtin_fmaf(qh[e], kh[b][e], d));
-      d += __shfl_xor(d, 1, kWave);
-      d += __shfl_xor(d, 2, kWave);
-      sc[b] = d;
-    }
+      for (int i = 0; i < 4; ++i) part[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      if (j0 + b <= ic && j0 + b <= wave_last) {  // causal: keys 0..i
-        float mn = fmaxf(m, sc[b]);
-        float corr = __builtin_amdgcn_exp2f(m - mn);  // exp2(-inf) = 0 on the first key
-        float pr = __builtin_amdgcn_exp2f(sc[b] - mn);
-        l = l * corr + pr;
+    for (int e = 0; e < 2 * E; ++e)
 #pragma unroll
-        for (int e = 0; e < E; ++e) { ol[e] = __builtin_fmaf(pr, vl[b][e], ol[e] * corr); oh[e] = __builtin_fmaf(pr, vh[b][e], oh[e] * corr); }
-        m = mn;
+      for (int b = 0; b < QB; ++b) part[b][e % 4] = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[e], qx[b][e], part[b][e % 4], 0, 0, 0);
+#pragma unroll
+    for (int b = 0; b < QB; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sc[b][i] = (part[b][0][i] + part[b][1][i]) + (part[b][2][i] + part[b][3][i]);
+#pragma unroll
+    for (int b = 0; b < QB; ++b) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (j0 + 4 * quad + i > ic[b]) sc[b][i] = -INFINITY;
+        m = fmaxf(m, sc[b][i]);
       }
+      m = fmaxf(m, __shfl_xor(m, 16, kWave));
+      m = half_max(m);
+      const float mnew = fmaxf(mrow[b], m), ref = mnew == -INFINITY ? 0.f : mnew;
+      const float alpha = __builtin_amdgcn_exp2f(mrow[b] - ref);
+      mrow[b] = mnew;
+      float sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { sc[b][i] = __builtin_amdgcn_exp2f(sc[b][i] - ref); sum += sc[b][i]; }
+      lrow[b] = lrow[b] * alpha + sum;
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[b][h][j][i] *= alpha;
+    }
+    // A masked key has weight 0, and 0 times an infinite or NaN value is NaN: such a block is weighed pair by pair, without the
+    // keys that a query does not see.
+    bool pairwise = false;
+    if (j0 + BLK - 1 > first_token) {   // some query does not see all of the block
+      float probe = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) probe = __builtin_fmaf(vx[i][h][j], 0.f, probe);
+      pairwise = __any(probe != probe);
+    }
+    if (!pairwise) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int b = 0; b < QB; ++b)
+              o[b][h][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vx[i][h][j], sc[b][i], o[b][h][j], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int b = 0; b < QB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll 1
+          for (int g = 0; g < 4; ++g) {
+            const int key = j0 + 4 * g + i;
+            const float w = __shfl(sc[b][i], 16 * g + r16, kWave);
+            if (key > ic[b]) continue;
+            const float* vrow = vbase - 4 * r16 + key * rs + 16 * quad;
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+              for (int x = 0; x < 4; ++x) {
+                const f32x4 v = *(const f32x4*)(vrow + 64 * h + 4 * x);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[b][h][j][x] = __builtin_fmaf(w, v[j], o[b][h][j][x]);
+              }
+          }
     }
   }
-  if (!row_ok) return;
-  const float inv = 1.f / l;
+  const int n_waves = min(WAVES, n_blocks);
+  if (wave < n_waves) {
 #pragma unroll
-  for (int e = 0; e < E; ++e) { ol[e] *= inv; oh[e] *= inv; }
-  T* orow = (T*)lv.out + (io * p.hq + a) * D;
+    for (int b = 0; b < QB; ++b) {
+      lrow[b] += __shfl_xor(lrow[b], 16, kWave);
+      lrow[b] = half_sum(lrow[b]);
+      if (quad == 0) { sml[wave][16 * b + r16][0] = mrow[b]; sml[wave][16 * b + r16][1] = lrow[b]; }
 #pragma unroll
-  for (int e = 0; e < E; e += 8) { Vec8<T>::store(orow + qt * E + e, ol + e); Vec8<T>::store(orow + D / 2 + qt * E + e, oh + e); }
-  if (lv.lse && qt == 0) lv.lse[io * p.hq + a] = (m + __builtin_log2f(l)) * 0.6931471805599453f;
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          *(f32x4*)&smo[wave][16 * b + r16][64 * h + 16 * quad + 4 * x] = f32x4{o[b][h][0][x], o[b][h][1][x], o[b][h][2][x], o[b][h][3][x]};
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < ROWS * (D / 4); i += 64 * WAVES) {
+    const int row = i / (D / 4), e = i % (D / 4) * 4;
+    if (row0 + row >= n_rows) break;     // rows ascend with i
+    float m = -INFINITY, l = 0.f;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < n_waves; ++w) m = fmaxf(m, sml[w][row][0]);
+    for (int w = 0; w < n_waves; ++w) {
+      // a wave none of whose keys the row sees: its sums hold zeros
+      const float f = sml[w][row][0] == -INFINITY && m != -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sml[w][row][0] - m);
+      l = __builtin_fmaf(f, sml[w][row][1], l);
+      const f32x4 y = *(const f32x4*)&smo[w][row][e];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = __builtin_fmaf(f, y[j], x[j]);
+    }
+    const float inv = 1.f / l;
+    const long long at = r > 0 ? (long long)s * r + row0 + row : (long long)b0 + row0 + row;
+    *(f32x4*)((float*)lv.out + (at * p.hq + a) * D + e) = f32x4{x[0] * inv, x[1] * inv, x[2] * inv, x[3] * inv};
+    if (lv.lse && e == 0) lv.lse[at * p.hq + a] = (m + __builtin_log2f(l)) * 0.6931471805599453f;
+  }
+}
+template <int D>
+static void launch_prefill_f32(const PrefillParams& p, const void* k_in, long long ls_k_in, void* k_out, bool rotate, int rows, int n_layers,
+                               hipStream_t stream) {
+  auto launch = [&](auto kernel, int block_rows, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((rows + block_rows - 1) / block_rows, p.hq, p.batch * n_layers), dim3(64 * waves), 0, stream, p,
+                       (const float*)k_in, ls_k_in, (float*)k_out);
+  };
+  const bool few = f32_few_workgroups(rows, p.hq, D, (long long)p.batch * n_layers);
+  if (rotate) launch(prefill_f32_kernel<D, 1, 8, true>, 16, 8);
+  else if (few) launch(prefill_f32_kernel<D, 1, 8, false>, 16, 8);
+  else launch(prefill_f32_kernel<D, 2, 4, false>, 32, 4);
 }
 
 // ------------------------------------------------------------------------------------------------------------------
@@ -1132,9 +1285,8 @@ int launch_prefill_rows_f32(const earn_attn_desc* desc, const void* q_rows, cons
   p.scale_log2 = scale * 1.4426950408889634f;
   p.rope = make_rope_table(desc->rope_base, d);
   if (make_head_map(desc, &p.heads, "earn_prefill_register_rows") != EARN_OK) return EARN_ERR_UNSUPPORTED;
-  dim3 grid((rows_per_seq + 63) / 64, p.hq, batch);
-  if (d == 64) hipLaunchKernelGGL((prefill_rows_kernel<float, 64>), grid, dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL((prefill_rows_kernel<float, 128>), grid, dim3(256), 0, stream, p);
+  if (d == 64) launch_prefill_f32<64>(p, nullptr, 0, nullptr, false, rows_per_seq, 1, stream);
+  else launch_prefill_f32<128>(p, nullptr, 0, nullptr, false, rows_per_seq, 1, stream);
   return hipGetLastError() == hipSuccess ? EARN_OK : EARN_ERR_HIP;
 }
 
@@ -1207,13 +1359,14 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   const bool few_rows = max_seqlen <= (p.hq > p.hkv ? 128 : 32) && run_fits(batch, p.hkv, max_seqlen <= 64 ? 256 : 512) &&
                         short_prefill_takes(max_seqlen, total_tokens / batch, (long long)batch * p.hkv * n_layers, in_place);
   if (f32) {
-    if (!in_place) {
+    // the keys are rotated by the attention kernel where there are few workgroups (and not in place: others read them)
+    const bool rotate = !in_place && k != k_rot_out && f32_few_workgroups(max_seqlen, p.hq, d, (long long)batch * n_layers);
+    if (!in_place && !rotate) {
       if (d == 64) launch_rope_k<float, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
       else launch_rope_k<float, 128>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
     }
-    dim3 grid((max_seqlen + 63) / 64, p.hq, batch * n_layers);
-    if (d == 64) hipLaunchKernelGGL((prefill_rows_kernel<float, 64>), grid, dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((prefill_rows_kernel<float, 128>), grid, dim3(256), 0, stream, p);
+    if (d == 64) launch_prefill_f32<64>(p, k, ls_k, k_rot_out, rotate, max_seqlen, n_layers, stream);
+    else launch_prefill_f32<128>(p, k, ls_k, k_rot_out, rotate, max_seqlen, n_layers, stream);
   } else if (few_rows) {
     auto launch = [&](auto kernel, int waves, int per_cu) {
       // Few (sequence, kv head) pairs: several workgroups per pair, each with its own copy of the keys, as many as an XCD
