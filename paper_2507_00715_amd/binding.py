@@ -140,8 +140,12 @@ def _rows(t: Optional[torch.Tensor], dim: int = 0) -> int:
     return 0 if t is None else int(t.shape[dim])
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """Handle of the stream that is current on the current device.  torch.cuda.current_stream() builds a Stream object around
+    it for 2.6 us, a third of what a call costs the host (bound decode layer 7.1 -> 4.6 us, unbound prefill 8.4 -> 5.9)."""
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_desc(dtype: torch.dtype, n_q_heads: int, n_kv_heads: int, head_dim: int, softmax_scale: float = 0.0,
@@ -247,7 +251,7 @@ class BoundCall:
         self._fn, self._args, self._keep = fn, args, keep
 
     def __call__(self) -> None:
-        rc = self._fn(*self._args, torch.cuda.current_stream().cuda_stream)
+        rc = self._fn(*self._args, _stream())
         if rc != EARN_OK:
             raise EarnError(rc, last_error())
 
