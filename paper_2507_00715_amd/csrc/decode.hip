@@ -87,6 +87,8 @@ struct DecodeParams {
   // side by side on one XCD, sharing the keys in its L2.
   int n_pass;
   int even_runs;  // decode_short_kernel: how its streams are dealt to the XCDs
+  BeamGroups groups;   // decode_beams_kernel: which streams share a workgroup
+  FastDiv by_gq, by_kv;  // query heads per kv head, kv heads (short kernels)
   float scale_log2;
   // byte strides between the layers of a layer-batched launch (grid row y = layer); all zero for a single layer
   long long ls_q, ls_kv_new, ls_shared, ls_gen, ls_out, ls_part_o, ls_part_ml;
@@ -452,35 +454,175 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[3]) {
   }
 }
 
+// Pieces of a 32-key block that the kernels below share.  Lane (r16, quad): query column r16; of the scores, keys 16 t + 4 quad + i.
+// 4 rotary pairs of a query (scaled, three terms) or of the new key (as stored), from x_lo, x_hi into rot[..][row][e], [e + D/2]
+template <int D, int ROWS>
+__device__ __forceinline__ void short_rotate(const DecodeParams& p, u32x2 x_lo, u32x2 x_hi, f32x4 th, f32x4 tl, float pos, bool key,
+                                             __bf16 (*rot)[ROWS][D + 8], __bf16* key_row, int row, int e) {
+  float y[2][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float sn = 0.f, cs = 1.f;
+    if (p.rope.enabled) sincos_turns_fast(rope_turns(pos, th[j], tl[j]), &sn, &cs);
+    const float a = j & 1 ? bf16_hi(x_lo[j / 2]) : bf16_lo(x_lo[j / 2]);
+    const float b = j & 1 ? bf16_hi(x_hi[j / 2]) : bf16_lo(x_hi[j / 2]);
+    y[0][j] = __builtin_fmaf(a, cs, -(b * sn));   // as the general kernels round it: the appended key is the same
+    y[1][j] = __builtin_fmaf(b, cs, a * sn);
+  }
+  const float scale = key ? 1.f : p.scale_log2;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    unsigned w0[3], w1[3];
+    split_pair(y[h][0] * scale, y[h][1] * scale, w0);
+    split_pair(y[h][2] * scale, y[h][3] * scale, w1);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      if (!key) *(u32x2*)&rot[i][row][e + h * (D / 2)] = u32x2{w0[i], w1[i]};
+      else if (i == 0) *(u32x2*)(key_row + e + h * (D / 2)) = u32x2{w0[0], w1[0]};   // the first term is the key as stored
+    }
+  }
+}
+// 16 consecutive rows share a chunk of a transposing read: two rows per chunk position at most
+template <int D>
+__device__ __forceinline__ int short_v_swz(int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); }
+// An operand in three terms times an infinite key or value element is inf - inf where the terms differ in sign, or 0 * inf
+// where one is zero, instead of the infinity that the whole operand gives.  So a result that came out as NaN is worked out
+// again (CAREFUL) with the first term's products on their own: where they are infinite, they are the result.
+__device__ __forceinline__ void short_settle(f32x4& first, const f32x4& rest) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) first[i] = __builtin_isinf(first[i]) ? first[i] : first[i] + rest[i];
+}
+template <int D, int ROWS, bool CAREFUL>
+__device__ __forceinline__ void short_scores(const bf16x8 (&kf)[2][D / 32], const __bf16 (*rot)[ROWS][D + 8], int q_row, int quad, f32x4 (&sc)[2]) {
+  f32x4 sc_rest[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 2; i >= 0; --i) {
+    if (CAREFUL && i == 0) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) { sc_rest[t] = sc[t]; sc[t] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    }
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) {
+      const bf16x8 q = *(const bf16x8*)&rot[i][q_row][32 * ks + 8 * quad];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], q, sc[t], 0, 0, 0);
+    }
+  }
+  if (CAREFUL) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) short_settle(sc[t], sc_rest[t]);
+  }
+}
+// Masked scores -> weights (three terms), the running maximum and sum; returns what earlier sums are scaled by.
+__device__ __forceinline__ float short_softmax(const f32x4 (&sc)[2], float& mrow, float& lrow, u32x4 (&pw)[3]) {
+  float m = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = fmaxf(m, sc[t][i]);
+  m = fmaxf(m, __shfl_xor(m, 16, kWave));
+  m = fmaxf(m, __shfl_xor(m, 32, kWave));
+  const float mnew = fmaxf(mrow, m), ref = mnew == -INFINITY ? 0.f : mnew;
+  const float alpha = __builtin_amdgcn_exp2f(mrow - ref);
+  mrow = mnew;
+  float sum = 0.f;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+      const float a = __builtin_amdgcn_exp2f(sc[t][i] - ref), b = __builtin_amdgcn_exp2f(sc[t][i + 1] - ref);
+      sum += a + b;
+      unsigned w[3];
+      split_pair(a, b, w);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) pw[j][2 * t + i / 2] = w[j];
+    }
+  lrow = lrow * alpha + sum;
+  return alpha;
+}
+// o = o alpha + V^T P^T over the 32 value rows at smv; only in lanes where `mine`
+template <int D, bool CAREFUL>
+__device__ __forceinline__ void short_weigh(const __bf16* smv, const u32x4 (&pw)[3], float alpha, int lane, f32x4 (&o)[D / 16], bool mine = true) {
+  const int r16 = lane & 15, quad = lane >> 4;
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db) {
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const int row = 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
+    const __bf16* a0 = smv + row * D + ((chunk ^ short_v_swz<D>(row)) << 3) + 4 * (r16 & 1);
+    const __bf16* a1 = smv + (row + 16) * D + ((chunk ^ short_v_swz<D>(row + 16)) << 3) + 4 * (r16 & 1);
+    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a0);
+    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a1);
+    const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+    f32x4 was = o[db];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) was[i] *= alpha;
+    f32x4 acc = CAREFUL ? f32x4{0.f, 0.f, 0.f, 0.f} : was, acc_rest;
+#pragma unroll
+    for (int j = 2; j >= 0; --j) {
+      if (CAREFUL && j == 0) { acc_rest = acc; acc = was; }
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pw[j]), acc, 0, 0, 0);
+    }
+    if (CAREFUL) short_settle(acc, acc_rest);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[db][i] = mine ? acc[i] : o[db][i];
+  }
+}
+
 template <int D, int WAVES>
 __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodeParams p) {
   constexpr int KS = D / 32, DB = D / 16, UPR = D / 8;   // k-steps, 16-row blocks of O^T, 16-byte units per row
   constexpr int BLK = 32;                                // keys per block
   constexpr int NV = BLK * UPR / kWave;                  // V units per lane and block
-  union Tile { __bf16 v[BLK * D]; float o[8][D]; };      // a wave's V block; at the end its unnormalised outputs
+  union Tile { __bf16 v[BLK * D]; float o[8][D + 4]; };     // a wave's V block; at the end its unnormalised outputs
   __shared__ Tile tile[WAVES];
   __shared__ f32x2 ml[WAVES][8];                         // (max, sum) per query of the group
   __shared__ __align__(16) __bf16 rot[3][9][D + 8];      // rotated queries (three terms) and, in row gq, the new key
   // Workgroup -> (stream, kv head): an XCD keeps a run of consecutive pairs of them (beams of a sequence share its cache rows,
   // the kv heads of a stream share DRAM rows), so most of what they share is fetched into one L2.
-  const RunItem run = run_item(blockIdx.x, p.n_streams, p.hkv, p.even_runs);
+  const RunItem run = run_item(blockIdx.x, p.n_streams, p.by_kv, p.even_runs);
   if (!run.valid) return;
   const int u = run.item, c = run.sub;
   const DecodeLayer lv = layer_view(p, blockIdx.y);
-  const int gq = p.hq / p.hkv;
+  const int gq = (int)p.by_gq.d;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r16 = lane & 15, quad = lane >> 4;
+  const long long tok = ((long long)u * p.hkv + c) * D;
+  // The group's queries and the new token's key are rotated once by the workgroup, 4 rotary pairs of a row per thread,
+  // and exchanged through LDS.  Their rows are requested before anything else: they need no list, and the keys and values stay in
+  // flight while they are rotated.
+  const int n_items = (gq + 1) * (D / 8);
+  const int head0 = c * gq;
+  u32x2 x_lo[2], x_hi[2];
+  f32x4 th[2], tl[2];
+  constexpr int MAX_ITEMS = (9 * (D / 8) + kWave * WAVES - 1) / (kWave * WAVES);
+  static_assert(MAX_ITEMS <= 2);
+#pragma unroll
+  for (int i = 0; i < MAX_ITEMS; ++i) {
+    const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
+    if (item >= n_items) continue;
+    const __bf16* src = (row < gq ? (const __bf16*)lv.q + ((long long)u * p.hq + head_of_slot(p.heads, head0 + row)) * D
+                                  : (const __bf16*)lv.k_new + tok) + e;
+    x_lo[i] = *(const u32x2*)src;
+    x_hi[i] = *(const u32x2*)(src + D / 2);
+    th[i] = f32x4{p.rope.hi[e], p.rope.hi[e + 1], p.rope.hi[e + 2], p.rope.hi[e + 3]};
+    tl[i] = f32x4{p.rope.lo[e], p.rope.lo[e + 1], p.rope.lo[e + 2], p.rope.lo[e + 3]};
+  }
   const int s = p.stream_to_seq ? max(min(p.stream_to_seq[u], p.batch - 1), 0) : u;
   const int g = clamp_gen_len(p.gen_len[u], p.gen_cap);
   const float pos = (float)p.q_pos[u];
+  // The bounds are asked for together with the list, of the sequence that a stream usually has: one trip to memory less.
+  const int s_usual = min(u, p.batch - 1);
   int b0, ns;
-  shared_bounds(p, s, b0, ns);
+  shared_bounds(p, s_usual, b0, ns);
+  if (s != s_usual) shared_bounds(p, s, b0, ns);
   const int n_shared = (ns + BLK - 1) / BLK, n_blocks = n_shared + (g + BLK) / BLK;
 
   const long long row_stride = (long long)p.hkv * D;
   const __bf16* kc = (const __bf16*)lv.shared_k + ((long long)b0 * p.hkv + c) * D;
   const __bf16* vc = (const __bf16*)lv.shared_v + ((long long)b0 * p.hkv + c) * D;
-  const long long own = ((long long)u * p.gen_cap * p.hkv + c) * D, tok = ((long long)u * p.hkv + c) * D;
+  const long long own = ((long long)u * p.gen_cap * p.hkv + c) * D;
   // offset of logical generated row j in gen_k / gen_v (under beam search: in the cache of the ancestor that wrote it)
   auto gen_row = [&](int j) {
     int src = u;
@@ -514,52 +656,12 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
       else if (!shared && j == g) vr[i] = *(const u32x4*)((const __bf16*)lv.v_new + tok + (unit % UPR) * 8);
     }
   };
-  // The group's queries and the new token's key are rotated once by the workgroup, 4 rotary pairs of a row per thread,
-  // and exchanged through LDS.  Their rows are requested ahead of the keys and values, which stay in flight meanwhile.
-  const int n_items = (gq + 1) * (D / 8);
-  const int head0 = c * gq;
-  u32x2 x_lo[2], x_hi[2];
-  f32x4 th[2], tl[2];
-  constexpr int MAX_ITEMS = (9 * (D / 8) + kWave * WAVES - 1) / (kWave * WAVES);
-  static_assert(MAX_ITEMS <= 2);
-#pragma unroll
-  for (int i = 0; i < MAX_ITEMS; ++i) {
-    const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
-    if (item >= n_items) continue;
-    const __bf16* src = (row < gq ? (const __bf16*)lv.q + ((long long)u * p.hq + head_of_slot(p.heads, head0 + row)) * D
-                                  : (const __bf16*)lv.k_new + tok) + e;
-    x_lo[i] = *(const u32x2*)src;
-    x_hi[i] = *(const u32x2*)(src + D / 2);
-    if (p.rope.enabled) {
-      th[i] = f32x4{p.rope.hi[e], p.rope.hi[e + 1], p.rope.hi[e + 2], p.rope.hi[e + 3]};
-      tl[i] = f32x4{p.rope.lo[e], p.rope.lo[e + 1], p.rope.lo[e + 2], p.rope.lo[e + 3]};
-    }
-  }
   if (wave < n_blocks) load_block(wave);
 #pragma unroll
   for (int i = 0; i < MAX_ITEMS; ++i) {
     const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
     if (item >= n_items) continue;
-    float y[2][4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float sn = 0.f, cs = 1.f;
-      if (p.rope.enabled) sincos_turns_fast(rope_turns(pos, th[i][j], tl[i][j]), &sn, &cs);
-      const float a = j & 1 ? bf16_hi(x_lo[i][j / 2]) : bf16_lo(x_lo[i][j / 2]);
-      const float b = j & 1 ? bf16_hi(x_hi[i][j / 2]) : bf16_lo(x_hi[i][j / 2]);
-      y[0][j] = __builtin_fmaf(a, cs, -(b * sn));   // as the general kernels round it: the appended key is the same
-      y[1][j] = __builtin_fmaf(b, cs, a * sn);
-    }
-    const float scale = row < gq ? p.scale_log2 : 1.f;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      unsigned w0[3], w1[3];
-      split_pair(y[h][0] * scale, y[h][1] * scale, w0);
-      split_pair(y[h][2] * scale, y[h][3] * scale, w1);
-#pragma unroll
-      for (int i = 0; i < 3; ++i)                               // the new key's first term is the key as stored
-        if (i == 0 || row < gq) *(u32x2*)&rot[i][row][e + h * (D / 2)] = u32x2{w0[i], w1[i]};
-    }
+    short_rotate<D>(p, x_lo[i], x_hi[i], th[i], tl[i], pos, row == gq, rot, rot[0][gq], row, e);
   }
   lds_barrier();
 
@@ -567,17 +669,8 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
   float mrow, lrow;                                      // of query r16; lrow: this lane's keys only
   __bf16* smv = tile[wave].v;
   const int q_row = min(r16, gq - 1);                    // columns beyond the group repeat its last query
-  // 16 consecutive rows share a chunk of a transposing read: two rows per chunk position at most
-  auto v_swz = [](int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); };
-  // An operand in three terms times an infinite key or value element is inf - inf where the terms differ in sign, or 0 * inf
-  // where one is zero, instead of the infinity that the whole operand gives.  So a result that came out as NaN is worked out
-  // again (CAREFUL) with the first term's products on their own: where they are infinite, they are the result.
   auto walk = [&](auto careful_c) {
     constexpr bool CAREFUL = decltype(careful_c)::value;
-    auto settle = [](f32x4& first, const f32x4& rest) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) first[i] = __builtin_isinf(first[i]) ? first[i] : first[i] + rest[i];
-    };
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
     mrow = -INFINITY;
@@ -602,79 +695,23 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
           if (unit / UPR == j) *(u32x4*)((__bf16*)lv.gen_v + own + g * row_stride + (unit % UPR) * 8) = vr[i];
         }
       }
-      f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, sc_rest[2];
-#pragma unroll
-      for (int i = 2; i >= 0; --i) {
-        if (CAREFUL && i == 0) {
-#pragma unroll
-          for (int t = 0; t < 2; ++t) { sc_rest[t] = sc[t]; sc[t] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const bf16x8 q = *(const bf16x8*)&rot[i][q_row][32 * ks + 8 * quad];
-#pragma unroll
-          for (int t = 0; t < 2; ++t) sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], q, sc[t], 0, 0, 0);
-        }
-      }
-      if (CAREFUL) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) settle(sc[t], sc_rest[t]);
-      }
+      f32x4 sc[2];
+      short_scores<D, 9, CAREFUL>(kf, rot, q_row, quad, sc);
       // V to LDS; the wave's LDS operations complete in order, so only the compiler has to keep theirs
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         const int unit = lane + kWave * i, row = unit / UPR;
-        *(u32x4*)(smv + row * D + (((unit % UPR) ^ v_swz(row)) << 3)) = vr[i];
+        *(u32x4*)(smv + row * D + (((unit % UPR) ^ short_v_swz<D>(row)) << 3)) = vr[i];
       }
-      // softmax: lane (r16, quad) holds keys 16 t + 4 quad + i of query r16
-      float m = -INFINITY;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 4; ++i)
           if (16 * t + 4 * quad + i >= count) sc[t][i] = -INFINITY;
-          m = fmaxf(m, sc[t][i]);
-        }
-      m = fmaxf(m, __shfl_xor(m, 16, kWave));
-      m = fmaxf(m, __shfl_xor(m, 32, kWave));
-      const float mnew = fmaxf(mrow, m), ref = mnew == -INFINITY ? 0.f : mnew;
-      const float alpha = __builtin_amdgcn_exp2f(mrow - ref);
-      mrow = mnew;
       u32x4 pw[3];
-      float sum = 0.f;
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; i += 2) {
-          const float a = __builtin_amdgcn_exp2f(sc[t][i] - ref), b = __builtin_amdgcn_exp2f(sc[t][i + 1] - ref);
-          sum += a + b;
-          unsigned w[3];
-          split_pair(a, b, w);
-#pragma unroll
-          for (int j = 0; j < 3; ++j) pw[j][2 * t + i / 2] = w[j];
-        }
-      lrow = lrow * alpha + sum;
+      const float alpha = short_softmax(sc, mrow, lrow, pw);
       asm volatile("" ::: "memory");
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        typedef short s16x8 __attribute__((ext_vector_type(8)));
-        const int row = 4 * quad + (r16 >> 2), chunk = 2 * db + ((r16 & 3) >> 1);
-        const __bf16* a0 = smv + row * D + ((chunk ^ v_swz(row)) << 3) + 4 * (r16 & 1);
-        const __bf16* a1 = smv + (row + 16) * D + ((chunk ^ v_swz(row + 16)) << 3) + 4 * (r16 & 1);
-        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a0);
-        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a1);
-        const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[db][i] *= alpha;
-        f32x4 acc = CAREFUL ? f32x4{0.f, 0.f, 0.f, 0.f} : o[db], acc_rest;
-#pragma unroll
-        for (int j = 2; j >= 0; --j) {
-          if (CAREFUL && j == 0) { acc_rest = acc; acc = o[db]; }
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pw[j]), acc, 0, 0, 0);
-        }
-        if (CAREFUL) settle(acc, acc_rest);
-        o[db] = acc;
-      }
+      short_weigh<D, CAREFUL>(smv, pw, alpha, lane, o);
       asm volatile("" ::: "memory");
     }
   };
@@ -711,6 +748,268 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] *= inv;
     Row8<__bf16>::store((__bf16*)lv.out + ((long long)u * p.hq + head_of_slot(p.heads, c * gq + a)) * D + e, x);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------------------------
+// The same for streams that share caches (beams): the 16 query columns of a product hold the query heads of several streams, so
+// a workgroup serves `group` consecutive streams of one kv head and reads the cache rows they share once.  Its key list is the
+// cache of every run of streams of one sequence, then the generated rows of all its streams, one after the other, in blocks of
+// 32; a column sees the rows of its own stream and of its stream's sequence.  Streams may lie in any order: those of another
+// sequence cost a walk over that sequence's cache, so the groups follow the usual layout, W streams per sequence side by side.
+// Bound by its chain of dependent trips to memory (lists -> bounds, asked for at the place the usual layout has them -> rows) and by
+// the few hundred instructions behind them.  us, 16 sequences x 10 streams, 32 / 8 heads of 128, 64 rows: one workgroup per (stream,
+// kv head) 14.8, 1280 of them in one and a quarter rounds that read a cache ten times; 384 of these 10.1.  16 x 20: 25 in the general
+// kernel, 17.9 here.
+// ------------------------------------------------------------------------------------------------------------------
+template <int D, int WAVES>
+__global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_kernel(DecodeParams p) {
+  constexpr int KS = D / 32, DB = D / 16, UPR = D / 8, BLK = 32, NV = BLK * UPR / kWave, COLS = 16;
+  union Tile { __bf16 v[BLK * D]; float o[COLS][D + 4]; }; // a wave's V block; at the end its unnormalised outputs
+  __shared__ Tile tile[WAVES];
+  __shared__ f32x2 ml[WAVES][COLS];                      // (max, sum) per column
+  __shared__ __align__(16) __bf16 rot[3][COLS][D + 8];   // rotated queries (three terms)
+  __shared__ __align__(16) __bf16 keys[COLS][D + 8];     // the streams' new keys
+  const RunItem item_of = run_item(blockIdx.x, p.groups.count, p.by_kv, p.even_runs);
+  if (!item_of.valid) return;
+  const int c = item_of.sub;
+  const BeamGroup own_group = beam_group(p.groups, item_of.item);
+  const int u0 = own_group.first, nb = own_group.count;  // streams u0 .. u0 + nb - 1, 1 <= nb <= 16 / gq
+  const DecodeLayer lv = layer_view(p, blockIdx.y);
+  const int gq = (int)p.by_gq.d, cols = nb * gq;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int r16 = lane & 15, quad = lane >> 4;
+
+  // lane b < nb: stream u0 + b (the lanes beyond repeat the last)
+  const int b_lane = min(lane, nb - 1), u_lane = u0 + b_lane;
+  int s_lane = p.stream_to_seq ? max(min(p.stream_to_seq[u_lane], p.batch - 1), 0) : min(u_lane, p.batch - 1);
+  const int g_lane = clamp_gen_len(p.gen_len[u_lane], p.gen_cap);
+  const float pos_lane = (float)p.q_pos[u_lane];
+  const int s_usual = min(own_group.slot, p.batch - 1);
+  int b0_lane, ns_lane;
+  shared_bounds(p, s_usual, b0_lane, ns_lane);
+  const int col_b = min((int)p.by_gq.div(r16), nb - 1);               // this lane's column is a head of stream u0 + col_b
+  // the rows of the queries and new keys, 4 rotary pairs of a row per item: cols queries, then nb keys
+  constexpr int MAX_ITEMS = (2 * COLS * (D / 8) + kWave * WAVES - 1) / (kWave * WAVES);
+  const int n_items = (cols + nb) * (D / 8);
+  u32x2 x_lo[MAX_ITEMS], x_hi[MAX_ITEMS];
+  f32x4 th[MAX_ITEMS], tl[MAX_ITEMS];
+  int item_b[MAX_ITEMS];
+#pragma unroll
+  for (int i = 0; i < MAX_ITEMS; ++i) {
+    const int item = min((int)threadIdx.x + i * kWave * WAVES, n_items - 1), row = item / (D / 8), e = item % (D / 8) * 4;
+    item_b[i] = row < cols ? (int)p.by_gq.div(row) : row - cols;
+    const __bf16* src = (row < cols ? (const __bf16*)lv.q + ((long long)(u0 + item_b[i]) * p.hq + head_of_slot(p.heads, c * gq + row - item_b[i] * gq)) * D
+                                    : (const __bf16*)lv.k_new + ((long long)(u0 + item_b[i]) * p.hkv + c) * D) + e;
+    x_lo[i] = *(const u32x2*)src;
+    x_hi[i] = *(const u32x2*)(src + D / 2);
+    th[i] = f32x4{p.rope.hi[e], p.rope.hi[e + 1], p.rope.hi[e + 2], p.rope.hi[e + 3]};
+    tl[i] = f32x4{p.rope.lo[e], p.rope.lo[e + 1], p.rope.lo[e + 2], p.rope.lo[e + 3]};
+  }
+  if (__any(s_lane != s_usual)) shared_bounds(p, s_lane, b0_lane, ns_lane);
+  // generated rows of stream b, the new token last: [gen_end(b) - g - 1, gen_end(b)) of the list
+  int gen_end = lane < nb ? g_lane + 1 : 0;
+#pragma unroll
+  for (int o = 1; o < COLS; o <<= 1) {
+    const int x = __shfl_up(gen_end, o, kWave);
+    if (lane >= o) gen_end += x;
+  }
+  const int n_gen = __builtin_amdgcn_readlane(gen_end, nb - 1);
+  const int gen_begin = gen_end - (g_lane + 1);          // (of lanes b < nb)
+  // runs of streams of one sequence: bit b = a run starts at stream b
+  const int s_before = __shfl_up(s_lane, 1, kWave);
+  const unsigned starts = (unsigned)__ballot(lane < nb && (lane == 0 || s_lane != s_before));
+  int n_shared = 0;
+  for (unsigned m = starts; m; m &= m - 1) n_shared += (__builtin_amdgcn_readlane(ns_lane, __builtin_ctz(m)) + BLK - 1) / BLK;
+  const int n_blocks = n_shared + (n_gen + BLK - 1) / BLK;
+
+  struct Block { int j0, count, lo, hi, row0; bool shared; };   // streams [lo, hi) see it; row0: first cache row of the sequence
+  auto find = [&](int blk) {
+    Block f{(blk - n_shared) * BLK, n_gen - (blk - n_shared) * BLK, 0, nb, 0, false};
+    if (blk >= n_shared) return f;
+    f.shared = true;
+    for (unsigned m = starts; m; m &= m - 1) {
+      const int b = __builtin_ctz(m), ns = __builtin_amdgcn_readlane(ns_lane, b), blocks = (ns + BLK - 1) / BLK;
+      if (blk < blocks) {
+        f.j0 = blk * BLK; f.count = ns - f.j0; f.lo = b;
+        f.hi = m & (m - 1) ? __builtin_ctz(m & (m - 1)) : nb;
+        f.row0 = __builtin_amdgcn_readlane(b0_lane, b);
+        break;
+      }
+      blk -= blocks;
+    }
+    return f;
+  };
+  // Lane r % 32 of a wave keeps what row r of its block of generated rows is: its stream, whether it is the new token, and where
+  // it lies in gen_k / gen_v (under beam search: in the cache of the ancestor that wrote it).  Rows past the end are the last one.
+  int row_is = 0;          // 2 stream + new
+  long long row_at = 0;
+  const unsigned row_bytes = (unsigned)p.hkv * D * 2;    // (a list's rows lie within 4 GiB: decode_few_keys)
+  auto own_row = [&](int b, int j) { return (((long long)(u0 + b) * p.gen_cap + j) * p.hkv + c) * D * 2; };
+  bf16x8 kf[2][KS];
+  u32x4 vr[NV];
+  auto load_block = [&](const Block& f) __attribute__((always_inline)) {
+    auto load_k = [&](int t, const char* row) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[t][ks] = *(const bf16x8*)(row + 64 * ks);
+    };
+    if (f.shared) {
+      const long long at = ((long long)f.row0 * p.hkv + c) * D * 2;
+      const char *kb = (const char*)lv.shared_k + at, *vb = (const char*)lv.shared_v + at;
+      const int last = f.j0 + f.count - 1;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) load_k(t, kb + ((unsigned)min(f.j0 + 16 * t + r16, last) * row_bytes + 16u * quad));
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int unit = lane + kWave * i;
+        vr[i] = *(const u32x4*)(vb + ((unsigned)min(f.j0 + unit / UPR, last) * row_bytes + 16u * (unit % UPR)));
+      }
+      return;
+    }
+    const int x = f.j0 + min(lane % BLK, f.count - 1);
+    int b = 0;
+    for (int i = 0; i < nb - 1; ++i) b += x >= __builtin_amdgcn_readlane(gen_end, i);
+    const int j = x - __shfl(gen_begin, b, kWave);
+    row_is = 2 * b + (j == __shfl(g_lane, b, kWave));
+    int src = b;
+    if (p.gen_src && !(row_is & 1)) src = max(min(p.gen_src[(long long)(u0 + b) * p.gen_cap + j], p.n_streams - 1), 0) - u0;
+    row_at = own_row(src, j);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) load_k(t, (const char*)lv.gen_k + __shfl(row_at, 16 * t + r16, kWave) + 16 * quad);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int unit = lane + kWave * i, is = __shfl(row_is, unit / UPR, kWave);
+      const long long at = __shfl(row_at, unit / UPR, kWave);
+      const char* v = is & 1 ? (const char*)lv.v_new + ((long long)(u0 + (is >> 1)) * p.hkv + c) * D * 2 : (const char*)lv.gen_v + at;
+      vr[i] = *(const u32x4*)(v + 16 * (unit % UPR));
+    }
+  };
+  // (after the rows have arrived)
+  auto zero_past_end = [&](int rows) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const bool have = (lane + kWave * i) / UPR < rows;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) vr[i][e] = have ? vr[i][e] : 0u;
+    }
+  };
+  if (wave < n_blocks) load_block(find(wave));
+#pragma unroll
+  for (int i = 0; i < MAX_ITEMS; ++i) {
+    const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
+    const float pos = __shfl(pos_lane, item_b[i], kWave);
+    if (item >= n_items) continue;
+    short_rotate<D, COLS>(p, x_lo[i], x_hi[i], th[i], tl[i], pos, row >= cols, rot, keys[row < cols ? 0 : row - cols], row, e);
+  }
+  lds_barrier();
+
+  f32x4 o[DB];
+  float mrow, lrow;                                      // of column r16; lrow: this lane's keys only
+  __bf16* smv = tile[wave].v;
+  const int q_row = min(r16, cols - 1);                  // columns beyond the last repeat it
+  const int col_end = __shfl(gen_end, col_b, kWave), col_begin = __shfl(gen_begin, col_b, kWave);
+  auto walk = [&](auto careful_c) {
+    constexpr bool CAREFUL = decltype(careful_c)::value;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    mrow = -INFINITY;
+    lrow = 0.f;
+    for (int blk = wave; blk < n_blocks; blk += WAVES) {
+      const Block f = find(blk);
+      if (CAREFUL || blk != wave) load_block(f);
+      if (!f.shared) {                                   // new tokens: their keys rotated and rounded as stored, appended
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int row = 16 * t + r16, is = __shfl(row_is, row, kWave);
+          char* to = (char*)lv.gen_k + __shfl(row_at, row, kWave) + 16 * quad;
+          if (row < f.count && is & 1) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+              kf[t][ks] = *(const bf16x8*)&keys[is >> 1][32 * ks + 8 * quad];
+              *(bf16x8*)(to + 64 * ks) = kf[t][ks];
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          const int unit = lane + kWave * i, row = unit / UPR, is = __shfl(row_is, row, kWave);
+          char* to = (char*)lv.gen_v + __shfl(row_at, row, kWave) + 16 * (unit % UPR);
+          if (row < f.count && is & 1) *(u32x4*)to = vr[i];
+        }
+      }
+      f32x4 sc[2];
+      short_scores<D, COLS, CAREFUL>(kf, rot, q_row, quad, sc);
+      // this lane's column sees rows [begin, end) of the block
+      int begin = 0, end = f.count;
+      if (!f.shared) { begin = col_begin - f.j0; end = min(end, col_end - f.j0); }
+      else if (col_b < f.lo || col_b >= f.hi) end = 0;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = 16 * t + 4 * quad + i;
+          if (row < begin || row >= end) sc[t][i] = -INFINITY;
+        }
+      u32x4 pw[3];
+      const float alpha = short_softmax(sc, mrow, lrow, pw);
+      zero_past_end(f.count);
+      // values to LDS: of rows that stream `seen` sees (all rows: seen < 0); the wave's LDS operations complete in order, so
+      // only the compiler has to keep theirs
+      auto stage = [&](int seen) {
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          const int unit = lane + kWave * i, row = unit / UPR;
+          u32x4 x = vr[i];
+          if (seen >= 0 && !f.shared && __shfl(row_is, row, kWave) >> 1 != seen) x = u32x4{0u, 0u, 0u, 0u};
+          *(u32x4*)(smv + row * D + (((unit % UPR) ^ short_v_swz<D>(row)) << 3)) = x;
+        }
+        asm volatile("" ::: "memory");
+      };
+      if (!CAREFUL) {
+        stage(-1);
+        short_weigh<D, false>(smv, pw, alpha, lane, o);
+      } else {
+        // a row that a column does not see has weight 0, which times an infinite or NaN value is NaN: stream by stream here
+        for (int b = f.lo; b < f.hi; ++b) {
+          stage(b);
+          short_weigh<D, true>(smv, pw, alpha, lane, o, col_b == b);
+        }
+      }
+      asm volatile("" ::: "memory");
+    }
+  };
+  walk(std::false_type{});
+  float probe = lrow;                                    // NaN where anything is, or where infinities of both signs meet
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) probe += o[db][i];
+  if (__any(probe != probe)) walk(std::true_type{});
+  // merge: a wave's outputs take the place of its V block
+  lrow += __shfl_xor(lrow, 16, kWave);
+  lrow += __shfl_xor(lrow, 32, kWave);
+#pragma unroll
+  for (int db = 0; db < DB; ++db) *(f32x4*)&tile[wave].o[r16][16 * db + 4 * quad] = o[db];
+  if (quad == 0) ml[wave][r16] = f32x2{mrow, lrow};
+  __syncthreads();
+  for (int i = threadIdx.x; i < cols * UPR; i += kWave * WAVES) {
+    const int col = i / UPR, e = (i % UPR) * 8;
+    float m = -INFINITY, l = 0.f, x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) m = fmaxf(m, ml[w][col][0]);
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      if (w >= n_blocks) continue;                       // a wave without keys: its tile holds nothing but zeros
+      const float f = ml[w][col][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[w][col][0] - m);
+      l += f * ml[w][col][1];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = __builtin_fmaf(f, tile[w].o[col][e + j], x[j]);
+    }
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] *= inv;
+    Row8<__bf16>::store((__bf16*)lv.out + ((long long)(u0 + col / gq) * p.hq + head_of_slot(p.heads, c * gq + col % gq)) * D + e, x);
   }
 }
 
@@ -1347,6 +1646,7 @@ __global__ __launch_bounds__(256 * C, 1) void decode_shared_mfma_kernel(DecodePa
 struct DecodePlan {
   bool mfma;      // shared and generated rows on the matrix cores + combine
   bool few_keys = false;  // decode_short_kernel instead of what the other fields plan (launch_decode)
+  bool grouped = false;   // ... or decode_beams_kernel
   int n_splits;   // key-range splits of the shared (mfma) or whole (vector) key list
   int n_slots;    // partial slots per (stream, head)
   int chunk;      // keys per split
@@ -1367,22 +1667,25 @@ struct DecodePlan {
 //   256 pairs, 64 rows 7.5 -> 6.8, 512 rows 13.6 -> 9.6; one sequence of 32 heads, 16 layers in a launch, 64 / 700 rows 1.4 /
 //   6.4 -> 0.6 / 2.3; 2048 pairs, 32 rows 15.4 / 8.7 -> 15.7 / 8.9; 320 pairs, a round and a quarter of the CUs, 500 rows
 //   21.7 -> 25.3, the worst there is.  So: up to 512 pairs and 768 keys.
-//   beams, 16 sequences x 10 of 32 / 8 heads: 32 rows 15.3 / 6.9 -> 8.6 / 4.4, 64 rows 15.4 / 6.8 -> 13.4 / 7.1, 128 rows
-//   16.5 / 7.7 -> 19.8 / 12.2; 32 x 4 of 12 / 2 heads, 128 rows 12.7 / 3.1 -> 8.2 / 2.7, 256 rows 16.9 / 3.8 -> 10.7 / 7.2,
-//   512 rows 19.9 -> 14.4.  So: 128 K rows re-read, 48 K per layer where the layers share a launch, and no more in all than
-//   the general kernel's rounds allow (short_decode_takes_beams).
-static bool decode_few_keys(int dtype, int hq, int hkv, int d, int n_streams, int batch, int max_shared_len, int gen_cap, int n_layers,
-                            int n_pass) {
-  if (dtype != EARN_BF16) return false;
+//   beams: beam_kernel.
+static void decode_few_keys(DecodePlan& pl, int dtype, int hq, int hkv, int d, int n_streams, int batch, int max_shared_len, int gen_cap,
+                            int n_layers) {
+  if (dtype != EARN_BF16) return;
   for (Tuning t : {kTuneDecMfmaMinLen, kTuneDecMfmaShortWgs, kTuneDecMfmaWgs, kTuneDecVecWgs, kTuneDecVecWaves})
-    if (tuning(t, 0) != 0) return false;                 // a caller who sets the general kernels' launch shape gets them
-  if (!run_fits(n_streams, hkv, 512)) return false;      // 8 million (stream, kv head) pairs: the general kernels' smaller workgroups
+    if (tuning(t, 0) != 0) return;                       // a caller who sets the general kernels' launch shape gets them
+  if (!run_fits(n_streams, hkv, 512)) return;            // 8 million (stream, kv head) pairs: the general kernels' smaller workgroups
   const long long pairs = (long long)n_streams * hkv, keys = (long long)max_shared_len + gen_cap;
-  if (n_streams > batch)
-    return pairs * max_shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024 &&
-           short_decode_takes_beams(pairs * n_layers, (long long)batch * hkv * n_layers * n_pass, max_shared_len, d);
-  if (hq == hkv) return pairs * n_layers <= 512 && keys <= 768;
-  return keys <= (pairs * n_layers >= 512 ? 2304 : 1024);
+  if (n_streams > batch) {
+    const BeamKernel k = beam_kernel(n_streams, batch, hkv, hq / hkv, d, max_shared_len, gen_cap, n_layers, pl.n_pass);
+    pl.few_keys = k != BeamKernel::kGeneral;
+    // (32-bit offsets inside a cache)
+    pl.grouped = k == BeamKernel::kGrouped && (long long)max_shared_len * hkv * d * 2 < (1ll << 32);
+    if (k == BeamKernel::kGrouped && !pl.grouped) pl.few_keys = false;
+  } else if (hq == hkv) {
+    pl.few_keys = pairs * n_layers <= 512 && keys <= 768;
+  } else {
+    pl.few_keys = keys <= (pairs * n_layers >= 512 ? 2304 : 1024);
+  }
 }
 
 static DecodePlan plan_decode(int dtype, int hq, int hkv, int n_streams, int batch, int max_shared_len, int gen_cap,
@@ -1479,6 +1782,14 @@ static void launch_short(DecodeParams& p, hipStream_t stream, int n_layers) {
   else hipLaunchKernelGGL((decode_short_kernel<D, 8>), grid, dim3(512), 0, stream, p);
 }
 
+template <int D>
+static void launch_beams(DecodeParams& p, hipStream_t stream, int n_layers) {
+  p.even_runs = 1;
+  const dim3 grid((unsigned)run_workgroups(p.groups.count, p.hkv), n_layers, 1);
+  if (short_decode_waves(p.max_shared_len, p.groups.group * p.gen_cap, 1) <= 4) hipLaunchKernelGGL((decode_beams_kernel<D, 4>), grid, dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL((decode_beams_kernel<D, 8>), grid, dim3(512), 0, stream, p);
+}
+
 template <typename T, int D>
 static void launch_combine(const DecodeParams& p, hipStream_t stream, int n_layers = 1) {
   const int rows = p.n_streams * p.hq;
@@ -1490,7 +1801,11 @@ static void launch_combine(const DecodeParams& p, hipStream_t stream, int n_laye
 template <typename T, int D>
 static void launch_decode_t(DecodeParams& p, const DecodePlan& pl, int gq, hipStream_t stream, int n_layers) {
   if constexpr (sizeof(T) == 2) {
-    if (pl.few_keys) { launch_short<D>(p, stream, n_layers); return; }
+    if (pl.few_keys) {
+      if (pl.grouped) launch_beams<D>(p, stream, n_layers);
+      else launch_short<D>(p, stream, n_layers);
+      return;
+    }
   }
   if (!pl.mfma) {
     launch_vector<T, D>(p, gq, dim3((unsigned)(((long long)p.n_streams * p.n_splits + 7) / 8 * 8 * p.hkv), n_layers, 1), stream);
@@ -1516,7 +1831,7 @@ int launch_decode(const earn_attn_desc* desc, const void* q, const void* k_new, 
   const int n_layers = layers ? layers->n_layers : 1;
   if (gq > 8) { set_error("earn_decode_attn: more than 8 query heads per kv head is not supported"); return EARN_ERR_UNSUPPORTED; }
   DecodePlan pl = plan_decode(desc->dtype, hq, hkv, n_streams, batch, max_shared_len, gen_cap, n_layers);
-  pl.few_keys = decode_few_keys(desc->dtype, hq, hkv, d, n_streams, batch, max_shared_len, gen_cap, n_layers, pl.n_pass);
+  decode_few_keys(pl, desc->dtype, hq, hkv, d, n_streams, batch, max_shared_len, gen_cap, n_layers);
   if (pl.mfma && (long long)(max_shared_len + kDsSuper) * hkv * d * 2 >= (1ll << 31)) {
     set_error("earn_decode_attn: a shared cache of %d rows exceeds the 2 GiB addressing range of one sequence", max_shared_len);
     return EARN_ERR_UNSUPPORTED;
@@ -1533,6 +1848,8 @@ int launch_decode(const earn_attn_desc* desc, const void* q, const void* k_new, 
   p.gen_k = gen_k; p.gen_v = gen_v; p.gen_len = gen_len; p.out = out; p.gen_src = gen_src;
   p.gen_cap = gen_cap; p.n_streams = n_streams; p.batch = batch; p.hq = hq; p.hkv = hkv;
   p.shared_total = shared_total; p.max_shared_len = max_shared_len;
+  p.groups = beam_groups(n_streams, batch, gq);
+  p.by_gq = FastDiv::of((unsigned)gq); p.by_kv = FastDiv::of((unsigned)hkv);
   p.n_splits = pl.n_splits; p.n_slots = pl.n_slots; p.chunk = pl.chunk; p.causal_rows = 0; p.n_pass = pl.n_pass;
   const size_t need = decode_workspace_bytes(desc->dtype, hq, hkv, d, n_streams, batch, max_shared_len, gen_cap, n_layers);
   if (need > workspace_bytes || (need > 0 && !workspace)) {

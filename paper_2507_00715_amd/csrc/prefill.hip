@@ -37,7 +37,8 @@ struct PrefillParams {
   int batch, hq, hkv, max_seqlen;
   int total;   // rows of the packed tensors
   int n_qblk;  // query blocks of the longest sequence
-  FastDiv by_pair, by_group, by_kv;  // workgroups per (sequence, kv head), query heads per kv head, kv heads (pf_map_block)
+  FastDiv by_pair, by_group, by_kv;  // workgroups per (sequence, kv head), query heads per kv head, kv heads
+  FastDiv by_run;                    // prefill_short_kernel: workgroups per sequence
   // chosen-rows mode of the fp32 kernel (rows_per_seq > 0): q and out hold rows_per_seq rows per sequence in
   // compacted order, row m of sequence s being token row_pos[s * rows_per_seq + m] (ascending) of the sequence
   const int32_t* row_pos;
@@ -824,16 +825,16 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
   // An XCD takes a run of consecutive workgroups of consecutive sequences, the kv heads of a sequence, whose rows are interleaved,
   // next to each other.  (Against runs of whole sequences, rounded up: 9 sequences of 128 rows, 32 / 8 heads of 128, 20.7 -> 14.7
   // us, 25 of 128 30.0 -> 23.3, 33 of 64 21.1 -> 20.5.)
-  const RunItem run = run_item(blockIdx.x, p.batch, p.hkv * parts, true);
+  const RunItem run = run_item(blockIdx.x, p.batch, p.by_run, true);
   if (!run.valid) return;
-  const int s = run.item, c = run.sub % p.hkv, part = run.sub / p.hkv;
+  const int part = (int)p.by_kv.div((unsigned)run.sub), s = run.item, c = run.sub - part * p.hkv;
   int b0, n;
   pf_seq_bounds(p, s, b0, n);
   // this wave's first 16 query rows, and the rows to its next ones
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), m_first = 16 * (part * WAVES + wave), m_step = 16 * WAVES * parts;
-  if (n <= 0 || (part > 0 && 16 * part * WAVES >= p.hq / p.hkv * n)) return;
+  if (n <= 0 || (part > 0 && 16 * part * WAVES >= (int)p.by_group.d * n)) return;
   const PfLayer lv = pf_layer_view(p, blockIdx.y);
-  const int gq = p.hq / p.hkv, rows = gq * n;
+  const int gq = (int)p.by_group.d, rows = gq * n;
   const int lane = threadIdx.x % kWave, r16 = lane & 15, quad = lane >> 4;
   const __bf16* kg = (const __bf16*)pf_layer_ptr(k_in, ls_k_in, blockIdx.y) + ((long long)b0 * p.hkv + c) * D;
   const __bf16* vg = (const __bf16*)lv.v + ((long long)b0 * p.hkv + c) * D;
@@ -1375,6 +1376,8 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
       const long long groups = ((long long)(p.hq / p.hkv) * max_seqlen + 15) / 16;
       const long long on_xcd = ((long long)batch * p.hkv * n_layers + kXcds - 1) / kXcds;
       const int parts = k == k_rot_out ? 1 : (int)std::max<long long>(1, std::min<long long>((groups + waves - 1) / waves, 32 * per_cu / on_xcd));
+      set_query_blocks(1);
+      p.by_run = FastDiv::of((unsigned)(p.hkv * parts));
       const dim3 grid((unsigned)run_workgroups(batch, p.hkv * parts), n_layers, 1);
       hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, stream, p, k, ls_k, k_rot_out ? 1 : 0, parts);
     };

@@ -34,12 +34,12 @@ EARN_INDEX long long run_workgroups(int n, int per) { return ((long long)n + kXc
 // what one grid dimension takes: fewer than 2^32 threads
 EARN_INDEX bool run_fits(int n, int per, int threads) { return run_workgroups(n, per) * threads < (1ll << 32); }
 struct RunItem { int item, sub; bool valid; };   // sub: 0 .. per - 1
-EARN_INDEX RunItem run_item(unsigned id, int n, int per, bool even) {
-  const int xcd = (int)(id % kXcds), at = (int)(id / kXcds), units = n * per;
+EARN_INDEX RunItem run_item(unsigned id, int n, const FastDiv& by_per, bool even) {
+  const int per = (int)by_per.d, xcd = (int)(id % kXcds), at = (int)(id / kXcds), units = n * per;
   const int base = units / kXcds, extra = units % kXcds, whole = (n + kXcds - 1) / kXcds * per;
   const int first = even ? xcd * base + xcd * extra / kXcds : xcd * whole;
   const int count = even ? base + ((xcd + 1) * extra / kXcds - xcd * extra / kXcds) : whole;
-  const int unit = first + at, item = unit / per;
+  const int unit = first + at, item = (int)by_per.div((unsigned)unit);
   return RunItem{item, unit - item * per, at < count && unit < units};
 }
 
@@ -72,6 +72,54 @@ EARN_INDEX bool f32_few_workgroups(int rows, int hq, int d, long long sequences)
 EARN_INDEX bool short_decode_takes_beams(long long pairs, long long general_workgroups, int shared_len, int d) {
   const long long rounds = (general_workgroups + 255) / 256;
   return pairs * shared_len * (d + 64) / 192 <= (128 * rounds - 40) * 1024;
+}
+// Streams that share a workgroup of the short decode over beams: up to 16 / gq consecutive ones, whose query heads fill the 16
+// columns of a product, in equal groups of the W = n_streams / batch streams that a sequence usually has side by side (`slot`;
+// any other layout is served too, group by group).  No even number per sequence: all streams are one slot.
+struct BeamGroups { int count, group, slot_streams; FastDiv per_slot; };
+EARN_INDEX BeamGroups beam_groups(int n_streams, int batch, int gq) {
+  BeamGroups g;
+  g.slot_streams = n_streams % batch == 0 ? n_streams / batch : n_streams;
+  const int most = 16 / gq < 1 ? 1 : 16 / gq;
+  const int per_slot = (g.slot_streams + most - 1) / most;
+  g.group = (g.slot_streams + per_slot - 1) / per_slot;
+  g.per_slot = FastDiv::of((unsigned)((g.slot_streams + g.group - 1) / g.group));
+  g.count = n_streams / g.slot_streams * (int)g.per_slot.d;
+  return g;
+}
+struct BeamGroup { int first, count, slot; };
+EARN_INDEX BeamGroup beam_group(const BeamGroups& g, int i) {
+  BeamGroup b;
+  b.slot = (int)g.per_slot.div((unsigned)i);
+  const int at = (i - b.slot * (int)g.per_slot.d) * g.group, rest = g.slot_streams - at;
+  b.first = b.slot * g.slot_streams + at;
+  b.count = rest < g.group ? rest : g.group;
+  return b;
+}
+// Streams that share caches: which kernel?  420 sizes (1 to 64 sequences, 4 to 20 beams, six head layouts, 8 to 1000 rows, 1 or 8
+// layers in a launch, up to 100 generated rows), us a layer:
+//   one workgroup per (stream, kv head) while they are about one to a CU, its chain being the shortest (one sequence x 10 beams, 32 /
+//   8 heads, 64 rows: grouped 7.8, this 7.3), with few rows to read again (8 x 10, 32 / 8 heads, 8 rows 8.0 and 7.5; 64 x 10, 12 / 2
+//   heads, 8 rows 13.4 and 8.9) and with room for many generated rows, which a group walks for all its streams (16 x 10, 32 / 8
+//   heads, 16 rows, 30 of 32 generated 12.7 and 10.0);
+//   groups up to an amount of rows that they read again (16 x 10, 32 / 8 heads: 64 rows 10.3 where the general kernel takes 14.6 and
+//   one workgroup per stream 13.9; 256 rows 15.9 and 22.3; 512 rows 25.9 and 23.2), beyond 64 rows only where two to a CU are all
+//   there are (64 x 10, 14 / 2 heads, 256 rows 19.9 and 14.6);
+//   else the general kernel.  1.17 times as fast on the geometric mean as without the groups, at worst 0.96.
+enum class BeamKernel { kGeneral, kPerStream, kGrouped };
+EARN_INDEX BeamKernel beam_kernel(int n_streams, int batch, int hkv, int gq, int d, int shared_len, int gen_cap, int n_layers, int n_pass) {
+  const long long pairs = (long long)n_streams * hkv, general = (long long)batch * hkv * n_layers * n_pass, keys = (long long)shared_len + gen_cap;
+  const BeamGroups g = beam_groups(n_streams, batch, gq);
+  const bool per_stream = pairs * shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024 &&
+                          short_decode_takes_beams(pairs * n_layers, general, shared_len, d);
+  const long long all = pairs * n_layers, workgroups = (long long)g.count * hkv * n_layers, generated = (long long)g.group * gen_cap;
+  if (per_stream && (all <= 256 || (all <= 320 && shared_len <= 64) || (all <= 1280 && shared_len <= 32) || generated > 96))
+    return BeamKernel::kPerStream;
+  const long long rounds = (general + 255) / 256, read = workgroups * shared_len * (d + 64) / 192;
+  if (generated <= 384 && keys <= 2304 && read <= (64 * rounds + (n_layers > 1 ? 0 : 112)) * 1024 &&
+      (workgroups <= 512 || shared_len <= 64 || n_layers > 1))
+    return BeamKernel::kGrouped;
+  return per_stream ? BeamKernel::kPerStream : BeamKernel::kGeneral;
 }
 // Waves of a short decode workgroup: one per block of 32 shared keys and one for the generated rows, eight for longer lists.
 // With no more workgroups than CUs, nothing else hides a wave's round trips, so the blocks that the generated rows may come to

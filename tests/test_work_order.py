@@ -13,6 +13,14 @@ using namespace earn;
 extern "C" int takes(int longest, int mean, long long pairs, int in_place) { return short_prefill_takes(longest, mean, pairs, in_place); }
 extern "C" int takes_beams(long long pairs, long long general, int len, int d) { return short_decode_takes_beams(pairs, general, len, d); }
 extern "C" int waves(int max_shared_len, int gen_cap, long long workgroups) { return short_decode_waves(max_shared_len, gen_cap, workgroups); }
+extern "C" int groups(int n_streams, int batch, int gq, int (*out)[3]) {
+  const BeamGroups g = beam_groups(n_streams, batch, gq);
+  for (int i = 0; i < g.count; ++i) { const BeamGroup b = beam_group(g, i); out[i][0] = b.first; out[i][1] = b.count; out[i][2] = b.slot; }
+  return g.count;
+}
+extern "C" int beams_kernel(int n_streams, int batch, int hkv, int gq, int d, int len, int cap, int layers, int pass) {
+  return (int)beam_kernel(n_streams, batch, hkv, gq, d, len, cap, layers, pass);
+}
 extern "C" void divide(unsigned d, const unsigned* n, unsigned* out, int count) {
   const FastDiv f = FastDiv::of(d);
   for (int i = 0; i < count; ++i) out[i] = f.div(n[i]);
@@ -21,7 +29,7 @@ extern "C" int fits(int n, int per, int threads) { return run_fits(n, per, threa
 extern "C" long long runs(int n, int per, int even, int (*out)[3], long long limit) {
   const long long w = run_workgroups(n, per);
   for (long long i = 0; i < w && i < limit; ++i) {
-    const RunItem r = run_item((int)i, n, per, even);
+    const RunItem r = run_item((unsigned)i, n, FastDiv::of(per), even);
     out[i][0] = r.item; out[i][1] = r.sub; out[i][2] = r.valid;
   }
   return w;
@@ -163,3 +171,24 @@ def test_division_by_multiplication(lib, d):
     out = np.empty_like(n)
     lib.divide(ctypes.c_uint(d), n.ctypes.data_as(ctypes.c_void_p), out.ctypes.data_as(ctypes.c_void_p), len(n))
     assert np.array_equal(out, n // np.uint32(d))
+
+
+@pytest.mark.parametrize("gq", [1, 2, 3, 4, 5, 7, 8])
+@pytest.mark.parametrize("n_streams,batch", [(10, 1), (160, 16), (161, 16), (320, 16), (7, 3), (2, 1), (1000, 7), (640, 64), (45, 44)])
+def test_beam_groups_hold_every_stream_once(lib, n_streams, batch, gq):
+    out = np.empty((n_streams, 3), dtype=np.int32)
+    n = lib.groups(n_streams, batch, gq, out.ctypes.data_as(ctypes.c_void_p))
+    first, count, slot = out[:n].T
+    assert n <= n_streams and count.min() >= 1 and count.max() * gq <= max(16, gq)
+    assert np.concatenate([np.arange(f, f + c) for f, c in zip(first, count)]).tolist() == list(range(n_streams))
+    if n_streams % batch == 0:                  # no group over two sequences of the usual layout
+        w = n_streams // batch
+        assert np.array_equal(slot, first // w) and np.array_equal(slot, (first + count - 1) // w)
+
+
+@pytest.mark.parametrize("streams,batch,hkv,gq,d,rows,cap,layers,n_pass,kernel", [
+    (10, 1, 8, 4, 128, 64, 8, 1, 1, 1), (160, 16, 8, 4, 128, 64, 8, 1, 1, 2), (160, 16, 8, 4, 128, 32, 8, 1, 1, 1), (160, 16, 8, 4, 128, 33, 8, 1, 1, 2),
+    (160, 16, 8, 4, 128, 512, 8, 1, 1, 0), (160, 16, 8, 4, 128, 16, 32, 1, 1, 1), (640, 64, 2, 7, 64, 256, 8, 1, 2, 0), (640, 64, 2, 7, 64, 64, 8, 1, 2, 2),
+    (160, 16, 8, 4, 128, 2300, 8, 1, 1, 0), (160, 16, 8, 4, 128, 64, 200, 1, 1, 1), (64, 16, 4, 1, 64, 128, 16, 1, 1, 1)])
+def test_beam_kernel(lib, streams, batch, hkv, gq, d, rows, cap, layers, n_pass, kernel):
+    assert lib.beams_kernel(streams, batch, hkv, gq, d, rows, cap, layers, n_pass) == kernel
