@@ -287,21 +287,26 @@ __global__ __launch_bounds__(64 * (8 / RB) * WC, 1) void linear_kernel(LinearPar
 }
 
 // Products of few rows (decode steps, small batches).  A tile of linear_kernel is 256 rows whatever the product has, so its
-// time is the same at 1 row as at 256 (0.86 us per K-tile of 64), on a third of the CUs: 1 row, k 4096, 11008 outputs 59 us,
-// here 21, with 18 for the weights' bytes at the rate of a large copy.  Here a tile is 32 NRB rows, just enough for the product's,
-// x 64 columns: twice as many tiles share the weights (a product that is split either way has as many workgroups, in half the
-// splits), and none multiplies padding beyond a 32-row block.  The four waves take one
-// 16-index step of every K-tile each (every byte of a tile is read from LDS once), and add their sums through LDS at the
-// end.  The ring of K-tiles takes most of the LDS: the weights' latency times rate is what has to be in flight.
-template <int NRB>
-constexpr int few_stages() { return NRB <= 2 ? 8 : NRB == 3 ? 7 : NRB == 4 ? 6 : 5; }
-template <int NRB>
-__global__ __launch_bounds__(256, 1) void linear_few_rows_kernel(LinearParams p) {
-  constexpr int ROWS = 32 * NRB, COLS = 64, KT = 64, S = few_stages<NRB>(), XI = NRB, WI = 2, LPT = XI + WI;
-  struct Stage { __bf16 x[ROWS * KT], w[COLS * KT]; };
-  union Shared { Stage ring[S]; f32x4 sum[4][4][4][kWave]; };   // at the end: [wave][tile of the round][quarter][lane]
+// time is the same at 1 row as at 256 (0.86 us per K-tile of 64), on a third of the CUs: 1 row, k 4096, 11008 outputs 55 us,
+// here 20, with 18 for the weights' bytes at the rate of a large copy.  Here a tile is 32 NRB rows, just enough for the product's,
+// x 64 HALVES columns, and none multiplies padding beyond a 32-row block.  Of a half's four waves each takes one 16-index step of
+// every K-tile (every byte of a tile is read from LDS once per half), and they add their sums through LDS at the end.  Two halves
+// share the activations and put two waves on a SIMD: 160 rows, k 4096, 11008 outputs 53 -> 38 us, 8192 x 10240 99 -> 48.  (The
+// loads of the tiles alone, without products, take 33 us in the 64-column and 26 in the 128-column form.)  The ring of K-tiles
+// takes most of the LDS: the weights' latency times rate is what has to be in flight.
+template <int NRB, int HALVES>
+constexpr int few_stages() { return HALVES == 2 ? (NRB <= 2 ? 5 : NRB <= 4 ? 4 : 3) : NRB <= 2 ? 8 : NRB == 3 ? 7 : NRB == 4 ? 6 : 5; }
+template <int NRB, int HALVES>
+__global__ __launch_bounds__(256 * HALVES, 1) void linear_few_rows_kernel(LinearParams p) {
+  // XI, WI: load instructions (8 rows each) per wave, K-tile and operand; a count of row blocks that does not divide among the waves
+  // is rounded up (rows past the end: zeros, without a trip to memory)
+  constexpr int WAVES = 4 * HALVES, COLS = 64 * HALVES, KT = 64, S = few_stages<NRB, HALVES>();
+  constexpr int XI = (4 * NRB + WAVES - 1) / WAVES, WI = COLS / 8 / WAVES, LPT = XI + WI;
+  struct Stage { __bf16 x[8 * XI * WAVES * KT], w[COLS * KT]; };
+  union Shared { Stage ring[S]; f32x4 sum[WAVES][4][4][kWave]; };   // at the end: [wave][tile of the round][quarter][lane]
   __shared__ Shared sm;
-  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x % kWave, wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wave = wave_id & 3, half = wave_id >> 2;   // its 16-index step of a K-tile, its 64 columns
   const int r32 = lane & 31, hf = lane >> 5;
   const int n0 = blockIdx.x * COLS, kt0 = blockIdx.y * p.split_tiles, n_kt = min(p.k / KT - kt0, p.split_tiles);
   const int pitch = p.k * 2;   // bytes, of activation and weight rows alike
@@ -310,22 +315,22 @@ __global__ __launch_bounds__(256, 1) void linear_few_rows_kernel(LinearParams p)
   int x_voff[XI], w_voff[WI];
 #pragma unroll
   for (int i = 0; i < XI; ++i) {
-    const int row = 8 * (wave + 4 * i) + lane / 8;
+    const int row = 8 * (wave_id + WAVES * i) + lane / 8;
     x_voff[i] = row * pitch + ((lane % 8) ^ swz<64>(row)) * 16;
   }
 #pragma unroll
   for (int i = 0; i < WI; ++i) {
-    const int row = 8 * (wave + 4 * i) + lane / 8;
+    const int row = 8 * (wave_id + WAVES * i) + lane / 8;
     w_voff[i] = row * pitch + ((lane % 8) ^ swz<64>(row)) * 16;
   }
   const unsigned lds = (unsigned)(size_t)(lds_void_ptr)&sm.ring[0];
   auto issue = [&](int kt) {
-    const unsigned to = lds + (unsigned)((kt % S) * sizeof(Stage) + wave * 1024);
+    const unsigned to = lds + (unsigned)((kt % S) * sizeof(Stage) + wave_id * 1024);
     const int off = (kt0 + kt) * (KT * 2);
 #pragma unroll
-    for (int i = 0; i < WI; ++i) dma16_to_lds(w_rsrc, to + (unsigned)(ROWS * KT * 2 + i * 4096), w_voff[i] + off);
+    for (int i = 0; i < WI; ++i) dma16_to_lds(w_rsrc, to + (unsigned)(sizeof(Stage::x) + i * WAVES * 1024), w_voff[i] + off);
 #pragma unroll
-    for (int i = 0; i < XI; ++i) dma16_to_lds(x_rsrc, to + (unsigned)(i * 4096), x_voff[i] + off);
+    for (int i = 0; i < XI; ++i) dma16_to_lds(x_rsrc, to + (unsigned)(i * WAVES * 1024), x_voff[i] + off);
   };
 #pragma unroll
   for (int t = 0; t < S; ++t)
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(256, 1) void linear_few_rows_kernel(LinearParams p)
   auto fetch = [&](int kt, int b) {
     const Stage& st = sm.ring[kt % S];
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) wf[b][cb] = *(const bf16x8*)(st.w + cb * 32 * KT + frag);
+    for (int cb = 0; cb < 2; ++cb) wf[b][cb] = *(const bf16x8*)(st.w + (2 * half + cb) * 32 * KT + frag);
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) xf[b][rb] = *(const bf16x8*)(st.x + rb * 32 * KT + frag);
   };
@@ -388,18 +393,18 @@ __global__ __launch_bounds__(256, 1) void linear_few_rows_kernel(LinearParams p)
       if (t0 + i < 2 * NRB) {
         const f32x16& a = acc[(t0 + i) / 2][(t0 + i) % 2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sm.sum[wave][i][j][lane] = f32x4{a[4 * j], a[4 * j + 1], a[4 * j + 2], a[4 * j + 3]};
+        for (int j = 0; j < 4; ++j) sm.sum[wave_id][i][j][lane] = f32x4{a[4 * j], a[4 * j + 1], a[4 * j + 2], a[4 * j + 3]};
       }
     __syncthreads();
     const int t = t0 + wave, m = 32 * (t / 2) + r32;
     if (t >= 2 * NRB || m >= p.rows) continue;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int col = n0 + 32 * (t % 2) + 8 * j + 4 * hf;
+      const int col = n0 + 64 * half + 32 * (t % 2) + 8 * j + 4 * hf;
       if (col >= p.n) continue;   // n is a multiple of 8: a group of 4 columns is inside or outside as a whole
-      f32x4 c = sm.sum[0][wave][j][lane];
+      f32x4 c = sm.sum[4 * half][wave][j][lane];
 #pragma unroll
-      for (int w = 1; w < 4; ++w) c += sm.sum[w][wave][j][lane];
+      for (int w = 1; w < 4; ++w) c += sm.sum[4 * half + w][wave][j][lane];
       if (p.n_split > 1) {
         *(f32x4*)(p.partial + ((long long)blockIdx.y * p.rows + m) * p.n + col) = c;
         continue;
@@ -412,15 +417,19 @@ __global__ __launch_bounds__(256, 1) void linear_few_rows_kernel(LinearParams p)
     }
   }
 }
-static void launch_few_rows(const LinearParams& p, hipStream_t stream) {
-  const dim3 grid((unsigned)((p.n + 63) / 64), (unsigned)p.n_split), block(256);
+template <int HALVES>
+static void launch_few_rows_cols(const LinearParams& p, hipStream_t stream) {
+  const dim3 grid((unsigned)((p.n + 64 * HALVES - 1) / (64 * HALVES)), (unsigned)p.n_split), block(256 * HALVES);
   switch ((p.rows + 31) / 32) {
-    case 1: hipLaunchKernelGGL((linear_few_rows_kernel<1>), grid, block, 0, stream, p); break;
-    case 2: hipLaunchKernelGGL((linear_few_rows_kernel<2>), grid, block, 0, stream, p); break;
-    case 3: hipLaunchKernelGGL((linear_few_rows_kernel<3>), grid, block, 0, stream, p); break;
-    case 4: hipLaunchKernelGGL((linear_few_rows_kernel<4>), grid, block, 0, stream, p); break;
-    default: hipLaunchKernelGGL((linear_few_rows_kernel<5>), grid, block, 0, stream, p); break;
+    case 1: hipLaunchKernelGGL((linear_few_rows_kernel<1, HALVES>), grid, block, 0, stream, p); break;
+    case 2: hipLaunchKernelGGL((linear_few_rows_kernel<2, HALVES>), grid, block, 0, stream, p); break;
+    case 3: hipLaunchKernelGGL((linear_few_rows_kernel<3, HALVES>), grid, block, 0, stream, p); break;
+    case 4: hipLaunchKernelGGL((linear_few_rows_kernel<4, HALVES>), grid, block, 0, stream, p); break;
+    default: hipLaunchKernelGGL((linear_few_rows_kernel<5, HALVES>), grid, block, 0, stream, p); break;
   }
+}
+static void launch_few_rows(const LinearParams& p, int halves, hipStream_t stream) {
+  if (halves == 2) launch_few_rows_cols<2>(p, stream); else launch_few_rows_cols<1>(p, stream);
 }
 
 // Second kernel of a split product: adds the splits' sums and applies the epilogue.  One thread per row and group of 4
@@ -487,23 +496,63 @@ static long long linear_grid(long long rows, int n, int cols, int* patch_rows, i
   return (patches + kXcds - 1) / kXcds * kXcds * (*patch_rows * *patch_cols);
 }
 
-// Does linear_few_rows_kernel take the product?  us, linear_kernel -> it, both with the splits they choose (k x n):
-//    1 row    4096 x 11008 59 -> 21   11008 x 4096 28 -> 22   4096 x 6144 19 -> 16   4096 x 4096 15 -> 11   1536 x 2048 11 -> 10
-//   64 rows                60 -> 28                30 -> 27               22 -> 19               17 -> 14                12 -> 10
-//   96 rows                58 -> 38                32 -> 33               22 -> 24               19 -> 17                13 -> 11
-//  160 rows                62 -> 55                38 -> 45               28 -> 34               22 -> 23                16 -> 15
-// Its activations come through every 64-column tile, linear_kernel's through every 128-column one, and what a CU loads into
-// its LDS (about 17 bytes a clock) is the limit of both.  Up to 64 rows every size gains.  With three blocks of 32 rows those
-// do that linear_kernel takes more than one round for (the splits of its tiles fill some XCD's 32 CUs and leave others idle:
-// 40 tiles, 0.62 - 0.70 of its time), not those where it just fits (44 - 60 tiles but 50: 1.00 - 1.11 of its time from k = 3072
-// on, 44 - 48, where the few-row tiles also leave CUs idle, up to 1.29; 24 - 32 tiles: 0.90 - 1.00 up to k = 8192, 1.00 - 1.04
-// beyond).  From there on only those widths gain that linear_kernel does not split, which leaves it on a third of the CUs (more
-// than 64 of its tiles), up to five blocks (rows: k x n):
-//  128, 160: 4096 x 8256 57 -> 42, 57 -> 53   4096 x 14336 57 -> 44, 57 -> 54   8192 x 10240 115 -> 78, 117 -> 99
-//            5120 x 13824 71 -> 55, 70 -> 66  2048 x 16384 62 -> 27, 61 -> 32   8192 x 28672 422 -> 159, 423 -> 199
-//  161-192 (a sixth block of accumulators, built to measure): 57 -> 60, 57 -> 61, 119 -> 113, 71 -> 76; only from 16384
-//            outputs on a gain, 62 -> 36, 425 -> 227.  193 and more: the accumulators spill, 58 -> 124 and up.
-static bool linear_few_rows(long long rows, int k, int n) {
+// Does linear_few_rows_kernel take the product, with 64-column (1) or 128-column tiles (2)?  What a CU loads bounds it, and the
+// activations come through every tile, so half as many tiles load far less once there are more than two blocks of 32 rows; with
+// fewer the weights are most of it, and more workgroups get them sooner.  us, linear_kernel, 64 columns, 128 columns, each with
+// the splits it chooses (k x n):
+//    1 row    4096 x 11008 55 20 24   11008 x 4096 28 22 22   4096 x 6144 18 14 14   4096 x 4096 15 11 12   896 x 1152 10 8.3 6.9
+//   64 rows                58 27 29                31 27 26               20 18 17               17 13 14              11 8.5 8.0
+//   96 rows                58 35 32                33 33 30               22 23 19               18 16 16              12 9.8 9.7
+//  160 rows                58 50 38                36 44 35               26 32 25               21 22 20              14 13 13
+//  8192 x 10240, 1 / 64 / 160 rows 111 40 38, 114 49 40, 119 92 48; 8192 x 28672 421 111 107, 428 122 111, 428 185 134;
+//  2048 x 16384, 1 / 64 / 128 / 160 rows 59 16 17, 62 18 21, 62 25 26, 63 29 30; 1536 x 4160, 64 / 128 rows 19 11 11, 23 15 15.
+// (Six blocks of accumulators do not fit the registers.)
+static int linear_few_rows(long long rows, int k, int n) {
+  if (tuning(kTuneLinearTile, 0) != 0 || rows > 160) return 0;
+  if (rows > 64) return n > 8192 && k <= 2048 && rows <= 128 ? 1 : 2;
+  if (k <= 1024 || (k >= 8192 && n > 8192)) return 2;
+  return rows > 32 && k >= 3072 && n > 4608 && n <= 8192 ? 2 : 1;
+}
+
+// Splits of the inner dimension for a product with few output rows.  Without a split such a product has one workgroup
+// per 128 columns, a fraction of the CUs, each streaming its slice of the weights alone at the rate one workgroup's few
+// tiles in flight allow; with z splits there are z times as many, at the price of z * rows * n fp32 partial sums written
+// and read again.  The workgroups hold most of a CU's LDS (one per CU at a time), so z is the largest count that still
+// fits ONE round of 256 workgroups; at least 4 K-tiles per split, the partial sums no larger than the weights, and
+// within the workspace given.  Measured (160 rows, k = 4096): 4096 outputs 56 -> 23 us, 6144 outputs 57 -> 28 us; with
+// 86 tiles (11008 outputs) two splits only add the partial sums (62 -> 70 us).  The 64-column tiles of the few-row kernel
+// follow the same rule with twice as many tiles; its 128-column tiles take what a count of the time says is best: K-tiles in a row
+// (0.0026 us per row and column of a tile), the reduction's launch, and the partial sums (160 rows, k = 4096: 4096 outputs in 4
+// / 8 splits 20.2 / 23.4 us, 6144 in 4 / 5 24.5 / 26.8, 11008 in 1 / 2 49 / 37; k = 11008, 4096 outputs 44 / 35).  (Q/K/V products of 8193 to 16384 outputs and k >= 8192 are left without a
+// split and with the general kernel, as its rotating epilogue asks: 8192 x 10240, 1 / 64 / 160 rows 109 / 115 / 118 us, in two
+// splits 112 / 115 / 121.)
+// least: 2 where an unsplit product could not take the few-row kernel (Q/K/V).
+static int linear_splits(long long rows, int k, int n, int few, int least, size_t workspace_bytes) {
+  const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128), half_tiles = (n + 63) / 64;
+  long long z;
+  if (few == 2) {
+    double best = 0.;
+    z = 0;
+    for (int i = least; i == least || (i <= 16 && i * tiles <= 256); ++i) {
+      const double t = ((k / 64 + i - 1) / i) * (double)((rows + 31) / 32 * 32 + 128) * 2.6e-3 + (i > 1 ? 5. + i * ((double)rows * n * 2e-6 + 0.3) : 0.);
+      if (z == 0 || t < best) { best = t; z = i; }
+    }
+  } else {
+    z = few ? std::max<long long>(1, 256 / half_tiles) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
+  }
+  z = std::min<long long>(z, k / 64 / 4);
+  z = std::min<long long>(z, k / (2 * rows));
+  z = std::min<long long>(z, 16);
+  const int forced = tuning(kTuneLinearSplits, 0);
+  if (forced > 0) z = std::min<long long>(forced, std::max(1, k / 64));
+  while (z > 1 && (size_t)z * rows * n * sizeof(float) > workspace_bytes) --z;
+  return (int)std::max<long long>(z, 1);
+}
+// The workspace that the query names, by which programs have sized their buffers: for as many splits as tiles of 64 columns (up
+// to 64 rows, and where 128-column tiles are more than one round of every XCD) or 128 leave room for in one round of workgroups.
+// A call uses what it is given: less means fewer splits, and a product that the query names nothing for is split as well where
+// the buffer is large enough for it (160 rows x 4096 x 11008, in the buffer of the layer's other products: 49 -> 37 us).
+static bool asked_as_few_rows(long long rows, int k, int n) {
   if (tuning(kTuneLinearTile, 0) != 0) return false;
   if (rows <= 64) return true;
   const int tiles = (n + 127) / 128;
@@ -515,31 +564,13 @@ static bool linear_few_rows(long long rows, int k, int n) {
   const bool one_round = patch_rows == 1 && fullest * (256 / tiles) <= 32;
   return !(one_round && (tiles >= 44 ? k >= 3072 : tiles >= 24 && k > 8192));
 }
-
-// Splits of the inner dimension for a product with few output rows.  Without a split such a product has one workgroup
-// per 128 columns, a fraction of the CUs, each streaming its slice of the weights alone at the rate one workgroup's few
-// tiles in flight allow; with z splits there are z times as many, at the price of z * rows * n fp32 partial sums written
-// and read again.  The workgroups hold most of a CU's LDS (one per CU at a time), so z is the largest count that still
-// fits ONE round of 256 workgroups; at least 4 K-tiles per split, the partial sums no larger than the weights, and
-// within the workspace given.  Measured (160 rows, k = 4096): 4096 outputs 56 -> 23 us, 6144 outputs 57 -> 28 us; with
-// 86 tiles (11008 outputs) two splits only add the partial sums (62 -> 70 us).  The 64-column tiles of the few-row kernel
-// follow the same rule with twice as many tiles.  (Q/K/V products of 8193 to 16384 outputs and k >= 8192 are left without a
-// split and with the general kernel, as its rotating epilogue asks: 8192 x 10240, 1 / 64 / 160 rows 109 / 115 / 118 us, in two
-// splits 112 / 115 / 121.)
-static int linear_splits(long long rows, int k, int n, size_t workspace_bytes) {
-  const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128), few = (n + 63) / 64;
-  long long z = linear_few_rows(rows, k, n) ? std::max<long long>(1, 256 / few) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
-  z = std::min<long long>(z, k / 64 / 4);
-  z = std::min<long long>(z, k / (2 * rows));
-  z = std::min<long long>(z, 16);
-  const int forced = tuning(kTuneLinearSplits, 0);
-  if (forced > 0) z = std::min<long long>(forced, std::max(1, k / 64));
-  while (z > 1 && (size_t)z * rows * n * sizeof(float) > workspace_bytes) --z;
-  return (int)std::max<long long>(z, 1);
-}
 size_t linear_workspace_bytes(long long rows, int k, int n) {
   if (rows <= 0 || k <= 0 || n <= 0 || k % kLinKMultiple != 0) return 0;
-  const int z = linear_splits(rows, k, n, ~(size_t)0);
+  const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128), few = (n + 63) / 64;
+  long long z = asked_as_few_rows(rows, k, n) ? std::max<long long>(1, 256 / few) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
+  z = std::min<long long>(std::min<long long>(z, 16), std::min<long long>(k / 64 / 4, k / (2 * rows)));
+  const int forced = tuning(kTuneLinearSplits, 0);
+  if (forced > 0) z = std::min<long long>(forced, std::max(1, k / 64));
   return z > 1 ? ((size_t)z * rows * n * sizeof(float) + 255) / 256 * 256 : 0;
 }
 
@@ -575,9 +606,9 @@ static bool linear_wide_tile(long long rows, int n) {
 }
 
 // tile shape, splits and grid of one product; fills the split fields of p
-struct LinearLaunch { bool few, wide; int splits; dim3 grid; };
-static int plan_linear(const char* who, LinearParams& p, void* workspace, size_t workspace_bytes, LinearLaunch* out) {
-  const int splits = workspace ? linear_splits(p.rows, p.k, p.n, workspace_bytes) : 1;
+struct LinearLaunch { int few; bool wide; int splits; dim3 grid; };
+static int plan_linear(const char* who, LinearParams& p, int least, void* workspace, size_t workspace_bytes, LinearLaunch* out) {
+  const int few = linear_few_rows(p.rows, p.k, p.n), splits = workspace ? linear_splits(p.rows, p.k, p.n, few, least, workspace_bytes) : 1;
   const bool wide = splits == 1 && linear_wide_tile(p.rows, p.n);
   const long long grid = linear_grid(p.rows, p.n, wide ? 256 : 128, &p.patch_rows, &p.patch_cols);
   if (grid > 0x7fffffffLL) { set_error("%s: grid too large", who); return EARN_ERR_UNSUPPORTED; }
@@ -586,7 +617,7 @@ static int plan_linear(const char* who, LinearParams& p, void* workspace, size_t
   p.split_tiles = (k_tiles + splits - 1) / splits;
   p.n_split = (k_tiles + p.split_tiles - 1) / p.split_tiles;  // no empty split
   p.partial = p.n_split > 1 ? (float*)workspace : nullptr;
-  out->few = linear_few_rows(p.rows, p.k, p.n); out->wide = wide; out->splits = p.n_split; out->grid = dim3((unsigned)grid, (unsigned)p.n_split, 1);
+  out->few = few; out->wide = wide; out->splits = p.n_split; out->grid = dim3((unsigned)grid, (unsigned)p.n_split, 1);
   return EARN_OK;
 }
 
@@ -598,8 +629,8 @@ int launch_linear(const void* x, const void* w, int rows, int k, int n, int acti
   memset(&p, 0, sizeof(p));
   p.x = (const __bf16*)x; p.w = (const __bf16*)w; p.rows = rows; p.k = k; p.n = n; p.out = (__bf16*)out; p.activation = activation;
   LinearLaunch ll;
-  if ((rc = plan_linear("earn_linear", p, workspace, workspace_bytes, &ll)) != EARN_OK) return rc;
-  if (ll.few) launch_few_rows(p, stream);
+  if ((rc = plan_linear("earn_linear", p, 1, workspace, workspace_bytes, &ll)) != EARN_OK) return rc;
+  if (ll.few) launch_few_rows(p, ll.few, stream);
   else if (ll.wide) hipLaunchKernelGGL((linear_kernel<0, 128, LIN_WIDE>), ll.grid, dim3(LIN_WIDE_THREADS), 0, stream, p);
   else hipLaunchKernelGGL((linear_kernel<0, 128, 2, 1, 64, 3>), ll.grid, dim3(256), 0, stream, p);
   if (ll.splits > 1) {
@@ -623,9 +654,9 @@ int launch_qkv_rope_project(const earn_attn_desc* desc, const void* x, const voi
   p.hq = desc->n_q_heads; p.hkv = desc->n_kv_heads; p.head_dim = desc->head_dim;
   p.rope = make_rope_table(desc->rope_base, desc->head_dim);
   LinearLaunch ll;
-  if ((rc = plan_linear("earn_qkv_rope_project", p, workspace, workspace_bytes, &ll)) != EARN_OK) return rc;
+  if ((rc = plan_linear("earn_qkv_rope_project", p, 2, workspace, workspace_bytes, &ll)) != EARN_OK) return rc;
   if (ll.few && ll.splits > 1) {   // (the kernel has no rotating epilogue: unsplit products keep the general one)
-    launch_few_rows(p, stream);
+    launch_few_rows(p, ll.few, stream);
   } else if (desc->head_dim == 64) {
     if (ll.wide) hipLaunchKernelGGL((linear_kernel<1, 64, LIN_WIDE>), ll.grid, dim3(LIN_WIDE_THREADS), 0, stream, p);
     else hipLaunchKernelGGL((linear_kernel<1, 64, 2, 1, 64, 3>), ll.grid, dim3(256), 0, stream, p);

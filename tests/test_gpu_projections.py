@@ -258,3 +258,47 @@ def test_linear_few_rows(rows, k, n, act, with_ws):
     # unit in the last place is at most 2^-8 of the value
     assert bool(((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 2e-5).all())
     assert bool((out[rows] == 7.0).all())
+
+
+# Tiles of 128 columns (65 rows and more, short inner dimensions, wide outputs): the edges of their halves and row blocks, K-tiles
+# around the ring's depth, and as many splits as the count of the time takes where the buffer is large.
+@pytest.mark.parametrize("size", [0, 1 << 20, 1 << 26])
+@pytest.mark.parametrize("rows,k,n,act", [(1, 64, 8, 0), (17, 256, 136, 0), (64, 1024, 192, 1), (65, 192, 128, 0), (97, 256, 328, 0),
+                                          (96, 320, 1000, 1), (129, 1280, 11008, 1), (160, 4096, 1096, 0), (160, 2112, 8200, 0),
+                                          (40, 8192, 8264, 0), (33, 3072, 6400, 0)])
+def test_linear_few_rows_128_columns(rows, k, n, act, size):
+    B = _B()
+    g = torch.Generator().manual_seed(rows + k + n)
+    x = torch.randn(rows, k, generator=g).to(torch.bfloat16)
+    w = (torch.randn(n, k, generator=g) * k ** -0.5).to(torch.bfloat16)
+    out = torch.full((rows + 1, n), 7.0, dtype=torch.bfloat16, device=DEV)
+    ws = torch.full((size + 256,), 3, dtype=torch.uint8, device=DEV)          # guard bytes behind the buffer
+    B.earn_linear(x.to(DEV), w.to(DEV), out[:rows], act, ws[:size] if size else None)
+    torch.cuda.synchronize()
+    ref = x.double() @ w.double().T
+    if act:
+        ref = ref / (1.0 + torch.exp(-ref))
+    got = out[:rows].cpu().double()
+    assert bool(((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 2e-5).all())    # (as in test_linear_few_rows)
+    assert bool((out[rows] == 7.0).all()) and bool((ws[size:] == 3).all())
+
+
+@pytest.mark.parametrize("with_ws", [False, True])
+@pytest.mark.parametrize("rows", [1, 64, 65, 160])
+@pytest.mark.parametrize("hq,hkv,d,dm", [(14, 2, 64, 896), (12, 2, 128, 1536)])
+def test_qkv_projection_of_few_rows(hq, hkv, d, dm, rows, with_ws):
+    B = _B()
+    g = torch.Generator().manual_seed(rows + dm)
+    n = (hq + 2 * hkv) * d
+    x = torch.randn(rows, dm, generator=g).to(torch.bfloat16)
+    w = (torch.randn(n, dm, generator=g) * dm ** -0.5).to(torch.bfloat16)
+    pos = torch.randint(0, 8000, (rows,), generator=g, dtype=torch.int32)
+    e = lambda h: torch.full((rows + 1, h, d), 7.0, dtype=torch.bfloat16, device=DEV)
+    q, kk, v = e(hq), e(hkv), e(hkv)
+    ws = torch.empty(max(256, B.earn_linear_workspace_bytes(rows, dm, n)), dtype=torch.uint8, device=DEV) if with_ws else None
+    B.earn_qkv_rope_project(B.make_desc(BF, hq, hkv, d), x.to(DEV), w.to(DEV), None, pos.to(DEV), 1, q[:rows], kk[:rows], v[:rows], ws)
+    torch.cuda.synchronize()
+    ref = O.qkv_project(W.to_f64(x), np.ascontiguousarray(W.to_f64(w).T), hq, hkv, d, pos.numpy())
+    for name, got in (("q", q), ("k", kk), ("v", v)):
+        check_attn(got[:rows], ref[name], BF, f"{name}, {rows} rows")
+        assert bool((got[rows] == 7.0).all())
