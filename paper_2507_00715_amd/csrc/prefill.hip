@@ -36,7 +36,7 @@ struct PrefillParams {
   void* out; float* lse;
   int batch, hq, hkv, max_seqlen;
   int total;   // rows of the packed tensors
-  int n_qblk;  // query blocks of the longest sequence
+  int n_qblk;  // workgroups of the longest sequence's (sequence, kv head) pair
   FastDiv by_pair, by_group, by_kv;  // workgroups per (sequence, kv head), query heads per kv head, kv heads
   FastDiv by_run;                    // prefill_short_kernel: workgroups per sequence
   // chosen-rows mode of the fp32 kernel (rows_per_seq > 0): q and out hold rows_per_seq rows per sequence in
@@ -412,31 +412,38 @@ static void launch_prefill_f32(const PrefillParams& p, const void* k_in, long lo
 // bf16 MFMA flash attention
 // ------------------------------------------------------------------------------------------------------------------
 
-// ---- workgroup -> (sequence, kv head, query block, head of the group), XCD aware ----
+// ---- workgroup -> (sequence, kv head) and its waves' (32 query rows, head of the group), XCD aware ----
 // Workgroups are handed to the 8 XCDs round-robin by linear id, and every XCD has its own L2.  Id (x, k) = the k-th
 // workgroup of XCD x.  Each XCD walks its own list of (sequence, kv head) pairs (pair % 8 == x) one pair at a time:
-// all query blocks of the pair (long, late blocks first) and all query heads of the group, so the workgroups that
+// all query rows of the pair (long, late ones first) and all query heads of the group, so the workgroups that
 // are resident on an XCD at any moment stream the SAME K/V rows and find them in that XCD's L2.
+// The pair's units of 32 rows of one head, heads innermost, go to the waves one after the other: the waves of a workgroup then
+// see about the same keys, so none waits at the diagonal for the others, and a sequence's end leaves less than a unit per head
+// idle (against 128 rows of one head to a workgroup: 256 sequences of 80-1040 rows, 12 / 2 heads of 128, 325 -> 292
+// us; 16 of 272-1040, 32 / 8 heads, 121 -> 113.  The same in the backward's dQ: 483 -> 505 us for the latter, not kept).  With one head per kv head the units of a workgroup are consecutive rows.
 struct PfBlock {
-  int c, a;     // kv head, query head
+  int c, a;     // kv head; this wave's query head
   int b0, n;    // first packed row and length of the sequence
-  int q0;       // first query row of the workgroup inside the sequence
+  int qw;       // this wave's first query row inside the sequence
+  int end;      // query rows of the workgroup end here (as far as the sequence has them)
   bool valid;
 };
-__device__ __forceinline__ PfBlock pf_map_block(const PrefillParams& p, int block_rows) {
+template <int WAVES>
+__device__ __forceinline__ PfBlock pf_map_block(const PrefillParams& p, int wave) {
   PfBlock b;
   b.valid = false;
   const unsigned gq = p.by_group.d, k_in_xcd = blockIdx.x / kXcds;
   const unsigned nth = p.by_pair.div(k_in_xcd), pair = nth * kXcds + blockIdx.x % kXcds;
   if (pair >= (unsigned)(p.batch * p.hkv)) return b;
-  const unsigned rem = k_in_xcd - nth * p.by_pair.d, from_last = p.by_group.div(rem);
-  const int qblk = p.n_qblk - 1 - (int)from_last;
   const unsigned s = p.by_kv.div(pair);
   b.c = (int)(pair - s * p.by_kv.d);
-  b.a = head_of_slot(p.heads, b.c * (int)gq + (int)(rem - from_last * gq));
   pf_seq_bounds(p, s, b.b0, b.n);
-  b.q0 = qblk * block_rows;
-  b.valid = b.q0 < b.n;
+  const unsigned first = (unsigned)(p.n_qblk - 1 - (int)(k_in_xcd - nth * p.by_pair.d)) * WAVES, unit = first + (unsigned)wave;
+  const unsigned rows32 = p.by_group.div(unit);
+  b.a = head_of_slot(p.heads, b.c * (int)gq + (int)(unit - rows32 * gq));
+  b.qw = (int)rows32 * 32;
+  b.end = min((int)p.by_group.div(first + WAVES - 1) * 32 + 32, b.n);
+  b.valid = (int)p.by_group.div(first) * 32 < b.n;
   return b;
 }
 
@@ -599,33 +606,32 @@ __device__ int g_pf_timeline_slots;
 #endif
 template <int D, int WAVES, int STAGES>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_kernel(PrefillParams p) {
-  constexpr int kBlockRows = 32 * WAVES;
   constexpr int DB = D / 32;             // 32-row blocks of O^T
   __shared__ __bf16 smk[STAGES][kTileKeys * D];  // tile t+1 arrives while tile t is read
   __shared__ __bf16 smv[STAGES][kTileKeys * D];
   PF_STAMP(0);
 
-  const PfBlock blk = pf_map_block(p, kBlockRows);
+  // the wave index is the same in all 64 lanes: say so, and everything derived from it (the wave's query window, its
+  // diagonal tile, the tile loop) lives in scalar registers and branches without touching the execution mask
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const PfBlock blk = pf_map_block<WAVES>(p, wave);
   PF_TIMELINE({
     const long long pf_wg = (long long)blockIdx.y * gridDim.x + blockIdx.x;
     if (threadIdx.x == 0 && g_pf_timeline && pf_wg < g_pf_timeline_slots) {
       g_pf_timeline[pf_wg * 8 + 6] = __smid();
-      g_pf_timeline[pf_wg * 8 + 7] = blk.valid ? (min(blk.q0 + kBlockRows, blk.n) + kTileKeys - 1) / kTileKeys : 0;
+      g_pf_timeline[pf_wg * 8 + 7] = blk.valid ? (blk.end + kTileKeys - 1) / kTileKeys : 0;
     }
   })
   if (!blk.valid) return;
   PF_STAMP(1);
   const PfLayer lv = pf_layer_view(p, blockIdx.y);
   const int b0 = blk.b0, n = blk.n;
-  // the wave index is the same in all 64 lanes: say so, and everything derived from it (the wave's query window, its
-  // diagonal tile, the tile loop) lives in scalar registers and branches without touching the execution mask
-  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r32 = lane & 31, hf = lane >> 5;
-  const int qw = blk.q0 + wave * 32;             // first query row of this wave
+  const int qw = blk.qw;                         // first query row of this wave
   const bool wave_active = qw < n;
   const int t_diag = qw / kTileKeys;             // last (diagonal) tile of this wave
   const int q_in_tile = qw - t_diag * kTileKeys; // offset of the wave's first query inside that tile
-  const int n_tiles = (min(blk.q0 + kBlockRows, n) + kTileKeys - 1) / kTileKeys;
+  const int n_tiles = (blk.end + kTileKeys - 1) / kTileKeys;
 
   TileStager<D, WAVES> stager;
   stager.init((const __bf16*)lv.k_rot + ((long long)b0 * p.hkv + blk.c) * D, (const __bf16*)lv.v + ((long long)b0 * p.hkv + blk.c) * D,
@@ -839,7 +845,17 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
   const __bf16* kg = (const __bf16*)pf_layer_ptr(k_in, ls_k_in, blockIdx.y) + ((long long)b0 * p.hkv + c) * D;
   const __bf16* vg = (const __bf16*)lv.v + ((long long)b0 * p.hkv + c) * D;
   const long long row_stride = (long long)p.hkv * D;
-  // everything that comes from memory is requested before anything is used
+  // Everything that comes from memory is requested before anything is used, the positions ahead of the rest: the rotary table is
+  // worked out while the rows are on their way.
+  constexpr int RI = NR * (D / 2) / THREADS, RSTEP = THREADS / (D / 2);   // rows of the table per thread, and from one to the next
+  int pos[RI];
+  if constexpr (ROPE) {
+#pragma unroll
+    for (int i = 0; i < RI; ++i) {
+      const int row = threadIdx.x / (D / 2) + i * RSTEP;
+      pos[i] = p.positions ? p.positions[b0 + min(row, n - 1)] : row;
+    }
+  }
   u32x2 k_lo[KI], k_hi[KI];
 #pragma unroll
   for (int i = 0; i < KI; ++i) {
@@ -855,9 +871,11 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
     vr[i] = u32x4{0u, 0u, 0u, 0u};       // rows past the end: weight 0, so the values must be finite
     if (row < n) vr[i] = *(const u32x4*)(vg + row * row_stride + (unit % UPR) * 8);
   }
-  // packed query row m is row m % n of the group's head m / n
+  // packed query row m is row m % n of the group's head m / n (n <= 128, m < 8 n up to the group: far inside what fp32 tells apart)
   u32x4 qr[KS];
-  auto q_index = [&](int m) { return (long long)(b0 + m % n) * p.hq + head_of_slot(p.heads, c * gq + m / n); };
+  const float inv_n = 1.f / (float)n;
+  auto head_of = [&](int m) { return (int)(((float)m + 0.5f) * inv_n); };
+  auto q_index = [&](int m) { const int h = head_of(m); return (long long)(b0 + m - h * n) * p.hq + head_of_slot(p.heads, c * gq + h); };
   auto load_q = [&](int m) {
     const __bf16* q = (const __bf16*)lv.q + q_index(m) * D + 8 * quad;
 #pragma unroll
@@ -867,10 +885,12 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
   if constexpr (ROPE) {
     const int e = threadIdx.x % (D / 2);
     const float hi = p.rope.hi[e], lo = p.rope.lo[e];
-    for (int row = threadIdx.x / (D / 2); row < n; row += THREADS / (D / 2)) {
-      const int pos = p.positions ? p.positions[b0 + row] : row;
+#pragma unroll
+    for (int i = 0; i < RI; ++i) {
+      const int row = threadIdx.x / (D / 2) + i * RSTEP;
+      if (row >= n) continue;
       float sn, cs;
-      sincos_turns_fast(rope_turns((float)pos, hi, lo), &sn, &cs);
+      sincos_turns_fast(rope_turns((float)pos[i], hi, lo), &sn, &cs);
       smc[row * CP + e] = f32x2{cs, sn};
     }
     __syncthreads();
@@ -909,7 +929,7 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
   __syncthreads();
 
   for (int m0 = m_first; m0 < rows; m0 += m_step) {
-    const int m = min(m0 + r16, rows - 1), qi = m % n;     // this lane's query row sees keys 0 .. qi
+    const int m = min(m0 + r16, rows - 1), qi = m - head_of(m) * n;   // this lane's query row sees keys 0 .. qi
     const long long io = q_index(m);
     bf16x8 qf[KS];
 #pragma unroll
@@ -929,7 +949,7 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
     }
     if (m0 + m_step < rows) load_q(min(m0 + m_step + r16, rows - 1));   // arrives while this one is worked on
     // key blocks that some row of the 16 sees: rows of one head run on, a second head starts again at 0
-    const int last = m0 / n == min(m0 + 15, rows - 1) / n ? min(m0 + 15, rows - 1) % n : n - 1;
+    const int m_end = min(m0 + 15, rows - 1), h_end = head_of(m_end), last = head_of(m0) == h_end ? m_end - h_end * n : n - 1;
     const int blocks = last / 32 + 1;
     f32x4 sc[2 * NB];
 #pragma unroll
@@ -1028,23 +1048,22 @@ __global__ __launch_bounds__(64 * WAVES, NR == 128 && (D == 64 || !ROPE) ? 4 : 1
 // ------------------------------------------------------------------------------------------------------------------
 template <int D, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_pipe_kernel(PrefillParams p) {
-  constexpr int kBlockRows = 32 * WAVES;
   constexpr int KSTEPS = D / 16, DB = D / 32;
   constexpr int UPM = 16 / (2 * KSTEPS);  // softmax units per score MFMA: 1 (D = 128) or 2 (D = 64)
   __shared__ __bf16 smk[3][kTileKeys * D];
   __shared__ __bf16 smv[2][kTileKeys * D];
 
-  const PfBlock blk = pf_map_block(p, kBlockRows);
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const PfBlock blk = pf_map_block<WAVES>(p, wave);
   if (!blk.valid) return;
   const PfLayer lv = pf_layer_view(p, blockIdx.y);
   const int b0 = blk.b0, n = blk.n;
-  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r32 = lane & 31, hf = lane >> 5;
-  const int qw = blk.q0 + wave * 32;
+  const int qw = blk.qw;
   const bool wave_active = qw < n;
   const int t_diag = qw / kTileKeys;
   const int q_in_tile = qw - t_diag * kTileKeys;
-  const int n_tiles = (min(blk.q0 + kBlockRows, n) + kTileKeys - 1) / kTileKeys;
+  const int n_tiles = (blk.end + kTileKeys - 1) / kTileKeys;
 
   TileStager<D, WAVES> stager;
   stager.init((const __bf16*)lv.k_rot + ((long long)b0 * p.hkv + blk.c) * D, (const __bf16*)lv.v + ((long long)b0 * p.hkv + blk.c) * D,
@@ -1343,10 +1362,10 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   p.rope = make_rope_table(desc->rope_base, d);
   if (make_head_map(desc, &p.heads, "earn_prefill_attn") != EARN_OK) return EARN_ERR_UNSUPPORTED;
   const bool f32 = desc->dtype == EARN_F32;
-  auto set_query_blocks = [&p](int n) {
+  auto set_query_blocks = [&p](int rows, int waves) {
     const unsigned gq = (unsigned)(p.hq / p.hkv);
-    p.n_qblk = n;
-    p.by_pair = FastDiv::of(n * gq); p.by_group = FastDiv::of(gq); p.by_kv = FastDiv::of((unsigned)p.hkv);
+    p.n_qblk = unit_blocks(rows, (int)gq, waves);
+    p.by_pair = FastDiv::of((unsigned)p.n_qblk); p.by_group = FastDiv::of(gq); p.by_kv = FastDiv::of((unsigned)p.hkv);
   };
   // prefill_short_kernel: grouped heads up to 128 rows (beyond 64: short_prefill_takes), single heads up to 32.  us per layer
   // with rotation, one launch per layer / 24 layers in one launch, the kernels of longer sequences (and a rotation pass) -> this one:
@@ -1376,7 +1395,7 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
       const long long groups = ((long long)(p.hq / p.hkv) * max_seqlen + 15) / 16;
       const long long on_xcd = ((long long)batch * p.hkv * n_layers + kXcds - 1) / kXcds;
       const int parts = k == k_rot_out ? 1 : (int)std::max<long long>(1, std::min<long long>((groups + waves - 1) / waves, 32 * per_cu / on_xcd));
-      set_query_blocks(1);
+      set_query_blocks(max_seqlen, waves);
       p.by_run = FastDiv::of((unsigned)(p.hkv * parts));
       const dim3 grid((unsigned)run_workgroups(batch, p.hkv * parts), n_layers, 1);
       hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, stream, p, k, ls_k, k_rot_out ? 1 : 0, parts);
@@ -1398,9 +1417,9 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
       if (d == 64) launch_rope_k<__bf16, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
       else launch_rope_k<__bf16, 128>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
     }
-    set_query_blocks(1);
+    set_query_blocks(max_seqlen, 2);
     const long long pairs8 = ((long long)batch * p.hkv + kXcds - 1) / kXcds * kXcds;
-    dim3 grid((unsigned)(pairs8 * (p.hq / p.hkv)), n_layers, 1);
+    dim3 grid((unsigned)(pairs8 * p.n_qblk), n_layers, 1);
     if (d == 64) hipLaunchKernelGGL((prefill_mfma_kernel<64, 2, 1>), grid, dim3(128), 0, stream, p);
     else hipLaunchKernelGGL((prefill_mfma_kernel<128, 2, 1>), grid, dim3(128), 0, stream, p);
   } else {
@@ -1416,9 +1435,9 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
     const int rows_set = tuning(kTunePrefillBlockRows, 0);
     const bool medium = max_seqlen <= 3072 || total_tokens / batch <= 2048;
     const int block_rows = rows_set == 128 || rows_set == 256 ? rows_set : (medium ? 128 : 256);
-    set_query_blocks((max_seqlen + block_rows - 1) / block_rows);
+    set_query_blocks(max_seqlen, block_rows / 32);
     const long long pairs8 = ((long long)batch * p.hkv + kXcds - 1) / kXcds * kXcds;
-    dim3 grid((unsigned)(pairs8 * p.n_qblk * (p.hq / p.hkv)), n_layers, 1);
+    dim3 grid((unsigned)(pairs8 * p.n_qblk), n_layers, 1);
     if (block_rows == 128) {
       if (d == 64) hipLaunchKernelGGL((prefill_mfma_kernel<64, 4, 2>), grid, dim3(256), 0, stream, p);
       else hipLaunchKernelGGL((prefill_mfma_kernel<128, 4, 2>), grid, dim3(256), 0, stream, p);

@@ -57,6 +57,8 @@ EARN_INDEX bool short_prefill_takes(int longest, int mean, long long pairs, bool
   if (keys_in_place) return pairs >= 128 && pairs <= 256 && longest <= 96 && 4ll * mean >= 3ll * longest;
   return pairs < 128 || 4ll * mean >= longest;
 }
+// Medium and long prefill: workgroups of a (sequence, kv head) pair whose waves take units of 32 rows of one query head.
+EARN_INDEX int unit_blocks(int rows, int heads, int waves) { return (int)(((rows + 31ll) / 32 * heads + waves - 1) / waves); }
 // fp32 prefill: are there so few workgroups of 16 query rows that the GPU holds them all at once (one or two a CU, by head
 // dimension)?  Then eight waves share a workgroup's keys and rotate them themselves, in one launch; else 32 rows share them, in
 // four waves, behind a rotation pass.  us, rotating / eight waves / four waves: 2 sequences of 132 rows, 4 heads of 64 (72
