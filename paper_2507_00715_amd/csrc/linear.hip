@@ -621,6 +621,19 @@ static int plan_linear(const char* who, LinearParams& p, int least, void* worksp
   return EARN_OK;
 }
 
+// Rows behind the last whole row tile, if they are worth a launch of their own: they would cost a round of 256 x 256 tiles, 1.6 us
+// for each K-tile, where the tiles of their count take 0.4 to 0.9.  us, in one launch / two: 16512 rows (64 row tiles and 128 rows)
+// x 4096 x 4096 522 / 489, x 11008 x 4096 1315 / 1208, 8256 x 4096 x 4096 297 / 240, 8300 x 2048 x 4096 165 / 140.  Short inner
+// dimensions do not pay for the second launch.  (A Q/K/V product's rotating epilogue asks for the narrow tiles of linear_kernel,
+// 0.86 a K-tile: 16512 x 4096 x 6144 766 / 762, left in one.)
+static int tail_rows(const LinearParams& p, const LinearLaunch& ll) {
+  const int whole = p.rows / kLinRows * kLinRows, tail = p.rows - whole;
+  if (!ll.wide || ll.splits != 1 || ll.few || whole == 0 || tail == 0 || tail > 160 || p.k < 1024 || tuning(kTuneLinearTile, 0) != 0) return 0;
+  int pr, pc;
+  auto rounds = [&](int rows) { return (linear_grid(rows, p.n, 256, &pr, &pc) + 255) / 256; };
+  return rounds(whole) < rounds(p.rows) ? tail : 0;
+}
+
 int launch_linear(const void* x, const void* w, int rows, int k, int n, int activation, void* out, void* workspace,
                   size_t workspace_bytes, hipStream_t stream) {
   int rc = check_linear_shape("earn_linear", rows, k, n);
@@ -630,6 +643,13 @@ int launch_linear(const void* x, const void* w, int rows, int k, int n, int acti
   p.x = (const __bf16*)x; p.w = (const __bf16*)w; p.rows = rows; p.k = k; p.n = n; p.out = (__bf16*)out; p.activation = activation;
   LinearLaunch ll;
   if ((rc = plan_linear("earn_linear", p, 1, workspace, workspace_bytes, &ll)) != EARN_OK) return rc;
+  if (const int tail = tail_rows(p, ll)) {
+    LinearParams t = p;
+    p.rows -= tail;
+    t.rows = tail; t.x += (long long)p.rows * k; t.out += (long long)p.rows * n;
+    ll.grid.x = (unsigned)linear_grid(p.rows, n, 256, &p.patch_rows, &p.patch_cols);
+    launch_few_rows(t, linear_few_rows(tail, k, n), stream);
+  }
   if (ll.few) launch_few_rows(p, ll.few, stream);
   else if (ll.wide) hipLaunchKernelGGL((linear_kernel<0, 128, LIN_WIDE>), ll.grid, dim3(LIN_WIDE_THREADS), 0, stream, p);
   else hipLaunchKernelGGL((linear_kernel<0, 128, 2, 1, 64, 3>), ll.grid, dim3(256), 0, stream, p);

@@ -302,3 +302,22 @@ def test_qkv_projection_of_few_rows(hq, hkv, d, dm, rows, with_ws):
     for name, got in (("q", q), ("k", kk), ("v", v)):
         check_attn(got[:rows], ref[name], BF, f"{name}, {rows} rows")
         assert bool((got[rows] == 7.0).all())
+
+
+@pytest.mark.parametrize("rows,k,n,act", [(8300, 1024, 4096, 0), (8193, 1024, 4096, 1), (8352, 1088, 4096, 0), (8353, 1024, 4096, 0)])
+def test_rows_behind_the_last_row_tile(rows, k, n, act):
+    """Up to 160 rows behind the whole row tiles are a launch of their own where they would cost a round of tiles."""
+    B = _B()
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    x = torch.randn(rows, k, generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn(n, k, generator=g, device=DEV) * k ** -0.5).to(torch.bfloat16)
+    out = torch.full((rows + 1, n), 7.0, dtype=torch.bfloat16, device=DEV)
+    B.earn_linear(x, w, out[:rows], act, None)
+    torch.cuda.synchronize()
+    sample = torch.cat([torch.arange(0, 8192, 97), torch.arange(8190, rows)])
+    ref = x[sample.to(DEV)].double().cpu() @ w.double().cpu().T
+    if act:
+        ref = ref / (1.0 + torch.exp(-ref))
+    got = out[sample.to(DEV)].double().cpu()
+    assert bool(((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 2e-5).all())    # (as in test_linear_few_rows)
+    assert bool((out[rows] == 7.0).all())
