@@ -206,6 +206,8 @@ __global__ __launch_bounds__(256) void bwd_dkv_kernel(BwdParams p) {
 // Bound by the instruction chain of a wave (matrix products, exponentials and splits of one tile: about 2 us, 3 us when two
 // waves share a SIMD) times the tiles it walks.  Measured, forward included, against the vector-ALU form that these kernels
 // replaced: 16 sequences of 272-1040 rows, 32 / 8 heads of 128: 18.36 -> 0.60 ms; 64 sequences of 68 rows: 1.01 -> 0.12 ms.
+// The gradients leave through LDS, whole rows at a time (32 stores of 8 bytes a lane, 32 rows each, before: backward alone 485 -> 476
+// and 84.0 -> 81.3 us at those sizes, 151 sequences of 140-189 rows 529 -> 498).
 // ------------------------------------------------------------------------------------------------------------------
 struct BwdBlock { int c, a, b0, n, row0; bool valid; };
 // Workgroup -> (sequence, kv head, block of owned rows, query head of the group)
@@ -348,16 +350,6 @@ __device__ __forceinline__ bool any_nan(const f32x16 (&o)[N]) {
   for (int i = 0; i < 16 * N; ++i) x += o[i / 16][i % 16];
   return __any(x != x);
 }
-template <int D>
-__device__ __forceinline__ void bwd_store_row(__bf16* row /* + 4 hf */, const f32x16 (&o)[D / 32], float scale) {
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      *(u32x2*)(row + 32 * db + 8 * j) = u32x2{pack_bf16(o[db][4 * j] * scale, o[db][4 * j + 1] * scale),
-                                               pack_bf16(o[db][4 * j + 2] * scale, o[db][4 * j + 3] * scale)};
-}
-
 // D and dQ of 32 * WAVES query rows of one head.  (Late queries, which see the most keys, are dispatched first: with early ones
 // first, 2 sequences of 2080 rows, 32 / 8 heads of 128, took 442 us for 423, 8 of 500-1000 with 12 / 2 heads 197 for 184.)
 template <int D, int WAVES>
@@ -458,7 +450,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void bwd_dq_mfma_kernel(BwdParams p)
     }
     return;
   }
-  if (qw + r32 < n) bwd_store_row<D>((__bf16*)p.dq + io * D + 4 * hf, o, p.scale);
+  // through the stage that the last tile, behind the last barrier, is not in: half of the waves in its K tile, half in its V tile
+  __bf16* own = (wave < WAVES / 2 ? smk[n_tiles & 1] : smv[n_tiles & 1]) + (wave % (WAVES / 2)) * 32 * D;
+  store_rows<D>((__bf16*)p.dq + ((long long)(b0 + qw) * p.hq + blk.a) * D, n - qw, (long long)p.hq * D, own, o, p.scale, lane);
 }
 
 // dK and dV of 32 * KW key rows of one kv head: walks the (head of the group, query tile) pairs from the block's own rows
@@ -613,6 +607,7 @@ __global__ __launch_bounds__(64 * KW * G, 2) void bwd_dkv_mfma_kernel(BwdParams 
   };
   add_groups(dv);
   add_groups(dk);
+  __syncthreads();            // the tiles' LDS is free
   if (grp > 0 || !active) return;
   constexpr int L = D / 16;   // lanes per row of the vector form
   if (any_nan(dk) || any_nan(dv)) {
@@ -622,9 +617,12 @@ __global__ __launch_bounds__(64 * KW * G, 2) void bwd_dkv_mfma_kernel(BwdParams 
     for (int r = 0; r < 32 && kw + r < n; r += kWave / L) bwd_dkv_row<__bf16, D, L>(p, b0, n, blk.c, kw + r + at / L, kw + r, at % L);
     return;
   }
-  if (kw + r32 >= n) return;
-  bwd_store_row<D>((__bf16*)p.dk + jo * D + 4 * hf, dk, p.scale);
-  bwd_store_row<D>((__bf16*)p.dv + jo * D + 4 * hf, dv, 1.f);
+  static_assert(sizeof(sm) >= KW * 32 * D * sizeof(__bf16));
+  __bf16* own = (__bf16*)&sm[0][0] + wave * 32 * D;
+  const long long at = ((long long)(b0 + kw) * p.hkv + blk.c) * D, row = (long long)p.hkv * D;
+  store_rows<D>((__bf16*)p.dk + at, n - kw, row, own, dk, p.scale, lane);
+  asm volatile("" ::: "memory");
+  store_rows<D>((__bf16*)p.dv + at, n - kw, row, own, dv, 1.f, lane);
 }
 
 size_t attn_backward_workspace_bytes(int hq, int total_tokens) { return ((size_t)total_tokens * hq * sizeof(float) + 255) / 256 * 256; }

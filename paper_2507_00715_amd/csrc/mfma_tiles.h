@@ -161,4 +161,26 @@ __device__ __forceinline__ bf16x8 read_v_fragment(const __bf16* smv, const FragO
   return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// 32 rows of accumulators (lane: row r32, elements 32 db + 8 j + 4 hf + (0..3)), scaled, as bf16 to memory through a 32 x D region
+// of LDS that is the wave's own: whole rows leave in 16-byte units.
+template <int D>
+__device__ __forceinline__ void store_rows(__bf16* out /* first row */, int rows, long long row_elems, __bf16* sm,
+                                              const f32x16 (&o)[D / 32], float inv, int lane) {
+  constexpr int UPR = D / 8, RPI = kWave / UPR;
+  const int r32 = lane & 31, hf = lane >> 5;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *(u32x2*)(sm + r32 * D + (((4 * db + j) ^ swz<D>(r32)) << 3) + 4 * hf) =
+          u32x2{pack_bf16(o[db][4 * j] * inv, o[db][4 * j + 1] * inv), pack_bf16(o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv)};
+  asm volatile("" ::: "memory");   // a wave's LDS operations complete in order: only the compiler has to keep theirs
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int row = RPI * i + lane / UPR;
+    const u32x4 x = *(const u32x4*)(sm + row * D + (lane % UPR) * 8);
+    if (row < rows) *(u32x4*)(out + row * row_elems + (((lane % UPR) ^ swz<D>(row)) << 3)) = x;
+  }
+}
+
 }  // namespace earn

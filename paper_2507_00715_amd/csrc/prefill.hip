@@ -549,27 +549,6 @@ __device__ __forceinline__ void pf_store_row(__bf16* orow /* row + 4 hf */, cons
     }
 }
 
-// The same through a 32 x D region of LDS that is the wave's own: whole rows leave in 16-byte units.
-template <int D>
-__device__ __forceinline__ void pf_store_rows(__bf16* out /* first row */, int rows, long long row_elems, __bf16* sm,
-                                              const f32x16 (&o)[D / 32], float inv, int lane) {
-  constexpr int UPR = D / 8, RPI = kWave / UPR;
-  const int r32 = lane & 31, hf = lane >> 5;
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      *(u32x2*)(sm + r32 * D + (((4 * db + j) ^ swz<D>(r32)) << 3) + 4 * hf) =
-          u32x2{pack_bf16(o[db][4 * j] * inv, o[db][4 * j + 1] * inv), pack_bf16(o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv)};
-  asm volatile("" ::: "memory");   // a wave's LDS operations complete in order: only the compiler has to keep theirs
-#pragma unroll
-  for (int i = 0; i < 32 / RPI; ++i) {
-    const int row = RPI * i + lane / UPR;
-    const u32x4 x = *(const u32x4*)(sm + row * D + (lane % UPR) * 8);
-    if (row < rows) *(u32x4*)(out + row * row_elems + (((lane % UPR) ^ swz<D>(row)) << 3)) = x;
-  }
-}
-
 // ------------------------------------------------------------------------------------------------------------------
 // Plain schedule: per tile  barrier -> S^T -> exponentials -> O^T.  One 32-query column block per wave.
 //   WAVES = 4: 128 query rows per workgroup, two workgroups per CU: less idle time on the causal diagonal of medium
@@ -791,7 +770,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
   if (lv.lse && hf == 0 && qi < n) lv.lse[(long long)(b0 + qi) * p.hq + blk.a] = (mrow + __builtin_log2f(ltot)) * 0.6931471805599453f;
   if constexpr (STAGES == 2) {
     // through the stage that the last tile, behind the last barrier, is not in
-    pf_store_rows<D>(out, n - qw, (long long)p.hq * D, own_region(n_tiles & 1), o, inv, lane);
+    store_rows<D>(out, n - qw, (long long)p.hq * D, own_region(n_tiles & 1), o, inv, lane);
   } else if (qi < n) {
     pf_store_row<D>(out + (long long)r32 * p.hq * D + 4 * hf, o, inv);
   }
