@@ -87,13 +87,13 @@ struct DecodeParams {
   // side by side on one XCD, sharing the keys in its L2.
   int n_pass;
   int even_runs;  // decode_short_kernel: how its streams are dealt to the XCDs
-  BeamGroups groups;   // decode_beams_kernel: which streams share a workgroup
-  FastDiv by_gq, by_kv;  // query heads per kv head, kv heads (short kernels)
   float scale_log2;
   // byte strides between the layers of a layer-batched launch (grid row y = layer); all zero for a single layer
   long long ls_q, ls_kv_new, ls_shared, ls_gen, ls_out, ls_part_o, ls_part_ml;
   RopeTable rope;
   HeadMap heads;
+  BeamGroups groups;     // decode_beams_kernel: which streams share a workgroup
+  FastDiv by_gq, by_kv;  // query heads per kv head, kv heads (short kernels)
 };
 
 // Bounds of sequence s's shared cache as the kernels use them: whatever shared_cu holds, rows [b0, b0 + ns) lie inside

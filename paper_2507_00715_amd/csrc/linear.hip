@@ -608,7 +608,13 @@ static bool linear_wide_tile(long long rows, int n) {
 // tile shape, splits and grid of one product; fills the split fields of p
 struct LinearLaunch { int few; bool wide; int splits; dim3 grid; };
 static int plan_linear(const char* who, LinearParams& p, int least, void* workspace, size_t workspace_bytes, LinearLaunch* out) {
-  const int few = linear_few_rows(p.rows, p.k, p.n), splits = workspace ? linear_splits(p.rows, p.k, p.n, few, least, workspace_bytes) : 1;
+  int few = linear_few_rows(p.rows, p.k, p.n), splits = workspace ? linear_splits(p.rows, p.k, p.n, few, least, workspace_bytes) : 1;
+  // few rows in 128-column tiles need their splits, which the buffer may not hold: 63 rows x 4096 x 6144 in 4 / 2 of them 16.8 / 21.1
+  // us, in two of 64-column tiles 18.3
+  if (few == 2 && p.rows <= 64 && splits < linear_splits(p.rows, p.k, p.n, few, 1, ~(size_t)0)) {
+    few = 1;
+    splits = workspace ? linear_splits(p.rows, p.k, p.n, few, least, workspace_bytes) : 1;
+  }
   const bool wide = splits == 1 && linear_wide_tile(p.rows, p.n);
   const long long grid = linear_grid(p.rows, p.n, wide ? 256 : 128, &p.patch_rows, &p.patch_cols);
   if (grid > 0x7fffffffLL) { set_error("%s: grid too large", who); return EARN_ERR_UNSUPPORTED; }

@@ -103,7 +103,8 @@ EARN_INDEX BeamGroup beam_group(const BeamGroups& g, int i) {
 //   one workgroup per (stream, kv head) while they are about one to a CU, its chain being the shortest (one sequence x 10 beams, 32 /
 //   8 heads, 64 rows: grouped 7.8, this 7.3), with few rows to read again (8 x 10, 32 / 8 heads, 8 rows 8.0 and 7.5; 64 x 10, 12 / 2
 //   heads, 8 rows 13.4 and 8.9) and with room for many generated rows, which a group walks for all its streams (16 x 10, 32 / 8
-//   heads, 16 rows, 30 of 32 generated 12.7 and 10.0);
+//   heads, 16 rows, 30 of 32 generated 12.7 and 10.0); with groups of two streams of 128 elements and few rows also where the streams
+//   are many (140 x 10, 12 / 2 heads, 25 rows, a step of 24 layers: 688 and 582; from 64 rows the two are level);
 //   groups up to an amount of rows that they read again (16 x 10, 32 / 8 heads: 64 rows 10.3 where the general kernel takes 14.6 and
 //   one workgroup per stream 13.9; 256 rows 15.9 and 22.3; 512 rows 25.9 and 23.2), beyond 64 rows only where two to a CU are all
 //   there are (64 x 10, 14 / 2 heads, 256 rows 19.9 and 14.6);
@@ -115,7 +116,8 @@ EARN_INDEX BeamKernel beam_kernel(int n_streams, int batch, int hkv, int gq, int
   const bool per_stream = pairs * shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024 &&
                           short_decode_takes_beams(pairs * n_layers, general, shared_len, d);
   const long long all = pairs * n_layers, workgroups = (long long)g.count * hkv * n_layers, generated = (long long)g.group * gen_cap;
-  if (per_stream && (all <= 256 || (all <= 320 && shared_len <= 64) || (all <= 1280 && shared_len <= 32) || generated > 96))
+  if (per_stream && (all <= 256 || (all <= 320 && shared_len <= 64) || (all <= 1280 && shared_len <= 32) || generated > 96 ||
+                     (d == 128 && g.group <= 2 && shared_len <= 32)))
     return BeamKernel::kPerStream;
   const long long rounds = (general + 255) / 256, read = workgroups * shared_len * (d + 64) / 192;
   if (generated <= 384 && keys <= 2304 && read <= (64 * rounds + (n_layers > 1 ? 0 : 112)) * 1024 &&

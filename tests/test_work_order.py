@@ -189,6 +189,7 @@ def test_beam_groups_hold_every_stream_once(lib, n_streams, batch, gq):
 @pytest.mark.parametrize("streams,batch,hkv,gq,d,rows,cap,layers,n_pass,kernel", [
     (10, 1, 8, 4, 128, 64, 8, 1, 1, 1), (160, 16, 8, 4, 128, 64, 8, 1, 1, 2), (160, 16, 8, 4, 128, 32, 8, 1, 1, 1), (160, 16, 8, 4, 128, 33, 8, 1, 1, 2),
     (160, 16, 8, 4, 128, 512, 8, 1, 1, 0), (160, 16, 8, 4, 128, 16, 32, 1, 1, 1), (640, 64, 2, 7, 64, 256, 8, 1, 2, 0), (640, 64, 2, 7, 64, 64, 8, 1, 2, 2),
-    (160, 16, 8, 4, 128, 2300, 8, 1, 1, 0), (160, 16, 8, 4, 128, 64, 200, 1, 1, 1), (64, 16, 4, 1, 64, 128, 16, 1, 1, 1)])
+    (160, 16, 8, 4, 128, 2300, 8, 1, 1, 0), (160, 16, 8, 4, 128, 64, 200, 1, 1, 1), (64, 16, 4, 1, 64, 128, 16, 1, 1, 1), (1400, 140, 2, 6, 128, 25, 16, 1, 1, 1),
+    (1400, 140, 2, 6, 128, 33, 16, 1, 1, 2), (1400, 140, 2, 7, 64, 25, 16, 1, 1, 2)])
 def test_beam_kernel(lib, streams, batch, hkv, gq, d, rows, cap, layers, n_pass, kernel):
     assert lib.beams_kernel(streams, batch, hkv, gq, d, rows, cap, layers, n_pass) == kernel
