@@ -66,12 +66,6 @@ struct Row8<__bf16> {
 };
 
 struct DecodeParams {
-  // What the short kernels find their work with, in the first 64 bytes: the rest lies as far from a cache line's start as without it.
-  // At the end of the block a step of 29 layers, 61 streams of 7 rows, took 217 us, here 211; in the middle, not a line long, the
-  // general kernel took 273 us where it takes 267.
-  BeamGroups groups;     // decode_beams_kernel: which streams share a workgroup
-  FastDiv by_gq, by_kv;  // query heads per kv head, kv heads (short kernels)
-  int unused_[4];
   const void* q; const void* k_new; const void* v_new; const int32_t* q_pos;
   const void* shared_k; const void* shared_v; const int32_t* shared_cu; const int32_t* stream_to_seq;
   void* gen_k; void* gen_v; const int32_t* gen_len;
@@ -92,12 +86,21 @@ struct DecodeParams {
   // used with causal rows, where passes differ widely in length and the long ones of a (sequence, kv head) then run
   // side by side on one XCD, sharing the keys in its L2.
   int n_pass;
-  int even_runs;  // decode_short_kernel: how its streams are dealt to the XCDs
+  int even_runs;  // short kernels: how the workgroups are dealt to the XCDs
   float scale_log2;
   // byte strides between the layers of a layer-batched launch (grid row y = layer); all zero for a single layer
   long long ls_q, ls_kv_new, ls_shared, ls_gen, ls_out, ls_part_o, ls_part_ml;
   RopeTable rope;
   HeadMap heads;
+};
+
+// What the short kernels find their work with: an argument of their own, ahead of the block that all kernels have.  (even_runs,
+// needed with it, is in that block: reading it brings the line of gen_cap and batch along, which decode_beams_kernel otherwise asks
+// for a trip to memory later, 10.3 -> 10.6 us for 16 sequences x 10 streams, 32 / 8 heads of 128, 64 rows.)
+struct alignas(64) ShortWork {
+  BeamGroups groups;     // decode_beams_kernel: which streams share a workgroup
+  FastDiv by_gq, by_kv;  // query heads per kv head, kv heads
+  FastDiv by_slot;       // streams that a sequence usually has side by side
 };
 
 // Bounds of sequence s's shared cache as the kernels use them: whatever shared_cu holds, rows [b0, b0 + ns) lie inside
@@ -575,7 +578,7 @@ __device__ __forceinline__ void short_weigh(const __bf16* smv, const u32x4 (&pw)
 }
 
 template <int D, int WAVES>
-__global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodeParams p) {
+__global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(ShortWork work, DecodeParams p) {
   constexpr int KS = D / 32, DB = D / 16, UPR = D / 8;   // k-steps, 16-row blocks of O^T, 16-byte units per row
   constexpr int BLK = 32;                                // keys per block
   constexpr int NV = BLK * UPR / kWave;                  // V units per lane and block
@@ -585,11 +588,11 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
   __shared__ __align__(16) __bf16 rot[3][9][D + 8];      // rotated queries (three terms) and, in row gq, the new key
   // Workgroup -> (stream, kv head): an XCD keeps a run of consecutive pairs of them (beams of a sequence share its cache rows,
   // the kv heads of a stream share DRAM rows), so most of what they share is fetched into one L2.
-  const RunItem run = run_item(blockIdx.x, p.n_streams, p.by_kv, p.even_runs);
+  const RunItem run = run_item(blockIdx.x, p.n_streams, work.by_kv, p.even_runs);
   if (!run.valid) return;
   const int u = run.item, c = run.sub;
   const DecodeLayer lv = layer_view(p, blockIdx.y);
-  const int gq = (int)p.by_gq.d;
+  const int gq = (int)work.by_gq.d;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r16 = lane & 15, quad = lane >> 4;
   const long long tok = ((long long)u * p.hkv + c) * D;
@@ -617,7 +620,7 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
   const int g = clamp_gen_len(p.gen_len[u], p.gen_cap);
   const float pos = (float)p.q_pos[u];
   // The bounds are asked for together with the list, of the sequence that a stream usually has: one trip to memory less.
-  const int s_usual = min(u, p.batch - 1);
+  const int s_usual = min((int)work.by_slot.div((unsigned)u), p.batch - 1);
   int b0, ns;
   shared_bounds(p, s_usual, b0, ns);
   if (s != s_usual) shared_bounds(p, s, b0, ns);
@@ -767,20 +770,20 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(DecodePa
 // kernel, 17.9 here.
 // ------------------------------------------------------------------------------------------------------------------
 template <int D, int WAVES>
-__global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_kernel(DecodeParams p) {
+__global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_kernel(ShortWork work, DecodeParams p) {
   constexpr int KS = D / 32, DB = D / 16, UPR = D / 8, BLK = 32, NV = BLK * UPR / kWave, COLS = 16;
   union Tile { __bf16 v[BLK * D]; float o[COLS][D + 4]; }; // a wave's V block; at the end its unnormalised outputs
   __shared__ Tile tile[WAVES];
   __shared__ f32x2 ml[WAVES][COLS];                      // (max, sum) per column
   __shared__ __align__(16) __bf16 rot[3][COLS][D + 8];   // rotated queries (three terms)
   __shared__ __align__(16) __bf16 keys[COLS][D + 8];     // the streams' new keys
-  const RunItem item_of = run_item(blockIdx.x, p.groups.count, p.by_kv, p.even_runs);
+  const RunItem item_of = run_item(blockIdx.x, work.groups.count, work.by_kv, p.even_runs);
   if (!item_of.valid) return;
   const int c = item_of.sub;
-  const BeamGroup own_group = beam_group(p.groups, item_of.item);
+  const BeamGroup own_group = beam_group(work.groups, item_of.item);
   const int u0 = own_group.first, nb = own_group.count;  // streams u0 .. u0 + nb - 1, 1 <= nb <= 16 / gq
   const DecodeLayer lv = layer_view(p, blockIdx.y);
-  const int gq = (int)p.by_gq.d, cols = nb * gq;
+  const int gq = (int)work.by_gq.d, cols = nb * gq;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r16 = lane & 15, quad = lane >> 4;
 
@@ -792,7 +795,7 @@ __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_k
   const int s_usual = min(own_group.slot, p.batch - 1);
   int b0_lane, ns_lane;
   shared_bounds(p, s_usual, b0_lane, ns_lane);
-  const int col_b = min((int)p.by_gq.div(r16), nb - 1);               // this lane's column is a head of stream u0 + col_b
+  const int col_b = min((int)work.by_gq.div(r16), nb - 1);               // this lane's column is a head of stream u0 + col_b
   // the rows of the queries and new keys, 4 rotary pairs of a row per item: cols queries, then nb keys
   constexpr int MAX_ITEMS = (2 * COLS * (D / 8) + kWave * WAVES - 1) / (kWave * WAVES);
   const int n_items = (cols + nb) * (D / 8);
@@ -802,7 +805,7 @@ __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_k
 #pragma unroll
   for (int i = 0; i < MAX_ITEMS; ++i) {
     const int item = min((int)threadIdx.x + i * kWave * WAVES, n_items - 1), row = item / (D / 8), e = item % (D / 8) * 4;
-    item_b[i] = row < cols ? (int)p.by_gq.div(row) : row - cols;
+    item_b[i] = row < cols ? (int)work.by_gq.div(row) : row - cols;
     const __bf16* src = (row < cols ? (const __bf16*)lv.q + ((long long)(u0 + item_b[i]) * p.hq + head_of_slot(p.heads, c * gq + row - item_b[i] * gq)) * D
                                     : (const __bf16*)lv.k_new + ((long long)(u0 + item_b[i]) * p.hkv + c) * D) + e;
     x_lo[i] = *(const u32x2*)src;
@@ -1769,6 +1772,14 @@ static void launch_vector(const DecodeParams& p, int gq, dim3 grid, hipStream_t 
   else launch_vector_w<T, D, 4>(p, gq, grid, stream);
 }
 
+static ShortWork short_work(const DecodeParams& p) {
+  ShortWork work;
+  work.groups = beam_groups(p.n_streams, p.batch, p.hq / p.hkv);
+  work.by_gq = FastDiv::of((unsigned)(p.hq / p.hkv));
+  work.by_kv = FastDiv::of((unsigned)p.hkv);
+  work.by_slot = FastDiv::of((unsigned)std::max(1, p.n_streams / p.batch));
+  return work;
+}
 // The XCDs take even runs of the streams, except where eight-wave workgroups outnumber the CUs: then a CU with two of them is
 // what the launch waits for, and it is done sooner when the last XCD leaves its share of the bandwidth to the others.  us per
 // layer, one launch per layer / 4 layers in one launch, whole -> even runs, 32 / 8 heads: 9 streams of 1000 rows 18.4 / 11.7 ->
@@ -1778,20 +1789,22 @@ static void launch_vector(const DecodeParams& p, int gq, dim3 grid, hipStream_t 
 template <int D>
 static void launch_short(DecodeParams& p, hipStream_t stream, int n_layers) {
   const int waves = short_decode_waves(p.max_shared_len, p.gen_cap, (long long)p.n_streams * p.hkv * n_layers);
+  const ShortWork work = short_work(p);
   p.even_runs = waves < 8 || (long long)p.n_streams * p.hkv <= 256;
   const dim3 grid((unsigned)run_workgroups(p.n_streams, p.hkv), n_layers, 1);
-  if (waves == 2) hipLaunchKernelGGL((decode_short_kernel<D, 2>), grid, dim3(128), 0, stream, p);
-  else if (waves == 3) hipLaunchKernelGGL((decode_short_kernel<D, 3>), grid, dim3(192), 0, stream, p);
-  else if (waves == 4) hipLaunchKernelGGL((decode_short_kernel<D, 4>), grid, dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL((decode_short_kernel<D, 8>), grid, dim3(512), 0, stream, p);
+  if (waves == 2) hipLaunchKernelGGL((decode_short_kernel<D, 2>), grid, dim3(128), 0, stream, work, p);
+  else if (waves == 3) hipLaunchKernelGGL((decode_short_kernel<D, 3>), grid, dim3(192), 0, stream, work, p);
+  else if (waves == 4) hipLaunchKernelGGL((decode_short_kernel<D, 4>), grid, dim3(256), 0, stream, work, p);
+  else hipLaunchKernelGGL((decode_short_kernel<D, 8>), grid, dim3(512), 0, stream, work, p);
 }
 
 template <int D>
 static void launch_beams(DecodeParams& p, hipStream_t stream, int n_layers) {
+  const ShortWork work = short_work(p);
   p.even_runs = 1;
-  const dim3 grid((unsigned)run_workgroups(p.groups.count, p.hkv), n_layers, 1);
-  if (short_decode_waves(p.max_shared_len, p.groups.group * p.gen_cap, 1) <= 4) hipLaunchKernelGGL((decode_beams_kernel<D, 4>), grid, dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL((decode_beams_kernel<D, 8>), grid, dim3(512), 0, stream, p);
+  const dim3 grid((unsigned)run_workgroups(work.groups.count, p.hkv), n_layers, 1);
+  if (short_decode_waves(p.max_shared_len, work.groups.group * p.gen_cap, 1) <= 4) hipLaunchKernelGGL((decode_beams_kernel<D, 4>), grid, dim3(256), 0, stream, work, p);
+  else hipLaunchKernelGGL((decode_beams_kernel<D, 8>), grid, dim3(512), 0, stream, work, p);
 }
 
 template <typename T, int D>
@@ -1852,8 +1865,6 @@ int launch_decode(const earn_attn_desc* desc, const void* q, const void* k_new, 
   p.gen_k = gen_k; p.gen_v = gen_v; p.gen_len = gen_len; p.out = out; p.gen_src = gen_src;
   p.gen_cap = gen_cap; p.n_streams = n_streams; p.batch = batch; p.hq = hq; p.hkv = hkv;
   p.shared_total = shared_total; p.max_shared_len = max_shared_len;
-  p.groups = beam_groups(n_streams, batch, gq);
-  p.by_gq = FastDiv::of((unsigned)gq); p.by_kv = FastDiv::of((unsigned)hkv);
   p.n_splits = pl.n_splits; p.n_slots = pl.n_slots; p.chunk = pl.chunk; p.causal_rows = 0; p.n_pass = pl.n_pass;
   const size_t need = decode_workspace_bytes(desc->dtype, hq, hkv, d, n_streams, batch, max_shared_len, gen_cap, n_layers);
   if (need > workspace_bytes || (need > 0 && !workspace)) {
