@@ -10,6 +10,7 @@
 //     across the 4 waves;
 //   * the key range of a long cache is split over several workgroups (split-K); partial (max, sum, out) triples go to
 //     the workspace and a second kernel merges them.
+#include <climits>
 #include <mutex>
 #include <type_traits>
 
@@ -101,6 +102,7 @@ struct alignas(64) ShortWork {
   BeamGroups groups;     // decode_beams_kernel: which streams share a workgroup
   FastDiv by_gq, by_kv;  // query heads per kv head, kv heads
   FastDiv by_slot;       // streams that a sequence usually has side by side
+  int max_runs;          // decode_beams_kernel: a group with more runs of streams of one sequence asks for other streams
 };
 
 // Bounds of sequence s's shared cache as the kernels use them: whatever shared_cu holds, rows [b0, b0 + ns) lie inside
@@ -762,13 +764,68 @@ __global__ __launch_bounds__(kWave * WAVES, 3) void decode_short_kernel(ShortWor
 // The same for streams that share caches (beams): the 16 query columns of a product hold the query heads of several streams, so
 // a workgroup serves `group` consecutive streams of one kv head and reads the cache rows they share once.  Its key list is the
 // cache of every run of streams of one sequence, then the generated rows of all its streams, one after the other, in blocks of
-// 32; a column sees the rows of its own stream and of its stream's sequence.  Streams may lie in any order: those of another
-// sequence cost a walk over that sequence's cache, so the groups follow the usual layout, W streams per sequence side by side.
+// 32; a column sees the rows of its own stream and of its stream's sequence.  The groups are cut from the streams as they come,
+// usually W of a sequence side by side; groups of many sequences, which would walk a cache each, deal their streams among them anew
+// (reorder_streams; when, and what it costs: beam_runs).
 // Bound by its chain of dependent trips to memory (lists -> bounds, asked for at the place the usual layout has them -> rows) and by
 // the few hundred instructions behind them.  us, 16 sequences x 10 streams, 32 / 8 heads of 128, 64 rows: one workgroup per (stream,
 // kv head) 14.8, 1280 of them in one and a quarter rounds that read a cache ten times; 384 of these 10.1.  16 x 20: 25 in the general
 // kernel, 17.9 here.
 // ------------------------------------------------------------------------------------------------------------------
+typedef const __attribute__((address_space(1))) u32x4* global_u32x4_ptr;
+
+// The streams of group `own`, whose places hold more than max_runs runs of streams of one sequence: such groups deal their streams
+// among them anew, in the order of the sequences, then of the streams.  Every workgroup comes to the same division by itself.  All
+// threads of the workgroup; lds: beam_order_ints() integers; out: 16 streams, of the calling wave.
+__device__ __forceinline__ void reorder_streams(const DecodeParams& p, const BeamGroups& g, int own, int max_runs, int threads, int* lds, int* out) {
+  const int n = p.n_streams, lane = threadIdx.x % kWave;
+  int *seq = lds, *changes = seq + n, *streams_of = changes + g.count;   // of a stream, a group, a sequence
+  for (int i = threadIdx.x; i < g.count + p.batch; i += threads) changes[i] = 0;
+  for (int u = threadIdx.x; u < n; u += threads) seq[u] = max(min(p.stream_to_seq[u], p.batch - 1), 0);
+  __syncthreads();
+  for (int u = threadIdx.x; u < n; u += threads) {
+    const int i = beam_group_of(g, u);
+    if (u > beam_group(g, i).first && seq[u] != seq[u - 1]) atomicAdd(&changes[i], 1);
+  }
+  __syncthreads();
+  for (int u = threadIdx.x; u < n; u += threads) {       // the streams of the other groups stay where they are
+    if (changes[beam_group_of(g, u)] + 1 > max_runs) atomicAdd(&streams_of[seq[u]], 1);
+    else seq[u] = -1;
+  }
+  __syncthreads();
+  // this group's places among those: [first, first + nb)
+  int first = 0;
+  const int nb = beam_group(g, own).count;
+  for (int i = lane; i < own; i += kWave) first += changes[i] + 1 > max_runs ? beam_group(g, i).count : 0;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) first += __shfl_xor(first, o, kWave);
+  // sequence by sequence
+  int before = 0;                                        // streams of the sequences so far
+  for (int s0 = 0; s0 < p.batch && before < first + nb; s0 += kWave) {
+    const int mine = s0 + lane < p.batch ? streams_of[s0 + lane] : 0;
+    int end = mine;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int x = __shfl_up(end, o, kWave);
+      if (lane >= o) end += x;
+    }
+    unsigned long long here = __ballot(mine > 0 && before + end > first && before + end - mine < first + nb);
+    for (; here; here &= here - 1) {
+      const int i = __builtin_ctzll(here);
+      int at = before + __builtin_amdgcn_readlane(end - mine, i) - first;   // where its next stream goes
+      for (int u = lane; u - lane < n && at < nb; u += kWave) {
+        const bool is = u < n && seq[u] == s0 + i;
+        const unsigned long long m = __ballot(is);
+        const int to = at + __popcll(m & ((1ull << lane) - 1));
+        if (is && to >= 0 && to < nb) out[to] = u;
+        at += __popcll(m);
+      }
+    }
+    before += __builtin_amdgcn_readlane(end, kWave - 1);
+  }
+  asm volatile("" ::: "memory");   // the wave's LDS operations complete in order: only the compiler has to keep theirs
+}
+
 template <int D, int WAVES>
 __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_kernel(ShortWork work, DecodeParams p) {
   constexpr int KS = D / 32, DB = D / 16, UPR = D / 8, BLK = 32, NV = BLK * UPR / kWave, COLS = 16;
@@ -777,58 +834,26 @@ __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_k
   __shared__ f32x2 ml[WAVES][COLS];                      // (max, sum) per column
   __shared__ __align__(16) __bf16 rot[3][COLS][D + 8];   // rotated queries (three terms)
   __shared__ __align__(16) __bf16 keys[COLS][D + 8];     // the streams' new keys
+  __shared__ int group_streams[WAVES][COLS], stays[WAVES];   // the group's streams; whether they are those at its places
   const RunItem item_of = run_item(blockIdx.x, work.groups.count, work.by_kv, p.even_runs);
   if (!item_of.valid) return;
   const int c = item_of.sub;
   const BeamGroup own_group = beam_group(work.groups, item_of.item);
-  const int u0 = own_group.first, nb = own_group.count;  // streams u0 .. u0 + nb - 1, 1 <= nb <= 16 / gq
+  const int u0 = own_group.first, nb = own_group.count;  // streams u0 .. u0 + nb - 1 in the order of sequences, 1 <= nb <= 16 / gq
   const DecodeLayer lv = layer_view(p, blockIdx.y);
   const int gq = (int)work.by_gq.d, cols = nb * gq;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r16 = lane & 15, quad = lane >> 4;
 
-  // lane b < nb: stream u0 + b (the lanes beyond repeat the last)
-  const int b_lane = min(lane, nb - 1), u_lane = u0 + b_lane;
-  int s_lane = p.stream_to_seq ? max(min(p.stream_to_seq[u_lane], p.batch - 1), 0) : min(u_lane, p.batch - 1);
-  const int g_lane = clamp_gen_len(p.gen_len[u_lane], p.gen_cap);
-  const float pos_lane = (float)p.q_pos[u_lane];
-  const int s_usual = min(own_group.slot, p.batch - 1);
-  int b0_lane, ns_lane;
-  shared_bounds(p, s_usual, b0_lane, ns_lane);
-  const int col_b = min((int)work.by_gq.div(r16), nb - 1);               // this lane's column is a head of stream u0 + col_b
-  // the rows of the queries and new keys, 4 rotary pairs of a row per item: cols queries, then nb keys
-  constexpr int MAX_ITEMS = (2 * COLS * (D / 8) + kWave * WAVES - 1) / (kWave * WAVES);
-  const int n_items = (cols + nb) * (D / 8);
-  u32x2 x_lo[MAX_ITEMS], x_hi[MAX_ITEMS];
-  f32x4 th[MAX_ITEMS], tl[MAX_ITEMS];
-  int item_b[MAX_ITEMS];
-#pragma unroll
-  for (int i = 0; i < MAX_ITEMS; ++i) {
-    const int item = min((int)threadIdx.x + i * kWave * WAVES, n_items - 1), row = item / (D / 8), e = item % (D / 8) * 4;
-    item_b[i] = row < cols ? (int)work.by_gq.div(row) : row - cols;
-    const __bf16* src = (row < cols ? (const __bf16*)lv.q + ((long long)(u0 + item_b[i]) * p.hq + head_of_slot(p.heads, c * gq + row - item_b[i] * gq)) * D
-                                    : (const __bf16*)lv.k_new + ((long long)(u0 + item_b[i]) * p.hkv + c) * D) + e;
-    x_lo[i] = *(const u32x2*)src;
-    x_hi[i] = *(const u32x2*)(src + D / 2);
-    th[i] = f32x4{p.rope.hi[e], p.rope.hi[e + 1], p.rope.hi[e + 2], p.rope.hi[e + 3]};
-    tl[i] = f32x4{p.rope.lo[e], p.rope.lo[e + 1], p.rope.lo[e + 2], p.rope.lo[e + 3]};
-  }
-  if (__any(s_lane != s_usual)) shared_bounds(p, s_lane, b0_lane, ns_lane);
-  // generated rows of stream b, the new token last: [gen_end(b) - g - 1, gen_end(b)) of the list
-  int gen_end = lane < nb ? g_lane + 1 : 0;
-#pragma unroll
-  for (int o = 1; o < COLS; o <<= 1) {
-    const int x = __shfl_up(gen_end, o, kWave);
-    if (lane >= o) gen_end += x;
-  }
-  const int n_gen = __builtin_amdgcn_readlane(gen_end, nb - 1);
-  const int gen_begin = gen_end - (g_lane + 1);          // (of lanes b < nb)
-  // runs of streams of one sequence: bit b = a run starts at stream b
-  const int s_before = __shfl_up(s_lane, 1, kWave);
-  const unsigned starts = (unsigned)__ballot(lane < nb && (lane == 0 || s_lane != s_before));
-  int n_shared = 0;
-  for (unsigned m = starts; m; m &= m - 1) n_shared += (__builtin_amdgcn_readlane(ns_lane, __builtin_ctz(m)) + BLK - 1) / BLK;
-  const int n_blocks = n_shared + (n_gen + BLK - 1) / BLK;
+  // lane b < nb: stream b of the group (the lanes beyond repeat the last)
+  const int b_lane = min(lane, nb - 1);
+  int u_lane, g_lane, b0_lane, ns_lane;
+  float pos_lane;
+  const int col_b = min((int)work.by_gq.div(r16), nb - 1);               // this lane's column is a head of stream col_b
+  // generated rows of stream b, the new token last: [gen_begin(b), gen_end(b)) of the list
+  int gen_begin, gen_end, n_gen;
+  unsigned starts;                                       // runs of streams of one sequence: bit b = a run starts at stream b
+  int n_shared, n_blocks;
 
   struct Block { int j0, count, lo, hi, row0; bool shared; };   // streams [lo, hi) see it; row0: first cache row of the sequence
   auto find = [&](int blk) {
@@ -852,7 +877,7 @@ __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_k
   int row_is = 0;          // 2 stream + new
   long long row_at = 0;
   const unsigned row_bytes = (unsigned)p.hkv * D * 2;    // (a list's rows lie within 4 GiB: decode_few_keys)
-  auto own_row = [&](int b, int j) { return (((long long)(u0 + b) * p.gen_cap + j) * p.hkv + c) * D * 2; };
+  auto own_row = [&](int u, int j) { return (((long long)u * p.gen_cap + j) * p.hkv + c) * D * 2; };
   bf16x8 kf[2][KS];
   u32x4 vr[NV];
   auto load_block = [&](const Block& f) __attribute__((always_inline)) {
@@ -876,19 +901,18 @@ __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_k
     const int x = f.j0 + min(lane % BLK, f.count - 1);
     int b = 0;
     for (int i = 0; i < nb - 1; ++i) b += x >= __builtin_amdgcn_readlane(gen_end, i);
-    const int j = x - __shfl(gen_begin, b, kWave);
+    const int j = x - __shfl(gen_begin, b, kWave), u = __shfl(u_lane, b, kWave);
     row_is = 2 * b + (j == __shfl(g_lane, b, kWave));
-    int src = b;
-    if (p.gen_src && !(row_is & 1)) src = max(min(p.gen_src[(long long)(u0 + b) * p.gen_cap + j], p.n_streams - 1), 0) - u0;
+    int src = u;
+    if (p.gen_src && !(row_is & 1)) src = max(min(p.gen_src[(long long)u * p.gen_cap + j], p.n_streams - 1), 0);
     row_at = own_row(src, j);
 #pragma unroll
     for (int t = 0; t < 2; ++t) load_k(t, (const char*)lv.gen_k + __shfl(row_at, 16 * t + r16, kWave) + 16 * quad);
+    const unsigned long long v_row = row_is & 1 ? (unsigned long long)lv.v_new + ((long long)u * p.hkv + c) * D * 2 : (unsigned long long)lv.gen_v + row_at;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const int unit = lane + kWave * i, is = __shfl(row_is, unit / UPR, kWave);
-      const long long at = __shfl(row_at, unit / UPR, kWave);
-      const char* v = is & 1 ? (const char*)lv.v_new + ((long long)(u0 + (is >> 1)) * p.hkv + c) * D * 2 : (const char*)lv.gen_v + at;
-      vr[i] = *(const u32x4*)(v + 16 * (unit % UPR));
+      const int unit = lane + kWave * i;
+      vr[i] = *(global_u32x4_ptr)(__shfl(v_row, unit / UPR, kWave) + 16 * (unit % UPR));
     }
   };
   // (after the rows have arrived)
@@ -900,15 +924,69 @@ __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_k
       for (int e = 0; e < 4; ++e) vr[i][e] = have ? vr[i][e] : 0u;
     }
   };
-  if (wave < n_blocks) load_block(find(wave));
+  // Everything ahead of the walk: the streams' lists, the rows of the queries and new keys (4 rotary pairs of a row per item: cols
+  // queries, then nb keys) and of the first block of keys.  ASIDE: the group's streams are in u_lane, not u0 .. u0 + nb - 1.
+  constexpr int MAX_ITEMS = (2 * COLS * (D / 8) + kWave * WAVES - 1) / (kWave * WAVES);
+  const int n_items = (cols + nb) * (D / 8);
+  auto prepare = [&](auto aside_c) __attribute__((always_inline)) {
+    constexpr bool ASIDE = decltype(aside_c)::value;
+    if (!ASIDE) u_lane = u0 + b_lane;
+    const int s_lane = max(min(p.stream_to_seq[u_lane], p.batch - 1), 0);
+    g_lane = clamp_gen_len(p.gen_len[u_lane], p.gen_cap);
+    pos_lane = (float)p.q_pos[u_lane];
+    const int s_usual = min(own_group.slot, p.batch - 1);
+    shared_bounds(p, s_usual, b0_lane, ns_lane);
+    u32x2 x_lo[MAX_ITEMS], x_hi[MAX_ITEMS];
+    f32x4 th[MAX_ITEMS], tl[MAX_ITEMS];
+    int item_b[MAX_ITEMS];
 #pragma unroll
-  for (int i = 0; i < MAX_ITEMS; ++i) {
-    const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
-    const float pos = __shfl(pos_lane, item_b[i], kWave);
-    if (item >= n_items) continue;
-    short_rotate<D, COLS>(p, x_lo[i], x_hi[i], th[i], tl[i], pos, row >= cols, rot, keys[row < cols ? 0 : row - cols], row, e);
-  }
+    for (int i = 0; i < MAX_ITEMS; ++i) {
+      const int item = min((int)threadIdx.x + i * kWave * WAVES, n_items - 1), row = item / (D / 8), e = item % (D / 8) * 4;
+      item_b[i] = row < cols ? (int)work.by_gq.div(row) : row - cols;
+      const int u = ASIDE ? __shfl(u_lane, item_b[i], kWave) : u0 + item_b[i];
+      const __bf16* src = (row < cols ? (const __bf16*)lv.q + ((long long)u * p.hq + head_of_slot(p.heads, c * gq + row - item_b[i] * gq)) * D
+                                      : (const __bf16*)lv.k_new + ((long long)u * p.hkv + c) * D) + e;
+      x_lo[i] = *(const u32x2*)src;
+      x_hi[i] = *(const u32x2*)(src + D / 2);
+      th[i] = f32x4{p.rope.hi[e], p.rope.hi[e + 1], p.rope.hi[e + 2], p.rope.hi[e + 3]};
+      tl[i] = f32x4{p.rope.lo[e], p.rope.lo[e + 1], p.rope.lo[e + 2], p.rope.lo[e + 3]};
+    }
+    if (__any(s_lane != s_usual)) shared_bounds(p, s_lane, b0_lane, ns_lane);
+    gen_end = lane < nb ? g_lane + 1 : 0;
+#pragma unroll
+    for (int o = 1; o < COLS; o <<= 1) {
+      const int x = __shfl_up(gen_end, o, kWave);
+      if (lane >= o) gen_end += x;
+    }
+    n_gen = __builtin_amdgcn_readlane(gen_end, nb - 1);
+    gen_begin = gen_end - (g_lane + 1);                  // (of lanes b < nb)
+    const int s_before = __shfl_up(s_lane, 1, kWave);
+    starts = (unsigned)__ballot(lane < nb && (lane == 0 || s_lane != s_before));
+    n_shared = 0;
+    for (unsigned m = starts; m; m &= m - 1) n_shared += (__builtin_amdgcn_readlane(ns_lane, __builtin_ctz(m)) + BLK - 1) / BLK;
+    n_blocks = n_shared + (n_gen + BLK - 1) / BLK;
+    if (wave < n_blocks) load_block(find(wave));
+#pragma unroll
+    for (int i = 0; i < MAX_ITEMS; ++i) {
+      const int item = threadIdx.x + i * kWave * WAVES, row = item / (D / 8), e = item % (D / 8) * 4;
+      const float pos = __shfl(pos_lane, item_b[i], kWave);
+      if (item >= n_items) continue;
+      short_rotate<D, COLS>(p, x_lo[i], x_hi[i], th[i], tl[i], pos, row >= cols, rot, keys[row < cols ? 0 : row - cols], row, e);
+    }
+  };
+  if (lane < COLS) group_streams[wave][lane] = u0 + b_lane;
+  prepare(std::false_type{});
+  if (lane == 0) stays[wave] = __builtin_popcount(starts) <= work.max_runs;
   lds_barrier();
+  bool all_stay = true;                                  // (one answer for the workgroup, whatever its waves have read)
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) all_stay &= stays[w] != 0;
+  if (!all_stay) {
+    reorder_streams(p, work.groups, item_of.item, work.max_runs, kWave * WAVES, (int*)&tile[0], group_streams[wave]);
+    u_lane = group_streams[wave][b_lane];
+    prepare(std::true_type{});
+    lds_barrier();
+  }
 
   f32x4 o[DB];
   float mrow, lrow;                                      // of column r16; lrow: this lane's keys only
@@ -1016,7 +1094,7 @@ __global__ __launch_bounds__(kWave * WAVES, D == 64 ? 3 : 2) void decode_beams_k
     const float inv = 1.f / l;
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] *= inv;
-    Row8<__bf16>::store((__bf16*)lv.out + ((long long)(u0 + col / gq) * p.hq + head_of_slot(p.heads, c * gq + col % gq)) * D + e, x);
+    Row8<__bf16>::store((__bf16*)lv.out + ((long long)group_streams[0][col / gq] * p.hq + head_of_slot(p.heads, c * gq + col % gq)) * D + e, x);
   }
 }
 
@@ -1800,10 +1878,14 @@ static void launch_short(DecodeParams& p, hipStream_t stream, int n_layers) {
 
 template <int D>
 static void launch_beams(DecodeParams& p, hipStream_t stream, int n_layers) {
-  const ShortWork work = short_work(p);
+  ShortWork work = short_work(p);
   p.even_runs = 1;
   const dim3 grid((unsigned)run_workgroups(work.groups.count, p.hkv), n_layers, 1);
-  if (short_decode_waves(p.max_shared_len, work.groups.group * p.gen_cap, 1) <= 4) hipLaunchKernelGGL((decode_beams_kernel<D, 4>), grid, dim3(256), 0, stream, work, p);
+  const int waves = short_decode_waves(p.max_shared_len, work.groups.group * p.gen_cap, 1) <= 4 ? 4 : 8;
+  // (reorder_streams has its integers in the tiles)
+  work.max_runs = (long long)p.n_streams + work.groups.count + p.batch > waves * 16 * (D + 4) ? INT_MAX
+                                                                                             : beam_runs(work.groups, p.n_streams, p.batch, p.max_shared_len);
+  if (waves == 4) hipLaunchKernelGGL((decode_beams_kernel<D, 4>), grid, dim3(256), 0, stream, work, p);
   else hipLaunchKernelGGL((decode_beams_kernel<D, 8>), grid, dim3(512), 0, stream, work, p);
 }
 

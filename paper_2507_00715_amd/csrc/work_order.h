@@ -98,6 +98,20 @@ EARN_INDEX BeamGroup beam_group(const BeamGroups& g, int i) {
   b.count = rest < g.group ? rest : g.group;
   return b;
 }
+EARN_INDEX int beam_group_of(const BeamGroups& g, int u) {
+  const int slot = u / g.slot_streams;
+  return slot * (int)g.per_slot.d + (u - slot * g.slot_streams) / g.group;
+}
+// Runs of streams of one sequence that a group takes as they come: those that streams in the order of their sequences give it, and
+// as many more as are ten blocks of 32 rows to walk.  A group with more of them looks its streams up anew, about 3 us.  us, streams
+// u of sequences u % batch, groups as they come -> anew: 16 x 20 streams, 32 / 8 heads, 16 rows 18.3 -> 23.3; 8 x 10, 8 / 8 heads of
+// 64, 64 rows 15.1 -> 10.4; 16 x 10, 32 / 8 heads, 64 rows 9.9 either way, 256 rows 37.7 -> 33.2; 8 x 10, 32 / 32 heads, 256 rows 60
+// -> 21.9.
+EARN_INDEX int beam_runs(const BeamGroups& g, int n_streams, int batch, int shared_len) {
+  const int per_sequence = n_streams / batch, blocks = (shared_len + 31) / 32;
+  const int in_order = n_streams % batch == 0 ? 1 : (g.group + per_sequence - 1) / per_sequence + 1;
+  return in_order + 10 / (blocks < 1 ? 1 : blocks);
+}
 // Streams that share caches: which kernel?  420 sizes (1 to 64 sequences, 4 to 20 beams, six head layouts, 8 to 1000 rows, 1 or 8
 // layers in a launch, up to 100 generated rows), us a layer:
 //   one workgroup per (stream, kv head) while they are about one to a CU, its chain being the shortest (one sequence x 10 beams, 32 /

@@ -59,6 +59,14 @@ def _layout(name, batch, beams, rng):
         rng.shuffle(s2s)
     elif name == "uneven":                       # a stream more: the groups follow no sequence
         s2s = np.concatenate([s2s, [batch - 1]])
+    elif name == "beams first":                  # the first beam of every sequence, then the second ones
+        s2s = np.tile(np.arange(batch), beams)
+    elif name == "pairs":                        # two streams of a sequence side by side, its others elsewhere
+        s2s = np.tile(np.repeat(np.arange(batch), 2), (beams + 1) // 2)
+    elif name == "last two swapped":
+        s2s[-1], s2s[-beams - 1] = s2s[-beams - 1], s2s[-1]
+    elif name == "few sequences":                # most sequences have no stream, one has most of them
+        s2s = np.where(rng.random(batch * beams) < 0.5, 2, rng.integers(0, batch, batch * beams) // 3 * 3)
     return s2s.tolist()
 
 
@@ -85,6 +93,54 @@ def test_grouped_streams(layout, hq, hkv, d, batch, beams, longest, table, layer
             assert torch.equal(gv[l, u, g], x["v_new"][l, u])
             gk[l, u, g], gv[l, u, g] = x["gen_k"][l, u, g], x["gen_v"][l, u, g]
         assert torch.equal(gk[l], x["gen_k"][l]) and torch.equal(gv[l], x["gen_v"][l])
+
+
+@pytest.mark.parametrize("layout", ["beams first", "pairs", "last two swapped", "few sequences"])
+@pytest.mark.parametrize("hq,hkv,d,batch,beams,longest,layers", [(16, 4, 128, 12, 10, 64, 1), (8, 8, 64, 9, 8, 33, 2), (14, 2, 64, 190, 9, 60, 1),
+                                                                 (12, 2, 128, 300, 6, 40, 1)])
+def test_streams_in_any_order(layout, hq, hkv, d, batch, beams, longest, layers):
+    """The groups are cut from the streams in the order of their sequences, whatever order they come in (up to 1800 streams: a
+    workgroup's check of the order takes several steps)."""
+    rng = np.random.default_rng(batch + beams)
+    s2s, cap = _layout(layout, batch, beams, rng), 5
+    lens = [int(n) for n in rng.integers(1, longest + 1, batch)]
+    gen_len = rng.integers(0, cap, len(s2s)).tolist()
+    x = _inputs(batch, len(s2s), lens, hq, hkv, d, cap, layers)
+    out, gk, gv, cu, q_pos = _run(x, lens, s2s, gen_len, cap, hq, hkv, d)
+    for l in range(layers):
+        ref, ref_k, _ = _oracle(x, l, cu, s2s, gen_len, q_pos)
+        check_attn(out[l], ref, BF, f"layer {l}")
+        at = (torch.arange(len(s2s)), torch.tensor(gen_len))
+        check_attn(gk[l][at], ref_k[at], BF, "appended keys")
+        assert torch.equal(gv[l][at], x["v_new"][l])
+
+
+@pytest.mark.parametrize("hq,hkv,d,batch,beams,rows", [(32, 32, 128, 8, 10, 256), (8, 8, 64, 16, 10, 256)])
+def test_order_of_streams_costs_little(hq, hkv, d, batch, beams, rows):
+    """Streams that do not lie side by side: groups of unlike streams walked a cache each, 4 to 6 times the time."""
+    from paper_2507_00715_amd import binding as B
+    cap, n = 8, batch * beams
+    x = {k: v.to(DEV) for k, v in _inputs(1, n, [rows] * batch, hq, hkv, d, cap, 1).items()}
+    out, desc = torch.empty_like(x["q"][0]), B.make_desc(BF, hq, hkv, d, 0.0, 10000.0)
+    cu, pos, gen = I32(rows * np.arange(batch + 1)), I32([rows + 5] * n), I32([5] * n)
+    ws = torch.empty(max(256, B.earn_decode_workspace_bytes(desc, n, batch, rows, cap)), dtype=torch.uint8, device=DEV)
+
+    def us(layout):
+        s2s = I32(_layout(layout, batch, beams, np.random.default_rng(0)))
+        call = B.bind_decode_attn(desc, x["q"][0], x["k_new"][0], x["v_new"][0], pos, x["k"][0], x["v"][0], cu, s2s, x["gen_k"][0],
+                                  x["gen_v"][0], gen, cap, n, batch, rows, out, ws)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            call()
+            a.record()
+            for _ in range(20):
+                call()
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) / 20 * 1e3)
+        return best
+    assert us("beams first") <= 2 * us("usual")
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(16, 4, 128), (8, 8, 64)])

@@ -18,6 +18,8 @@ extern "C" int groups(int n_streams, int batch, int gq, int (*out)[3]) {
   for (int i = 0; i < g.count; ++i) { const BeamGroup b = beam_group(g, i); out[i][0] = b.first; out[i][1] = b.count; out[i][2] = b.slot; }
   return g.count;
 }
+extern "C" int group_of(int n_streams, int batch, int gq, int u) { return beam_group_of(beam_groups(n_streams, batch, gq), u); }
+extern "C" int runs_taken(int n_streams, int batch, int gq, int len) { return beam_runs(beam_groups(n_streams, batch, gq), n_streams, batch, len); }
 extern "C" int beams_kernel(int n_streams, int batch, int hkv, int gq, int d, int len, int cap, int layers, int pass) {
   return (int)beam_kernel(n_streams, batch, hkv, gq, d, len, cap, layers, pass);
 }
@@ -181,6 +183,11 @@ def test_beam_groups_hold_every_stream_once(lib, n_streams, batch, gq):
     first, count, slot = out[:n].T
     assert n <= n_streams and count.min() >= 1 and count.max() * gq <= max(16, gq)
     assert np.concatenate([np.arange(f, f + c) for f, c in zip(first, count)]).tolist() == list(range(n_streams))
+    assert [lib.group_of(n_streams, batch, gq, u) for u in range(n_streams)] == np.repeat(np.arange(n), count).tolist()
+    # streams in the order of their sequences, as many of each as can be, stay in their groups
+    sequence = np.arange(n_streams) * batch // n_streams
+    runs = [1 + int((np.diff(sequence[f:f + c]) != 0).sum()) for f, c in zip(first, count)]
+    assert max(runs) <= lib.runs_taken(n_streams, batch, gq, 2048)
     if n_streams % batch == 0:                  # no group over two sequences of the usual layout
         w = n_streams // batch
         assert np.array_equal(slot, first // w) and np.array_equal(slot, (first + count - 1) // w)
