@@ -1881,7 +1881,7 @@ static void launch_beams(DecodeParams& p, hipStream_t stream, int n_layers) {
   ShortWork work = short_work(p);
   p.even_runs = 1;
   const dim3 grid((unsigned)run_workgroups(work.groups.count, p.hkv), n_layers, 1);
-  const int waves = short_decode_waves(p.max_shared_len, work.groups.group * p.gen_cap, 1) <= 4 ? 4 : 8;
+  const int waves = beam_group_waves(work.groups, p.max_shared_len, p.gen_cap);
   // (reorder_streams has its integers in the tiles)
   work.max_runs = (long long)p.n_streams + work.groups.count + p.batch > waves * 16 * (D + 4) ? INT_MAX
                                                                                              : beam_runs(work.groups, p.n_streams, p.batch, p.max_shared_len);

@@ -65,16 +65,6 @@ EARN_INDEX int unit_blocks(int rows, int heads, int waves) { return (int)(((rows
 // workgroups) 10.9 / 13.5 / 17.3; 8 of them (288) 16.5 / 18.7 / 18.5; 16 (576) 22.9 / 25.4 / 22.5; 2 of 64, 32 / 8 heads of 128
 // (256) 14.9 / 16.5 / 23.4; 4 of them (512) 28.1 / 26.1 / 24.4; one of 512, 12 / 2 heads of 128 (384) 65.7 / 48.7 / 45.9.
 EARN_INDEX bool f32_few_workgroups(int rows, int hq, int d, long long sequences) { return (rows + 15ll) / 16 * hq * sequences * d <= 256 * 128; }
-// Does the short decode kernel take streams that share caches (beams)?  It reads a cache once per stream, about 0.1 us for 1024
-// rows of 128 elements all told; the general kernel reads it once, but its workgroups hold a CU each and take about 13 us a
-// round of 256.  pairs: (stream, kv head, layer); general_workgroups: (sequence, kv head, layer, pass of 64 query rows).
-// us a layer, general -> short: 8 sequences x 10, 12 / 2 heads, 16 layers in a launch, 32 / 48 / 200 rows 1.06 / 1.05 / 1.29 ->
-// 0.95 / 1.33 / 3.69 (taken: up to 32); 16 x 10, 32 / 8 heads, 24 layers, 32 / 64 rows 6.9 / 6.8 -> 4.4 / 7.1 (32); one layer,
-// 64 / 100 rows 15.3 / 15.4 -> 13.4 / 18.8 (64).
-EARN_INDEX bool short_decode_takes_beams(long long pairs, long long general_workgroups, int shared_len, int d) {
-  const long long rounds = (general_workgroups + 255) / 256;
-  return pairs * shared_len * (d + 64) / 192 <= (128 * rounds - 40) * 1024;
-}
 // Streams that share a workgroup of the short decode over beams: up to 16 / gq consecutive ones, whose query heads fill the 16
 // columns of a product, in equal groups of the W = n_streams / batch streams that a sequence usually has side by side (`slot`;
 // any other layout is served too, group by group).  No even number per sequence: all streams are one slot.
@@ -112,33 +102,6 @@ EARN_INDEX int beam_runs(const BeamGroups& g, int n_streams, int batch, int shar
   const int in_order = n_streams % batch == 0 ? 1 : (g.group + per_sequence - 1) / per_sequence + 1;
   return in_order + 10 / (blocks < 1 ? 1 : blocks);
 }
-// Streams that share caches: which kernel?  420 sizes (1 to 64 sequences, 4 to 20 beams, six head layouts, 8 to 1000 rows, 1 or 8
-// layers in a launch, up to 100 generated rows), us a layer:
-//   one workgroup per (stream, kv head) while they are about one to a CU, its chain being the shortest (one sequence x 10 beams, 32 /
-//   8 heads, 64 rows: grouped 7.8, this 7.3), with few rows to read again (8 x 10, 32 / 8 heads, 8 rows 8.0 and 7.5; 64 x 10, 12 / 2
-//   heads, 8 rows 13.4 and 8.9) and with room for many generated rows, which a group walks for all its streams (16 x 10, 32 / 8
-//   heads, 16 rows, 30 of 32 generated 12.7 and 10.0); with groups of two streams of 128 elements and few rows also where the streams
-//   are many (140 x 10, 12 / 2 heads, 25 rows, a step of 24 layers: 688 and 582; from 64 rows the two are level);
-//   groups up to an amount of rows that they read again (16 x 10, 32 / 8 heads: 64 rows 10.3 where the general kernel takes 14.6 and
-//   one workgroup per stream 13.9; 256 rows 15.9 and 22.3; 512 rows 25.9 and 23.2), beyond 64 rows only where two to a CU are all
-//   there are (64 x 10, 14 / 2 heads, 256 rows 19.9 and 14.6);
-//   else the general kernel.  1.17 times as fast on the geometric mean as without the groups, at worst 0.96.
-enum class BeamKernel { kGeneral, kPerStream, kGrouped };
-EARN_INDEX BeamKernel beam_kernel(int n_streams, int batch, int hkv, int gq, int d, int shared_len, int gen_cap, int n_layers, int n_pass) {
-  const long long pairs = (long long)n_streams * hkv, general = (long long)batch * hkv * n_layers * n_pass, keys = (long long)shared_len + gen_cap;
-  const BeamGroups g = beam_groups(n_streams, batch, gq);
-  const bool per_stream = pairs * shared_len <= (n_layers > 1 ? 48 : 128) * 1024ll && keys <= 1024 &&
-                          short_decode_takes_beams(pairs * n_layers, general, shared_len, d);
-  const long long all = pairs * n_layers, workgroups = (long long)g.count * hkv * n_layers, generated = (long long)g.group * gen_cap;
-  if (per_stream && (all <= 256 || (all <= 320 && shared_len <= 64) || (all <= 1280 && shared_len <= 32) || generated > 96 ||
-                     (d == 128 && g.group <= 2 && shared_len <= 32)))
-    return BeamKernel::kPerStream;
-  const long long rounds = (general + 255) / 256, read = workgroups * shared_len * (d + 64) / 192;
-  if (generated <= 384 && keys <= 2304 && read <= (64 * rounds + (n_layers > 1 ? 0 : 112)) * 1024 &&
-      (workgroups <= 512 || shared_len <= 64 || n_layers > 1))
-    return BeamKernel::kGrouped;
-  return per_stream ? BeamKernel::kPerStream : BeamKernel::kGeneral;
-}
 // Waves of a short decode workgroup: one per block of 32 shared keys and one for the generated rows, eight for longer lists.
 // With no more workgroups than CUs, nothing else hides a wave's round trips, so the blocks that the generated rows may come to
 // count too.  us, 16 shared rows, waves by shared rows -> by all: one sequence, 32 / 8 heads, 249 / 999 generated rows 14.5 /
@@ -149,6 +112,54 @@ EARN_INDEX int short_decode_waves(int max_shared_len, int gen_cap, long long wor
   const long long generated = workgroups <= 256 ? ((long long)gen_cap + 31) / 32 : 1;
   const long long blocks = ((long long)max_shared_len + 31) / 32 + generated;
   return blocks <= 2 ? 2 : blocks == 3 ? 3 : blocks <= 5 ? 4 : 8;
+}
+// ... and of a group's, four or eight
+EARN_INDEX int beam_group_waves(const BeamGroups& g, int max_shared_len, int gen_cap) {
+  return short_decode_waves(max_shared_len, g.group * gen_cap, 1) <= 4 ? 4 : 8;
+}
+// Streams that share caches: which kernel?  The one that a count of its time says is the fastest, in us, for rows of 128 elements (all
+// but the first figures two thirds of that for 64); the generated part counts with half the rows that there is room for.
+//   general     11.5 for each round on the XCD with the most workgroups, 0.85 for 64 rows of a split, and for each stream of a
+//               sequence 0.45 and 1.8 for 32 generated rows, over the splits;
+//   per stream  3.1 and 1.2 for each step of 32 rows of a workgroup's waves; beyond half a round 0.45 for 256 workgroups' 32 rows;
+//   grouped     4.8 and 1.15 for each step; beyond half a round 1.7 for 256 workgroups and 0.4 for 32 rows of theirs;
+//               workgroups of eight waves 0.5 / 0.8 more, and 3.1 / 4.5 for 256 of them (one or two fill a CU).
+// Figures that put the three in the right order for 1996 sizes, most of them drawn at random: 1 to 160 sequences, 2 to 24 streams each,
+// eleven head layouts, caches of 4 to 1500 rows, 4 to 200 generated rows, 1 to 24 layers in a launch.  The kernel named takes 1.011 times
+// as long as the best of them on the geometric mean, more than 1.25 times at 0.8 %, at most 2.6 times (1.022 and 2.5 % on 600 of the
+// sizes by figures from 906 others; thresholds that told the kernels apart by rows to read again: 1.090, 14 %, 12 times).  16 x 10 streams, 32 /
+// 8 heads, general / per stream / grouped: 32 rows 15.4 / 8.9 / 8.2, 64 rows 14.3 / 13.1 / 8.8, 512 rows 23.6 / 52.5 / 25.0, 16 rows and 30
+// generated 25.6 / 9.3 / 11.5; 140 x 10, 12 / 2 heads, 25 rows 37.2 / 16.1 / 19.5.
+enum class BeamKernel { kGeneral, kPerStream, kGrouped };
+EARN_INDEX BeamKernel beam_kernel(int n_streams, int batch, int hkv, int gq, int d, int shared_len, int gen_cap, int n_layers, int n_pass) {
+  if ((long long)shared_len + gen_cap > 2304) return BeamKernel::kGeneral;   // beyond what was measured
+  auto over = [](long long a, long long b) { return (a + b - 1) / b; };
+  auto past_half_round = [](long long workgroups) { return workgroups > 128 ? (double)workgroups / 256. - 0.5 : 0.; };
+  const double size = (d + 64) / 192.;
+  const long long generated = gen_cap < 2 ? 1 : gen_cap / 2, blocks = over(shared_len, 32);
+
+  const long long lists = (long long)batch * n_pass;
+  long long splits = over(256, lists * hkv * n_layers);
+  if (splits > over(shared_len, 256)) splits = over(shared_len, 256);
+  if (splits < 1) splits = 1;
+  const double t_general = (double)over(over(lists * splits, kXcds) * hkv * n_layers, 32) *
+                           (11.5 + size * (0.85 * (double)over(over(shared_len, 64), splits) +
+                                          (double)over(n_streams, batch) * (0.45 + 1.8 / 32. * (double)generated) / (double)splits));
+
+  const long long pairs = (long long)n_streams * hkv * n_layers, stream_blocks = blocks + over(generated, 32);
+  const int waves = short_decode_waves(shared_len, gen_cap, pairs);
+  const double t_per_stream = (waves == 8 ? 3.6 : 3.1) + size * (1.2 * (double)over(stream_blocks, waves) +
+                              past_half_round(pairs) * ((waves == 8 ? 3.1 : 0.) + 0.45 * (double)stream_blocks));
+
+  const BeamGroups g = beam_groups(n_streams, batch, gq);
+  const long long workgroups = (long long)g.count * hkv * n_layers;
+  const long long caches = n_streams % batch == 0 ? 1 : over(g.group - 1, n_streams / batch) + 1;   // of streams in the order of their sequences
+  const long long group_blocks = blocks * caches + over(g.group * generated, 32);
+  const int group_waves = beam_group_waves(g, shared_len, gen_cap);
+  const double t_grouped = (group_waves == 8 ? 5.6 : 4.8) + size * (1.15 * (double)over(group_blocks, group_waves) +
+                           past_half_round(workgroups) * ((group_waves == 8 ? 6.2 : 1.7) + 0.4 * (double)group_blocks));
+  if (t_general <= t_per_stream && t_general <= t_grouped) return BeamKernel::kGeneral;
+  return t_per_stream <= t_grouped ? BeamKernel::kPerStream : BeamKernel::kGrouped;
 }
 
 // ---- attention backward (bf16): (sequence, kv head) pairs, blocks of owned rows, query heads of the group ----

@@ -10,6 +10,13 @@ from parity import check_attn
 
 pytestmark = pytest.mark.gpu
 DEV, BF = "cuda:0", torch.bfloat16
+# sizes that the rule gives to decode_beams_kernel (test_work_order.py checks that it does): with one layer a launch and with three,
+# also with a stream more than the sequences share evenly; 8 generated rows
+GROUPED = [(16, 4, 128, 8, 13, 130), (4, 4, 64, 17, 6, 131), (8, 4, 64, 24, 8, 65), (12, 4, 64, 12, 7, 129)]
+# ... and in the usual order
+ANY_ORDER, ANY_ORDER_ROOM = [(16, 4, 128, 12, 10, 64, 3), (8, 8, 64, 9, 8, 33, 2), (4, 4, 64, 200, 9, 60, 1), (12, 2, 128, 300, 6, 100, 1)], 5
+STAY_AWAY = [(16, 4, 128, 12, 9, 100), (8, 8, 64, 12, 9, 100)]
+TIMED = [(32, 32, 128, 8, 10, 256), (8, 8, 64, 16, 10, 256)]
 I32 = lambda x: torch.tensor([int(v) for v in x], dtype=torch.int32, device=DEV)
 
 
@@ -72,7 +79,7 @@ def _layout(name, batch, beams, rng):
 
 @pytest.mark.parametrize("layout", ["usual", "uneven", "shuffled"])
 @pytest.mark.parametrize("hq,hkv,d,batch,beams,longest", [(16, 4, 128, 12, 10, 64), (14, 2, 64, 30, 7, 70), (8, 8, 64, 9, 8, 33),
-                                                          (16, 2, 128, 30, 6, 100), (12, 4, 64, 13, 9, 300)])
+                                                          (16, 2, 128, 30, 6, 100), (12, 4, 64, 13, 9, 300), *GROUPED])
 @pytest.mark.parametrize("table,layers", [(False, 1), (False, 3), (True, 1)])
 def test_grouped_streams(layout, hq, hkv, d, batch, beams, longest, table, layers):
     rng = np.random.default_rng(batch + beams + longest)
@@ -96,13 +103,12 @@ def test_grouped_streams(layout, hq, hkv, d, batch, beams, longest, table, layer
 
 
 @pytest.mark.parametrize("layout", ["beams first", "pairs", "last two swapped", "few sequences"])
-@pytest.mark.parametrize("hq,hkv,d,batch,beams,longest,layers", [(16, 4, 128, 12, 10, 64, 1), (8, 8, 64, 9, 8, 33, 2), (14, 2, 64, 190, 9, 60, 1),
-                                                                 (12, 2, 128, 300, 6, 40, 1)])
+@pytest.mark.parametrize("hq,hkv,d,batch,beams,longest,layers", ANY_ORDER)
 def test_streams_in_any_order(layout, hq, hkv, d, batch, beams, longest, layers):
     """The groups are cut from the streams in the order of their sequences, whatever order they come in (up to 1800 streams: a
     workgroup's check of the order takes several steps)."""
     rng = np.random.default_rng(batch + beams)
-    s2s, cap = _layout(layout, batch, beams, rng), 5
+    s2s, cap = _layout(layout, batch, beams, rng), ANY_ORDER_ROOM
     lens = [int(n) for n in rng.integers(1, longest + 1, batch)]
     gen_len = rng.integers(0, cap, len(s2s)).tolist()
     x = _inputs(batch, len(s2s), lens, hq, hkv, d, cap, layers)
@@ -115,7 +121,7 @@ def test_streams_in_any_order(layout, hq, hkv, d, batch, beams, longest, layers)
         assert torch.equal(gv[l][at], x["v_new"][l])
 
 
-@pytest.mark.parametrize("hq,hkv,d,batch,beams,rows", [(32, 32, 128, 8, 10, 256), (8, 8, 64, 16, 10, 256)])
+@pytest.mark.parametrize("hq,hkv,d,batch,beams,rows", TIMED)
 def test_order_of_streams_costs_little(hq, hkv, d, batch, beams, rows):
     """Streams that do not lie side by side: groups of unlike streams walked a cache each, 4 to 6 times the time."""
     from paper_2507_00715_amd import binding as B
@@ -143,12 +149,13 @@ def test_order_of_streams_costs_little(hq, hkv, d, batch, beams, rows):
     assert us("beams first") <= 2 * us("usual")
 
 
-@pytest.mark.parametrize("hq,hkv,d", [(16, 4, 128), (8, 8, 64)])
+@pytest.mark.parametrize("n", [40, STAY_AWAY[0][5]])
+@pytest.mark.parametrize("hq,hkv,d", [x[:3] for x in STAY_AWAY])
 @pytest.mark.parametrize("layout", ["usual", "shuffled"])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-def test_rows_of_other_streams_stay_away(hq, hkv, d, layout, value):
+def test_rows_of_other_streams_stay_away(hq, hkv, d, layout, value, n):
     """Values of one stream's generated rows, its new token, and one sequence's cache reach only the streams that see them."""
-    batch, beams, cap, n = 12, 9, 8, 40
+    batch, beams, cap = 12, 9, 8
     rng = np.random.default_rng(5)
     s2s, lens = _layout(layout, batch, beams, rng), [n] * batch
     gen_len = rng.integers(1, cap, len(s2s)).tolist()

@@ -11,7 +11,6 @@ SOURCE = r'''
 #include "work_order.h"
 using namespace earn;
 extern "C" int takes(int longest, int mean, long long pairs, int in_place) { return short_prefill_takes(longest, mean, pairs, in_place); }
-extern "C" int takes_beams(long long pairs, long long general, int len, int d) { return short_decode_takes_beams(pairs, general, len, d); }
 extern "C" int waves(int max_shared_len, int gen_cap, long long workgroups) { return short_decode_waves(max_shared_len, gen_cap, workgroups); }
 extern "C" int groups(int n_streams, int batch, int gq, int (*out)[3]) {
   const BeamGroups g = beam_groups(n_streams, batch, gq);
@@ -155,15 +154,6 @@ def test_short_prefill_takes(lib, longest, mean, pairs, in_place, short):
     assert bool(lib.takes(longest, mean, ctypes.c_longlong(pairs), in_place)) == short
 
 
-@pytest.mark.parametrize("batch,beams,hkv,d,layers,rows,short", [
-    (8, 10, 2, 128, 16, 32, True), (8, 10, 2, 128, 16, 48, False),          # one round of the general kernel
-    (16, 10, 8, 128, 24, 32, True), (16, 10, 8, 128, 24, 64, False),        # twelve
-    (16, 10, 8, 128, 1, 64, True), (16, 10, 8, 128, 1, 100, False), (32, 4, 2, 64, 1, 512, True), (1, 1, 1, 64, 1, 0, True)])
-def test_short_decode_takes_beams(lib, batch, beams, hkv, d, layers, rows, short):
-    ll = ctypes.c_longlong
-    assert bool(lib.takes_beams(ll(batch * beams * hkv * layers), ll(batch * hkv * layers), rows, d)) == short
-
-
 @pytest.mark.parametrize("d", [1, 2, 3, 5, 7, 12, 17, 32, 100, 1041, 65535, 65537, 524288, 2 ** 30 + 1, 2 ** 31 - 1])
 def test_division_by_multiplication(lib, d):
     k = np.arange(1, 2000, dtype=np.uint64)
@@ -193,10 +183,41 @@ def test_beam_groups_hold_every_stream_once(lib, n_streams, batch, gq):
         assert np.array_equal(slot, first // w) and np.array_equal(slot, (first + count - 1) // w)
 
 
+GENERAL, PER_STREAM, GROUPED = range(3)
+
+
+# The fastest kernel of each size as measured (us a layer: general, one workgroup per stream, groups), or one within a tenth of that
 @pytest.mark.parametrize("streams,batch,hkv,gq,d,rows,cap,layers,n_pass,kernel", [
-    (10, 1, 8, 4, 128, 64, 8, 1, 1, 1), (160, 16, 8, 4, 128, 64, 8, 1, 1, 2), (160, 16, 8, 4, 128, 32, 8, 1, 1, 1), (160, 16, 8, 4, 128, 33, 8, 1, 1, 2),
-    (160, 16, 8, 4, 128, 512, 8, 1, 1, 0), (160, 16, 8, 4, 128, 16, 32, 1, 1, 1), (640, 64, 2, 7, 64, 256, 8, 1, 2, 0), (640, 64, 2, 7, 64, 64, 8, 1, 2, 2),
-    (160, 16, 8, 4, 128, 2300, 8, 1, 1, 0), (160, 16, 8, 4, 128, 64, 200, 1, 1, 1), (64, 16, 4, 1, 64, 128, 16, 1, 1, 1), (1400, 140, 2, 6, 128, 25, 16, 1, 1, 1),
-    (1400, 140, 2, 6, 128, 33, 16, 1, 1, 2), (1400, 140, 2, 7, 64, 25, 16, 1, 1, 2)])
+    (10, 1, 8, 4, 128, 64, 8, 1, 1, PER_STREAM),
+    (160, 16, 8, 4, 128, 64, 8, 1, 1, GROUPED),              # 14.3  13.1   8.8
+    (160, 16, 8, 4, 128, 32, 8, 1, 1, PER_STREAM),           # 15.4   8.9   8.2 (where the two cross)
+    (160, 16, 8, 4, 128, 33, 8, 1, 1, GROUPED),              # 14.6  11.9   8.4
+    (160, 16, 8, 4, 128, 100, 8, 1, 1, GROUPED),             # 15.2  17.7  11.3
+    (160, 16, 8, 4, 128, 512, 8, 1, 1, GENERAL),             # 23.6  52.5  25.0
+    (160, 16, 8, 4, 128, 16, 32, 1, 1, PER_STREAM),          # 25.6   9.3  11.5
+    (160, 16, 8, 4, 128, 64, 200, 1, 1, PER_STREAM),         # 53.8  26.6  28.7
+    (160, 16, 8, 4, 128, 64, 8, 24, 1, GROUPED),             #  6.7   7.3   5.0
+    (80, 8, 2, 6, 128, 32, 8, 16, 1, PER_STREAM),            # 1.04  0.99  1.17
+    (80, 8, 2, 6, 128, 200, 8, 16, 1, GENERAL),              # 1.23  3.43  2.46
+    (320, 16, 8, 4, 128, 64, 8, 1, 2, GROUPED),              # 19.8  19.9  14.1
+    (640, 64, 2, 7, 64, 256, 8, 1, 2, GENERAL),              # 14.1  19.1  18.8
+    (640, 64, 2, 7, 64, 64, 8, 1, 2, PER_STREAM),            # 12.3   7.7   7.4
+    (128, 32, 2, 7, 64, 512, 8, 1, 1, GROUPED),              # 14.3   9.2   9.7
+    (64, 16, 4, 1, 64, 128, 16, 1, 1, PER_STREAM),           # 10.0   6.7   6.8
+    (1400, 140, 2, 6, 128, 25, 16, 1, 1, PER_STREAM),        # 37.2  16.1  19.5
+    (1400, 140, 2, 6, 128, 33, 16, 1, 1, PER_STREAM),        # 36.3  20.7  20.4
+    (1400, 140, 2, 7, 64, 25, 16, 1, 2, PER_STREAM),         # 38.9  10.6  12.0
+    (160, 16, 8, 4, 128, 2300, 8, 1, 1, GENERAL)])
 def test_beam_kernel(lib, streams, batch, hkv, gq, d, rows, cap, layers, n_pass, kernel):
     assert lib.beams_kernel(streams, batch, hkv, gq, d, rows, cap, layers, n_pass) == kernel
+
+
+def test_sizes_of_the_group_tests_are_grouped(lib):
+    from test_gpu_beam_groups import ANY_ORDER, ANY_ORDER_ROOM, GROUPED as SIZES, STAY_AWAY, TIMED
+    runs = [(x, 8, layers, more) for x in SIZES for layers in (1, 3) for more in (0, 1)]
+    runs += [(x[:6], ANY_ORDER_ROOM, x[6], 0) for x in ANY_ORDER] + [(x, 8, 1, 0) for x in STAY_AWAY + TIMED]
+    for (hq, hkv, d, batch, beams, rows), cap, layers, more in runs:
+        n, gq = batch * beams + more, hq // hkv
+        rows_bound, rows_mean = gq * (n - batch + 1), gq * ((n + batch - 1) // batch)
+        n_pass = (rows_mean + 63) // 64 if rows_bound > 32 and rows_mean > 64 else 1
+        assert lib.beams_kernel(n, batch, hkv, gq, d, rows, cap, layers, n_pass) == GROUPED, (hq, hkv, d, batch, beams, rows, layers, more)
