@@ -326,10 +326,10 @@ size_t earn_prefill_register_rows_workspace_bytes(const earn_attn_desc* desc, in
  * one row of k inputs per output.
  *   workspace  device, optional (NULL / 0: never needed for a correct result).  A product with few rows (register rows,
  *              decode rows) has too few output tiles to occupy the GPU; given earn_linear_workspace_bytes(rows, k, n)
- *              bytes (256-byte aligned; 0 when the product is large enough as it is) the inner dimension is split over
+ *              bytes (256-byte aligned; 0 when the product is large enough as it is) the inner dimension may be split over
  *              more workgroups, fp32 partial sums pass through the workspace and a second kernel adds them and applies
  *              the epilogue.  Same results up to fp32 summation order.  For earn_qkv_rope_project, n = (Hq + 2 Hkv) d.
- *              A larger buffer may be used: of up to 160 rows, products with wide outputs (size 0 here) then split too.
+ *              A smaller buffer is used as far as it goes (fewer splits).
  * Errors: NULL pointer, non-positive size, positions and cu_seqlens both NULL with rotation on -> INVALID_ARG;
  * desc->dtype != EARN_BF16, an inner dimension that is not a multiple of 64, an output width that is not a multiple of
  * 8, 256 rows of the inner dimension reaching 2 GiB -> UNSUPPORTED.  Enqueue on `stream`, allocate nothing.

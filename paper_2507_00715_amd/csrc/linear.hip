@@ -514,6 +514,13 @@ static int linear_few_rows(long long rows, int k, int n) {
   return rows > 32 && k >= 3072 && n > 4608 && n <= 8192 ? 2 : 1;
 }
 
+// us of linear_few_rows_kernel in z splits, by a count: K-tiles in a row, for each row and column of a tile, the reduction's launch and
+// the partial sums (160 rows, k = 4096, 128 columns: 4096 outputs in 4 / 8 splits 19.9 / 19.8, 6144 in 4 / 8 25.1 / 24.5, 11008 in 1 /
+// 2 49 / 37; k = 11008, 4096 outputs 44 / 35).
+static double few_rows_us(long long rows, int k, int n, int few, int z) {
+  return ((k / 64 + z - 1) / z) * (double)((rows + 31) / 32 * 32 + 64 * few) * (few == 2 ? 2.6e-3 : 3.4e-3) +
+         (z > 1 ? 5. + z * ((double)rows * n * 2e-6 + 0.3) : 0.);
+}
 // Splits of the inner dimension for a product with few output rows.  Without a split such a product has one workgroup
 // per 128 columns, a fraction of the CUs, each streaming its slice of the weights alone at the rate one workgroup's few
 // tiles in flight allow; with z splits there are z times as many, at the price of z * rows * n fp32 partial sums written
@@ -521,12 +528,9 @@ static int linear_few_rows(long long rows, int k, int n) {
 // fits ONE round of 256 workgroups; at least 4 K-tiles per split, the partial sums no larger than the weights, and
 // within the workspace given.  Measured (160 rows, k = 4096): 4096 outputs 56 -> 23 us, 6144 outputs 57 -> 28 us; with
 // 86 tiles (11008 outputs) two splits only add the partial sums (62 -> 70 us).  The 64-column tiles of the few-row kernel
-// follow the same rule with twice as many tiles; its 128-column tiles take what a count of the time says is best: K-tiles in a row
-// (0.0026 us per row and column of a tile), the reduction's launch, and the partial sums (160 rows, k = 4096: 4096 outputs in 4
-// / 8 splits 20.2 / 23.4 us, 6144 in 4 / 5 24.5 / 26.8, 11008 in 1 / 2 49 / 37; k = 11008, 4096 outputs 44 / 35).  (Q/K/V products of 8193 to 16384 outputs and k >= 8192 are left without a
-// split and with the general kernel, as its rotating epilogue asks: 8192 x 10240, 1 / 64 / 160 rows 109 / 115 / 118 us, in two
-// splits 112 / 115 / 121.)
-// least: 2 where an unsplit product could not take the few-row kernel (Q/K/V).
+// follow the same rule with twice as many tiles; its 128-column tiles take what few_rows_us says is best.
+// least: 2 where an unsplit product could not take the few-row kernel, which has no rotating epilogue (Q/K/V: 8192 x 10240, 1 / 64 /
+// 160 rows, the general kernel unsplit 109 / 115 / 118 us, the few-row kernel in two splits 42 / 46 / 62, in three 38 / 40 / 49).
 static int linear_splits(long long rows, int k, int n, int few, int least, size_t workspace_bytes) {
   const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128), half_tiles = (n + 63) / 64;
   long long z;
@@ -534,8 +538,8 @@ static int linear_splits(long long rows, int k, int n, int few, int least, size_
     double best = 0.;
     z = 0;
     for (int i = least; i == least || (i <= 16 && i * tiles <= 256); ++i) {
-      const double t = ((k / 64 + i - 1) / i) * (double)((rows + 31) / 32 * 32 + 128) * 2.6e-3 + (i > 1 ? 5. + i * ((double)rows * n * 2e-6 + 0.3) : 0.);
-      if (z == 0 || t < best) { best = t; z = i; }
+      const double t = few_rows_us(rows, k, n, few, i);
+      if (z == 0 || t < 0.99 * best) { best = t; z = i; }   // (no more for nothing: 96 rows x 4096 x 4096 in 4 / 6 / 8 splits 14.8 / 16.0 / 16.0 us)
     }
   } else {
     z = few ? std::max<long long>(1, 256 / half_tiles) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
@@ -548,29 +552,12 @@ static int linear_splits(long long rows, int k, int n, int few, int least, size_
   while (z > 1 && (size_t)z * rows * n * sizeof(float) > workspace_bytes) --z;
   return (int)std::max<long long>(z, 1);
 }
-// The workspace that the query names, by which programs have sized their buffers: for as many splits as tiles of 64 columns (up
-// to 64 rows, and where 128-column tiles are more than one round of every XCD) or 128 leave room for in one round of workgroups.
-// A call uses what it is given: less means fewer splits, and a product that the query names nothing for is split as well where
-// the buffer is large enough for it (160 rows x 4096 x 11008, in the buffer of the layer's other products: 49 -> 37 us).
-static bool asked_as_few_rows(long long rows, int k, int n) {
-  if (tuning(kTuneLinearTile, 0) != 0) return false;
-  if (rows <= 64) return true;
-  const int tiles = (n + 127) / 128;
-  if (tiles > 64) return rows <= 160;
-  if (rows > 96) return false;
-  int patch_rows, patch_cols;
-  linear_grid(rows, n, 128, &patch_rows, &patch_cols);
-  const int patches = (tiles + patch_cols - 1) / patch_cols, fullest = (patches + kXcds - 1) / kXcds * patch_cols;
-  const bool one_round = patch_rows == 1 && fullest * (256 / tiles) <= 32;
-  return !(one_round && (tiles >= 44 ? k >= 3072 : tiles >= 24 && k > 8192));
-}
+// What a launch with a large enough buffer splits into, as either kind of product (a call uses what it is given: less means fewer
+// splits).
 size_t linear_workspace_bytes(long long rows, int k, int n) {
   if (rows <= 0 || k <= 0 || n <= 0 || k % kLinKMultiple != 0) return 0;
-  const long long tiles = ((rows + kLinRows - 1) / kLinRows) * ((n + 127) / 128), few = (n + 63) / 64;
-  long long z = asked_as_few_rows(rows, k, n) ? std::max<long long>(1, 256 / few) : tiles <= 64 ? 256 / tiles : (tiles <= 128 && k >= 8192 ? 2 : 1);
-  z = std::min<long long>(std::min<long long>(z, 16), std::min<long long>(k / 64 / 4, k / (2 * rows)));
-  const int forced = tuning(kTuneLinearSplits, 0);
-  if (forced > 0) z = std::min<long long>(forced, std::max(1, k / 64));
+  const int few = linear_few_rows(rows, k, n);
+  const int z = std::max(linear_splits(rows, k, n, few, 1, ~(size_t)0), linear_splits(rows, k, n, few, 2, ~(size_t)0));
   return z > 1 ? ((size_t)z * rows * n * sizeof(float) + 255) / 256 * 256 : 0;
 }
 
@@ -609,11 +596,14 @@ static bool linear_wide_tile(long long rows, int n) {
 struct LinearLaunch { int few; bool wide; int splits; dim3 grid; };
 static int plan_linear(const char* who, LinearParams& p, int least, void* workspace, size_t workspace_bytes, LinearLaunch* out) {
   int few = linear_few_rows(p.rows, p.k, p.n), splits = workspace ? linear_splits(p.rows, p.k, p.n, few, least, workspace_bytes) : 1;
-  // few rows in 128-column tiles need their splits, which the buffer may not hold: 63 rows x 4096 x 6144 in 4 / 2 of them 16.8 / 21.1
-  // us, in two of 64-column tiles 18.3
-  if (few == 2 && p.rows <= 64 && splits < linear_splits(p.rows, p.k, p.n, few, 1, ~(size_t)0)) {
-    few = 1;
-    splits = workspace ? linear_splits(p.rows, p.k, p.n, few, least, workspace_bytes) : 1;
+  // Few rows in 128-column tiles need their splits, which the buffer may not hold.  us, in 128- / 64-column tiles with the same buffer:
+  // 64 rows x 4096 x 6144 in one / two splits 28.7 / 21.4, 24.2 / 18.7; 96 rows x 4096 x 11008 in one 39.2, 34.4; x 11008 x 4096 in one /
+  // two / four 99 / 57 / 36, 80 / 48 / 32.  Not with more than three blocks of rows (112 x 4096 x 11008 41.3, 41.7), nor from two on where
+  // the weights come out of a cache (96 x 4096 x 4096 in one / two 26.6 / 19.3, 31.1 / 21.1).
+  if (few == 2 && p.rows <= 96 && (p.rows <= 64 || (long long)p.k * p.n >= 24ll << 20) &&
+      splits < linear_splits(p.rows, p.k, p.n, few, 1, ~(size_t)0)) {
+    const int narrow = workspace ? linear_splits(p.rows, p.k, p.n, 1, least, workspace_bytes) : 1;
+    if (few_rows_us(p.rows, p.k, p.n, 1, narrow) < few_rows_us(p.rows, p.k, p.n, 2, splits)) { few = 1; splits = narrow; }
   }
   const bool wide = splits == 1 && linear_wide_tile(p.rows, p.n);
   const long long grid = linear_grid(p.rows, p.n, wide ? 256 : 128, &p.patch_rows, &p.patch_cols);

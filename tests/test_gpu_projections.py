@@ -265,7 +265,7 @@ def test_linear_few_rows(rows, k, n, act, with_ws):
 @pytest.mark.parametrize("size", [0, 1 << 20, 1 << 26])
 @pytest.mark.parametrize("rows,k,n,act", [(1, 64, 8, 0), (17, 256, 136, 0), (64, 1024, 192, 1), (65, 192, 128, 0), (97, 256, 328, 0),
                                           (96, 320, 1000, 1), (129, 1280, 11008, 1), (160, 4096, 1096, 0), (160, 2112, 8200, 0),
-                                          (40, 8192, 8264, 0), (33, 3072, 6400, 0)])
+                                          (40, 8192, 8264, 0), (33, 3072, 6400, 0), (65, 4096, 6408, 0), (96, 4096, 6152, 1)])
 def test_linear_few_rows_128_columns(rows, k, n, act, size):
     B = _B()
     g = torch.Generator().manual_seed(rows + k + n)
@@ -281,6 +281,21 @@ def test_linear_few_rows_128_columns(rows, k, n, act, size):
     got = out[:rows].cpu().double()
     assert bool(((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 2e-5).all())    # (as in test_linear_few_rows)
     assert bool((out[rows] == 7.0).all()) and bool((ws[size:] == 3).all())
+
+
+@pytest.mark.parametrize("rows,k,n", [(160, 4096, 11008), (144, 2048, 8200), (96, 4096, 6152), (65, 1536, 4160), (64, 4096, 6144), (1, 1024, 256),
+                                      (161, 4096, 1096)])
+def test_the_size_that_is_asked_for_is_all_that_a_product_uses(rows, k, n):
+    """Behind the workspace of the query a product runs as behind a far larger one: the same sums in the same order."""
+    B = _B()
+    g = torch.Generator(device=DEV).manual_seed(rows + k + n)
+    x = torch.randn(rows, k, generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn(n, k, generator=g, device=DEV) * k ** -0.5).to(torch.bfloat16)
+    asked, much = (torch.empty(rows, n, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    B.earn_linear(x, w, asked)
+    B.earn_linear(x, w, much, 0, torch.empty(1 << 27, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(asked, much)
 
 
 @pytest.mark.parametrize("with_ws", [False, True])
