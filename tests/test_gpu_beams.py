@@ -139,16 +139,25 @@ def test_beam_reorder_table():
 
 
 BEAM_CASES = [
-    # dtype, hq, hkv, d, shared lengths, beams, steps, vocab
-    (BF, 32, 8, 128, [64, 300], 20, 4, 256),        # the paper's beam width: 80 query rows per cache, matrix-core kernel
-    (BF, 8, 8, 64, [33, 16, 700], 4, 5, 50),        # vector kernel (one query head per kv head, short caches)
-    (BF, 14, 2, 64, [1000, 130], 3, 3, 1000),       # key splits + combine
-    (F32, 4, 2, 64, [40, 9], 5, 4, 16),
+    # dtype, hq, hkv, d, shared lengths, beams, steps, vocab (the kernels that bf16 takes by rule: test_work_order.py)
+    (BF, 32, 8, 128, [64, 300], 20, 4, 256),        # the paper's beam width: 80 query rows per cache; groups / two passes of the matrix-core kernel
+    (BF, 8, 8, 64, [33, 16, 700], 4, 5, 50),        # one query head per kv head; one workgroup per stream / matrix-core kernel, key splits + combine
+    (BF, 14, 2, 64, [1000, 130], 3, 3, 1000),       # one workgroup per stream / key splits + combine
+    (F32, 4, 2, 64, [40, 9], 5, 4, 16),             # vector kernel
 ]
 
 
+@pytest.fixture(params=[False, True], ids=["by rule", "general kernels"])
+def general(request):
+    B = _B()
+    if request.param:
+        B.earn_set_tuning("decode_vec_wgs", 1024)   # the default, set: the general kernels
+    yield request.param
+    B.earn_set_tuning("decode_vec_wgs", 0)
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d,slens,beams,steps,vocab", BEAM_CASES)
-def test_beam_search_decode_loop_matches_oracle(dtype, hq, hkv, d, slens, beams, steps, vocab):
+def test_beam_search_decode_loop_matches_oracle(dtype, hq, hkv, d, slens, beams, steps, vocab, general):
     B = _B()
     batch, S = len(slens), len(slens) * beams
     g = torch.Generator().manual_seed(sum(slens) + beams)

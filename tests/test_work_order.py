@@ -221,3 +221,10 @@ def test_sizes_of_the_group_tests_are_grouped(lib):
         rows_bound, rows_mean = gq * (n - batch + 1), gq * ((n + batch - 1) // batch)
         n_pass = (rows_mean + 63) // 64 if rows_bound > 32 and rows_mean > 64 else 1
         assert lib.beams_kernel(n, batch, hkv, gq, d, rows, cap, layers, n_pass) == GROUPED, (hq, hkv, d, batch, beams, rows, layers, more)
+
+
+def test_kernels_of_the_beam_search_tests(lib):
+    from test_gpu_beams import BEAM_CASES
+    kernels = [lib.beams_kernel(len(lens) * beams, len(lens), hkv, hq // hkv, d, max(lens), steps, 1, 2 if beams * hq // hkv > 64 else 1)
+               for _, hq, hkv, d, lens, beams, steps, _ in BEAM_CASES[:3]]
+    assert kernels == [GROUPED, PER_STREAM, PER_STREAM]
