@@ -2,8 +2,8 @@
 fp64 oracle called with the same options: an explicit softmax scale (Eq. 3's 1/sqrt(d) replaced by 0.37), rotation
 switched off (rope_base = 0), and an explicit, permuted grouped-query head map (q_to_kv).
 
-Kernel families reached: bf16 prefill in the 64-row (register layers), 128-row and 256-row (pipelined) forms, the fp32
-vector prefill, the vector decode kernel (bf16 and fp32), the matrix-core decode kernel, and the register-rows entry
+Kernel families reached: bf16 prefill in the 64-row (register layers), 128-row and 256-row (pipelined) forms, the
+fp32 prefill, the vector decode kernel (bf16 and fp32), the matrix-core decode kernel, and the register-rows entry
 point in both of its forms.
 """
 import numpy as np
@@ -67,7 +67,7 @@ PREFILL_SHAPES = [
     (BF, 8, 2, 128, [40, 16, 64]),          # one K/V tile per sequence: the register-layer kernel
     (BF, 14, 2, 64, [300, 61, 1000]),       # 128-row workgroups
     (BF, 4, 2, 128, [3300, 1000]),          # long on average (mean > 2048 rows): the pipelined kernel
-    (F32, 6, 2, 64, [130, 70]),             # vector kernel
+    (F32, 6, 2, 64, [130, 70]),             # fp32 matrix products
 ]
 
 

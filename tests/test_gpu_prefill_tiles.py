@@ -16,6 +16,27 @@ DEV, BF = "cuda:0", torch.bfloat16
 @pytest.mark.parametrize("hq,hkv,d", [(4, 4, 128), (6, 2, 64), (4, 2, 128)])
 @pytest.mark.parametrize("lens", [[129, 1, 31, 128, 32, 33], [193, 64, 65, 127, 63, 191], [257, 96, 97, 160, 255], [385, 0, 2]])
 def test_prefill_at_tile_edges(lens, hq, hkv, d, rope_base):
+    _check(lens, hq, hkv, d, rope_base)
+
+
+@pytest.fixture
+def long_kernel():
+    from paper_2507_00715_amd import binding as B
+    B.earn_set_tuning("prefill_block_rows", 256)
+    yield
+    B.earn_set_tuning("prefill_block_rows", 0)
+
+
+@pytest.mark.parametrize("rope_base", [10000.0, 0.0])
+@pytest.mark.parametrize("hq,hkv,d", [(14, 2, 64), (12, 2, 128), (3, 1, 128), (6, 2, 64)])
+@pytest.mark.parametrize("lens", [[200, 1, 31, 32, 33, 63, 64, 65], [321, 0, 129, 96, 257], [577, 2, 449]])
+def test_long_prefill_over_heads_that_do_not_fill_a_workgroup(long_kernel, lens, hq, hkv, d, rope_base):
+    """Eight waves take units of 32 rows of one head: with groups of 3, 6 and 7 heads a workgroup's units straddle row blocks, and
+    the last workgroup of a sequence holds units that do not exist."""
+    _check(lens, hq, hkv, d, rope_base)
+
+
+def _check(lens, hq, hkv, d, rope_base):
     from paper_2507_00715_amd import binding as B
     g = torch.Generator().manual_seed(sum(lens) + hq)
     T = sum(lens)
