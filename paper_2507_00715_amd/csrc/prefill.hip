@@ -1358,14 +1358,16 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
   const bool few_rows = max_seqlen <= (p.hq > p.hkv ? 128 : 32) && run_fits(batch, p.hkv, max_seqlen <= 64 ? 256 : 512) &&
                         short_prefill_takes(max_seqlen, total_tokens / batch, (long long)batch * p.hkv * n_layers, in_place);
   if (f32) {
+    // (the bound given may be far above any sequence; none is longer than all of them together)
+    const int longest = std::min(max_seqlen, total_tokens);
     // the keys are rotated by the attention kernel where there are few workgroups (and not in place: others read them)
-    const bool rotate = !in_place && k != k_rot_out && f32_few_workgroups(max_seqlen, p.hq, d, (long long)batch * n_layers);
+    const bool rotate = !in_place && k != k_rot_out && f32_few_workgroups(longest, p.hq, d, (long long)batch * n_layers);
     if (!in_place && !rotate) {
       if (d == 64) launch_rope_k<float, 64>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
       else launch_rope_k<float, 128>(k, (void*)k_rot, cu_seqlens, positions, batch, total_tokens, p.hkv, p.rope, cs, stream, n_layers, ls_k, ls_kr);
     }
-    if (d == 64) launch_prefill_f32<64>(p, k, ls_k, k_rot_out, rotate, max_seqlen, n_layers, stream);
-    else launch_prefill_f32<128>(p, k, ls_k, k_rot_out, rotate, max_seqlen, n_layers, stream);
+    if (d == 64) launch_prefill_f32<64>(p, k, ls_k, k_rot_out, rotate, longest, n_layers, stream);
+    else launch_prefill_f32<128>(p, k, ls_k, k_rot_out, rotate, longest, n_layers, stream);
   } else if (few_rows) {
     auto launch = [&](auto kernel, int waves, int per_cu) {
       // Few (sequence, kv head) pairs: several workgroups per pair, each with its own copy of the keys, as many as an XCD

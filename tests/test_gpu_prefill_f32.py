@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 DEV, F32 = "cuda:0", torch.float32
 
 
-def _run(lens, hq, hkv, d, rope_base=10000.0, positions=None, in_place=False, edit=None, seed=0):
+def _run(lens, hq, hkv, d, rope_base=10000.0, positions=None, in_place=False, edit=None, seed=0, bound=None):
     from paper_2507_00715_amd import binding as B
     g = torch.Generator().manual_seed(seed + sum(lens) + hq)
     T = sum(lens)
@@ -25,7 +25,7 @@ def _run(lens, hq, hkv, d, rope_base=10000.0, positions=None, in_place=False, ed
     out, lse = torch.full((T, hq, d), 7.0, device=DEV), torch.empty(T, hq, device=DEV)
     k_rot = d_k if in_place else torch.empty_like(d_k)
     B.earn_prefill_attn(desc, q.to(DEV), d_k, v.to(DEV), torch.from_numpy(cu).to(DEV), None if positions is None else positions.to(DEV),
-                        len(lens), T, max(lens), out, k_rot, lse, torch.empty(256, dtype=torch.uint8, device=DEV))
+                        len(lens), T, bound or max(lens), out, k_rot, lse, torch.empty(256, dtype=torch.uint8, device=DEV))
     torch.cuda.synchronize()
     return q, k, v, cu, out, k_rot, lse
 
@@ -57,3 +57,12 @@ def test_values_behind_the_mask_stay_away(d, batch):
     assert (got[:, :at_inf] - clean.view(batch, n, 4, d)[:, :at_inf]).abs().max() <= 2e-6
     assert bool((got[:, at_inf:at_nan] == float("inf")).all())
     assert bool(torch.isnan(got[:, at_nan:]).all())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_bound_far_above_the_sequences(d):
+    """max_seqlen is an upper bound: one whose workgroups no grid takes gives what a tight one gives."""
+    lens = [20, 1, 33]
+    tight, loose = _run(lens, 4, 2, d), _run(lens, 4, 2, d, bound=600_000_000)
+    for a, b in zip(tight[4:], loose[4:]):
+        assert torch.equal(a, b)
