@@ -224,10 +224,14 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 || QB == 1 ? 2 : 1) void prefil
   };
   auto rotate = [&](float* x, int token) {
     const int pos = (p.positions && r == 0) ? p.positions[b0 + token] : token;
+    int at = quad * E;
+    // The table is read again for every block: kept, its 32 registers had 17 others spilled.  us: one sequence of 128 rows, 32 / 8 heads
+    // 18.1 -> 17.1, two of 64 14.5 -> 14.4; one of 60, 12 / 2 heads, a block to a wave, 12.8 -> 13.1.
+    if (D == 128) asm volatile("" : "+v"(at));
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       float sn, cs;
-      sincos_turns_precise(rope_turns((float)pos, p.rope.hi[quad * E + e], p.rope.lo[quad * E + e]), &sn, &cs);
+      sincos_turns_precise(rope_turns((float)pos, p.rope.hi[at + e], p.rope.lo[at + e]), &sn, &cs);
       const float lo = x[e], hi = x[E + e];
       x[e] = lo * cs - hi * sn;
       x[E + e] = hi * cs + lo * sn;
