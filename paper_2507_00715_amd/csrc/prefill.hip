@@ -486,8 +486,18 @@ __device__ __forceinline__ void pf_rotate_q(const PrefillParams& p, Unit&& unit,
 // 32 query rows of a wave, whole rows at a time, into its own 32 x D region of LDS (swizzled like a K tile); rows past the
 // sequence's end read as zeros.
 template <int D>
-__device__ __forceinline__ void pf_stage_q(const __bf16* q /* first row */, int rows, int row_bytes, unsigned lds, int lane) {
+__device__ __forceinline__ void pf_stage_q(const __bf16* q /* first row */, int rows, int row_bytes, __bf16* own, int lane) {
   constexpr int UPR = D / 8, RPI = kWave / UPR;
+  const unsigned lds = (unsigned)(size_t)(lds_void_ptr)own;
+  if ((unsigned long long)q & 15) {   // loads into LDS are for whole 16-byte units: rows that start elsewhere pass through registers
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+      const int row = RPI * i + lane / UPR;
+      const u32x4 x = *(const u32x4*)((const char*)q + (long long)min(row, min(rows, 32) - 1) * row_bytes + ((lane % UPR) ^ swz<D>(row)) * 16);
+      *(u32x4*)(own + i * 512 + lane * 8) = x;
+    }
+    return;
+  }
   const u32x4 rsrc = raw_buffer(q, (min(rows, 32) - 1) * row_bytes + D * 2);
 #pragma unroll
   for (int i = 0; i < 32 / RPI; ++i) {
@@ -642,10 +652,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
   f32x4 cs[D / 8];
   if constexpr (STAGES == 2) {
     // through the second stage, which nothing uses before the first barrier
-    const __bf16* own = own_region(1);
-    if (wave_active)
-      pf_stage_q<D>((const __bf16*)lv.q + ((long long)(b0 + qw) * p.hq + blk.a) * D, n - qw, p.hq * D * 2,
-                    (unsigned)(size_t)(lds_void_ptr)own, lane);
+    __bf16* own = own_region(1);
+    if (wave_active) pf_stage_q<D>((const __bf16*)lv.q + ((long long)(b0 + qw) * p.hq + blk.a) * D, n - qw, p.hq * D * 2, own, lane);
     issue_tile(0);
     pf_load_cs<D>(p, b0 + q_c, hf, cs);
     asm volatile("" ::: "memory");

@@ -36,7 +36,14 @@ def test_long_prefill_over_heads_that_do_not_fill_a_workgroup(long_kernel, lens,
     _check(lens, hq, hkv, d, rope_base)
 
 
-def _check(lens, hq, hkv, d, rope_base):
+@pytest.mark.parametrize("offset", [1, 4])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (6, 2, 64)])
+def test_queries_and_outputs_that_start_anywhere(hq, hkv, d, offset):
+    """Rows that do not start on 16 bytes: queries cannot be loaded into LDS directly."""
+    _check([129, 1, 31, 128, 32, 33, 200], hq, hkv, d, 10000.0, offset)
+
+
+def _check(lens, hq, hkv, d, rope_base, offset=0):
     from paper_2507_00715_amd import binding as B
     g = torch.Generator().manual_seed(sum(lens) + hq)
     T = sum(lens)
@@ -45,10 +52,11 @@ def _check(lens, hq, hkv, d, rope_base):
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     desc = B.make_desc(BF, hq, hkv, d, 0.0, rope_base)
     pad = 3                                      # rows before and behind the batch, which keep their sentinel
-    out = torch.full((T + 2 * pad, hq, d), 7.0, dtype=BF, device=DEV)
+    moved = lambda t: torch.cat([t.new_zeros(offset), t.flatten()])[offset:].view(t.shape)   # contiguous, `offset` elements into its memory
+    out = moved(torch.full((T + 2 * pad, hq, d), 7.0, dtype=BF, device=DEV))
     lse = torch.empty(T, hq, dtype=torch.float32, device=DEV)
     k_rot = torch.empty(T, hkv, d, dtype=BF, device=DEV)
-    B.earn_prefill_attn(desc, q.to(DEV), k.to(DEV), v.to(DEV), torch.from_numpy(cu).to(DEV), pos.to(DEV), len(lens), T, max(lens),
+    B.earn_prefill_attn(desc, moved(q.to(DEV)), k.to(DEV), v.to(DEV), torch.from_numpy(cu).to(DEV), pos.to(DEV), len(lens), T, max(lens),
                         out[pad:pad + T], k_rot, lse, None)
     torch.cuda.synchronize()
     ref = O.prefill_attn(W.to_f64(q), W.to_f64(k), W.to_f64(v), cu, positions=pos.numpy(), rope_base=rope_base)
