@@ -1257,7 +1257,7 @@ static size_t k_rot_bytes(const earn_attn_desc* desc, int total_tokens) {
   const size_t e = desc->dtype == EARN_F32 ? 4 : 2;
   return ((size_t)total_tokens * desc->n_kv_heads * desc->head_dim * e + 255) / 256 * 256;
 }
-// (cos, sin) table of the bf16 paths: [tokens][d/2] pairs of floats
+// (cos, sin) table of the bf16 paths: [d/4][tokens] of four floats, two pairs
 static size_t cs_table_bytes(const earn_attn_desc* desc, int total_tokens) {
   if (desc->dtype == EARN_F32) return 0;
   return ((size_t)total_tokens * (desc->head_dim / 2) * sizeof(f32x2) + 255) / 256 * 256;
@@ -1281,7 +1281,7 @@ static void launch_rope_k(const void* k, void* k_rot, const int32_t* cu, const i
                      (const T*)k, (T*)k_rot, cu, positions, batch, total, hkv, rope, cs_out, hpt, ls_k, ls_k_rot);
 }
 
-// fp32: the chosen rows of every sequence (q_rows, out_rows: [batch * r, Hq, d]) against the rotated keys, vector kernel
+// fp32: the chosen rows of every sequence (q_rows, out_rows: [batch * r, Hq, d]) against the rotated keys
 int launch_prefill_rows_f32(const earn_attn_desc* desc, const void* q_rows, const void* k_rot, const void* v,
                             const int32_t* cu_seqlens, const int32_t* row_pos, int batch, int total_tokens,
                             int max_seqlen, int rows_per_seq, void* out_rows, hipStream_t stream) {

@@ -59,9 +59,9 @@ EARN_INDEX bool short_prefill_takes(int longest, int mean, long long pairs, bool
 }
 // Medium and long prefill: workgroups of a (sequence, kv head) pair whose waves take units of 32 rows of one query head.
 EARN_INDEX int unit_blocks(int rows, int heads, int waves) { return (int)(((rows + 31ll) / 32 * heads + waves - 1) / waves); }
-// fp32 prefill: are there so few workgroups of 16 query rows that the GPU holds them all at once (one or two a CU, by head
-// dimension)?  Then eight waves share a workgroup's keys and rotate them themselves, in one launch; else 32 rows share them, in
-// four waves, behind a rotation pass.  us, rotating / eight waves / four waves: 2 sequences of 132 rows, 4 heads of 64 (72
+// fp32 prefill: are there so few workgroups of 16 query rows (a CU holds one) that their chains, not the products, are what a
+// launch costs: 512 of 64 elements, 256 of 128?  Then eight waves share a workgroup's keys and rotate them themselves, in one launch;
+// else 32 rows share them, in four waves, behind a rotation pass.  The line lies where the two were measured to cross.  us, rotating / eight waves / four waves: 2 sequences of 132 rows, 4 heads of 64 (72
 // workgroups) 10.9 / 13.5 / 17.3; 8 of them (288) 16.5 / 18.7 / 18.5; 16 (576) 22.9 / 25.4 / 22.5; 2 of 64, 32 / 8 heads of 128
 // (256) 14.9 / 16.5 / 23.4; 4 of them (512) 28.1 / 26.1 / 24.4; one of 512, 12 / 2 heads of 128 (384) 65.7 / 48.7 / 45.9.
 EARN_INDEX bool f32_few_workgroups(int rows, int hq, int d, long long sequences) { return (rows + 15ll) / 16 * hq * sequences * d <= 256 * 128; }
