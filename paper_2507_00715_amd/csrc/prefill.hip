@@ -484,12 +484,11 @@ __device__ __forceinline__ void pf_rotate_q(const PrefillParams& p, Unit&& unit,
 }
 
 // 32 query rows of a wave, whole rows at a time, into its own 32 x D region of LDS (swizzled like a K tile); rows past the
-// sequence's end read as zeros.
-template <int D>
+// sequence's end are not used.  DIRECT: every row starts on 16 bytes.
+template <int D, bool DIRECT>
 __device__ __forceinline__ void pf_stage_q(const __bf16* q /* first row */, int rows, int row_bytes, __bf16* own, int lane) {
   constexpr int UPR = D / 8, RPI = kWave / UPR;
-  const unsigned lds = (unsigned)(size_t)(lds_void_ptr)own;
-  if ((unsigned long long)q & 15) {   // loads into LDS are for whole 16-byte units: rows that start elsewhere pass through registers
+  if constexpr (!DIRECT) {   // loads into LDS are for whole 16-byte units: rows that start elsewhere pass through registers
 #pragma unroll
     for (int i = 0; i < 32 / RPI; ++i) {
       const int row = RPI * i + lane / UPR;
@@ -498,6 +497,7 @@ __device__ __forceinline__ void pf_stage_q(const __bf16* q /* first row */, int 
     }
     return;
   }
+  const unsigned lds = (unsigned)(size_t)(lds_void_ptr)own;
   const u32x4 rsrc = raw_buffer(q, (min(rows, 32) - 1) * row_bytes + D * 2);
 #pragma unroll
   for (int i = 0; i < 32 / RPI; ++i) {
@@ -597,7 +597,9 @@ __device__ int g_pf_timeline_slots;
 #define PF_TIMELINE(code)
 #define PF_STAMP(i)
 #endif
-template <int D, int WAVES, int STAGES>
+// DIRECT_Q (two stages): the queries start on 16 bytes.  Those that do not have a form of their own, so that the others stay without
+// its instructions (the choice inside the kernel: 0.4 % and less at the first of those sizes, no more than two runs differ by).
+template <int D, int WAVES, int STAGES, bool DIRECT_Q = true>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_kernel(PrefillParams p) {
   constexpr int DB = D / 32;             // 32-row blocks of O^T
   __shared__ __bf16 smk[STAGES][kTileKeys * D];  // tile t+1 arrives while tile t is read
@@ -653,7 +655,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void prefill_mfma_k
   if constexpr (STAGES == 2) {
     // through the second stage, which nothing uses before the first barrier
     __bf16* own = own_region(1);
-    if (wave_active) pf_stage_q<D>((const __bf16*)lv.q + ((long long)(b0 + qw) * p.hq + blk.a) * D, n - qw, p.hq * D * 2, own, lane);
+    if (wave_active) pf_stage_q<D, DIRECT_Q>((const __bf16*)lv.q + ((long long)(b0 + qw) * p.hq + blk.a) * D, n - qw, p.hq * D * 2, own, lane);
     issue_tile(0);
     pf_load_cs<D>(p, b0 + q_c, hf, cs);
     asm volatile("" ::: "memory");
@@ -1432,8 +1434,10 @@ int launch_prefill(const earn_attn_desc* desc, const void* q, const void* k, con
     const long long pairs8 = ((long long)batch * p.hkv + kXcds - 1) / kXcds * kXcds;
     dim3 grid((unsigned)(pairs8 * p.n_qblk), n_layers, 1);
     if (block_rows == 128) {
-      if (d == 64) hipLaunchKernelGGL((prefill_mfma_kernel<64, 4, 2>), grid, dim3(256), 0, stream, p);
-      else hipLaunchKernelGGL((prefill_mfma_kernel<128, 4, 2>), grid, dim3(256), 0, stream, p);
+      auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p); };
+      const bool direct_q = (((unsigned long long)q | (unsigned long long)p.ls_q) & 15) == 0;
+      if (d == 64) direct_q ? launch(prefill_mfma_kernel<64, 4, 2>) : launch(prefill_mfma_kernel<64, 4, 2, false>);
+      else direct_q ? launch(prefill_mfma_kernel<128, 4, 2>) : launch(prefill_mfma_kernel<128, 4, 2, false>);
     } else {
       if (d == 64) hipLaunchKernelGGL((prefill_pipe_kernel<64, 8>), grid, dim3(512), 0, stream, p);
       else hipLaunchKernelGGL((prefill_pipe_kernel<128, 8>), grid, dim3(512), 0, stream, p);
