@@ -61,9 +61,10 @@ EARN_INDEX bool short_prefill_takes(int longest, int mean, long long pairs, bool
 EARN_INDEX int unit_blocks(int rows, int heads, int waves) { return (int)(((rows + 31ll) / 32 * heads + waves - 1) / waves); }
 // fp32 prefill: are there so few workgroups of 16 query rows (a CU holds one) that their chains, not the products, are what a
 // launch costs: 512 of 64 elements, 256 of 128?  Then eight waves share a workgroup's keys and rotate them themselves, in one launch;
-// else 32 rows share them, in four waves, behind a rotation pass.  The line lies where the two were measured to cross.  us, rotating / eight waves / four waves: 2 sequences of 132 rows, 4 heads of 64 (72
-// workgroups) 10.9 / 13.5 / 17.3; 8 of them (288) 16.5 / 18.7 / 18.5; 16 (576) 22.9 / 25.4 / 22.5; 2 of 64, 32 / 8 heads of 128
-// (256) 14.9 / 16.5 / 23.4; 4 of them (512) 28.1 / 26.1 / 24.4; one of 512, 12 / 2 heads of 128 (384) 65.7 / 48.7 / 45.9.
+// else 32 rows share them, in four waves, behind a rotation pass.  The line lies where the two were measured to cross.  us,
+// rotating / eight waves / four waves: 2 sequences of 132 rows, 4 heads of 64 (72 workgroups) 10.3 / 12.2 / 16.0; 8 of them (288) 16.0 /
+// 17.6 / 17.2; 16 (576) 22.1 / 24.3 / 21.2; 2 of 64, 32 / 8 heads of 128 (256) 13.9 / 14.7 / 22.0; 3 of them (384) 25.6 / 23.7 / 22.6; one
+// of 256, 16 / 4 heads of 128 (256), whose late rows rotate many keys, 22.8 / 20.3 / 31.9; one of 512, 12 / 2 (384) 67.9 / 47.3 / 43.8.
 EARN_INDEX bool f32_few_workgroups(int rows, int hq, int d, long long sequences) { return (rows + 15ll) / 16 * hq * sequences * d <= 256 * 128; }
 // Streams that share a workgroup of the short decode over beams: up to 16 / gq consecutive ones, whose query heads fill the 16
 // columns of a product, in equal groups of the W = n_streams / batch streams that a sequence usually has side by side (`slot`;
